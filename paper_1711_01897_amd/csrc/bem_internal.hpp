@@ -56,7 +56,6 @@ struct ReqDev {
     const int32_t *fstar;      // P1: the mesh star table (packed triangle << 2 | local vertex); block
                                // records name the fixed dof's entries [s0, s1)
     const int32_t *lane;       // triangle per lane position
-    const int4 *chunk;         // per chunk: first lane, lanes, first dof, dofs
     const int32_t *seg_ptr;    // P1: per lane-side dof, range into seg
     const int32_t *seg;        // P1: packed (lane slot within the chunk << 2 | local vertex)
     const int32_t *lpos;       // P1: output position of each lane-side dof (null: its own index)
@@ -70,7 +69,14 @@ struct ReqDev {
     int32_t near_error;
     double k;                  // wavenumber
     double kk;                 // k / (2 pi): phase in turns per unit length
+    double kl;                 // k / pi - 2 kk: what the FP64 phase adds to 2 kk (wave_low)
 };
+
+// k / pi minus its rounded value 2 kk, from 64-bit mantissas.
+inline double wave_low(double k, double kk)
+{
+    return (double)((long double)k / 3.14159265358979323846264338327950288L - 2.0L * (long double)kk);
+}
 
 struct EntryBlock {  // one workgroup of entry work (64 bytes, read with one scalar load)
     int32_t req;           // (request index << 1) | 1 if the test side is fixed (row request): the kernel
@@ -353,13 +359,13 @@ struct LaneSet {
     std::vector<int32_t> pos;         // P1: output position of each lane-side dof when the set was
                                       // reordered for locality (empty: identity)
     int64_t nchunk() const { return (int64_t)chunk.size() / 4; }
-    size_t ints() const { return chunk.size() + lane.size() + seg_ptr.size() + seg.size() + pos.size(); }
+    // what is staged for the device (block records carry the chunks)
+    size_t ints() const { return lane.size() + seg_ptr.size() + seg.size() + pos.size(); }
 };
 
 struct LaneRef {                      // device pointers of a resident LaneSet
     const int32_t *lane = nullptr, *seg_ptr = nullptr, *seg = nullptr;
-    const int4 *chunk = nullptr;
-    const int32_t *chunk_host = nullptr;   // host copy of the chunk table (block records carry it)
+    const int32_t *chunk_host = nullptr;   // the chunk table (host; block records carry it)
     const float *geo = nullptr;            // FP32 records gathered per lane position
     const int4 *meta = nullptr;            // their vertex ids
     int64_t ndof = 0, nlane = 0, nseg = 0, nchunk = 0, ndistinct = 0;

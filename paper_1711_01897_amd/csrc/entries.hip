@@ -34,6 +34,7 @@
 #include <hip/hip_ext.h>
 
 #include "bem_internal.hpp"
+#include "f64_math.hpp"
 #include "quad_rules.hpp"
 
 namespace bem {
@@ -226,6 +227,12 @@ __device__ __forceinline__ void load32(const float *__restrict__ g, int t, float
     expand32<Q>(ldg(p), ldg(p + 1), ldg(p + 2), ldg(p + 3), v);
 }
 
+// FP64 records in constant memory space: wave-uniform reads become scalar
+// loads (records are written once, when their mesh is created).
+typedef const __attribute__((address_space(4))) double *ConstF64;
+
+__device__ __forceinline__ Wave64 wave64(const ReqDev &R) { return {R.k, 2.0 * R.kk, R.kl}; }
+
 template <int Q>
 __device__ __forceinline__ void load64(const double *__restrict__ g, int t, double *v)
 {
@@ -334,31 +341,94 @@ __device__ __forceinline__ void kern_f32(float r2, float n, float w, float kf, c
     }
 }
 
+// Green's function at r^2, FP64, without 1/4pi.  SLP: 1/r; DLP: 1/r^3 (the
+// (x-y).n_y factor depends on the test point alone and is applied by the
+// caller); Helmholtz: times e^{ikr}, respectively e^{ikr} (1 - ikr).
 template <int OP>
-__device__ __forceinline__ void kern_f64(double dx, double dy, double dz, const double *n, double w, double k,
-                                         double &sr, double &si)
+__device__ __forceinline__ void green_f64(double r2, const Wave64 &wv, double &gr, double &gi)
 {
-    const double r2 = dx * dx + dy * dy + dz * dz;
-    const double ri = rsqrt(r2);
-    if constexpr (OP == LSLP) {
-        sr += w * ri;
-    } else if constexpr (OP == LDLP) {
-        const double dn = dx * n[0] + dy * n[1] + dz * n[2];
-        sr += w * dn * ri * ri * ri;
+    const double ri = rsqrt64(r2);
+    if constexpr (!is_cplx<OP>()) {
+        gr = is_dlp<OP>() ? ri * ri * ri : ri;
+        gi = 0.0;
     } else {
         const double r = r2 * ri;
         double sn, cs;
-        sincos(k * r, &sn, &cs);
-        if constexpr (OP == HSLP) {
-            const double g = w * ri;
-            sr += g * cs;
-            si += g * sn;
+        unsigned flip;
+        cis64(r, wv, cs, sn, flip);
+        if constexpr (is_dlp<OP>()) {
+            const double g = flip_sign(ri * ri * ri, flip), kr = wv.k * r;
+            gr = g * fma(sn, kr, cs);
+            gi = g * fma(-cs, kr, sn);
         } else {
-            const double dn = dx * n[0] + dy * n[1] + dz * n[2];
-            const double g = w * dn * ri * ri * ri;
-            const double kr = k * r;
-            sr += g * (cs + sn * kr);
-            si += g * (sn - cs * kr);
+            const double g = flip_sign(ri, flip);
+            gr = g * cs;
+            gi = g * sn;
+        }
+    }
+}
+
+// Weights times local basis functions, w_p lam_a(p) (rows 0..2), and the
+// weights alone (row 3), read at wave-uniform indices.
+template <int Q>
+struct BasisTab {
+    double v[4][Q];
+    constexpr BasisTab() : v()
+    {
+        for (int p = 0; p < Q; ++p) {
+            for (int a = 0; a < 3; ++a) v[a][p] = rule::Rule<Q>::w[p] * rule::lam<Q>(a, p);
+            v[3][p] = rule::Rule<Q>::w[p];
+        }
+    }
+};
+__constant__ BasisTab<6> c_basis6{};
+__constant__ BasisTab<4> c_basis4{};
+template <int Q>
+__device__ __forceinline__ const double *basis_row(int a)
+{
+    if constexpr (Q == 6) return c_basis6.v[a];
+    else return c_basis4.v[a];
+}
+
+// The inner sums of an FP64 pair: for every point l of the lane triangle L
+// (registers) U[l] = sum_f wu[f] K(f, l) over the points f of the fixed
+// triangle F, and with TWO also V[l] = sum_f wv[f] K(f, l).  LTRIAL: the lane
+// is the trial side.  The fixed side's points are wave-uniform (LDS or
+// constant memory) and their loop stays rolled: the lane's points must be
+// indexed statically to stay in registers, and six unrolled evaluations give
+// enough independent chains.
+template <int OP, int Q, bool LTRIAL, bool TWO, typename FP>
+__device__ __forceinline__ void sweep_f64(FP F, const double *L, const double *wu, const double *wv,
+                                          const Wave64 &wave, double *ur, double *ui, double *vr, double *vi)
+{
+#pragma unroll
+    for (int l = 0; l < Q; ++l) ur[l] = ui[l] = vr[l] = vi[l] = 0.0;
+#pragma unroll 1
+    for (int f = 0; f < Q; ++f) {
+        const double fx = F[4 + 3 * f], fy = F[5 + 3 * f], fz = F[6 + 3 * f];
+        double w = wu[f];
+        // (x_f - y).n_y is the same for every trial point: they lie in one plane
+        if constexpr (is_dlp<OP>() && LTRIAL)
+            w *= fma(fx - L[4], L[0], fma(fy - L[5], L[1], (fz - L[6]) * L[2]));
+#pragma unroll
+        for (int l = 0; l < Q; ++l) {
+            const double dx = fx - L[4 + 3 * l], dy = fy - L[5 + 3 * l], dz = fz - L[6 + 3 * l];
+            double gr, gi;
+            green_f64<OP>(fma(dx, dx, fma(dy, dy, dz * dz)), wave, gr, gi);
+            ur[l] = fma(w, gr, ur[l]);
+            if constexpr (is_cplx<OP>()) ui[l] = fma(w, gi, ui[l]);
+            if constexpr (TWO) {
+                vr[l] = fma(wv[f], gr, vr[l]);
+                if constexpr (is_cplx<OP>()) vi[l] = fma(wv[f], gi, vi[l]);
+            }
+        }
+    }
+    if constexpr (is_dlp<OP>() && !LTRIAL) {
+#pragma unroll
+        for (int l = 0; l < Q; ++l) {
+            const double an = fma(L[4 + 3 * l] - F[4], F[0], fma(L[5 + 3 * l] - F[5], F[1], (L[6 + 3 * l] - F[6]) * F[2]));
+            ur[l] *= an;
+            if constexpr (is_cplx<OP>()) ui[l] *= an;
         }
     }
 }
@@ -418,25 +488,18 @@ __device__ __forceinline__ void pair_p0_f32(const float *T, const float *S, floa
     vi = hi + li;
 }
 
-template <int OP>
-constexpr int f64_unroll() { return is_cplx<OP>() ? 1 : 8; }
-
-template <int OP, int Q>
-__device__ __forceinline__ void pair_p0_f64(const double *T, const double *S, double k, double &vr, double &vi)
+// FP64, fixed triangle F against lane triangle L.
+template <int OP, int Q, bool LTRIAL, typename FP>
+__device__ __forceinline__ void pair_p0_f64(FP F, const double *L, const Wave64 &wave, double &vr, double &vi)
 {
-    double ar = 0.0, ai = 0.0;
+    double ur[Q], ui[Q], xr[Q], xi[Q];
+    sweep_f64<OP, Q, LTRIAL, false>(F, L, basis_row<Q>(3), nullptr, wave, ur, ui, xr, xi);
+    vr = vi = 0.0;
 #pragma unroll
-    for (int p = 0; p < Q; ++p) {
-        double sr = 0.0, si = 0.0;
-#pragma unroll f64_unroll<OP>()
-        for (int q = 0; q < Q; ++q)
-            kern_f64<OP>(T[4 + 3 * p] - S[4 + 3 * q], T[5 + 3 * p] - S[5 + 3 * q], T[6 + 3 * p] - S[6 + 3 * q], S,
-                         rule::Rule<Q>::w[q], k, sr, si);
-        ar += rule::Rule<Q>::w[p] * sr;
-        ai += rule::Rule<Q>::w[p] * si;
+    for (int l = 0; l < Q; ++l) {
+        vr = fma(rule::Rule<Q>::w[l], ur[l], vr);
+        if constexpr (is_cplx<OP>()) vi = fma(rule::Rule<Q>::w[l], ui[l], vi);
     }
-    vr = ar;
-    vi = ai;
 }
 
 // ---------------------------------------------------------------------------
@@ -707,123 +770,62 @@ __device__ __forceinline__ void pair_p1_hyp_f32(const float *T, const float *S, 
     }
 }
 
-// Hypersingular operator, P1, FP64: the same terms from absolute points.
-template <int OP, int Q, bool TESTFIX>
-__device__ __forceinline__ void pair_p1_hyp_f64(const double *T, const double *S, int fix, double k, double *vr,
+// Hypersingular operator, P1, FP64: the same terms from absolute points, the
+// fixed triangle's vertex `fix` against the lane triangle's three.
+template <int OP, int Q, bool LTRIAL, typename FP>
+__device__ __forceinline__ void pair_p1_hyp_f64(FP F, const double *L, int fix, const Wave64 &wave, double *vr,
                                                 double *vi)
 {
     constexpr int G = is_cplx<OP>() ? HSLP : LSLP;
-    double t0r = 0.0, t0i = 0.0, t1r[3] = {0.0, 0.0, 0.0}, t1i[3] = {0.0, 0.0, 0.0};
+    double ur[Q], ui[Q], br[Q], bi[Q];
+    sweep_f64<G, Q, LTRIAL, is_cplx<OP>()>(F, L, basis_row<Q>(3), basis_row<Q>(fix), wave, ur, ui, br, bi);
+    double t0r = 0.0, t0i = 0.0;
 #pragma unroll
-    for (int p = 0; p < Q; ++p) {
-        double ur = 0.0, ui = 0.0, br[3] = {0.0, 0.0, 0.0}, bi[3] = {0.0, 0.0, 0.0};
-#pragma unroll f64_unroll<OP>()
-        for (int q = 0; q < Q; ++q) {
-            double gr = 0.0, gi = 0.0;
-            kern_f64<G>(T[4 + 3 * p] - S[4 + 3 * q], T[5 + 3 * p] - S[5 + 3 * q], T[6 + 3 * p] - S[6 + 3 * q], S, 1.0,
-                        k, gr, gi);
-            const double w = rule::Rule<Q>::w[q];
-            ur += w * gr;
-            ui += w * gi;
-            if constexpr (is_cplx<OP>()) {
-                if constexpr (TESTFIX) {
-#pragma unroll
-                    for (int e = 0; e < 3; ++e) {
-                        br[e] += w * rule::lam<Q>(e, q) * gr;
-                        bi[e] += w * rule::lam<Q>(e, q) * gi;
-                    }
-                } else {
-                    const double l = fix == 0 ? rule::Rule<Q>::l0[q] : (fix == 1 ? rule::Rule<Q>::l1[q] : rule::Rule<Q>::l2[q]);
-                    br[0] += w * l * gr;
-                    bi[0] += w * l * gi;
-                }
-            }
-        }
-        const double wp = rule::Rule<Q>::w[p];
-        t0r += wp * ur;
-        t0i += wp * ui;
-        if constexpr (is_cplx<OP>()) {
-            if constexpr (TESTFIX) {
-                const double l = fix == 0 ? rule::Rule<Q>::l0[p] : (fix == 1 ? rule::Rule<Q>::l1[p] : rule::Rule<Q>::l2[p]);
-#pragma unroll
-                for (int e = 0; e < 3; ++e) {
-                    t1r[e] += wp * l * br[e];
-                    t1i[e] += wp * l * bi[e];
-                }
-            } else {
-#pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    t1r[d] += wp * rule::lam<Q>(d, p) * br[0];
-                    t1i[d] += wp * rule::lam<Q>(d, p) * bi[0];
-                }
-            }
-        }
+    for (int l = 0; l < Q; ++l) {
+        t0r = fma(rule::Rule<Q>::w[l], ur[l], t0r);
+        if constexpr (is_cplx<OP>()) t0i = fma(rule::Rule<Q>::w[l], ui[l], t0i);
     }
+    // edge opposite the fixed vertex, and the lane triangle's three
+    const int f1 = 4 + 3 * (Q - 3 + (fix + 1) % 3), f2 = 4 + 3 * (Q - 3 + (fix + 2) % 3);
     const double vs = vscale<Q>();
-    double ET[3][3], ES[3][3];
-#pragma unroll
-    for (int e = 0; e < 3; ++e)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const int i1 = 4 + 3 * vpt<Q>((e + 1) % 3) + c, i2 = 4 + 3 * vpt<Q>((e + 2) % 3) + c;
-            ET[e][c] = (T[i1] - T[i2]) * vs;
-            ES[e][c] = (S[i1] - S[i2]) * vs;
-        }
-    const double inv = 1.0 / (T[3] * S[3]);
-    const double nn = is_cplx<OP>() ? (T[0] * S[0] + T[1] * S[1] + T[2] * S[2]) * k * k : 0.0;
+    const double ex = (F[f1] - F[f2]) * vs, ey = (F[f1 + 1] - F[f2 + 1]) * vs, ez = (F[f1 + 2] - F[f2 + 2]) * vs;
+    const double inv = 1.0 / (F[3] * L[3]);
+    const double nn = is_cplx<OP>() ? (F[0] * L[0] + F[1] * L[1] + F[2] * L[2]) * wave.k * wave.k : 0.0;
 #pragma unroll
     for (int e = 0; e < 3; ++e) {
-        const double *et = TESTFIX ? (fix == 0 ? ET[0] : (fix == 1 ? ET[1] : ET[2])) : ET[e];
-        const double *es = TESTFIX ? ES[e] : (fix == 0 ? ES[0] : (fix == 1 ? ES[1] : ES[2]));
-        const double cc = (et[0] * es[0] + et[1] * es[1] + et[2] * es[2]) * inv;
-        vr[e] = cc * t0r - nn * t1r[e];
-        vi[e] = cc * t0i - nn * t1i[e];
+        const int l1 = 4 + 3 * vpt<Q>((e + 1) % 3), l2 = 4 + 3 * vpt<Q>((e + 2) % 3);
+        const double cc = (ex * ((L[l1] - L[l2]) * vs) + ey * ((L[l1 + 1] - L[l2 + 1]) * vs) +
+                           ez * ((L[l1 + 2] - L[l2 + 2]) * vs)) * inv;
+        vr[e] = cc * t0r;
+        vi[e] = cc * t0i;
+        if constexpr (is_cplx<OP>()) {
+            double t1r = 0.0, t1i = 0.0;
+#pragma unroll
+            for (int l = 0; l < Q; ++l) {
+                const double wl = rule::Rule<Q>::w[l] * rule::lam<Q>(e, l);
+                t1r = fma(wl, br[l], t1r);
+                t1i = fma(wl, bi[l], t1i);
+            }
+            vr[e] -= nn * t1r;
+            vi[e] -= nn * t1i;
+        }
     }
 }
 
-// FP64: general form with explicit test basis (a) and trial basis (b); the
-// free side (a or b == -1) is returned for all three local vertices.
-template <int OP, int Q, bool TESTFIX>
-__device__ __forceinline__ void pair_p1_f64(const double *T, const double *S, int fixloc, double k, double *vr,
-                                            double *vi)
+// FP64: the fixed triangle's vertex `fix` against the lane triangle's three.
+template <int OP, int Q, bool LTRIAL, typename FP>
+__device__ __forceinline__ void pair_p1_f64(FP F, const double *L, int fix, const Wave64 &wave, double *vr, double *vi)
 {
+    double ur[Q], ui[Q], xr[Q], xi[Q];
+    sweep_f64<OP, Q, LTRIAL, false>(F, L, basis_row<Q>(fix), nullptr, wave, ur, ui, xr, xi);
 #pragma unroll
-    for (int e = 0; e < 3; ++e) vr[e] = vi[e] = 0.0;
+    for (int e = 0; e < 3; ++e) {
+        vr[e] = vi[e] = 0.0;
 #pragma unroll
-    for (int p = 0; p < Q; ++p) {
-        double sr[3] = {0.0, 0.0, 0.0}, si[3] = {0.0, 0.0, 0.0};
-#pragma unroll f64_unroll<OP>()
-        for (int q = 0; q < Q; ++q) {
-            double kr = 0.0, ki = 0.0;
-            kern_f64<OP>(T[4 + 3 * p] - S[4 + 3 * q], T[5 + 3 * p] - S[5 + 3 * q], T[6 + 3 * p] - S[6 + 3 * q], S,
-                         rule::Rule<Q>::w[q], k, kr, ki);
-            if constexpr (TESTFIX) {
-#pragma unroll
-                for (int e = 0; e < 3; ++e) {
-                    sr[e] += rule::lam<Q>(e, q) * kr;
-                    si[e] += rule::lam<Q>(e, q) * ki;
-                }
-            } else {
-                const double l = fixloc == 0 ? rule::Rule<Q>::l0[q] : (fixloc == 1 ? rule::Rule<Q>::l1[q] : rule::Rule<Q>::l2[q]);
-                sr[0] += l * kr;
-                si[0] += l * ki;
-            }
-        }
-        if constexpr (TESTFIX) {
-            const double l = fixloc == 0 ? rule::Rule<Q>::l0[p] : (fixloc == 1 ? rule::Rule<Q>::l1[p] : rule::Rule<Q>::l2[p]);
-            const double w = rule::Rule<Q>::w[p] * l;
-#pragma unroll
-            for (int e = 0; e < 3; ++e) {
-                vr[e] += w * sr[e];
-                vi[e] += w * si[e];
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 3; ++e) {
-                const double w = rule::Rule<Q>::w[p] * rule::lam<Q>(e, p);
-                vr[e] += w * sr[0];
-                vi[e] += w * si[0];
-            }
+        for (int l = 0; l < Q; ++l) {
+            const double wl = rule::Rule<Q>::w[l] * rule::lam<Q>(e, l);
+            vr[e] = fma(wl, ur[l], vr[e]);
+            if constexpr (is_cplx<OP>()) vi[e] = fma(wl, ui[l], vi[e]);
         }
     }
 }
@@ -923,16 +925,16 @@ __device__ __forceinline__ void p0_body_f64(const ReqDev &R, const EntryBlock &B
     const int li = ch.x + (act ? t : 0);
     const int tf = B.s0;
     const int tn = R.lane[li];
-    const int test = ROWFIX ? tf : tn, trial = ROWFIX ? tn : tf;
     const bool sep = B.lgeo && !B.lmeta;   // separated sides: no vertex-sharing pair (workgroup-uniform)
-    const bool adj = !sep && share_vertex(R.vtx[test], R.vtx[trial]);
+    const bool adj = !sep && share_vertex(R.vtx[tf], R.vtx[tn]);
     double vr = 0.0, vi = 0.0;
     if (!adj) {
-        double T[n64<Q>()], S[n64<Q>()];
-        load64<Q>(R.g64, test, T);
-        load64<Q>(R.g64, trial, S);
-        pair_p0_f64<OP, Q>(T, S, R.k, vr, vi);
-        const double sc = T[3] * S[3] * kInv4Pi;
+        double L[n64<Q>()];
+        load64<Q>(R.g64, tn, L);
+        // the fixed record is the workgroup's: scalar loads
+        const ConstF64 F = (ConstF64)(R.g64 + (size_t)tf * kGeo64Stride);
+        pair_p0_f64<OP, Q, ROWFIX>(F, L, wave64(R), vr, vi);
+        const double sc = F[3] * L[3] * kInv4Pi;
         vr *= sc;
         vi *= sc;
     } else if (act && R.near_error) {
@@ -1300,6 +1302,7 @@ __device__ __forceinline__ void p1_body_f64(const ReqDev &R, const EntryBlock &B
     const int4 vn = sep ? make_int4(-1, -1, -1, -1) : R.vtx[tn];
     double L[n64<Q>()];
     load64<Q>(R.g64, tn, L);
+    const Wave64 wave = wave64(R);
     double ar[3] = {0.0, 0.0, 0.0}, ai[3] = {0.0, 0.0, 0.0};
     const int s0 = B.s0, s1 = B.s1;
     SegPrefetch pf;
@@ -1312,21 +1315,13 @@ __device__ __forceinline__ void p1_body_f64(const ReqDev &R, const EntryBlock &B
                 if (act && R.near_error) put<SYS>(R.status, 1);
                 continue;
             }
-            double F[n64<Q>()];
-#pragma unroll
-            for (int i = 0; i < n64<Q>(); ++i) F[i] = sG[s][i];
-            const int loc = sL[s];
+            const double *F = sG[s];
+            const int loc = __builtin_amdgcn_readfirstlane(sL[s]);   // the wave's: selects the basis row
             double vr[3], vi[3];
-            if constexpr (is_hyp<OP>()) {
-                if constexpr (ROWFIX)
-                    pair_p1_hyp_f64<OP, Q, true>(F, L, loc, R.k, vr, vi);
-                else
-                    pair_p1_hyp_f64<OP, Q, false>(L, F, loc, R.k, vr, vi);
-            } else if constexpr (ROWFIX) {
-                pair_p1_f64<OP, Q, true>(F, L, loc, R.k, vr, vi);
-            } else {
-                pair_p1_f64<OP, Q, false>(L, F, loc, R.k, vr, vi);
-            }
+            if constexpr (is_hyp<OP>())
+                pair_p1_hyp_f64<OP, Q, ROWFIX>(F, L, loc, wave, vr, vi);
+            else
+                pair_p1_f64<OP, Q, ROWFIX>(F, L, loc, wave, vr, vi);
             const double sc = F[3] * L[3] * kInv4Pi;
 #pragma unroll
             for (int e = 0; e < 3; ++e) {
@@ -1857,36 +1852,41 @@ __device__ __forceinline__ void pair_local_f32(const float *T, const float *S, c
     }
 }
 
-// The same in FP64 from absolute points.
-template <int OP, int Q>
-__device__ __forceinline__ void pair_local_f64(const double *T, const double *S, double k, double (*Mr)[3],
+// The same in FP64 from absolute points; the test record T is wave-uniform.
+template <int OP, int Q, typename FP>
+__device__ __forceinline__ void pair_local_f64(FP T, const double *S, const Wave64 &wave, double (*Mr)[3],
                                                double (*Mi)[3])
 {
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
         for (int b = 0; b < 3; ++b) Mr[a][b] = Mi[a][b] = 0.0;
+#pragma unroll 1
+    for (int p = 0; p < Q; ++p) {
+        const double px = T[4 + 3 * p], py = T[5 + 3 * p], pz = T[6 + 3 * p];
+        double sr[3] = {0.0, 0.0, 0.0}, si[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        double ur[3] = {0.0, 0.0, 0.0}, ui[3] = {0.0, 0.0, 0.0};
-#pragma unroll f64_unroll<OP>()
-        for (int p = 0; p < Q; ++p) {
-            double kr = 0.0, ki = 0.0;
-            kern_f64<OP>(T[4 + 3 * p] - S[4 + 3 * q], T[5 + 3 * p] - S[5 + 3 * q], T[6 + 3 * p] - S[6 + 3 * q], S,
-                         rule::Rule<Q>::w[p], k, kr, ki);
+        for (int q = 0; q < Q; ++q) {
+            const double dx = px - S[4 + 3 * q], dy = py - S[5 + 3 * q], dz = pz - S[6 + 3 * q];
+            double gr, gi;
+            green_f64<OP>(fma(dx, dx, fma(dy, dy, dz * dz)), wave, gr, gi);
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                ur[a] += rule::lam<Q>(a, p) * kr;
-                ui[a] += rule::lam<Q>(a, p) * ki;
+            for (int b = 0; b < 3; ++b) {
+                const double wl = rule::Rule<Q>::w[q] * rule::lam<Q>(b, q);
+                sr[b] = fma(wl, gr, sr[b]);
+                if constexpr (is_cplx<OP>()) si[b] = fma(wl, gi, si[b]);
             }
         }
+        double an = 1.0;
+        if constexpr (is_dlp<OP>()) an = fma(px - S[4], S[0], fma(py - S[5], S[1], (pz - S[6]) * S[2]));
 #pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const double wl = rule::Rule<Q>::w[q] * rule::lam<Q>(b, q);
+        for (int a = 0; a < 3; ++a) {
+            double wa = basis_row<Q>(a)[p];
+            if constexpr (is_dlp<OP>()) wa *= an;
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                Mr[a][b] += wl * ur[a];
-                Mi[a][b] += wl * ui[a];
+            for (int b = 0; b < 3; ++b) {
+                Mr[a][b] = fma(wa, sr[b], Mr[a][b]);
+                if constexpr (is_cplx<OP>()) Mi[a][b] = fma(wa, si[b], Mi[a][b]);
             }
         }
     }
@@ -1963,7 +1963,7 @@ template <int OP, int Q>
 __global__ __launch_bounds__(kBlockLanes) void k_local_f64(const double *__restrict__ g64, const int4 *__restrict__ vtx,
                                                            const int32_t *__restrict__ test, int ntest,
                                                            const int32_t *__restrict__ trial, int ntrial,
-                                                           double *__restrict__ Lr, double *__restrict__ Li, double k)
+                                                           double *__restrict__ Lr, double *__restrict__ Li, Wave64 wave)
 {
     constexpr int W = n64<Q>();
     __shared__ double sT[kLocalTile][W];
@@ -1990,10 +1990,8 @@ __global__ __launch_bounds__(kBlockLanes) void k_local_f64(const double *__restr
 #pragma unroll
                 for (int b = 0; b < 3; ++b) Mr[a][b] = Mi[a][b] = 0.0;
         } else {
-            double T[W];
-#pragma unroll
-            for (int w = 0; w < W; ++w) T[w] = sT[i][w];
-            pair_local_f64<OP, Q>(T, S, k, Mr, Mi);
+            const double *T = sT[i];
+            pair_local_f64<OP, Q>(T, S, wave, Mr, Mi);
             const double sc = T[3] * S[3] * kInv4Pi;
 #pragma unroll
             for (int a = 0; a < 3; ++a)
@@ -2086,6 +2084,7 @@ hipError_t local_launch(bool fp32, int q, const bem_mesh &m, const int32_t *test
                     (unsigned)((ntest + kLocalTile - 1) / kLocalTile));
     const float kf = (float)k;
     const double kk = k / (2.0 * 3.14159265358979323846);
+    const Wave64 wave{k, 2.0 * kk, wave_low(k, kk)};
     if (fp32) {
         if (q == 6)
             hipLaunchKernelGGL((k_local_f32<OP, 6>), grid, dim3(kBlockLanes), 0, s, m.d_g32, m.d_vtx, test, ntest,
@@ -2096,10 +2095,10 @@ hipError_t local_launch(bool fp32, int q, const bem_mesh &m, const int32_t *test
     } else {
         if (q == 6)
             hipLaunchKernelGGL((k_local_f64<OP, 6>), grid, dim3(kBlockLanes), 0, s, m.d_g64, m.d_vtx, test, ntest,
-                               trial, ntrial, (double *)Lr, (double *)Li, k);
+                               trial, ntrial, (double *)Lr, (double *)Li, wave);
         else
             hipLaunchKernelGGL((k_local_f64<OP, 4>), grid, dim3(kBlockLanes), 0, s, m.d_g64, m.d_vtx, test, ntest,
-                               trial, ntrial, (double *)Lr, (double *)Li, k);
+                               trial, ntrial, (double *)Lr, (double *)Li, wave);
     }
     return hipGetLastError();
 }

@@ -310,8 +310,7 @@ int make_resident(const bem_mesh &m, int space, const std::vector<std::pair<cons
                 if (lists[i].first) build_lane_set(m, space, lists[i].first, lists[i].second, sets[i]);
         });
     for (auto &x : th) x.join();
-    // one int32 buffer: per set, the chunk table (16-byte aligned int4
-    // records), lanes, segment pointers and segments
+    // one int32 buffer: per set, lanes, segment pointers and segments
     auto pad4 = [](size_t x) { return (x + 3) & ~(size_t)3; };
     size_t total = 0;
     for (auto &ls : sets) total += pad4(ls.ints());
@@ -322,7 +321,7 @@ int make_resident(const bem_mesh &m, int space, const std::vector<std::pair<cons
     for (size_t i = 0; i < n; ++i) {
         at[i] = pos;
         const LaneSet &ls = sets[i];
-        for (const std::vector<int32_t> *v : {&ls.chunk, &ls.lane, &ls.seg_ptr, &ls.seg}) {
+        for (const std::vector<int32_t> *v : {&ls.lane, &ls.seg_ptr, &ls.seg}) {
             std::copy(v->begin(), v->end(), host.begin() + pos);
             pos += v->size();
         }
@@ -370,12 +369,10 @@ int make_resident(const bem_mesh &m, int space, const std::vector<std::pair<cons
         r.nseg = (int64_t)ls.seg.size();
         r.nchunk = ls.nchunk();
         r.ndistinct = ls.ndistinct;
-        r.chunk = ls.chunk.empty() ? nullptr : reinterpret_cast<const int4 *>(base);
         r.chunk_host = out.chunk_host.data() + ch_at[i];
         const bool has = out.geo && !ls.lane.empty();
         r.geo = has ? out.geo + kGeo32Stride * lane_at[i] : nullptr;
         r.meta = has ? out.meta + lane_at[i] : nullptr;
-        base += ls.chunk.size();
         r.lane = ls.lane.empty() ? nullptr : base;
         base += ls.lane.size();
         r.seg_ptr = ls.seg_ptr.empty() ? nullptr : base;

@@ -744,12 +744,10 @@ void describe_request(const Request &r, ReqDev &d)
     d.g64 = m.d_g64;
     d.vtx = m.d_vtx;
     if (r.ext) {
-        d.chunk = r.ext->chunk;
         d.lane = r.ext->lane;
         d.seg_ptr = r.ext->seg_ptr;
         d.seg = r.ext->seg;
     } else {
-        d.chunk = nullptr;
         d.lane = d.seg_ptr = d.seg = nullptr;
     }
     d.lpos = nullptr;
@@ -769,6 +767,7 @@ void describe_request(const Request &r, ReqDev &d)
     d.near_error = r.near == BEM_NEAR_ERROR ? 1 : 0;
     d.k = r.k;
     d.kk = r.k / (2.0 * 3.14159265358979323846);
+    d.kl = wave_low(r.k, d.kk);
     d.out = nullptr;
     d.status = nullptr;
 }
@@ -786,8 +785,6 @@ size_t stage_own_inputs(const Request &r, char *host_base, char *dev_base, size_
         dv += 4 * v.size();
         return dp;
     };
-    // the chunk table (int4 records) goes first: the section starts 16-byte aligned
-    d.chunk = reinterpret_cast<const int4 *>(put(r.own.chunk));
     d.lane = put(r.own.lane);
     d.seg_ptr = put(r.own.seg_ptr);
     d.seg = put(r.own.seg);

@@ -40,14 +40,22 @@
 // (omega = k |c|, pi the Laplace case's radial polynomial, identical pairs
 // after folding xi eta1 eta2 into one radius with weight (1 - p)^2) taken
 // as its power series sum_n (i omega)^n mu_n c_n / n! (mu_n the moments of
-// pi, c_n = 1, or 1 - n with the double layer's factor), 48 terms in Horner
-// form: ~1e-14 relative at omega = 6 (two elements per wavelength reach
-// omega ~ 2 pi), 5e-10 at omega = 12 where the alternating terms cancel.
+// pi, c_n = 1, or 1 - n with the double layer's factor), up to 48 terms in
+// Horner form (series_terms): ~1e-14 relative at omega = 6 (two elements per
+// wavelength reach omega ~ 2 pi), 5e-10 at omega = 12 where the alternating
+// terms cancel.
+// What bounds these kernels is FP64 arithmetic: one workgroup per pair, a
+// thousand or more products per thread, 184 bytes read and at most 160 written.
+// P1 Helmholtz single layer, 2,900 pairs of a 100 x 100 leaf at 10 elements per
+// wavelength: 101 us (336 us with 48 terms from LDS, the nine entries
+// accumulated at every point and a tree reduction); P1 Laplace, the pairs of
+// one dense leaf: 20 us a launch in an H-matrix assembly (41 us).
 // The adjoint double layer is the double layer with test and trial exchanged
 // (the host builds its items that way).
 #include <hip/hip_runtime.h>
 
 #include "bem_internal.hpp"
+#include "f64_math.hpp"
 
 namespace bem {
 namespace {
@@ -87,94 +95,108 @@ struct Cx {
     double re, im;
 };
 
-// Power series of the radial integral: coefficients of omega^(2m) (real
-// part) and omega^(2m+1) (imaginary part), signs of i^n included.
+// Power series of the radial integrals
+//   int_0^1 rho^A (1 - rho)^B e^{i om rho} (1 - i om rho)^[DL] d rho  (B <= 2):
+// coefficients of om^(2m) (real part) and om^(2m+1) (imaginary part), signs of
+// i^n included, moments of rho^A (1 - rho)^B.  N = 1: one integral; N = 3: A,
+// A + 1 and A + 2 interleaved (the P1 local matrices, whose barycentrics are
+// affine in rho).
 constexpr int kSeries = 48;
-template <int POLY, bool DL>
-struct RadialSeries {
-    double re[kSeries / 2], im[kSeries / 2];
-    constexpr RadialSeries() : re(), im()
+template <int A, int B, bool DL, int N>
+struct RadialTable {
+    double v[2 * N * (kSeries / 2)];
+    constexpr RadialTable() : v()
     {
-        double fact = 1.0;
-        for (int n = 0; n < kSeries; ++n) {
-            if (n > 0) fact *= n;
-            const double nn = n;
-            const double mu = POLY == 0 ? 2.0 / ((nn + 1) * (nn + 2) * (nn + 3))
-                            : POLY == 1 ? 1.0 / ((nn + 2) * (nn + 3))
-                            : POLY == 2 ? 1.0 / ((nn + 1) * (nn + 2))
-                            : POLY == 3 ? 1.0 / (nn + 3)
-                                        : 1.0 / (nn + 2);
-            const double a = mu * (DL ? 1.0 - nn : 1.0) / fact;
-            const int m = n / 2;
-            const double sgn = (m % 2) ? -1.0 : 1.0;
-            if (n % 2 == 0)
-                re[m] = sgn * a;
-            else
-                im[m] = sgn * a;
+        for (int j = 0; j < N; ++j) {
+            double fact = 1.0;
+            for (int n = 0; n < kSeries; ++n) {
+                if (n > 0) fact *= n;
+                const double e = n + A + j;
+                const double mu = B == 0 ? 1.0 / (e + 1)
+                                : B == 1 ? 1.0 / ((e + 1) * (e + 2))
+                                         : 2.0 / ((e + 1) * (e + 2) * (e + 3));
+                const double a = mu * (DL ? 1.0 - n : 1.0) / fact;
+                const int m = n / 2;
+                v[2 * N * m + 2 * j + n % 2] = (m % 2) ? -a : a;
+            }
         }
     }
 };
+// P0: identical (after folding xi eta1 eta2 into one radius), common edge and
+// common vertex; single and double layer
+__constant__ RadialTable<0, 2, false, 1> c_rad_s0{};
+__constant__ RadialTable<1, 1, false, 1> c_rad_s1{};
+__constant__ RadialTable<2, 0, false, 1> c_rad_s2{};
+__constant__ RadialTable<0, 1, true, 1> c_rad_d1{};
+__constant__ RadialTable<1, 0, true, 1> c_rad_d2{};
+// P1: identical and common vertex, common edge
+__constant__ RadialTable<2, 0, false, 3> c_tab_s2{};
+__constant__ RadialTable<1, 1, false, 3> c_tab_s1{};
+__constant__ RadialTable<1, 0, true, 3> c_tab_d2{};
+__constant__ RadialTable<0, 1, true, 3> c_tab_d1{};
 
-// int_0^1 pi(rho) e^{i om rho} (1 - i om rho)^[DL] d rho.
-template <int POLY, bool DL>
-__device__ __forceinline__ Cx radial(double om)
+// Series terms a pair needs: the smallest multiple of 8 for which
+// om^n / n! <= 2^-64 at the largest omega of its integration domain, so that
+// what is left out is far below the rounding of what is kept; all 48 beyond
+// om = 5.2.  omega = k |c| <= k times the largest distance of two of the pair's
+// vertices (c is a difference of points of the two triangles, |c| convex in
+// both).  Ten elements per wavelength reach om = 1.3 and take 24 terms, half
+// the work of the fixed 48; the count is the workgroup's, so the coefficients
+// come through scalar loads and feed two evaluations each (held in LDS they
+// cost a broadcast read per product, which bound the kernel).
+__device__ __forceinline__ int series_terms(const NearItem &it)
 {
-    constexpr RadialSeries<POLY, DL> c{};
-    const double w2 = om * om;
-    double r = c.re[kSeries / 2 - 1], i = c.im[kSeries / 2 - 1];
-#pragma unroll
-    for (int m = kSeries / 2 - 2; m >= 0; --m) {
-        r = fma(r, w2, c.re[m]);
-        i = fma(i, w2, c.im[m]);
-    }
-    return {r, om * i};
+    const int nv = 3 + it.kind;
+    double d2 = 0.0;
+    for (int i = 0; i < nv; ++i)
+        for (int j = i + 1; j < nv; ++j) {
+            const double x = it.v[3 * i] - it.v[3 * j], y = it.v[3 * i + 1] - it.v[3 * j + 1],
+                         z = it.v[3 * i + 2] - it.v[3 * j + 2];
+            d2 = fmax(d2, x * x + y * y + z * z);
+        }
+    const double w2 = d2 * it.k * it.k;
+    const int n = w2 <= 0.0147 * 0.0147 ? 8 : w2 <= 0.425 * 0.425 ? 16 : w2 <= 1.54 * 1.54 ? 24
+                : w2 <= 3.19 * 3.19 ? 32 : w2 <= 5.2 * 5.2 ? 40 : kSeries;
+    return __builtin_amdgcn_readfirstlane(n);
 }
 
-// int_0^1 rho^A (1 - rho)^B e^{i om rho} (1 - i om rho)^[DL] d rho (B <= 2)
-// by the same 48-term series (moments of rho^A (1 - rho)^B).
-template <int A, int B, bool DL>
-struct MomentSeries {
-    double re[kSeries / 2], im[kSeries / 2];
-    constexpr MomentSeries() : re(), im()
-    {
-        double fact = 1.0;
-        for (int n = 0; n < kSeries; ++n) {
-            if (n > 0) fact *= n;
-            const double e = n + A;
-            const double mu = B == 0 ? 1.0 / (e + 1) : B == 1 ? 1.0 / ((e + 1) * (e + 2)) : 2.0 / ((e + 1) * (e + 2) * (e + 3));
-            const double a = mu * (DL ? 1.0 - n : 1.0) / fact;
-            const int m = n / 2;
-            const double sgn = (m % 2) ? -1.0 : 1.0;
-            if (n % 2 == 0)
-                re[m] = sgn * a;
-            else
-                im[m] = sgn * a;
+// N radial integrals at two omegas, Horner in omega^2, highest term first.
+template <int N>
+__device__ __forceinline__ void radial2(double oa, double ob, const double *tab, int terms, Cx *Ja, Cx *Jb)
+{
+    const double wa = oa * oa, wb = ob * ob;
+#pragma unroll
+    for (int j = 0; j < N; ++j) Ja[j] = Jb[j] = {0.0, 0.0};
+#pragma unroll 1
+    for (int m = terms / 2 - 4; m >= 0; m -= 4) {
+#pragma unroll
+        for (int u = 3; u >= 0; --u) {
+            const double *c = tab + 2 * N * (m + u);
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                Ja[j].re = fma(Ja[j].re, wa, c[2 * j]);
+                Ja[j].im = fma(Ja[j].im, wa, c[2 * j + 1]);
+                Jb[j].re = fma(Jb[j].re, wb, c[2 * j]);
+                Jb[j].im = fma(Jb[j].im, wb, c[2 * j + 1]);
+            }
         }
     }
-};
-
-template <int A, int B, bool DL>
-__device__ __forceinline__ Cx moment(double om)
-{
-    constexpr MomentSeries<A, B, DL> c{};
-    const double w2 = om * om;
-    double r = c.re[kSeries / 2 - 1], i = c.im[kSeries / 2 - 1];
 #pragma unroll
-    for (int m = kSeries / 2 - 2; m >= 0; --m) {
-        r = fma(r, w2, c.re[m]);
-        i = fma(i, w2, c.im[m]);
+    for (int j = 0; j < N; ++j) {
+        Ja[j].im *= oa;
+        Jb[j].im *= ob;
     }
-    return {r, om * i};
 }
 
 // Helmholtz share of this thread (op 2 single layer, op 3 double layer),
-// without jt js / 4 pi (and (a.n_y) for common-edge double layers).
+// without jt js / 4 pi and (a.n_y) for common-edge double layers.
 template <int OP>
 __device__ Cx pair_part_helmholtz(const NearItem &it, const double *sx, const double *sw)
 {
     constexpr bool DL = OP == 3;
     const int t = threadIdx.x;
     const double k = it.k;
+    const int terms = series_terms(it);
     if (it.kind == 0) {
         if (DL || t >= 3 * kIdPts) return {0.0, 0.0};
         const V3 V0 = ld(it.v), V1 = ld(it.v + 3), V2 = ld(it.v + 6);
@@ -183,8 +205,9 @@ __device__ Cx pair_part_helmholtz(const NearItem &it, const double *sx, const do
         const double e = (c_x[kk % kGL] + (double)(kk / kGL)) * (1.0 / kIdPanels);
         const double w = c_w[kk % kGL] * (1.0 / kIdPanels);
         const V3 c = line == 0 ? fma3(e, E1, E2) : (line == 1 ? fma3(e, E2, E1) : fma3(-e, E1, mul(1.0 - e, E2)));
-        const double ri = rsqrt(dot(c, c));
-        const Cx rad = radial<0, false>(k / ri);
+        const double c2 = dot(c, c), ri = rsqrt64(c2);
+        Cx rad, unused;
+        radial2<1>(k * c2 * ri, 0.0, c_rad_s0.v, terms, &rad, &unused);
         return {w * ri * rad.re, w * ri * rad.im};
     }
     double ar = 0.0, ai = 0.0;
@@ -204,14 +227,20 @@ __device__ Cx pair_part_helmholtz(const NearItem &it, const double *sx, const do
         } else {
             c0 = fma3(-p, E, mul(-q1, b)), c1 = a, s1c = 0.0, s1q = 1.0, fw = 1.0;
         }
-        for (int j = 0; j < kPts / 4; ++j) {
-            const double q = sx[g + 4 * j];
-            const V3 c = fma3(q, c1, c0);
-            const double ri = rsqrt(dot(c, c));
-            const Cx rad = radial<DL ? 2 : 1, DL>(k / ri);
-            const double f = sw[g + 4 * j] * (DL ? fma(q, s1q, s1c) * ri * ri * ri : ri);
-            ar += f * rad.re;
-            ai += f * rad.im;
+        for (int j = 0; j < kPts / 4; j += 2) {
+            double f[2], om[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const double q = sx[g + 4 * (j + h)];
+                const V3 c = fma3(q, c1, c0);
+                const double c2 = dot(c, c), ri = rsqrt64(c2);
+                f[h] = sw[g + 4 * (j + h)] * (DL ? fma(q, s1q, s1c) * ri * ri * ri : ri);
+                om[h] = k * c2 * ri;
+            }
+            Cx J[2];
+            radial2<1>(om[0], om[1], DL ? c_rad_d1.v : c_rad_s1.v, terms, J, J + 1);
+            ar += f[0] * J[0].re + f[1] * J[1].re;
+            ai += f[0] * J[0].im + f[1] * J[1].im;
         }
         const double wf = sw[ip] * fw;
         return {wf * ar, wf * ai};
@@ -224,8 +253,9 @@ __device__ Cx pair_part_helmholtz(const NearItem &it, const double *sx, const do
     for (int kz = 0; kz < kPts; ++kz) {
         const double z = sx[kz], wz = sw[kz] * z;
         const V3 d1 = fma3(-z, b, a), d2 = fma3(z, a, mul(-1.0, b));
-        const double r1 = rsqrt(dot(d1, d1)), r2 = rsqrt(dot(d2, d2));
-        const Cx g1 = radial<DL ? 4 : 3, DL>(k / r1), g2 = radial<DL ? 4 : 3, DL>(k / r2);
+        const double q1 = dot(d1, d1), q2 = dot(d2, d2), r1 = rsqrt64(q1), r2 = rsqrt64(q2);
+        Cx g1, g2;
+        radial2<1>(k * q1 * r1, k * q2 * r2, DL ? c_rad_d2.v : c_rad_s2.v, terms, &g1, &g2);
         const double f1 = wz * an * (DL ? r1 * r1 * r1 : r1);
         const double f2 = wz * an * (DL ? z * r2 * r2 * r2 : r2);
         ar += f1 * g1.re + f2 * g2.re;
@@ -240,7 +270,7 @@ __device__ Cx pair_part_helmholtz(const NearItem &it, const double *sx, const do
 template <int OP>
 __device__ __forceinline__ double kern(V3 c, double num)
 {
-    const double ri = rsqrt(dot(c, c));
+    const double ri = rsqrt64(dot(c, c));
     if constexpr (OP == 0) return ri;
     return num * ri * ri * ri;
 }
@@ -320,36 +350,43 @@ __device__ double pair_scale(const NearItem &it)
     return radial * it.jt * it.js * kInv4PiD;
 }
 
+// Sum of x over the wavefront in a fixed order (butterfly), in every lane.
+__device__ __forceinline__ double wave_sum(double x)
+{
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) x += __shfl_xor(x, h);
+    return x;
+}
+
+// The pair's value, in thread 0: butterfly sums within the wavefronts, then
+// the four wavefronts in order (a tree over 256 LDS words took eight barriers
+// for what is a few hundred products per thread).
 template <int OP>
 __device__ Cx pair_value(const NearItem &it)
 {
     __shared__ double sx[kPts], sw[kPts];
-    __shared__ double red[2][kNearThreads];
+    __shared__ double red[2][kNearThreads / 64];
     const int t = threadIdx.x;
     if (t < kPts) {
         sx[t] = 0.5 * (c_x[t % kGL] + (double)(t / kGL));
         sw[t] = 0.5 * c_w[t % kGL];
     }
     __syncthreads();
-    if constexpr (OP >= 2) {
-        const Cx v = pair_part_helmholtz<OP>(it, sx, sw);
-        red[0][t] = v.re;
-        red[1][t] = v.im;
-    } else {
-        red[0][t] = pair_part<OP>(it, sx, sw);
-        red[1][t] = 0.0;
+    Cx v{0.0, 0.0};
+    if constexpr (OP >= 2)
+        v = pair_part_helmholtz<OP>(it, sx, sw);
+    else
+        v.re = pair_part<OP>(it, sx, sw);
+    v.re = wave_sum(v.re);
+    if constexpr (OP >= 2) v.im = wave_sum(v.im);
+    if ((t & 63) == 0) {
+        red[0][t >> 6] = v.re;
+        red[1][t >> 6] = v.im;
     }
     __syncthreads();
-    // fixed-order tree reduction over the workgroup
-    for (int h = kNearThreads / 2; h > 0; h >>= 1) {
-        if (t < h) {
-            red[0][t] += red[0][t + h];
-            red[1][t] += red[1][t + h];
-        }
-        __syncthreads();
-    }
     const double sc = pair_scale<OP>(it);
-    return {red[0][0] * sc, red[1][0] * sc};
+    return {(red[0][0] + red[0][1] + red[0][2] + red[0][3]) * sc,
+            (red[1][0] + red[1][1] + red[1][2] + red[1][3]) * sc};
 }
 
 template <int OP, bool FP32>
@@ -377,282 +414,176 @@ __global__ __launch_bounds__(kNearThreads) void k_near_p0(const NearItem *__rest
 // the pair's barycentrics in the item's vertex order (test (V0, V1, V2),
 // (P, Q, A), (P, A, B); trial (V0, V1, V2), (P, Q, B), (P, C, D) for the
 // identical, common-edge and common-vertex kinds).  Same coordinates and face
-// rules as P0; the barycentrics are affine in the radius (bilinear in radius
-// and along-edge coordinate; for identical pairs polynomial in xi, eta1,
-// eta2), so those directions take Gauss rules exact for the degrees that
-// occur: 3 points for the radius (degree 4), 2 for the rest (degree <= 3).
+// rules as P0.  The barycentrics are affine in the radius, so every point of
+// the remaining rule needs the radial integral against 1, rho and rho^2
+// (J0, J1, J2: numbers for Laplace, the power series for Helmholtz).  What the
+// barycentrics add over the loops a thread runs is polynomial, so the loops
+// sum a few moments and the nine entries are formed from them: at the end
+// (common vertex: the loop coordinate z enters linearly) or per point from
+// averages over the along-edge coordinate (common edge).
 
-// 2- and 3-point Gauss-Legendre rules on [0, 1].
-constexpr double kG2x[2] = {0.5 - 0.28867513459481288225, 0.5 + 0.28867513459481288225};
-constexpr double kG3x[3] = {0.5 - 0.38729833462074168852, 0.5, 0.5 + 0.38729833462074168852};
-constexpr double kG3w[3] = {5.0 / 18.0, 8.0 / 18.0, 5.0 / 18.0};
-
-struct L3 {
-    double v[3];
-};
-
-// acc[3a + b] += w * l[a] * m[b]
-__device__ __forceinline__ void outer_acc(double *acc, double w, const L3 &l, const L3 &m)
+// Radial moments of the kernel: Laplace closed forms, 1 / (n + 1) or
+// 1 / ((n + 1) (n + 2)).
+template <int OP, bool EDGE>
+__device__ __forceinline__ void moments(double oa, double ob, int terms, Cx *Ja, Cx *Jb)
 {
+    constexpr bool DL = OP == 1 || OP == 3;
+    if constexpr (OP >= 2) {
+        if constexpr (EDGE) radial2<3>(oa, ob, DL ? c_tab_d1.v : c_tab_s1.v, terms, Ja, Jb);
+        else radial2<3>(oa, ob, DL ? c_tab_d2.v : c_tab_s2.v, terms, Ja, Jb);
+    } else {
+        constexpr double n = (EDGE ? 1 : 2) - (DL ? 1 : 0);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const double wa = w * l.v[a];
-#pragma unroll
-        for (int b = 0; b < 3; ++b) acc[3 * a + b] = fma(wa, m.v[b], acc[3 * a + b]);
+        for (int j = 0; j < 3; ++j)
+            Ja[j] = Jb[j] = {EDGE ? 1.0 / ((n + j + 1) * (n + j + 2)) : 1.0 / (n + j + 1), 0.0};
     }
 }
 
-// This thread's share of the 9 local integrals (without jt js / 4 pi and,
-// for the common-edge double layer, without (a.n_y)).
 template <int OP>
-__device__ void pair_part_p1(const NearItem &it, const double *sx, const double *sw, double *acc)
+__device__ __forceinline__ void cfma(Cx &acc, double w, const Cx &x)
 {
-    const int t = threadIdx.x;
-    if (it.kind == 0) {
-        if (OP == 1 || t >= 3 * kIdPts) return;
-        const V3 V0 = ld(it.v), V1 = ld(it.v + 3), V2 = ld(it.v + 6);
-        const V3 E1 = sub(V1, V0), E2 = sub(V2, V1);
-        const int line = t / kIdPts, kk = t - line * kIdPts;
-        const double e3 = (c_x[kk % kGL] + (double)(kk / kGL)) * (1.0 / kIdPanels);
-        const double w3 = c_w[kk % kGL] * (1.0 / kIdPanels);
-        const V3 c = line == 0 ? fma3(e3, E1, E2) : (line == 1 ? fma3(e3, E2, E1) : fma3(-e3, E1, mul(1.0 - e3, E2)));
-        const double ic = rsqrt(dot(c, c));
-        // barycentrics of V0 + a E1 + b E2: (1 - a, a - b, b)
-        auto lam = [](double a, double b) { return L3{{1.0 - a, a - b, b}}; };
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int l = 0; l < 2; ++l) {
-                    const double xi = kG3x[i], e1 = kG2x[j], e2 = kG2x[l];
-                    double xa, xb, ya, yb;
-                    if (line == 0) {
-                        xa = xi, xb = xi * (1.0 - e1 + e1 * e2), ya = xi * (1.0 - e1 * e2 * e3), yb = xi * (1.0 - e1);
-                    } else if (line == 1) {
-                        xa = xi, xb = xi * e1 * (1.0 - e2 + e2 * e3), ya = xi * (1.0 - e1 * e2), yb = xi * e1 * (1.0 - e2);
-                    } else {
-                        xa = xi * (1.0 - e1 * e2 * e3), xb = xi * e1 * (1.0 - e2 * e3), ya = xi, yb = xi * e1 * (1.0 - e2);
-                    }
-                    const L3 lx = lam(xa, xb), ly = lam(ya, yb);
-                    const double w = w3 * kG3w[i] * 0.25 * xi * xi * e1 * ic;
-                    // the region and its mirror (x and y exchanged)
-                    outer_acc(acc, w, lx, ly);
-                    outer_acc(acc, w, ly, lx);
-                }
-        return;
-    }
-    if (it.kind == 1) {
-        const V3 P = ld(it.v), Q = ld(it.v + 3), A = ld(it.v + 6), B = ld(it.v + 9);
-        const V3 E = sub(Q, P), a = sub(A, P), b = sub(B, P);
-        const int face = t >> 6, ip = (t >> 2) & (kPts - 1), g = t & 3;
-        const double p = sx[ip], q1 = 1.0 - p;
-        for (int j = 0; j < kPts / 4; ++j) {
-            const double q = sx[g + 4 * j];
-            double dh, s1h, s2h, fw;
-            if (face == 0)
-                dh = p, s1h = q1 * q, s2h = 1.0, fw = q1;
-            else if (face == 1)
-                dh = p, s1h = q1, s2h = q, fw = 1.0;
-            else if (face == 2)
-                dh = -p, s1h = 1.0, s2h = q1 * q, fw = q1;
-            else
-                dh = -p, s1h = q, s2h = q1, fw = 1.0;
-            const V3 c = fma3(dh, E, fma3(s1h, a, mul(-s2h, b)));
-            const double ic = rsqrt(dot(c, c));
-            const double K = sw[ip] * sw[g + 4 * j] * fw * (OP == 0 ? ic : s1h * ic * ic * ic);
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int l = 0; l < 2; ++l) {
-                    const double rho = kG3x[i], tau = kG2x[l];
-                    double u1, u2;
-                    if (face < 2) {
-                        u2 = (1.0 - rho) * tau;
-                        u1 = u2 + rho * dh;
-                    } else {
-                        u1 = (1.0 - rho) * tau;
-                        u2 = u1 - rho * dh;
-                    }
-                    const double s1 = rho * s1h, s2 = rho * s2h;
-                    const double rad = OP == 0 ? rho * (1.0 - rho) : 1.0 - rho;
-                    outer_acc(acc, K * kG3w[i] * 0.5 * rad, L3{{1.0 - u1 - s1, u1, s1}}, L3{{1.0 - u2 - s2, u2, s2}});
-                }
-        }
-        return;
-    }
-    const V3 P = ld(it.v), A = ld(it.v + 3), B = ld(it.v + 6), C = ld(it.v + 9), D = ld(it.v + 12);
-    const int iu = t / kPts, iv = t % kPts;
-    const double u = sx[iu], v = sx[iv];
-    const V3 av = fma3(u, sub(B, A), sub(A, P));
-    const V3 bv = fma3(v, sub(D, C), sub(C, P));
-    const double an = OP == 1 ? dot(av, ld(it.ny)) : 1.0;
-    const double wuv = sw[iu] * sw[iv];
-    for (int kz = 0; kz < kPts; ++kz) {
-        const double z = sx[kz];
-        const V3 c1 = fma3(-z, bv, av), c2 = fma3(z, av, mul(-1.0, bv));
-        const double i1 = rsqrt(dot(c1, c1)), i2 = rsqrt(dot(c2, c2));
-        const double f = wuv * sw[kz] * z * an;
-        const double k1 = f * (OP == 0 ? i1 : i1 * i1 * i1), k2 = f * (OP == 0 ? i2 : z * i2 * i2 * i2);
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const double s = kG3x[i], sz = s * z;
-            const double rad = kG3w[i] * (OP == 0 ? s * s : s);
-            outer_acc(acc, rad * k1, L3{{1.0 - s, s * (1.0 - u), s * u}}, L3{{1.0 - sz, sz * (1.0 - v), sz * v}});
-            outer_acc(acc, rad * k2, L3{{1.0 - sz, sz * (1.0 - u), sz * u}}, L3{{1.0 - s, s * (1.0 - v), s * v}});
-        }
-    }
+    acc.re = fma(w, x.re, acc.re);
+    if constexpr (OP >= 2) acc.im = fma(w, x.im, acc.im);
 }
 
-// The three series J_m = int rho^(A0 + m) (1 - rho)^B e^{i om rho} (...)
-// (m = 0, 1, 2) evaluated together from a coefficient table staged in LDS
-// (interleaved re/im of the three per power of om^2): literal FP64
-// coefficients would otherwise be held in registers across the face loops.
-template <int A0, int B, bool DL>
-struct MomentTable3 {
-    double v[6 * (kSeries / 2)];
-    constexpr MomentTable3() : v()
-    {
-        const MomentSeries<A0, B, DL> s0{};
-        const MomentSeries<A0 + 1, B, DL> s1{};
-        const MomentSeries<A0 + 2, B, DL> s2{};
-        for (int m = 0; m < kSeries / 2; ++m) {
-            v[6 * m] = s0.re[m], v[6 * m + 1] = s0.im[m];
-            v[6 * m + 2] = s1.re[m], v[6 * m + 3] = s1.im[m];
-            v[6 * m + 4] = s2.re[m], v[6 * m + 5] = s2.im[m];
-        }
-    }
-};
-constexpr int kTab3 = 6 * (kSeries / 2);
-__constant__ MomentTable3<2, 0, false> c_tab_s20{};   // identical and common-vertex single layer
-__constant__ MomentTable3<1, 1, false> c_tab_s11{};   // common-edge single layer
-__constant__ MomentTable3<1, 0, true> c_tab_d10{};    // common-vertex double layer
-__constant__ MomentTable3<0, 1, true> c_tab_d01{};    // common-edge double layer
-
-__device__ __forceinline__ void moment3(double om, const double *tab, Cx &J0, Cx &J1, Cx &J2)
-{
-    const double w2 = om * om;
-    const double *t = tab + 6 * (kSeries / 2 - 1);
-    double r0 = t[0], i0 = t[1], r1 = t[2], i1 = t[3], r2 = t[4], i2 = t[5];
-#pragma unroll 4
-    for (int m = kSeries / 2 - 2; m >= 0; --m) {
-        t = tab + 6 * m;
-        r0 = fma(r0, w2, t[0]);
-        i0 = fma(i0, w2, t[1]);
-        r1 = fma(r1, w2, t[2]);
-        i1 = fma(i1, w2, t[3]);
-        r2 = fma(r2, w2, t[4]);
-        i2 = fma(i2, w2, t[5]);
-    }
-    J0 = {r0, om * i0};
-    J1 = {r1, om * i1};
-    J2 = {r2, om * i2};
-}
-
-// acc[3a + b] += K (alpha_a gamma_b J0 + (alpha_a delta_b + beta_a gamma_b) J1
-// + beta_a delta_b J2): the radial integral of (alpha + beta rho)(gamma +
-// delta rho) against the moments J_m (complex), times K.
-__device__ __forceinline__ void moment_acc(double *ar, double *ai, double K, const L3 &al, const L3 &be, const L3 &ga,
-                                           const L3 &de, const Cx &J0, const Cx &J1, const Cx &J2)
-{
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const double c0 = K * al.v[a] * ga.v[b], c1 = K * (al.v[a] * de.v[b] + be.v[a] * ga.v[b]),
-                         c2 = K * be.v[a] * de.v[b];
-            ar[3 * a + b] += c0 * J0.re + c1 * J1.re + c2 * J2.re;
-            ai[3 * a + b] += c0 * J0.im + c1 * J1.im + c2 * J2.im;
-        }
-}
-
-// P1 Helmholtz (op 2 single, op 3 double layer): the Laplace P1 scheme with
-// the radial factor e^{ikr}: at each face point the barycentrics are
-// alpha + beta rho (test) and gamma + delta rho (trial), and the radial
-// integrals are three moment series (identical pairs: the radius xi, the
-// moments at omega eta1 eta2, eta1 and eta2 on the 8-point rule).
-// tr: the radial table of identical and common-vertex pairs, te: of
-// common-edge pairs (both in LDS).
+// This thread's share of the 9 local integrals (row-major; without jt js / 4 pi
+// and, for the common-edge double layer, without (a.n_y)).  Op 0, 1: Laplace
+// single, double layer; 2, 3: Helmholtz.
 template <int OP>
-__device__ void pair_part_p1_helmholtz(const NearItem &it, const double *sx, const double *sw, const double *tr,
-                                       const double *te, double *ar, double *ai)
+__device__ __forceinline__ void pair_part_p1(const NearItem &it, const double *sx, const double *sw, Cx *M)
 {
-    constexpr bool DL = OP == 3;
+    constexpr bool CPLX = OP >= 2, DL = OP == 1 || OP == 3;
     const int t = threadIdx.x;
     const double k = it.k;
+    int terms = 0;
+    if constexpr (CPLX) terms = series_terms(it);
     if (it.kind == 0) {
-        if (DL || t >= 3 * kIdPts) return;
+        if constexpr (DL) return;
         const V3 V0 = ld(it.v), V1 = ld(it.v + 3), V2 = ld(it.v + 6);
         const V3 E1 = sub(V1, V0), E2 = sub(V2, V1);
-        const int line = t / kIdPts, kk = t - line * kIdPts;
-        const double e3 = (c_x[kk % kGL] + (double)(kk / kGL)) * (1.0 / kIdPanels);
-        const double w3 = c_w[kk % kGL] * (1.0 / kIdPanels);
-        const V3 c = line == 0 ? fma3(e3, E1, E2) : (line == 1 ? fma3(e3, E2, E1) : fma3(-e3, E1, mul(1.0 - e3, E2)));
-        const double ic = rsqrt(dot(c, c));
-        const double om = k / ic;
-        // loops kept rolled: the unrolled series would hold every node's
-        // coefficients in registers
-#pragma unroll 1
-        for (int j = 0; j < kGL; ++j)
-#pragma unroll 1
-            for (int l = 0; l < kGL; ++l) {
-                const double e1 = c_x[j], e2 = c_x[l];
-                // x = xi (A1, B1), y = xi (A2, B2) in the (a, b) coordinates
-                double A1, B1, A2, B2;
-                if (line == 0) {
-                    A1 = 1.0, B1 = 1.0 - e1 + e1 * e2, A2 = 1.0 - e1 * e2 * e3, B2 = 1.0 - e1;
-                } else if (line == 1) {
-                    A1 = 1.0, B1 = e1 * (1.0 - e2 + e2 * e3), A2 = 1.0 - e1 * e2, B2 = e1 * (1.0 - e2);
-                } else {
-                    A1 = 1.0 - e1 * e2 * e3, B1 = e1 * (1.0 - e2 * e3), A2 = 1.0, B2 = e1 * (1.0 - e2);
-                }
-                const double w = w3 * c_w[j] * c_w[l] * e1 * ic;
-                const double oe = om * e1 * e2;
-                Cx J0, J1, J2;
-                moment3(oe, tr, J0, J1, J2);
-                const L3 al{{1.0, 0.0, 0.0}}, bx{{-A1, A1 - B1, B1}}, by{{-A2, A2 - B2, B2}};
-                moment_acc(ar, ai, w, al, bx, al, by, J0, J1, J2);   // the region
-                moment_acc(ar, ai, w, al, by, al, bx, J0, J1, J2);   // and its mirror
+        // |c| on line `line` at eta3 = e3
+        auto length2 = [&](int line, double e3) {
+            const V3 c = line == 0 ? fma3(e3, E1, E2) : (line == 1 ? fma3(e3, E2, E1) : fma3(-e3, E1, mul(1.0 - e3, E2)));
+            return dot(c, c);
+        };
+        // adds the node (line, e1, e2, e3), region and mirror (x and y exchanged: symmetric)
+        auto node = [&](int line, double e1, double e2, double e3, double w, const Cx *J) {
+            // x = xi (A1, B1), y = xi (A2, B2) in the (a, b) coordinates, barycentrics (1 - a, a - b, b)
+            double A1, B1, A2, B2;
+            if (line == 0) {
+                A1 = 1.0, B1 = 1.0 - e1 + e1 * e2, A2 = 1.0 - e1 * e2 * e3, B2 = 1.0 - e1;
+            } else if (line == 1) {
+                A1 = 1.0, B1 = e1 * (1.0 - e2 + e2 * e3), A2 = 1.0 - e1 * e2, B2 = e1 * (1.0 - e2);
+            } else {
+                A1 = 1.0 - e1 * e2 * e3, B1 = e1 * (1.0 - e2 * e3), A2 = 1.0, B2 = e1 * (1.0 - e2);
             }
+            const double x[3] = {-A1, A1 - B1, B1}, y[3] = {-A2, A2 - B2, B2};
+            cfma<OP>(M[0], 2.0 * w, J[0]);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                cfma<OP>(M[a], (a == 0 ? 2.0 : 1.0) * w * (x[a] + y[a]), J[1]);
+#pragma unroll
+                for (int b = a; b < 3; ++b) cfma<OP>(M[3 * a + b], w * fma(x[a], y[b], x[b] * y[a]), J[2]);
+            }
+        };
+        if constexpr (CPLX) {
+            // Thread t takes the point (eta1, eta2) of the 8 x 8 rule and every
+            // fourth (line, eta3) node, two at a time: a wavefront shares its
+            // line.  Beyond omega = 3.2 e^{i omega eta1 eta2} needs two panels per
+            // direction (one left 7e-8 at omega = 11).
+            const int panels = terms > 32 ? 2 : 1;
+            const double sc = 1.0 / panels;
+#pragma unroll 1
+            for (int pp = 0; pp < panels * panels; ++pp) {
+                const double e1 = (c_x[(t >> 3) & 7] + (pp >> 1)) * sc, e2 = (c_x[t & 7] + (pp & 1)) * sc;
+                const double w12 = c_w[(t >> 3) & 7] * c_w[t & 7] * e1 * sc * sc;
+#pragma unroll 1
+                for (int i = 0; i < 3 * kIdPts / 8; ++i) {
+                    double om[2], e3[2], w[2];
+                    int line = 0;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {   // four nodes apart, on one line
+                        const int n = (t >> 6) + 4 * (2 * i + h);
+                        line = n / kIdPts;
+                        const int kk = n - line * kIdPts;
+                        e3[h] = (c_x[kk % kGL] + (double)(kk / kGL)) * (1.0 / kIdPanels);
+                        const double c2 = length2(line, e3[h]), ic = rsqrt64(c2);
+                        om[h] = k * c2 * ic * e1 * e2;
+                        w[h] = w12 * c_w[kk % kGL] * (1.0 / kIdPanels) * ic;
+                    }
+                    Cx J[2][3];
+                    moments<OP, false>(om[0], om[1], terms, J[0], J[1]);
+                    node(line, e1, e2, e3[0], w[0], J[0]);
+                    node(line, e1, e2, e3[1], w[1], J[1]);
+                }
+            }
+        } else {
+            // polynomial in eta1, eta2 too (degrees 3 and 2): 2 x 2 points times
+            // the (line, eta3) nodes, spread over the threads
+            constexpr double g2x[2] = {0.5 - 0.28867513459481288225, 0.5 + 0.28867513459481288225};
+            Cx J[3], unused[3];
+            moments<OP, false>(0.0, 0.0, 0, J, unused);
+            for (int n = t; n < 4 * 3 * kIdPts; n += kNearThreads) {
+                const int q = n / (3 * kIdPts), lk = n - q * (3 * kIdPts), line = lk / kIdPts, kk = lk - line * kIdPts;
+                const double e1 = g2x[q >> 1], e2 = g2x[q & 1];
+                const double e3 = (c_x[kk % kGL] + (double)(kk / kGL)) * (1.0 / kIdPanels);
+                node(line, e1, e2, e3, 0.25 * e1 * c_w[kk % kGL] * (1.0 / kIdPanels) * rsqrt64(length2(line, e3)), J);
+            }
+        }
+        M[3] = M[1];
+        M[6] = M[2];
+        M[7] = M[5];
         return;
     }
     if (it.kind == 1) {
         const V3 P = ld(it.v), Q = ld(it.v + 3), A = ld(it.v + 6), B = ld(it.v + 9);
         const V3 E = sub(Q, P), a = sub(A, P), b = sub(B, P);
         const int face = t >> 6, ip = (t >> 2) & (kPts - 1), g = t & 3;
+        const bool ahead = face < 2, odd = face & 1;   // faces 0, 1: the test point ahead along the edge
         const double p = sx[ip], q1 = 1.0 - p;
 #pragma unroll 1
-        for (int j = 0; j < kPts / 4; ++j) {
-            const double q = sx[g + 4 * j];
-            double dh, s1h, s2h, fw;
-            if (face == 0)
-                dh = p, s1h = q1 * q, s2h = 1.0, fw = q1;
-            else if (face == 1)
-                dh = p, s1h = q1, s2h = q, fw = 1.0;
-            else if (face == 2)
-                dh = -p, s1h = 1.0, s2h = q1 * q, fw = q1;
-            else
-                dh = -p, s1h = q, s2h = q1, fw = 1.0;
-            const V3 c = fma3(dh, E, fma3(s1h, a, mul(-s2h, b)));
-            const double ic = rsqrt(dot(c, c));
-            const double om = k / ic;
-            const double K = sw[ip] * sw[g + 4 * j] * fw * (DL ? s1h * ic * ic * ic : ic);
-            Cx J0, J1, J2;
-            moment3(om, te, J0, J1, J2);
+        for (int j = 0; j < kPts / 4; j += 2) {
+            double dh[2], s1[2], s2[2], K[2], om[2];
 #pragma unroll
-            for (int l = 0; l < 2; ++l) {
-                const double tau = kG2x[l];
-                L3 al, be, ga, de;
-                al = L3{{1.0 - tau, tau, 0.0}};
-                ga = L3{{1.0 - tau, tau, 0.0}};
-                if (face < 2) {   // u2 = (1 - rho) tau, u1 = u2 + rho dh
-                    be = L3{{tau - dh - s1h, dh - tau, s1h}};
-                    de = L3{{tau - s2h, -tau, s2h}};
-                } else {          // u1 = (1 - rho) tau, u2 = u1 - rho dh
-                    be = L3{{tau - s1h, -tau, s1h}};
-                    de = L3{{tau + dh - s2h, -dh - tau, s2h}};
-                }
-                moment_acc(ar, ai, 0.5 * K, al, be, ga, de, J0, J1, J2);
+            for (int h = 0; h < 2; ++h) {
+                // (dh, s1, s2): face 0 (p, q1 q, 1), 1 (p, q1, q), 2 (-p, 1, q1 q), 3 (-p, q, q1)
+                const double q = sx[g + 4 * (j + h)];
+                const double X = odd ? q1 : q1 * q, Y = odd ? q : 1.0, fw = odd ? 1.0 : q1;
+                dh[h] = ahead ? p : -p;
+                s1[h] = ahead ? X : Y;
+                s2[h] = ahead ? Y : X;
+                const V3 c = fma3(dh[h], E, fma3(s1[h], a, mul(-s2[h], b)));
+                const double c2 = dot(c, c), ic = rsqrt64(c2);
+                K[h] = sw[ip] * sw[g + 4 * (j + h)] * fw * (DL ? s1[h] * ic * ic * ic : ic);
+                om[h] = k * c2 * ic;
+            }
+            Cx J[2][3];
+            moments<OP, true>(om[0], om[1], terms, J[0], J[1]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                // With tau in [0, 1] along the edge the barycentrics are
+                // (1 - tau, tau, 0) + rho be(tau) on the test side and
+                // (1 - tau, tau, 0) + rho de(tau) on the trial side, be =
+                // (tau - bx - s1, bx - tau, s1), de = (tau - dx - s2, dx - tau,
+                // s2), where faces 0, 1 (x ahead along the edge) have bx = dh,
+                // dx = 0 and faces 2, 3 bx = 0, dx = -dh.  Below, the averages
+                // over tau of their products (<tau> = 1/2, <tau^2> = 1/3).
+                const double bx = ahead ? dh[h] : 0.0, dx = ahead ? 0.0 : -dh[h];
+                const double be[3] = {-bx - s1[h], bx, s1[h]}, de[3] = {-dx - s2[h], dx, s2[h]};   // at tau = 0
+                constexpr double sl[3] = {1.0, -1.0, 0.0};                     // slopes in tau
+                constexpr double a0[3] = {0.5, 0.5, 0.0}, a1[3] = {1.0 / 6.0, 1.0 / 3.0, 0.0};   // <al>, <tau al>
+                constexpr double aa[3][3] = {{1.0 / 3.0, 1.0 / 6.0, 0.0}, {1.0 / 6.0, 1.0 / 3.0, 0.0}, {0.0, 0.0, 0.0}};
+                Cx k0{K[h] * J[h][0].re, K[h] * J[h][0].im}, k1{K[h] * J[h][1].re, K[h] * J[h][1].im},
+                    k2{K[h] * J[h][2].re, K[h] * J[h][2].im};
+#pragma unroll
+                for (int r = 0; r < 3; ++r)
+#pragma unroll
+                    for (int s = 0; s < 3; ++s) {
+                        Cx &m = M[3 * r + s];
+                        if (r < 2 && s < 2) cfma<OP>(m, aa[r][s], k0);
+                        cfma<OP>(m, fma(a0[r], de[s], a1[r] * sl[s]) + fma(a0[s], be[r], a1[s] * sl[r]), k1);
+                        cfma<OP>(m, fma(be[r], de[s], 0.5 * fma(be[r], sl[s], de[s] * sl[r])) + sl[r] * sl[s] * (1.0 / 3.0), k2);
+                    }
             }
         }
         return;
@@ -664,101 +595,91 @@ __device__ void pair_part_p1_helmholtz(const NearItem &it, const double *sx, con
     const V3 bv = fma3(v, sub(D, C), sub(C, P));
     const double an = DL ? dot(av, ld(it.ny)) : 1.0;
     const double wuv = sw[iu] * sw[iv];
-    const L3 al{{1.0, 0.0, 0.0}}, bu{{-1.0, 1.0 - u, u}}, bvv{{-1.0, 1.0 - v, v}};
+    // x = P + s a(u), y = P + s z b(v) and x = P + s z a(u), y = P + s b(v):
+    // barycentrics e0 + s X, e0 + s z Y (resp. z on X), X = (-1, 1 - u, u), Y =
+    // (-1, 1 - v, v).  Sums over z of the coefficients of e0 e0, X e0, e0 Y, X Y.
+    Cx S0{0.0, 0.0}, Sx{0.0, 0.0}, Sy{0.0, 0.0}, Sxy{0.0, 0.0};
 #pragma unroll 1
     for (int kz = 0; kz < kPts; ++kz) {
         const double z = sx[kz];
         const V3 c1 = fma3(-z, bv, av), c2 = fma3(z, av, mul(-1.0, bv));
-        const double i1 = rsqrt(dot(c1, c1)), i2 = rsqrt(dot(c2, c2));
+        const double q1 = dot(c1, c1), q2 = dot(c2, c2), i1 = rsqrt64(q1), i2 = rsqrt64(q2);
         const double f = wuv * sw[kz] * z * an;
         const double k1 = f * (DL ? i1 * i1 * i1 : i1), k2 = f * (DL ? z * i2 * i2 * i2 : i2);
-        Cx J0, J1, J2, H0, H1, H2;
-        moment3(k / i1, tr, J0, J1, J2);
-        moment3(k / i2, tr, H0, H1, H2);
-        const L3 zbv{{-z, z * (1.0 - v), z * v}}, zbu{{-z, z * (1.0 - u), z * u}};
-        moment_acc(ar, ai, k1, al, bu, al, zbv, J0, J1, J2);    // x = P + s a(u), y = P + s z b(v)
-        moment_acc(ar, ai, k2, al, zbu, al, bvv, H0, H1, H2);   // x = P + s z a(u), y = P + s b(v)
+        Cx J[3], H[3];
+        moments<OP, false>(k * q1 * i1, k * q2 * i2, terms, J, H);
+        cfma<OP>(S0, k1, J[0]);
+        cfma<OP>(S0, k2, H[0]);
+        cfma<OP>(Sx, k1, J[1]);
+        cfma<OP>(Sx, k2 * z, H[1]);
+        cfma<OP>(Sy, k1 * z, J[1]);
+        cfma<OP>(Sy, k2, H[1]);
+        cfma<OP>(Sxy, k1 * z, J[2]);
+        cfma<OP>(Sxy, k2 * z, H[2]);
+    }
+    const double X[3] = {-1.0, 1.0 - u, u}, Y[3] = {-1.0, 1.0 - v, v};
+    M[0] = S0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        cfma<OP>(M[3 * a], X[a], Sx);
+        cfma<OP>(M[a], Y[a], Sy);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) cfma<OP>(M[3 * a + b], X[a] * Y[b], Sxy);
     }
 }
 
-// WITH_P0 (the Helmholtz hypersingular operator): the pair's P0 single-layer
-// value follows the 9 complex local-matrix values (20 doubles per pair).
+// One workgroup per pair.  Its 9 (18: complex) sums over 256 threads go
+// through LDS once: eight threads per value add 32 partials each, a butterfly
+// adds the eight (fixed order, two barriers; the tree over all values took
+// eight).  WITH_P0 (the Helmholtz hypersingular operator): the pair's P0
+// single-layer value, the sum of the nine entries (the hat functions sum to
+// one), follows them (20 doubles per pair).
 template <int OP, bool WITH_P0>
-__global__ __launch_bounds__(kNearThreads) void k_near_p1_helmholtz(const NearItem *__restrict__ items, int64_t n)
-{
-    if ((int64_t)blockIdx.x >= n) return;
-    const NearItem &it = items[blockIdx.x];
-    __shared__ double sx[kPts], sw[kPts];
-    __shared__ double tr[kTab3], te[kTab3];
-    __shared__ double red[18][kNearThreads];
-    const int t = threadIdx.x;
-    if (t < kPts) {
-        sx[t] = 0.5 * (c_x[t % kGL] + (double)(t / kGL));
-        sw[t] = 0.5 * c_w[t % kGL];
-    }
-    for (int i = t; i < kTab3; i += kNearThreads) {
-        tr[i] = OP == 3 ? c_tab_d10.v[i] : c_tab_s20.v[i];
-        te[i] = OP == 3 ? c_tab_d01.v[i] : c_tab_s11.v[i];
-    }
-    __syncthreads();
-    double ar[9], ai[9];
-#pragma unroll
-    for (int kk = 0; kk < 9; ++kk) ar[kk] = ai[kk] = 0.0;
-    pair_part_p1_helmholtz<OP>(it, sx, sw, tr, te, ar, ai);
-#pragma unroll
-    for (int kk = 0; kk < 9; ++kk) {
-        red[2 * kk][t] = ar[kk];
-        red[2 * kk + 1][t] = ai[kk];
-    }
-    __syncthreads();
-    for (int h = kNearThreads / 2; h > 0; h >>= 1) {
-        if (t < h)
-#pragma unroll
-            for (int kk = 0; kk < 18; ++kk) red[kk][t] += red[kk][t + h];
-        __syncthreads();
-    }
-    if (t < 18) {
-        const double an = (OP == 3 && it.kind == 1) ? dot(sub(ld(it.v + 6), ld(it.v)), ld(it.ny)) : 1.0;
-        static_cast<double *>(it.out)[t] = red[t][0] * an * it.jt * it.js * kInv4PiD;
-    }
-    if constexpr (WITH_P0) {
-        const Cx v = pair_value<2>(it);
-        if (t == 0) {
-            static_cast<double *>(it.out)[18] = v.re;
-            static_cast<double *>(it.out)[19] = v.im;
-        }
-    }
-}
-
-template <int OP>
 __global__ __launch_bounds__(kNearThreads) void k_near_p1(const NearItem *__restrict__ items, int64_t n)
 {
+    constexpr int NV = OP >= 2 ? 18 : 9, NR = NV / 9;
     if ((int64_t)blockIdx.x >= n) return;
     const NearItem &it = items[blockIdx.x];
     __shared__ double sx[kPts], sw[kPts];
-    __shared__ double red[9][kNearThreads];
+    __shared__ double red[NV][kNearThreads + 8];   // rows 8 words of 64 bits apart from a multiple of the banks
     const int t = threadIdx.x;
     if (t < kPts) {
         sx[t] = 0.5 * (c_x[t % kGL] + (double)(t / kGL));
         sw[t] = 0.5 * c_w[t % kGL];
     }
     __syncthreads();
-    double acc[9];
+    Cx M[9];
 #pragma unroll
-    for (int k = 0; k < 9; ++k) acc[k] = 0.0;
-    pair_part_p1<OP>(it, sx, sw, acc);
+    for (int i = 0; i < 9; ++i) M[i] = {0.0, 0.0};
+    pair_part_p1<OP>(it, sx, sw, M);
 #pragma unroll
-    for (int k = 0; k < 9; ++k) red[k][t] = acc[k];
-    __syncthreads();
-    for (int h = kNearThreads / 2; h > 0; h >>= 1) {
-        if (t < h)
-#pragma unroll
-            for (int k = 0; k < 9; ++k) red[k][t] += red[k][t + h];
-        __syncthreads();
+    for (int i = 0; i < 9; ++i) {
+        red[NR * i][t] = M[i].re;
+        if constexpr (OP >= 2) red[2 * i + 1][t] = M[i].im;
     }
-    if (t < 9) {
-        const double an = (OP == 1 && it.kind == 1) ? dot(sub(ld(it.v + 6), ld(it.v)), ld(it.ny)) : 1.0;
-        static_cast<double *>(it.out)[t] = red[t][0] * an * it.jt * it.js * kInv4PiD;
+    __syncthreads();
+    if (t < 8 * NV) {
+        const double *r = red[t >> 3] + (t & 7);
+        double s = 0.0;
+#pragma unroll 8
+        for (int i = 0; i < kNearThreads / 8; ++i) s += r[8 * i];
+#pragma unroll
+        for (int h = 4; h > 0; h >>= 1) s += __shfl_xor(s, h);
+        const double an = ((OP == 1 || OP == 3) && it.kind == 1) ? dot(sub(ld(it.v + 6), ld(it.v)), ld(it.ny)) : 1.0;
+        s *= an * it.jt * it.js * kInv4PiD;
+        if ((t & 7) == 0) {
+            static_cast<double *>(it.out)[t >> 3] = s;
+            if constexpr (WITH_P0) red[t >> 3][0] = s;
+        }
+    }
+    if constexpr (WITH_P0) {
+        __syncthreads();
+        if (t < 2) {
+            double s = 0.0;
+#pragma unroll
+            for (int i = 0; i < 9; ++i) s += red[2 * i + t][0];
+            static_cast<double *>(it.out)[18 + t] = s;
+        }
     }
 }
 
@@ -824,17 +745,17 @@ hipError_t launch_near_p1(int op, const NearItem *items, int64_t n, hipStream_t 
     if (n > INT32_MAX || op < 0 || (op > 3 && op != BEM_LAPLACE_HYPS && op != BEM_HELMHOLTZ_HYPS))
         return hipErrorInvalidValue;
     if (op == 2)
-        hipLaunchKernelGGL((k_near_p1_helmholtz<2, false>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
+        hipLaunchKernelGGL((k_near_p1<2, false>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
     else if (op == 3)
-        hipLaunchKernelGGL((k_near_p1_helmholtz<3, false>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
+        hipLaunchKernelGGL((k_near_p1<3, false>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
     else if (op == BEM_HELMHOLTZ_HYPS)
-        hipLaunchKernelGGL((k_near_p1_helmholtz<2, true>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
+        hipLaunchKernelGGL((k_near_p1<2, true>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
     else if (op == BEM_LAPLACE_HYPS)
         hipLaunchKernelGGL(k_near_slp_value, dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
     else if (op == 0)
-        hipLaunchKernelGGL((k_near_p1<0>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
+        hipLaunchKernelGGL((k_near_p1<0, false>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
     else
-        hipLaunchKernelGGL((k_near_p1<1>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
+        hipLaunchKernelGGL((k_near_p1<1, false>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
     return hipGetLastError();
 }
 

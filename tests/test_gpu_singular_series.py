@@ -1,0 +1,90 @@
+"""GPU: the singular pairs' radial power series at every number of terms it
+is cut to (8, 16, ... 48, by omega = k times the pair's extent), and the P1
+local matrices formed from its moments.
+
+Single pairs of triangles through the discontinuous P1 space (the entries of
+two triangles' dofs are the pair's local matrix) and P0, against the
+Sauter-Schwab transformations with a 12-point Gauss-Legendre rule in each of
+the four directions, written here.  That rule is accurate to about 1e-11 on
+these triangles (1e-9 at omega = 11, where the kernel turns twice over a
+pair); the library states 1e-12 for its own rules and 5e-10 for the series at
+omega = 12.  Bounds: 1e-10, and 4e-9 from omega = 6 on.
+"""
+import numpy as np
+import pytest
+
+from paper_1711_01897_amd import bem, inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def schwab(kind, n=12):
+    """Points (x1, x2, y1, y2) on {0 <= x2 <= x1 <= 1} and weights."""
+    x, w = np.polynomial.legendre.leggauss(n)
+    x, w = 0.5 * (x + 1), 0.5 * w
+    e, a, b, c = (v.ravel() for v in np.meshgrid(x, x, x, x, indexing="ij"))
+    W = np.einsum("i,j,k,l->ijkl", w, w, w, w).ravel() * e ** 3
+    if kind == 3:
+        h = [(e, e * (1 - a + a * b), e * (1 - a * b * c), e * (1 - a)),
+             (e, e * a * (1 - b + b * c), e * (1 - a * b), e * a * (1 - b)),
+             (e * (1 - a * b * c), e * a * (1 - b * c), e, e * a * (1 - b))]
+        parts = [(p, W * a * a * b) for p in h + [(p[2], p[3], p[0], p[1]) for p in h]]
+    elif kind == 2:
+        parts = [((e, e * a * c, e * (1 - a * b), e * a * (1 - b)), W * a * a),
+                 ((e, e * a, e * (1 - a * b * c), e * a * b * (1 - c)), W * a * a * b),
+                 ((e * (1 - a * b), e * a * (1 - b), e, e * a * b * c), W * a * a * b),
+                 ((e * (1 - a * b * c), e * a * b * (1 - c), e, e * a), W * a * a * b),
+                 ((e * (1 - a * b * c), e * a * (1 - b * c), e, e * a * b), W * a * a * b)]
+    else:
+        parts = [((e, e * a, e * b, e * b * c), W * b), ((e * b, e * b * c, e, e * a), W * b)]
+    return np.concatenate([np.stack(p) for p, _ in parts], axis=1), np.concatenate([v for _, v in parts])
+
+
+def local(xyz, tri, T, S, k, dlp):
+    """3 x 3 local matrix of the vertex-sharing pair (T, S)."""
+    shared = [v for v in tri[T] if v in tri[S]]
+    tl = shared + [v for v in tri[T] if v not in shared]
+    sl = shared + [v for v in tri[S] if v not in shared]
+    P, W = schwab(len(shared))
+    bx, by = np.stack([1 - P[0], P[0] - P[1], P[1]]), np.stack([1 - P[2], P[2] - P[3], P[3]])
+    t, s = xyz[tl], xyz[sl]
+    d = (np.outer(t[1] - t[0], P[0]) + np.outer(t[2] - t[1], P[1]) - np.outer(s[1] - s[0], P[2])
+         - np.outer(s[2] - s[1], P[3]))
+    r = np.sqrt((d * d).sum(axis=0))
+    g = np.exp(1j * k * r) / (4 * np.pi * r)
+    v = xyz[tri[S]]
+    n = np.cross(v[1] - v[0], v[2] - v[0])
+    js, n = np.linalg.norm(n), n / np.linalg.norm(n)
+    if dlp:
+        g = 0 * g if len(shared) == 3 else g * (1 - 1j * k * r) * (n @ d) / r ** 2
+    v = xyz[tri[T]]
+    jt = np.linalg.norm(np.cross(v[1] - v[0], v[2] - v[0]))
+    M = np.einsum("an,bn,n->ab", bx, by, g * W) * jt * js
+    return M[np.ix_([tl.index(x) for x in tri[T]], [sl.index(x) for x in tri[S]])]
+
+
+@pytest.mark.parametrize("omega", [0.0, 0.01, 0.3, 1.2, 2.5, 4.0, 11.0])
+def test_local_matrices(omega):
+    xyz, tri = inputs.icosphere(1)
+    tri = np.asarray(tri)
+    rng = np.random.Generator(np.random.PCG64(5))
+    xyz = xyz + rng.uniform(-0.03, 0.03, size=xyz.shape)
+    mesh = bem.mesh_create(xyz, tri, 6)
+    bound = 4e-9 if omega >= 6.0 else 1e-10
+    try:
+        for shared in (3, 2, 1):
+            S = next(b for b in range(len(tri)) if len(set(tri[7]) & set(tri[b])) == shared)
+            pts = xyz[np.union1d(tri[7], tri[S])]
+            span = max(np.linalg.norm(a - b) for a in pts for b in pts)
+            k = omega / span
+            for dlp in (False, True):
+                op = ((bem.LAPLACE_SLP, bem.LAPLACE_DLP) if omega == 0.0 else (bem.HELMHOLTZ_SLP, bem.HELMHOLTZ_DLP))[dlp]
+                ref = local(xyz, tri, 7, S, k, dlp)
+                dofs = np.arange(3, dtype=np.int32)
+                got = bem.eval_entries(mesh, op, bem.DP1, k, 21 + dofs, 3 * S + dofs, prec=bem.FP64,
+                                       near=bem.NEAR_SINGULAR)
+                one = bem.eval_entries(mesh, op, bem.P0, k, [7], [S], prec=bem.FP64, near=bem.NEAR_SINGULAR)
+                assert np.abs(got - ref).max() <= bound * np.abs(ref).max(), (shared, dlp)
+                assert abs(one[0, 0] - ref.sum()) <= bound * np.abs(ref).sum(), (shared, dlp)
+    finally:
+        mesh.destroy()

@@ -207,86 +207,61 @@ hipError_t launch_geometry(const double *xyz, const int32_t *tri, int64_t nt, in
 // ids (w = index[i] & 3 when shift == 2, else 0); i < n.
 hipError_t launch_gather(const float *g32, const int4 *vtx, const int32_t *index, int shift, int64_t n, float *geo,
                          int4 *meta, hipStream_t s);
-// One vertex-sharing (singular) P0 triangle pair of a BEM_NEAR_SINGULAR
-// request, integrated by near.hip.  Vertices in the layout of its kind:
-//   kind 0, identical:   v = V0, V1, V2 (the triangle in its own order)
-//   kind 1, common edge: v = P, Q, A, B (shared edge P-Q; A the test
-//                        triangle's third vertex, B the trial triangle's)
-//   kind 2, common vertex: v = P, A, B, C, D (shared P; A, B the test
-//                        triangle's others, C, D the trial triangle's)
-// ny: unit normal of the trial triangle; jt, js: |cross| of the test and
-// trial triangles (twice their areas).  out: the entry's address; the
-// kernel adds the pair's value to what the entry kernel stored there.
-struct NearItem {
-    double v[15];
-    double ny[3];
-    double jt, js;
-    double k;   // wavenumber (Helmholtz)
+// ---------------------------------------------------------------------------
+// Vertex-sharing (singular) triangle pairs of BEM_NEAR_SINGULAR requests
+// (near.hip).  The host lists the pairs by triangle index; the device finds
+// the shared vertices, integrates each pair (one workgroup) and, for P1 and
+// DP1, adds the pairs' 3 x 3 local matrices to the entries (one thread per
+// entry of a row that has any).  The requests of a batch with one operator,
+// space and precision share a region: staged part (copied to the device) |
+// what the kernels write for each other.
+struct NearPair {
+    int32_t a, b;              // row-side and column-side triangle
+    int32_t req, pad;          // request within the region
+    int64_t entry;             // P0: the entry's position in the output
+};
+static_assert(sizeof(NearPair) == 24, "near pairs are 24 bytes");
+
+struct NearReq {
+    const double *xyz;         // mesh: vertices, FP64 records, vertex ids per triangle
+    const double *g64;
+    const int4 *vtx;
     void *out;
-    int32_t kind;
-    int32_t pad;
+    // P1 and DP1: pairs [gptr[s], gptr[s + 1]) of the region belong to the
+    // request's row-side triangle s; row r's star is rs[rptr[r] .. rptr[r + 1])
+    // (triangle s << 2 | local vertex); cols: the column dofs
+    const int32_t *gptr, *rptr, *rs, *cols;
+    double k;                  // wavenumber
+    int32_t ncols;
+    int32_t transposed;        // the kernel's test triangle is the column's (adjoint double layer)
+    int32_t dp1, pad;
 };
-static_assert(sizeof(NearItem) == 184, "near items are 184 bytes");
 
-// Adds each item's singular pair integral (FP64; radial integral in closed
-// form for Laplace, by an 8-point rule for Helmholtz; composite
-// Gauss-Legendre for the rest) to its entry: the Laplace single (op 0) or
-// double layer (op 1), the Helmholtz single (op 2) or double layer (op 3),
-// into float / complex<float> (fp32 = true) or double / complex<double>
-// entries.  One workgroup per item.
-// P1 singular region of a request: items | gather records | sources |
-// source weights (hypersingular operator) | local values (9 per pair, 1 for
-// the hypersingular operator); offsets from the region's start, each
-// 256-byte aligned.
-struct NearP1Layout {
-    size_t items, recs, src, wt, local, bytes;
-    int per;       // doubles per pair in the local values
-    int src_per;   // gather source units per pair (9 values, 9 complex values, or 1)
-    bool weighted, cplx;
+struct NearBlock {             // P1: up to 256 columns of one row
+    int32_t req, row, col0, pad;
 };
-// mode: 0 real 3 x 3 local matrices, 1 Laplace hypersingular (one value per
-// pair, weighted sources), 2 complex 3 x 3 local matrices, 3 Helmholtz
-// hypersingular (complex 3 x 3 single-layer local matrix and P0 value,
-// weighted sources)
-NearP1Layout near_p1_layout(int mode, int64_t items, int64_t recs, int64_t src);
-int near_p1_mode(const Request &r);
-NearP1Layout near_p1_layout(const Request &r);
-// Writes request r's part of a region's host image at host (dev: the region's
-// device address, out_dev: r's output on the device), its pairs, records and
-// sources after the first pb, rb and sb of the region (requests of one
-// kernel and precision share a region).
-void stage_near_p1(const Request &r, const NearP1Layout &L, char *host, char *dev, char *out_dev, int64_t pb,
-                   int64_t rb, int64_t sb);
-// Enqueues the P1 singular pairs of a staged region (local matrices, then the
-// gather into the entries).
-hipError_t launch_near_p1_region(int op, bool fp32, const NearP1Layout &L, char *dev, int64_t items, int64_t recs,
-                                 hipStream_t s);
-// Index of the P1 singular run of a request (kernel and precision), 0..11:
-// 2 g + fp32 with g = 0 single, 1 double layer, 2 hypersingular (Laplace),
-// 3 single, 4 double layer, 5 hypersingular (Helmholtz).
-int near_p1_group(const Request &r);
 
-hipError_t launch_near(int op, bool fp32, const NearItem *items, int64_t n, hipStream_t s);
-
-// P1: one entry's singular contributions, src[first .. first + count) into
-// the pairs' local matrices (9 doubles per pair, row-major test x trial).
-struct NearGather {
-    void *out;
-    int32_t first, count;
+struct NearCount {             // sizes of a region, or the part of it that precedes a request
+    int64_t reqs = 0, pairs = 0, blocks = 0, ints = 0;
 };
-static_assert(sizeof(NearGather) == 16, "gather records are 16 bytes");
 
-// P1 Laplace single (op 0) or double layer (op 1): each item's 3 x 3 local
-// matrix (FP64) into the 9 doubles at item.out; Helmholtz single (op 2) or
-// double layer (op 3): 9 complex values (18 doubles); Laplace hypersingular
-// operator (op 6): the pair's P0 single-layer integral into the double at
-// item.out.  One workgroup per item.
-hipError_t launch_near_p1(int op, const NearItem *items, int64_t n, hipStream_t s);
-// Adds each record's fixed-order sum of local values (times the source
-// weights when wt is not null) to its float (fp32) or double entry.  One
-// thread per record.
-hipError_t launch_near_gather(bool fp32, bool cplx, const NearGather *recs, int64_t n, const int32_t *src,
-                              const double *wt, const double *local, hipStream_t s);
+struct NearLayout {
+    size_t pairs, blocks, ints, staged;   // the requests' descriptors come first; `staged` bytes are copied
+    size_t keys, local, bytes;            // written on the device: column dofs per pair, local matrices
+};
+
+// Region kind of a request: 2 g + fp32, g = 0..3 the P0 kernel operators, 4 + (0..3) the P1 ones, 8 and 9 the
+// Laplace and Helmholtz hypersingular operators.
+constexpr int kNearKinds = 20;
+int near_kind(const Request &r);
+NearCount near_count(const Request &r);
+NearLayout near_layout(int kind, const NearCount &n);
+// Writes request r's part of a region's staged image at host (dev: the
+// region's device address, out_dev: r's output on the device); `at` is
+// advanced past it.
+void stage_near(const Request &r, const NearLayout &L, char *host, char *dev, char *out_dev, NearCount &at);
+// Enqueues the kernels of a staged region.
+hipError_t launch_near(int kind, const NearLayout &L, const NearCount &n, char *dev, hipStream_t s);
 
 // Copies bytes (a multiple of 16, both addresses 16-byte aligned) from src
 // (device-visible host staging) to dst (device) with a kernel on stream s.
@@ -317,13 +292,14 @@ struct bem_mesh {
     std::vector<int64_t> star_ptr;    // nv + 1
     std::vector<int32_t> star;        // packed (triangle << 2 | local vertex), ascending triangles
     std::vector<int32_t> dp1_star;    // 3 nt: star-table position of (triangle t, local vertex a) at 3 t + a
-    double mean_J = 0.0, mean_edge = 0.0;
+    double mean_J = 0.0, mean_edge = 0.0, max_edge = 0.0;
     double box_lo[3] = {0.0, 0.0, 0.0}, box_inv[3] = {0.0, 0.0, 0.0};   // bounding box: low corner, 1/extent
     int max_star = 0;
     int device = 0;
     float *d_g32 = nullptr;
     double *d_g64 = nullptr;
     int4 *d_vtx = nullptr;
+    double *d_xyz = nullptr;     // vertices (the singular pairs read them)
     int32_t *d_star = nullptr;   // star table on the device (packed triangle << 2 | local vertex)
     float *d_sgeo = nullptr;     // FP32 record per star entry
     int4 *d_smeta = nullptr;     // vertex ids per star entry, w = local vertex
@@ -415,16 +391,11 @@ struct Request {
     // server's dispatcher copies them into a batch and fills in what depends
     // on the batch: the request index of each block, the staged inputs, the
     // output and status addresses
-    std::vector<NearItem> near_items;     // BEM_NEAR_SINGULAR: the request's vertex-sharing pairs
-    std::vector<int64_t> near_index;      // P0: their entries' positions in the output
-    struct NearRec {
-        int64_t entry;                    // position in the output
-        int32_t first, count;             // into near_src
-    };
-    std::vector<NearRec> near_recs;       // P1: entries with singular contributions, ascending
-    std::vector<int32_t> near_src;        // P1: pair * 9 + 3 a + b of each contribution, per entry ascending
-                                          // (hypersingular operator: the pair)
-    std::vector<double> near_wt;          // P1 hypersingular operator: curl_a . curl_b of each contribution
+    std::vector<NearPair> near_pairs;     // BEM_NEAR_SINGULAR: the request's vertex-sharing pairs
+    std::vector<int32_t> near_ints;       // P1: gptr | rptr | rs of NearReq (pair indices within the request);
+                                          // the column dofs follow when staged
+    int32_t near_slots = 0;               // row-side triangles
+    std::vector<int32_t> near_rows;       // P1: rows with at least one pair
     int key = 0;                          // launch group (operator, space, precision, rule)
     std::vector<EntryBlock> pre_blocks;   // `req` holds the fixed-side bit only
     ReqDev pre_dev{};

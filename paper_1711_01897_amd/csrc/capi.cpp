@@ -136,15 +136,19 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
     const size_t off_b = off;
     off = al(off + sizeof(EntryBlock) * (size_t)r.nblocks);
     const size_t off_near = off;
-    const bool p1_near = r.space != BEM_P0 && !r.near_items.empty();
-    off = al(off + (p1_near ? near_p1_layout(r).bytes : sizeof(NearItem) * r.near_items.size()));
+    const bool near = !r.near_pairs.empty();
+    const NearCount near_n = near_count(r);
+    const NearLayout near_l = near_layout(near_kind(r), near_n);
+    off = al(off + (near ? near_l.staged : 0));
     const size_t off_in = off;
     off = al(off + r.in_bytes);
     const size_t off_status = off;
     off = al(off + 8);
     const size_t in_total = off;
-    if (fixed && in_total > fixed_bytes)
-        return fail(BEM_E_OOM, "request needs " + std::to_string(in_total) + " bytes of workspace, more than the " +
+    // what the singular kernels write for each other follows the staged part
+    const size_t ws_total = in_total + (near ? near_l.bytes - near_l.staged : 0);
+    if (fixed && ws_total > fixed_bytes)
+        return fail(BEM_E_OOM, "request needs " + std::to_string(ws_total) + " bytes of workspace, more than the " +
                                    std::to_string(fixed_bytes) + "-byte static workspace of the no-allocation entry point");
     char *host = nullptr;
     thread_local std::vector<char> pageable;
@@ -160,7 +164,7 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
     }
     char *ws = fixed;
     if (!fixed) {
-        hipError_t e = hipMallocAsync((void **)&ws, in_total, s);
+        hipError_t e = hipMallocAsync((void **)&ws, ws_total, s);
         if (e != hipSuccess) {
             pinned_release(host, nullptr);
             return fail(BEM_E_DEVICE, std::string("hipMallocAsync: ") + hipGetErrorString(e));
@@ -172,14 +176,13 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
     d.out = dev_out;
     std::memcpy(host + off_req, &d, sizeof(ReqDev));
     write_blocks(r, 0, reinterpret_cast<EntryBlock *>(host + off_b));
-    if (p1_near) {
-        stage_near_p1(r, near_p1_layout(r), host + off_near, ws + off_near, static_cast<char *>(dev_out), 0, 0, 0);
-    } else {
-        NearItem *q = reinterpret_cast<NearItem *>(host + off_near);
-        for (size_t j = 0; j < r.near_items.size(); ++j) {
-            q[j] = r.near_items[j];
-            q[j].out = static_cast<char *>(dev_out) + (size_t)r.near_index[j] * r.elem_bytes;
-        }
+    NearLayout nl = near_l;
+    if (near) {
+        // the device-only part sits past the staged image of the whole request
+        nl.keys += in_total - off_near - near_l.staged;
+        nl.local += in_total - off_near - near_l.staged;
+        NearCount at;
+        stage_near(r, nl, host + off_near, ws + off_near, static_cast<char *>(dev_out), at);
     }
     hipError_t e = hipMemcpyAsync(ws, host, in_total, hipMemcpyHostToDevice, s);
     if (!fixed) {
@@ -192,14 +195,7 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
     const ReqDev *dreq = (const ReqDev *)(ws + off_req);
     Variant v{kernel_op(r.op), r.space, r.prec, mesh->q};
     BEM_HIP_TRY(launch_entries(v, dreq, (const EntryBlock *)(ws + off_b), r.nblocks, s));
-    if (p1_near)
-        BEM_HIP_TRY(launch_near_p1_region(r.op == BEM_LAPLACE_HYPS || r.op == BEM_HELMHOLTZ_HYPS ? (int)r.op
-                                                                                                : kernel_op(r.op),
-                                          r.prec == BEM_FP32, near_p1_layout(r), ws + off_near,
-                                          (int64_t)r.near_items.size(), (int64_t)r.near_recs.size(), s));
-    else
-        BEM_HIP_TRY(launch_near(kernel_op(r.op), r.prec == BEM_FP32, (const NearItem *)(ws + off_near),
-                                (int64_t)r.near_items.size(), s));
+    if (near) BEM_HIP_TRY(launch_near(near_kind(r), nl, near_n, ws + off_near, s));
     if (!fixed) BEM_HIP_TRY(hipFreeAsync(ws, s));
     return BEM_OK;
 }

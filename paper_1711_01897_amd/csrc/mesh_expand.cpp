@@ -253,54 +253,22 @@ void build_lane_set(const bem_mesh &m, int space, const int32_t *dofs, int64_t n
 
 namespace {
 
-// Largest |c| over a singular item's integration domain, where the device
-// writes x - y = rho c with the radius rho in [0, 1] and the Helmholtz
-// radial integrals take omega = k |c| (near.hip).  |c| is convex in each
-// coordinate of the (bi)linear parameterisations, so its maximum sits at the
-// corners of the parameter domain:
-//   identical:     c runs along the three edge vectors, the longest edge;
-//   common edge:   c = dh E + s1 a - s2 b on four faces, dh in {0, +-1},
-//                  s1, s2 in {0, 1} at the corners;
-//   common vertex: c = a(u) - z b(v) or z a(u) - b(v), u, v, z in {0, 1}.
-double near_span(const NearItem &q)
+// Largest distance of two points of triangles T and S (at two of their
+// vertices).  The device writes x - y = rho c over a singular pair with the
+// radius rho in [0, 1] and takes omega = k |c|; c is itself a difference x - y of
+// points of the two triangles, at the corners of its domain of their vertices:
+//   identical:     c runs along the three edge vectors;
+//   common edge:   c = dh E + s1 a - s2 b on four faces;
+//   common vertex: c = a(u) - z b(v) or z a(u) - b(v), u, v, z in [0, 1].
+double near_span(const bem_mesh &m, int32_t T, int32_t S)
 {
-    auto dist = [](const double *a, const double *b) {
-        const double d0 = a[0] - b[0], d1 = a[1] - b[1], d2 = a[2] - b[2];
-        return std::sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-    };
-    const double *v = q.v;
-    if (q.kind == 0) return std::max(std::max(dist(v + 3, v), dist(v + 6, v + 3)), dist(v + 6, v));
-    if (q.kind == 1) {
-        double E[3], a[3], b[3];
-        for (int d = 0; d < 3; ++d) {
-            E[d] = v[3 + d] - v[d];
-            a[d] = v[6 + d] - v[d];
-            b[d] = v[9 + d] - v[d];
-        }
-        double best = 0.0;
-        for (int face = 0; face < 4; ++face)
-            for (int p = 0; p <= 1; ++p)
-                for (int qq = 0; qq <= 1; ++qq) {
-                    double dh, s1, s2;
-                    if (face == 0) dh = p, s1 = (1 - p) * qq, s2 = 1;
-                    else if (face == 1) dh = p, s1 = 1 - p, s2 = qq;
-                    else if (face == 2) dh = -p, s1 = 1, s2 = (1 - p) * qq;
-                    else dh = -p, s1 = qq, s2 = 1 - p;
-                    double c2 = 0.0;
-                    for (int d = 0; d < 3; ++d) {
-                        const double c = dh * E[d] + s1 * a[d] - s2 * b[d];
-                        c2 += c * c;
-                    }
-                    best = std::max(best, std::sqrt(c2));
-                }
-        return best;
-    }
-    const double *P = v, *T[2] = {v + 3, v + 6}, *S[2] = {v + 9, v + 12};
     double best = 0.0;
-    for (int i = 0; i < 2; ++i) {
-        best = std::max(best, std::max(dist(T[i], P), dist(S[i], P)));
-        for (int j = 0; j < 2; ++j) best = std::max(best, dist(T[i], S[j]));
-    }
+    for (int i = 0; i < 3; ++i)
+        for (int j = 0; j < 3; ++j) {
+            const double *x = &m.xyz[3 * (size_t)m.tri[3 * (size_t)T + i]], *y = &m.xyz[3 * (size_t)m.tri[3 * (size_t)S + j]];
+            const double d0 = x[0] - y[0], d1 = x[1] - y[1], d2 = x[2] - y[2];
+            best = std::max(best, std::sqrt(d0 * d0 + d1 * d1 + d2 * d2));
+        }
     return best;
 }
 
@@ -312,9 +280,10 @@ constexpr double kOmegaMax = 12.0;
 
 int check_near_omega(const Request &r)
 {
-    if (!is_complex_op(r.op)) return BEM_OK;
+    // two triangles that share a vertex reach two edges at most
+    if (!is_complex_op(r.op) || r.k * 2.0 * r.mesh->max_edge <= kOmegaMax) return BEM_OK;
     double span = 0.0;
-    for (const NearItem &q : r.near_items) span = std::max(span, near_span(q));
+    for (const NearPair &q : r.near_pairs) span = std::max(span, near_span(*r.mesh, q.a, q.b));
     if (r.k * span > kOmegaMax)
         return fail(BEM_E_ARG, "BEM_NEAR_SINGULAR Helmholtz pair with k |x - y| up to " + std::to_string(r.k * span) +
                                    " > 12: the singular scheme's radial series is accurate only below that (the mesh "
@@ -322,331 +291,220 @@ int check_near_omega(const Request &r)
     return BEM_OK;
 }
 
-// The vertex-sharing pairs of a P0 request in the layouts of NearItem.  The
-// kernels' test triangle is the row's (the column's for the adjoint double
-// layer, evaluated as the transposed double layer).
-void build_near_items(Request &r)
+// Per-thread marks of triangles and of column dofs (vertices or triangles).
+struct NearScratch {
+    std::vector<uint32_t> tri, col, slot;
+    std::vector<int32_t> slot_of, head, next;
+    uint32_t tgen = 0, cgen = 0, sgen = 0;
+    static uint32_t fresh(std::vector<uint32_t> &v, uint32_t &gen, size_t n)
+    {
+        if (v.size() < n) {
+            v.assign(n, 0);
+            gen = 0;
+        }
+        if (++gen == 0) {
+            std::fill(v.begin(), v.end(), 0);
+            gen = 1;
+        }
+        return gen;
+    }
+};
+thread_local NearScratch g_near;
+
+bool same_pair_vanishes(const Request &r)
+{
+    // (x - y).n_y = 0 on a flat triangle
+    return kernel_op(r.op) == BEM_LAPLACE_DLP || kernel_op(r.op) == BEM_HELMHOLTZ_DLP;
+}
+
+// The triangles that share a vertex with a, ascending, appended to out.
+void neighbours(const bem_mesh &m, int32_t a, std::vector<int32_t> &out)
+{
+    NearScratch &sc = g_near;
+    const uint32_t g = NearScratch::fresh(sc.tri, sc.tgen, (size_t)m.nt);
+    out.clear();
+    for (int k = 0; k < 3; ++k) {
+        const int32_t v = m.tri[3 * (size_t)a + k];
+        for (int64_t s = m.star_ptr[v]; s < m.star_ptr[v + 1]; ++s) {
+            const int32_t b = m.star[s] >> 2;
+            if (sc.tri[b] == g) continue;
+            sc.tri[b] = g;
+            out.push_back(b);
+        }
+    }
+    std::sort(out.begin(), out.end());
+}
+
+// P0: one pair per entry whose two triangles share a vertex.
+void build_near_p0(Request &r)
 {
     const bem_mesh &m = *r.mesh;
-    const bool adj = is_adjoint_op(r.op);
-    std::vector<std::pair<int32_t, int64_t>> colpos((size_t)r.ncols);
-    for (int64_t c = 0; c < r.ncols; ++c) colpos[c] = {r.cols[c], c};
-    std::sort(colpos.begin(), colpos.end());
-    auto vtx = [&](int32_t t, int k) { return &m.xyz[3 * (size_t)m.tri[3 * (size_t)t + k]]; };
-    auto put3 = [](double *dst, const double *src) {
-        dst[0] = src[0];
-        dst[1] = src[1];
-        dst[2] = src[2];
-    };
-    auto cross_len = [&](int32_t t, double *n) {
-        const double *a = vtx(t, 0), *b = vtx(t, 1), *c = vtx(t, 2);
-        const double e1[3] = {b[0] - a[0], b[1] - a[1], b[2] - a[2]}, e2[3] = {c[0] - a[0], c[1] - a[1], c[2] - a[2]};
-        const double N[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2], e1[0] * e2[1] - e1[1] * e2[0]};
-        const double J = std::sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
-        if (n)
-            for (int d = 0; d < 3; ++d) n[d] = N[d] / J;
-        return J;
-    };
+    NearScratch &sc = g_near;
+    const uint32_t cg = NearScratch::fresh(sc.col, sc.cgen, (size_t)std::max(m.nt, m.nv));
+    if (sc.head.size() < sc.col.size()) sc.head.resize(sc.col.size());
+    sc.next.resize((size_t)r.ncols);
+    for (int64_t c = r.ncols - 1; c >= 0; --c) {   // positions of a column in ascending order
+        const int32_t t = r.cols[c];
+        sc.next[c] = sc.col[t] == cg ? sc.head[t] : -1;
+        sc.col[t] = cg;
+        sc.head[t] = (int32_t)c;
+    }
+    const bool skip_same = same_pair_vanishes(r);
     std::vector<int32_t> nb;
-    for (int64_t ri = 0; ri < r.nrows; ++ri) {
-        const int32_t a = r.rows[ri];
-        nb.clear();
-        for (int k = 0; k < 3; ++k) {
-            const int32_t v = m.tri[3 * (size_t)a + k];
-            for (int64_t s = m.star_ptr[v]; s < m.star_ptr[v + 1]; ++s) nb.push_back(m.star[s] >> 2);
-        }
-        std::sort(nb.begin(), nb.end());
-        nb.erase(std::unique(nb.begin(), nb.end()), nb.end());
+    for (int64_t i = 0; i < r.nrows; ++i) {
+        const int32_t a = r.rows[i];
+        neighbours(m, a, nb);
         for (int32_t b : nb) {
-            auto it = std::lower_bound(colpos.begin(), colpos.end(), std::make_pair(b, (int64_t)-1));
-            for (; it != colpos.end() && it->first == b; ++it) {
-                const int32_t T = adj ? b : a, S = adj ? a : b;   // kernel test and trial triangles
-                NearItem q{};
-                const int32_t *tv = &m.tri[3 * (size_t)T], *sv = &m.tri[3 * (size_t)S];
-                int shared = 0, ts[3], ss[3];
-                for (int i = 0; i < 3; ++i)
-                    for (int j = 0; j < 3; ++j)
-                        if (tv[i] == sv[j]) {
-                            ts[shared] = i;
-                            ss[shared] = j;
-                            ++shared;
-                        }
-                q.k = is_complex_op(r.op) ? r.k : 0.0;
-                q.jt = cross_len(T, nullptr);
-                q.js = cross_len(S, q.ny);
-                if (shared == 3) {
-                    // the double layer of a flat triangle on itself vanishes ((x - y).n_y = 0)
-                    if (kernel_op(r.op) == BEM_LAPLACE_DLP || kernel_op(r.op) == BEM_HELMHOLTZ_DLP) continue;
-                    q.kind = 0;
-                    for (int k = 0; k < 3; ++k) put3(q.v + 3 * k, vtx(T, k));
-                } else if (shared == 2) {
-                    q.kind = 1;
-                    put3(q.v, vtx(T, ts[0]));
-                    put3(q.v + 3, vtx(T, ts[1]));
-                    put3(q.v + 6, vtx(T, 3 - ts[0] - ts[1]));
-                    put3(q.v + 9, vtx(S, 3 - ss[0] - ss[1]));
-                } else {
-                    q.kind = 2;
-                    put3(q.v, vtx(T, ts[0]));
-                    put3(q.v + 3, vtx(T, (ts[0] + 1) % 3));
-                    put3(q.v + 6, vtx(T, (ts[0] + 2) % 3));
-                    put3(q.v + 9, vtx(S, (ss[0] + 1) % 3));
-                    put3(q.v + 12, vtx(S, (ss[0] + 2) % 3));
-                }
-                r.near_items.push_back(q);
-                r.near_index.push_back(ri * r.ncols + it->second);
-            }
+            if (sc.col[b] != cg || (skip_same && a == b)) continue;
+            for (int32_t c = sc.head[b]; c >= 0; c = sc.next[c])
+                r.near_pairs.push_back({a, b, 0, 0, i * r.ncols + c});
         }
     }
 }
 
-// The vertex-sharing pairs of a P1 (or DP1) request and, per output entry,
-// the local matrix values that sum into it.  A pair (a on the row side, b
-// adjacent to it) counts if a lies in the star of a requested row vertex
-// (DP1: is the triangle of a requested row dof) and b touches a requested
-// column vertex (DP1: is the triangle of a requested column dof); its local
-// matrix M[i][j] (kernel test vertex i, trial vertex j) goes to the entries
-// of the row and column positions of those vertices (DP1: of the dofs (a, i)
-// and (b, j), one entry each), exchanged for the adjoint double layer.
-void build_near_items_p1(Request &r)
+// P1 and DP1: the pairs (a, b) with a in the star of a requested row dof and
+// b, adjacent to it, in the star of a requested column dof, grouped by a in
+// the order the rows' stars name them, each once; the rows' stars as (group,
+// local vertex).
+void build_near_p1(Request &r)
 {
     const bem_mesh &m = *r.mesh;
-    const bool adj = is_adjoint_op(r.op);
-    const bool dlp = kernel_op(r.op) == BEM_LAPLACE_DLP || kernel_op(r.op) == BEM_HELMHOLTZ_DLP;
-    const bool hyps = r.op == BEM_LAPLACE_HYPS, hhyps = r.op == BEM_HELMHOLTZ_HYPS;
-    std::vector<std::pair<int32_t, int64_t>> rowpos((size_t)r.nrows), colpos((size_t)r.ncols);
-    for (int64_t i = 0; i < r.nrows; ++i) rowpos[i] = {r.rows[i], i};
-    for (int64_t i = 0; i < r.ncols; ++i) colpos[i] = {r.cols[i], i};
-    std::sort(rowpos.begin(), rowpos.end());
-    std::sort(colpos.begin(), colpos.end());
-    auto first_of = [](const std::vector<std::pair<int32_t, int64_t>> &v, int32_t x) {
-        return std::lower_bound(v.begin(), v.end(), std::make_pair(x, (int64_t)-1));
-    };
-    auto vtx = [&](int32_t t, int k) { return &m.xyz[3 * (size_t)m.tri[3 * (size_t)t + k]]; };
-    auto put3 = [](double *dst, const double *src) {
-        dst[0] = src[0];
-        dst[1] = src[1];
-        dst[2] = src[2];
-    };
-    auto cross_len = [&](int32_t t, double *n) {
-        const double *a = vtx(t, 0), *b = vtx(t, 1), *c = vtx(t, 2);
-        const double e1[3] = {b[0] - a[0], b[1] - a[1], b[2] - a[2]}, e2[3] = {c[0] - a[0], c[1] - a[1], c[2] - a[2]};
-        const double N[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2], e1[0] * e2[1] - e1[1] * e2[0]};
-        const double J = std::sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
-        if (n)
-            for (int d = 0; d < 3; ++d) n[d] = N[d] / J;
-        return J;
-    };
-    auto star_of = [&](const int32_t *verts, int nv, std::vector<int32_t> &out) {
-        out.clear();
-        for (int k = 0; k < nv; ++k)
-            for (int64_t s = m.star_ptr[verts[k]]; s < m.star_ptr[verts[k] + 1]; ++s) out.push_back(m.star[s] >> 2);
-        std::sort(out.begin(), out.end());
-        out.erase(std::unique(out.begin(), out.end()), out.end());
-    };
-    // P1 dofs are vertices; a DP1 dof is (triangle t, local vertex) = 3 t + local
     const bool dp1 = r.space == BEM_DP1;
-    auto dof_of = [&](int32_t t, int32_t v) -> int32_t {
-        if (!dp1) return v;
-        int i = 0;
-        while (m.tri[3 * (size_t)t + i] != v) ++i;
-        return 3 * t + i;
-    };
-    std::vector<int32_t> rt, nb;
-    {
-        std::vector<int32_t> rv(r.rows.begin(), r.rows.end());
-        std::sort(rv.begin(), rv.end());
-        rv.erase(std::unique(rv.begin(), rv.end()), rv.end());
-        rt.clear();
-        for (int32_t v : rv) {
-            if (dp1) {
-                rt.push_back(v / 3);
-                continue;
-            }
-            for (int64_t s = m.star_ptr[v]; s < m.star_ptr[v + 1]; ++s) rt.push_back(m.star[s] >> 2);
+    NearScratch &sc = g_near;
+    const uint32_t cg = NearScratch::fresh(sc.col, sc.cgen, (size_t)std::max(m.nt, m.nv));
+    for (int32_t d : r.cols) sc.col[dp1 ? d / 3 : d] = cg;   // P1: vertices, DP1: triangles
+    const uint32_t sg = NearScratch::fresh(sc.slot, sc.sgen, (size_t)m.nt);
+    if (sc.slot_of.size() < (size_t)m.nt) sc.slot_of.resize((size_t)m.nt);
+    const bool skip_same = same_pair_vanishes(r);
+    std::vector<int32_t> nb, gptr{0}, rptr{0}, rs;
+    rptr.reserve((size_t)r.nrows + 1);
+    for (int64_t i = 0; i < r.nrows; ++i) {
+        int64_t s0, s1;
+        if (dp1) {
+            s0 = m.dp1_star[r.rows[i]];
+            s1 = s0 + 1;
+        } else {
+            s0 = m.star_ptr[r.rows[i]];
+            s1 = m.star_ptr[r.rows[i] + 1];
         }
-        std::sort(rt.begin(), rt.end());
-        rt.erase(std::unique(rt.begin(), rt.end()), rt.end());
-    }
-    // surface curl of the hat function of global vertex v on triangle t: with
-    // the mesh's vertex order (v0, v1, v2) and J = |(v1 - v0) x (v2 - v0)|,
-    // curl lambda_i = (v_{i+1} - v_{i+2}) / J
-    auto curl = [&](int32_t t, int32_t v, double *c) {
-        int i = 0;
-        while (m.tri[3 * (size_t)t + i] != v) ++i;
-        const double *p1 = vtx(t, (i + 1) % 3), *p2 = vtx(t, (i + 2) % 3);
-        const double J = cross_len(t, nullptr);
-        for (int d = 0; d < 3; ++d) c[d] = (p1[d] - p2[d]) / J;
-    };
-    struct Contrib {
-        int64_t entry;
-        int32_t src;
-        double wt;
-        bool operator<(const Contrib &o) const { return entry != o.entry ? entry < o.entry : src < o.src; }
-    };
-    std::vector<Contrib> contrib;
-    for (int32_t a : rt) {
-        star_of(&m.tri[3 * (size_t)a], 3, nb);
-        for (int32_t b : nb) {
-            bool touches = false;
-            for (int k = 0; k < 3 && !touches; ++k) {
-                const int32_t v = dp1 ? 3 * b + k : m.tri[3 * (size_t)b + k];
-                auto it = first_of(colpos, v);
-                touches = it != colpos.end() && it->first == v;
-            }
-            if (!touches) continue;
-            const int32_t T = adj ? b : a, S = adj ? a : b;   // kernel test and trial triangles
-            const int32_t *tv = &m.tri[3 * (size_t)T], *sv = &m.tri[3 * (size_t)S];
-            int shared = 0, ts[3], ss[3];
-            for (int i = 0; i < 3; ++i)
-                for (int j = 0; j < 3; ++j)
-                    if (tv[i] == sv[j]) {
-                        ts[shared] = i;
-                        ss[shared] = j;
-                        ++shared;
+        bool any = false;
+        for (int64_t s = s0; s < s1; ++s) {
+            const int32_t a = m.star[s] >> 2;
+            if (sc.slot[a] != sg) {
+                sc.slot[a] = sg;
+                sc.slot_of[a] = (int32_t)gptr.size() - 1;
+                neighbours(m, a, nb);
+                for (int32_t b : nb) {
+                    bool touches;
+                    if (dp1) {
+                        touches = sc.col[b] == cg;
+                    } else {
+                        const int32_t *v = &m.tri[3 * (size_t)b];
+                        touches = sc.col[v[0]] == cg || sc.col[v[1]] == cg || sc.col[v[2]] == cg;
                     }
-            if (shared == 3 && dlp) continue;   // (x - y).n_y = 0 on a flat triangle
-            NearItem q{};
-            q.k = is_complex_op(r.op) ? r.k : 0.0;
-            int32_t tl[3], sl[3];   // global vertices in the kernel's local orders
-            double nt[3];
-            q.jt = cross_len(T, nt);
-            q.js = cross_len(S, q.ny);
-            if (shared == 3) {
-                q.kind = 0;
-                for (int k = 0; k < 3; ++k) {
-                    put3(q.v + 3 * k, vtx(T, k));
-                    tl[k] = sl[k] = tv[k];
+                    if (touches && !(skip_same && a == b)) r.near_pairs.push_back({a, b, 0, 0, 0});
                 }
-            } else if (shared == 2) {
-                q.kind = 1;
-                const int t3 = 3 - ts[0] - ts[1], s3 = 3 - ss[0] - ss[1];
-                put3(q.v, vtx(T, ts[0]));
-                put3(q.v + 3, vtx(T, ts[1]));
-                put3(q.v + 6, vtx(T, t3));
-                put3(q.v + 9, vtx(S, s3));
-                tl[0] = tv[ts[0]], tl[1] = tv[ts[1]], tl[2] = tv[t3];
-                sl[0] = sv[ss[0]], sl[1] = sv[ss[1]], sl[2] = sv[s3];
-            } else {
-                q.kind = 2;
-                for (int k = 0; k < 3; ++k) {
-                    put3(q.v + 3 * k, vtx(T, (ts[0] + k) % 3));
-                    tl[k] = tv[(ts[0] + k) % 3];
-                }
-                put3(q.v + 9, vtx(S, (ss[0] + 1) % 3));
-                put3(q.v + 12, vtx(S, (ss[0] + 2) % 3));
-                for (int k = 0; k < 3; ++k) sl[k] = sv[(ss[0] + k) % 3];
+                gptr.push_back((int32_t)r.near_pairs.size());
             }
-            const int32_t pi = (int32_t)r.near_items.size();
-            r.near_items.push_back(q);
-            for (int i = 0; i < 3; ++i)
-                for (int j = 0; j < 3; ++j) {
-                    const int32_t rv = adj ? dof_of(S, sl[j]) : dof_of(T, tl[i]);
-                    const int32_t cv = adj ? dof_of(T, tl[i]) : dof_of(S, sl[j]);
-                    double w = 1.0;
-                    if (hyps || hhyps) {
-                        double ct[3], cs[3];
-                        curl(T, tl[i], ct);
-                        curl(S, sl[j], cs);
-                        w = ct[0] * cs[0] + ct[1] * cs[1] + ct[2] * cs[2];
-                    }
-                    // Helmholtz hypersingular: curl products times the P0 value (source 9 of the pair)
-                    // minus k^2 n_x . n_y times the single layer's local matrix
-                    const double wn = -r.k * r.k * (nt[0] * q.ny[0] + nt[1] * q.ny[1] + nt[2] * q.ny[2]);
-                    for (auto ri = first_of(rowpos, rv); ri != rowpos.end() && ri->first == rv; ++ri)
-                        for (auto ci = first_of(colpos, cv); ci != colpos.end() && ci->first == cv; ++ci) {
-                            const int64_t e = ri->second * r.ncols + ci->second;
-                            if (hhyps) {
-                                contrib.push_back({e, pi * 10 + 9, w});
-                                contrib.push_back({e, pi * 10 + 3 * i + j, wn});
-                            } else {
-                                contrib.push_back({e, hyps ? pi : pi * 9 + 3 * i + j, w});
-                            }
-                        }
-                }
+            const int32_t slot = sc.slot_of[a];
+            if (gptr[slot + 1] == gptr[slot]) continue;
+            rs.push_back((slot << 2) | (m.star[s] & 3));
+            any = true;
         }
+        rptr.push_back((int32_t)rs.size());
+        if (any) r.near_rows.push_back((int32_t)i);
     }
-    std::sort(contrib.begin(), contrib.end());
-    r.near_src.resize(contrib.size());
-    if (hyps || hhyps) r.near_wt.resize(contrib.size());
-    for (size_t k = 0; k < contrib.size(); ++k) {
-        r.near_src[k] = contrib[k].src;
-        if (hyps || hhyps) r.near_wt[k] = contrib[k].wt;
-        if (k == 0 || contrib[k].entry != contrib[k - 1].entry)
-            r.near_recs.push_back({contrib[k].entry, (int32_t)k, 0});
-        ++r.near_recs.back().count;
-    }
+    r.near_slots = (int32_t)gptr.size() - 1;
+    r.near_ints = std::move(gptr);
+    r.near_ints.insert(r.near_ints.end(), rptr.begin(), rptr.end());
+    r.near_ints.insert(r.near_ints.end(), rs.begin(), rs.end());
+}
+
+void clear_near(Request &r)
+{
+    r.near_pairs.clear();
+    r.near_ints.clear();
+    r.near_rows.clear();
+    r.near_slots = 0;
 }
 
 }  // namespace
 
-static size_t align256_sz(size_t x) { return (x + 255) & ~(size_t)255; }
-
-NearP1Layout near_p1_layout(int mode, int64_t items, int64_t recs, int64_t src)
+int near_kind(const Request &r)
 {
-    NearP1Layout L;
-    L.per = mode == 1 ? 1 : (mode == 2 ? 18 : (mode == 3 ? 20 : 9));
-    L.src_per = mode == 1 ? 1 : (mode == 3 ? 10 : 9);
-    L.weighted = mode == 1 || mode == 3;
-    L.cplx = mode >= 2;
-    L.items = 0;
-    L.recs = align256_sz(sizeof(NearItem) * (size_t)items);
-    L.src = L.recs + align256_sz(sizeof(NearGather) * (size_t)recs);
-    L.wt = L.src + align256_sz(sizeof(int32_t) * (size_t)src);
-    L.local = L.wt + (L.weighted ? align256_sz(sizeof(double) * (size_t)src) : 0);
-    L.bytes = L.local + align256_sz(L.per * sizeof(double) * (size_t)items);
-    return L;
-}
-
-int near_p1_mode(const Request &r)
-{
-    return r.op == BEM_LAPLACE_HYPS ? 1 : (r.op == BEM_HELMHOLTZ_HYPS ? 3 : (is_complex_op(r.op) ? 2 : 0));
-}
-
-NearP1Layout near_p1_layout(const Request &r)
-{
-    return near_p1_layout(near_p1_mode(r), (int64_t)r.near_items.size(), (int64_t)r.near_recs.size(),
-                          (int64_t)r.near_src.size());
-}
-
-int near_p1_group(const Request &r)
-{
-    const int kop = kernel_op(r.op);
-    const int g = r.op == BEM_LAPLACE_HYPS   ? 2
-                : r.op == BEM_HELMHOLTZ_HYPS ? 5
-                : kop == BEM_HELMHOLTZ_SLP   ? 3
-                : kop == BEM_HELMHOLTZ_DLP   ? 4
-                                             : kop;
+    const int g = r.op == BEM_LAPLACE_HYPS   ? 8
+                : r.op == BEM_HELMHOLTZ_HYPS ? 9
+                                             : kernel_op(r.op) + (r.space == BEM_P0 ? 0 : 4);
     return 2 * g + (r.prec == BEM_FP32 ? 1 : 0);
 }
 
-void stage_near_p1(const Request &r, const NearP1Layout &L, char *host, char *dev, char *out_dev, int64_t pb,
-                   int64_t rb, int64_t sb)
+NearCount near_count(const Request &r)
 {
-    NearItem *q = reinterpret_cast<NearItem *>(host + L.items) + pb;
-    for (size_t j = 0; j < r.near_items.size(); ++j) {
-        q[j] = r.near_items[j];
-        q[j].out = dev + L.local + L.per * sizeof(double) * ((size_t)pb + j);
+    NearCount n;
+    if (r.near_pairs.empty()) return n;
+    n.reqs = 1;
+    n.pairs = (int64_t)r.near_pairs.size();
+    if (r.space != BEM_P0) {
+        n.blocks = (int64_t)r.near_rows.size() * ((r.ncols + 255) / 256);
+        n.ints = (int64_t)r.near_ints.size() + r.ncols;
     }
-    NearGather *g = reinterpret_cast<NearGather *>(host + L.recs) + rb;
-    for (size_t j = 0; j < r.near_recs.size(); ++j)
-        g[j] = {out_dev + (size_t)r.near_recs[j].entry * r.elem_bytes, (int32_t)(sb + r.near_recs[j].first),
-                r.near_recs[j].count};
-    int32_t *src = reinterpret_cast<int32_t *>(host + L.src) + sb;
-    for (size_t j = 0; j < r.near_src.size(); ++j) src[j] = (int32_t)(L.src_per * pb) + r.near_src[j];
-    if (L.weighted && !r.near_wt.empty())
-        std::memcpy(reinterpret_cast<double *>(host + L.wt) + sb, r.near_wt.data(), sizeof(double) * r.near_wt.size());
+    return n;
 }
 
-hipError_t launch_near_p1_region(int op, bool fp32, const NearP1Layout &L, char *dev, int64_t items, int64_t recs,
-                                 hipStream_t s)
+NearLayout near_layout(int kind, const NearCount &n)
 {
-    hipError_t e = launch_near_p1(op, reinterpret_cast<const NearItem *>(dev + L.items), items, s);
-    if (e != hipSuccess) return e;
-    return launch_near_gather(fp32, L.cplx, reinterpret_cast<const NearGather *>(dev + L.recs), recs,
-                              reinterpret_cast<const int32_t *>(dev + L.src),
-                              L.weighted ? reinterpret_cast<const double *>(dev + L.wt) : nullptr,
-                              reinterpret_cast<const double *>(dev + L.local), s);
+    auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    const int g = kind >> 1;
+    const bool p0 = g < 4, cplx = p0 ? g >= 2 : (g == 6 || g == 7 || g == 9);
+    NearLayout L;
+    L.pairs = al(sizeof(NearReq) * (size_t)n.reqs);
+    L.blocks = al(L.pairs + sizeof(NearPair) * (size_t)n.pairs);
+    L.ints = al(L.blocks + sizeof(NearBlock) * (size_t)n.blocks);
+    L.staged = al(L.ints + sizeof(int32_t) * (size_t)n.ints);
+    L.keys = L.staged;
+    L.local = p0 ? L.keys : al(L.keys + sizeof(int4) * (size_t)n.pairs);
+    L.bytes = p0 ? L.local : al(L.local + 9 * (cplx ? 2 : 1) * sizeof(double) * (size_t)n.pairs);
+    return L;
+}
+
+void stage_near(const Request &r, const NearLayout &L, char *host, char *dev, char *out_dev, NearCount &at)
+{
+    const bem_mesh &m = *r.mesh;
+    NearReq d{};
+    d.xyz = m.d_xyz;
+    d.g64 = m.d_g64;
+    d.vtx = m.d_vtx;
+    d.out = out_dev;
+    d.k = is_complex_op(r.op) ? r.k : 0.0;
+    d.ncols = (int32_t)r.ncols;
+    d.transposed = is_adjoint_op(r.op) ? 1 : 0;
+    d.dp1 = r.space == BEM_DP1 ? 1 : 0;
+    NearPair *q = reinterpret_cast<NearPair *>(host + L.pairs) + at.pairs;
+    for (size_t j = 0; j < r.near_pairs.size(); ++j) {
+        q[j] = r.near_pairs[j];
+        q[j].req = (int32_t)at.reqs;
+    }
+    const NearCount n = near_count(r);
+    if (r.space != BEM_P0) {
+        int32_t *h = reinterpret_cast<int32_t *>(host + L.ints) + at.ints;
+        const int32_t *dv = reinterpret_cast<const int32_t *>(dev + L.ints) + at.ints;
+        const size_t ng = (size_t)r.near_slots + 1;
+        for (size_t j = 0; j < ng; ++j) h[j] = r.near_ints[j] + (int32_t)at.pairs;   // indices into the region
+        std::memcpy(h + ng, r.near_ints.data() + ng, sizeof(int32_t) * (r.near_ints.size() - ng));
+        std::memcpy(h + r.near_ints.size(), r.cols.data(), sizeof(int32_t) * (size_t)r.ncols);
+        d.gptr = dv;
+        d.rptr = dv + ng;
+        d.rs = dv + ng + r.nrows + 1;
+        d.cols = dv + r.near_ints.size();
+        NearBlock *b = reinterpret_cast<NearBlock *>(host + L.blocks) + at.blocks;
+        for (int32_t row : r.near_rows)
+            for (int64_t c = 0; c < r.ncols; c += 256) *b++ = {(int32_t)at.reqs, row, (int32_t)c, 0};
+    }
+    reinterpret_cast<NearReq *>(host)[at.reqs] = d;
+    at.reqs += n.reqs;
+    at.pairs += n.pairs;
+    at.blocks += n.blocks;
+    at.ints += n.ints;
 }
 
 int expand_request(Request &r)
@@ -684,16 +542,12 @@ int expand_request(Request &r)
     r.nlane = (int64_t)r.own.lane.size();
     r.nchunk = r.own.nchunk();
     r.ndistinct = r.own.ndistinct;
-    r.near_items.clear();
-    r.near_index.clear();
-    r.near_recs.clear();
-    r.near_src.clear();
-    r.near_wt.clear();
+    clear_near(r);
     if (r.near == BEM_NEAR_SINGULAR) {
         if (r.space == BEM_P0)
-            build_near_items(r);
+            build_near_p0(r);
         else
-            build_near_items_p1(r);
+            build_near_p1(r);
         const int rc = check_near_omega(r);
         if (rc != BEM_OK) return rc;
     }
@@ -703,11 +557,7 @@ int expand_request(Request &r)
 
 void expand_single_fixed(Request &r, int32_t dof, int rowfix, const LaneRef *ext)
 {
-    r.near_items.clear();
-    r.near_index.clear();
-    r.near_recs.clear();
-    r.near_src.clear();
-    r.near_wt.clear();
+    clear_near(r);
     r.ext = ext;
     r.fixrows = rowfix;
     r.rowfix = is_adjoint_op(r.op) ? 1 - rowfix : rowfix;
@@ -734,7 +584,7 @@ size_t request_bytes(const Request &r)
 {
     // descriptor, inputs, status, outputs, block table, launch-timing records
     return sizeof(ReqDev) + r.in_bytes + 8 + r.out_bytes + (size_t)r.nblocks * (sizeof(EntryBlock) + 16) +
-           (r.space != BEM_P0 ? near_p1_layout(r).bytes : r.near_items.size() * sizeof(NearItem)) + 512;
+           (r.near_pairs.empty() ? 0 : near_layout(near_kind(r), near_count(r)).bytes) + 512;
 }
 
 void describe_request(const Request &r, ReqDev &d)
@@ -907,8 +757,11 @@ int mesh_create_impl(const double *xyz, int64_t nv, const int32_t *tri, int64_t 
         const double N[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2], e1[0] * e2[1] - e1[1] * e2[0]};
         sj += std::sqrt(N[0] * N[0] + N[1] * N[1] + N[2] * N[2]);
         double e3[3] = {c[0] - b[0], c[1] - b[1], c[2] - b[2]};
-        se += std::sqrt(e1[0] * e1[0] + e1[1] * e1[1] + e1[2] * e1[2]) + std::sqrt(e2[0] * e2[0] + e2[1] * e2[1] + e2[2] * e2[2]) +
-              std::sqrt(e3[0] * e3[0] + e3[1] * e3[1] + e3[2] * e3[2]);
+        const double l1 = std::sqrt(e1[0] * e1[0] + e1[1] * e1[1] + e1[2] * e1[2]),
+                     l2 = std::sqrt(e2[0] * e2[0] + e2[1] * e2[1] + e2[2] * e2[2]),
+                     l3 = std::sqrt(e3[0] * e3[0] + e3[1] * e3[1] + e3[2] * e3[2]);
+        se += l1 + l2 + l3;
+        m->max_edge = std::max(m->max_edge, std::max(l1, std::max(l2, l3)));
     }
     m->mean_J = sj / nt;
     m->mean_edge = se / (3.0 * nt);
@@ -923,7 +776,6 @@ int mesh_create_impl(const double *xyz, int64_t nv, const int32_t *tri, int64_t 
     }
 
     hipError_t e = hipGetDevice(&m->device);
-    double *d_xyz = nullptr;
     int32_t *d_tri = nullptr, *d_bad = nullptr;
     const size_t b32 = sizeof(float) * kGeo32Stride * nt, b64 = sizeof(double) * kGeo64Stride * nt,
                  bv = sizeof(int4) * nt;
@@ -932,13 +784,13 @@ int mesh_create_impl(const double *xyz, int64_t nv, const int32_t *tri, int64_t 
     if (e == hipSuccess) e = hipMalloc(&m->d_g32, b32);
     if (e == hipSuccess) e = hipMalloc(&m->d_g64, b64);
     if (e == hipSuccess) e = hipMalloc(&m->d_vtx, bv);
-    if (e == hipSuccess) e = hipMalloc(&d_xyz, sizeof(double) * 3 * nv);
+    if (e == hipSuccess) e = hipMalloc(&m->d_xyz, sizeof(double) * 3 * nv);
     if (e == hipSuccess) e = hipMalloc(&d_tri, sizeof(int32_t) * 3 * nt);
     if (e == hipSuccess) e = hipMalloc(&d_bad, sizeof(int32_t));
-    if (e == hipSuccess) e = hipMemcpy(d_xyz, xyz, sizeof(double) * 3 * nv, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(m->d_xyz, xyz, sizeof(double) * 3 * nv, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(d_tri, tri, sizeof(int32_t) * 3 * nt, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(d_bad, &bad, sizeof(int32_t), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = launch_geometry(d_xyz, d_tri, nt, q, m->d_g32, m->d_g64, m->d_vtx, d_bad, 0);
+    if (e == hipSuccess) e = launch_geometry(m->d_xyz, d_tri, nt, q, m->d_g32, m->d_g64, m->d_vtx, d_bad, 0);
     if (e == hipSuccess) e = hipMemcpy(&bad, d_bad, sizeof(int32_t), hipMemcpyDeviceToHost);
     // star tables: the packed star entries and, per entry, its triangle's
     // FP32 record and vertex ids with the local vertex in w
@@ -949,7 +801,6 @@ int mesh_create_impl(const double *xyz, int64_t nv, const int32_t *tri, int64_t 
     if (e == hipSuccess) e = hipMemcpy(m->d_star, m->star.data(), sizeof(int32_t) * ns, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = launch_gather(m->d_g32, m->d_vtx, m->d_star, 2, ns, m->d_sgeo, m->d_smeta, 0);
     if (e == hipSuccess) e = hipStreamSynchronize(0);
-    if (d_xyz) (void)hipFree(d_xyz);
     if (d_tri) (void)hipFree(d_tri);
     if (d_bad) (void)hipFree(d_bad);
     if (e != hipSuccess)
@@ -958,12 +809,12 @@ int mesh_create_impl(const double *xyz, int64_t nv, const int32_t *tri, int64_t 
         rc = fail(BEM_E_ARG, "degenerate triangle (zero area)");
     if (rc != BEM_OK) {
         for (void *p : {(void *)m->d_g32, (void *)m->d_g64, (void *)m->d_vtx, (void *)m->d_star, (void *)m->d_sgeo,
-                        (void *)m->d_smeta})
+                        (void *)m->d_smeta, (void *)m->d_xyz})
             if (p) (void)hipFree(p);
         delete m;
         return rc;
     }
-    m->dev_bytes = b32 + b64 + bv + 3 * (size_t)nt * (4 + 4 * kGeo32Stride + sizeof(int4));
+    m->dev_bytes = b32 + b64 + bv + sizeof(double) * 3 * (size_t)nv + 3 * (size_t)nt * (4 + 4 * kGeo32Stride + sizeof(int4));
     *out = m;
     return BEM_OK;
 }
@@ -973,7 +824,7 @@ int mesh_destroy_impl(bem_mesh *m)
     if (!m) return fail(BEM_E_ARG, "null mesh");
     if (m->inflight.load() != 0) return fail(BEM_E_BUSY, "requests on this mesh are still in flight");
     for (void *p : {(void *)m->d_g32, (void *)m->d_g64, (void *)m->d_vtx, (void *)m->d_star, (void *)m->d_sgeo,
-                    (void *)m->d_smeta})
+                    (void *)m->d_smeta, (void *)m->d_xyz})
         (void)hipFree(p);
     delete m;
     return BEM_OK;

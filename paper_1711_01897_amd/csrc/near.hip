@@ -91,6 +91,82 @@ __device__ __forceinline__ V3 mul(double s, V3 a) { return {s * a.x, s * a.y, s 
 __device__ __forceinline__ V3 fma3(double s, V3 a, V3 b) { return {fma(s, a.x, b.x), fma(s, a.y, b.y), fma(s, a.z, b.z)}; }
 __device__ __forceinline__ double dot(V3 a, V3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
 
+// A vertex-sharing pair as the integrals need it (workgroup-uniform, built
+// from the mesh by scalar loads):
+//   kind 0, identical:     v = V0, V1, V2 (the triangle in its own order)
+//   kind 1, common edge:   v = P, Q, A, B (shared edge P-Q; A the test
+//                          triangle's third vertex, B the trial triangle's)
+//   kind 2, common vertex: v = P, A, B, C, D (shared P; A, B the test
+//                          triangle's others, C, D the trial triangle's)
+// ny: unit normal of the trial triangle; jt, js: |cross| of the test and trial
+// triangles (twice their areas); pt, ps: the triangles' local vertices in the
+// order of v.
+struct Pair {
+    double v[15];
+    double ny[3], nt[3];
+    double jt, js, k;
+    int kind;
+    int T, S;
+    int pt[3], ps[3];
+};
+
+// Mesh tables and lists in constant memory space: written before the kernels
+// that read them, and read here at wave-uniform addresses (scalar loads).
+#define BEM_CONST(T) const __attribute__((address_space(4))) T
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ Pair load_pair(const NearReq &R, int a, int b)
+{
+    Pair q;
+    q.T = R.transposed ? b : a;
+    q.S = R.transposed ? a : b;
+    q.k = R.k;
+    BEM_CONST(i32x4) *vtx = (BEM_CONST(i32x4) *)R.vtx;
+    const i32x4 tv = vtx[q.T], sv = vtx[q.S];
+    // bit 3 i + j: test vertex i is trial vertex j; the first two give the
+    // shared vertices' local numbers t0, s0 and t1, s1 in the test triangle's
+    // order (scalar arithmetic: the vertices then come through scalar loads)
+    unsigned m = 0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) m |= (tv[i] == sv[j] ? 1u : 0u) << (3 * i + j);
+    m = __builtin_amdgcn_readfirstlane(m);
+    const int n = __builtin_popcount(m);
+    const unsigned m2 = m & (m - 1);
+    const int b0 = m ? __builtin_ctz(m) : 0, b1 = m2 ? __builtin_ctz(m2) : 0;
+    const int t0 = b0 / 3, s0 = b0 - 3 * t0, t1 = b1 / 3, s1 = b1 - 3 * t1;
+    q.kind = n >= 3 ? 0 : (n == 2 ? 1 : 2);
+    auto next = [](int i) { return i == 2 ? 0 : i + 1; };
+    q.pt[0] = q.kind == 0 ? 0 : t0;
+    q.pt[1] = q.kind == 0 ? 1 : (q.kind == 1 ? t1 : next(t0));
+    q.pt[2] = 3 - q.pt[0] - q.pt[1];
+    q.ps[0] = q.kind == 0 ? 0 : s0;
+    q.ps[1] = q.kind == 0 ? 1 : (q.kind == 1 ? s1 : next(s0));
+    q.ps[2] = 3 - q.ps[0] - q.ps[1];
+    auto pick = [](const i32x4 &v, int i) { return i == 0 ? v.x : (i == 1 ? v.y : v.z); };
+    // v[3], v[4]: the trial triangle's vertices that are not shared (B; C, D),
+    // the shared vertex where there is no such vertex
+    const int id[5] = {pick(tv, q.pt[0]), pick(tv, q.pt[1]), pick(tv, q.pt[2]),
+                       q.kind == 0 ? pick(tv, 0) : pick(sv, q.kind == 1 ? q.ps[2] : q.ps[1]),
+                       q.kind == 2 ? pick(sv, q.ps[2]) : pick(tv, q.pt[0])};
+    BEM_CONST(double) *xyz = (BEM_CONST(double) *)R.xyz;
+#pragma unroll
+    for (int i = 0; i < 5; ++i)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) q.v[3 * i + d] = xyz[3 * (size_t)id[i] + d];
+    BEM_CONST(double) *gt = (BEM_CONST(double) *)(R.g64 + (size_t)q.T * kGeo64Stride);
+    BEM_CONST(double) *gs = (BEM_CONST(double) *)(R.g64 + (size_t)q.S * kGeo64Stride);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        q.nt[d] = gt[d];
+        q.ny[d] = gs[d];
+    }
+    q.jt = gt[3];
+    q.js = gs[3];
+    return q;
+}
+
 struct Cx {
     double re, im;
 };
@@ -144,12 +220,13 @@ __constant__ RadialTable<0, 1, true, 3> c_tab_d1{};
 // the work of the fixed 48; the count is the workgroup's, so the coefficients
 // come through scalar loads and feed two evaluations each (held in LDS they
 // cost a broadcast read per product, which bound the kernel).
-__device__ __forceinline__ int series_terms(const NearItem &it)
+__device__ __forceinline__ int series_terms(const Pair &it)
 {
-    const int nv = 3 + it.kind;
     double d2 = 0.0;
-    for (int i = 0; i < nv; ++i)
-        for (int j = i + 1; j < nv; ++j) {
+#pragma unroll
+    for (int i = 0; i < 5; ++i)   // vertices a kind lacks repeat the first
+#pragma unroll
+        for (int j = i + 1; j < 5; ++j) {
             const double x = it.v[3 * i] - it.v[3 * j], y = it.v[3 * i + 1] - it.v[3 * j + 1],
                          z = it.v[3 * i + 2] - it.v[3 * j + 2];
             d2 = fmax(d2, x * x + y * y + z * z);
@@ -191,7 +268,7 @@ __device__ __forceinline__ void radial2(double oa, double ob, const double *tab,
 // Helmholtz share of this thread (op 2 single layer, op 3 double layer),
 // without jt js / 4 pi and (a.n_y) for common-edge double layers.
 template <int OP>
-__device__ Cx pair_part_helmholtz(const NearItem &it, const double *sx, const double *sw)
+__device__ Cx pair_part_helmholtz(const Pair &it, const double *sx, const double *sw)
 {
     constexpr bool DL = OP == 3;
     const int t = threadIdx.x;
@@ -278,7 +355,7 @@ __device__ __forceinline__ double kern(V3 c, double num)
 // This thread's share of the pair integral (without jt js / 4 pi and the
 // radial factor, which pair_scale gives); sx, sw hold the 16-point rule.
 template <int OP>
-__device__ double pair_part(const NearItem &it, const double *sx, const double *sw)
+__device__ double pair_part(const Pair &it, const double *sx, const double *sw)
 {
     const int t = threadIdx.x;
     if (it.kind == 0) {
@@ -334,7 +411,7 @@ __device__ double pair_part(const NearItem &it, const double *sx, const double *
 
 // jt js / 4 pi times the closed-form radial integral of the pair's kind.
 template <int OP>
-__device__ double pair_scale(const NearItem &it)
+__device__ double pair_scale(const Pair &it)
 {
     if constexpr (OP >= 2) {
         const double an = (OP == 3 && it.kind == 1) ? dot(sub(ld(it.v + 6), ld(it.v)), ld(it.ny)) : 1.0;
@@ -362,7 +439,7 @@ __device__ __forceinline__ double wave_sum(double x)
 // the four wavefronts in order (a tree over 256 LDS words took eight barriers
 // for what is a few hundred products per thread).
 template <int OP>
-__device__ Cx pair_value(const NearItem &it)
+__device__ Cx pair_value(const Pair &it)
 {
     __shared__ double sx[kPts], sw[kPts];
     __shared__ double red[2][kNearThreads / 64];
@@ -389,20 +466,23 @@ __device__ Cx pair_value(const NearItem &it)
             (red[1][0] + red[1][1] + red[1][2] + red[1][3]) * sc};
 }
 
+// P0: one workgroup per pair, which is one entry.
 template <int OP, bool FP32>
-__global__ __launch_bounds__(kNearThreads) void k_near_p0(const NearItem *__restrict__ items, int64_t n)
+__global__ __launch_bounds__(kNearThreads) void k_near_p0(const NearReq *__restrict__ reqs,
+                                                          const NearPair *__restrict__ pairs, int64_t n)
 {
     if ((int64_t)blockIdx.x >= n) return;
-    const NearItem &it = items[blockIdx.x];
-    const Cx v = pair_value<OP>(it);
+    const NearPair np = pairs[blockIdx.x];
+    const NearReq &R = reqs[np.req];
+    const Cx v = pair_value<OP>(load_pair(R, np.a, np.b));
     if (threadIdx.x == 0) {
         constexpr int kParts = OP >= 2 ? 2 : 1;   // complex entries: (re, im)
         if constexpr (FP32) {
-            float *o = static_cast<float *>(it.out);
+            float *o = static_cast<float *>(R.out) + kParts * np.entry;
             o[0] = (float)((double)o[0] + v.re);
             if constexpr (kParts == 2) o[1] = (float)((double)o[1] + v.im);
         } else {
-            double *o = static_cast<double *>(it.out);
+            double *o = static_cast<double *>(R.out) + kParts * np.entry;
             o[0] = o[0] + v.re;
             if constexpr (kParts == 2) o[1] = o[1] + v.im;
         }
@@ -450,7 +530,7 @@ __device__ __forceinline__ void cfma(Cx &acc, double w, const Cx &x)
 // and, for the common-edge double layer, without (a.n_y)).  Op 0, 1: Laplace
 // single, double layer; 2, 3: Helmholtz.
 template <int OP>
-__device__ __forceinline__ void pair_part_p1(const NearItem &it, const double *sx, const double *sw, Cx *M)
+__device__ __forceinline__ void pair_part_p1(const Pair &it, const double *sx, const double *sw, Cx *M)
 {
     constexpr bool CPLX = OP >= 2, DL = OP == 1 || OP == 3;
     const int t = threadIdx.x;
@@ -628,18 +708,25 @@ __device__ __forceinline__ void pair_part_p1(const NearItem &it, const double *s
     }
 }
 
-// One workgroup per pair.  Its 9 (18: complex) sums over 256 threads go
-// through LDS once: eight threads per value add 32 partials each, a butterfly
-// adds the eight (fixed order, two barriers; the tree over all values took
-// eight).  WITH_P0 (the Helmholtz hypersingular operator): the pair's P0
-// single-layer value, the sum of the nine entries (the hat functions sum to
-// one), follows them (20 doubles per pair).
-template <int OP, bool WITH_P0>
-__global__ __launch_bounds__(kNearThreads) void k_near_p1(const NearItem *__restrict__ items, int64_t n)
+// One workgroup per pair: its 3 x 3 local matrix in the triangles' own vertex
+// orders (row-major test x trial, complex (re, im)) into local[pair], and the
+// column dofs of its column-side triangle into keys[pair].  The 9 (18: complex)
+// sums over 256 threads go through LDS once: eight threads per value add 32
+// partials each, a butterfly adds the eight (fixed order, two barriers; a tree
+// over all values took eight).
+// HYP: the hypersingular operator (Eq. hypsHelmholtz), from the single layer's
+// matrix M: curl_a . curl_b times the pair's P0 value, which is the sum of M
+// (the hat functions sum to one), minus k^2 n_x . n_y M.
+template <int OP, bool HYP>
+__global__ __launch_bounds__(kNearThreads, OP >= 2 ? 4 : 5) void k_near_p1(const NearReq *__restrict__ reqs,
+                                                          const NearPair *__restrict__ pairs, int64_t n,
+                                                          int4 *__restrict__ keys, double *__restrict__ local)
 {
     constexpr int NV = OP >= 2 ? 18 : 9, NR = NV / 9;
     if ((int64_t)blockIdx.x >= n) return;
-    const NearItem &it = items[blockIdx.x];
+    const NearPair np = pairs[blockIdx.x];
+    const NearReq &R = reqs[np.req];
+    const Pair it = load_pair(R, np.a, np.b);
     __shared__ double sx[kPts], sw[kPts];
     __shared__ double red[NV][kNearThreads + 8];   // rows 8 words of 64 bits apart from a multiple of the banks
     const int t = threadIdx.x;
@@ -658,146 +745,190 @@ __global__ __launch_bounds__(kNearThreads) void k_near_p1(const NearItem *__rest
         if constexpr (OP >= 2) red[2 * i + 1][t] = M[i].im;
     }
     __syncthreads();
+    const int e = (t >> 3) / NR, part = (t >> 3) % NR;   // entry in the order of v, (re, im)
+    double s = 0.0;
     if (t < 8 * NV) {
         const double *r = red[t >> 3] + (t & 7);
-        double s = 0.0;
 #pragma unroll 8
         for (int i = 0; i < kNearThreads / 8; ++i) s += r[8 * i];
 #pragma unroll
         for (int h = 4; h > 0; h >>= 1) s += __shfl_xor(s, h);
         const double an = ((OP == 1 || OP == 3) && it.kind == 1) ? dot(sub(ld(it.v + 6), ld(it.v)), ld(it.ny)) : 1.0;
         s *= an * it.jt * it.js * kInv4PiD;
-        if ((t & 7) == 0) {
-            static_cast<double *>(it.out)[t >> 3] = s;
-            if constexpr (WITH_P0) red[t >> 3][0] = s;
-        }
     }
-    if constexpr (WITH_P0) {
-        __syncthreads();
-        if (t < 2) {
-            double s = 0.0;
+    if (t < 8 * NV && (t & 7) == 0) {
+        if constexpr (HYP) red[t >> 3][0] = s;
+    }
+    if constexpr (HYP) __syncthreads();
+    if (t < 8 * NV && (t & 7) == 0) {
+        const int i = e / 3, j = e - 3 * i;
+        const int tl = i == 0 ? it.pt[0] : (i == 1 ? it.pt[1] : it.pt[2]);
+        const int sl = j == 0 ? it.ps[0] : (j == 1 ? it.ps[1] : it.ps[2]);
+        if constexpr (HYP) {
+            double p0 = 0.0;
 #pragma unroll
-            for (int i = 0; i < 9; ++i) s += red[2 * i + t][0];
-            static_cast<double *>(it.out)[18 + t] = s;
+            for (int x = 0; x < 9; ++x) p0 += red[NR * x + part][0];
+            // surface curl of local vertex i: (v_{i+1} - v_{i+2}) / J in the mesh's order
+            const int4 tv = R.vtx[it.T], sv = R.vtx[it.S];
+            auto id = [](const int4 &v, int x) { return x == 0 ? v.x : (x == 1 ? v.y : v.z); };
+            auto edge = [&](const int4 &v, int x) {
+                return sub(ld(R.xyz + 3 * (size_t)id(v, (x + 1) % 3)), ld(R.xyz + 3 * (size_t)id(v, (x + 2) % 3)));
+            };
+            const double cc = dot(edge(tv, tl), edge(sv, sl)) / (it.jt * it.js);
+            const double nn = dot(ld(it.nt), ld(it.ny));
+            s = cc * p0 - it.k * it.k * nn * s;
         }
+        local[(size_t)NV * blockIdx.x + NR * (3 * tl + sl) + part] = s;
+    }
+    if (t == 0) {
+        int4 kv = R.vtx[np.b];
+        if (R.dp1) kv = make_int4(3 * np.b, 3 * np.b + 1, 3 * np.b + 2, 0);
+        keys[blockIdx.x] = kv;
     }
 }
 
-// Laplace hypersingular operator (Eq. hypsHelmholtz at k = 0): the hat
-// functions' surface curls are constant per triangle, so a pair's local
-// matrix is curl_a . curl_b times its P0 single-layer integral; the pair
-// kernel stores that integral, the gather applies the curl products.
-__global__ __launch_bounds__(kNearThreads) void k_near_slp_value(const NearItem *__restrict__ items, int64_t n)
-{
-    if ((int64_t)blockIdx.x >= n) return;
-    const NearItem &it = items[blockIdx.x];
-    const Cx v = pair_value<0>(it);
-    if (threadIdx.x == 0) *static_cast<double *>(it.out) = v.re;
-}
+// Adds the local matrices to the entries: one workgroup per row and 256
+// columns, one thread per entry.  The row's pairs (about 80: six triangles
+// with 13 neighbours each) and their matrices are gathered in LDS, and every
+// thread then adds those whose column-side triangle has its dof, in the order
+// of the row's star and of each triangle's list.  Entries without a pair are
+// not touched.  Bound by latency, not by its few bytes: with the matrices read
+// where they are added (a wait per pair) it took 30 us on a 100 x 100 leaf, from
+// LDS 9.9 us.
+constexpr int kGatherPairs = 128;   // pairs in LDS at a time
 
-// Each record sums its sources (indices into the local values, times the
-// source's weight when wt is given) in order and adds the sum to its entry.
 template <bool FP32, bool CPLX>
-__global__ void k_near_gather(const NearGather *__restrict__ recs, int64_t n, const int32_t *__restrict__ src,
-                              const double *__restrict__ wt, const double *__restrict__ local)
+__global__ __launch_bounds__(256) void k_near_gather(const NearReq *__restrict__ reqs,
+                                                     const NearBlock *__restrict__ blocks,
+                                                     const int4 *__restrict__ keys, const double *__restrict__ local)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const NearGather g = recs[i];
-    if constexpr (CPLX) {   // complex local values (re, im) and entries
-        double sr = 0.0, si = 0.0;
-        for (int32_t k = 0; k < g.count; ++k) {
-            const int64_t q = 2 * (int64_t)src[g.first + k];
-            const double w = wt ? wt[g.first + k] : 1.0;
-            sr += w * local[q];
-            si += w * local[q + 1];
-        }
-        if constexpr (FP32) {
-            float *o = static_cast<float *>(g.out);
-            o[0] = (float)((double)o[0] + sr);
-            o[1] = (float)((double)o[1] + si);
-        } else {
-            double *o = static_cast<double *>(g.out);
-            o[0] = o[0] + sr;
-            o[1] = o[1] + si;
-        }
-        return;
+    constexpr int NR = CPLX ? 2 : 1;
+    __shared__ int4 star[256];                        // per star triangle: first pair, pairs, local vertex
+    __shared__ int4 list[kGatherPairs];               // column dofs of a pair's three vertices, its vertex of the row
+    __shared__ int pair[kGatherPairs];
+    __shared__ double val[kGatherPairs * 9 * NR];
+    const NearBlock B = blocks[blockIdx.x];
+    const NearReq &R = reqs[B.req];
+    const int t = threadIdx.x;
+    const int c = B.col0 + t;
+    const int key = c < R.ncols ? R.cols[c] : -1;
+    const int step = R.transposed ? 3 : 1;   // the row-side triangle's vertex is the second index
+    const int lead = R.transposed ? 1 : 3;
+    const int e0 = R.rptr[B.row], ne = R.rptr[B.row + 1] - e0;   // at most 256 triangles around a vertex
+    if (t < ne) {
+        const int pk = R.rs[e0 + t], p0 = R.gptr[pk >> 2];
+        star[t] = make_int4(p0, R.gptr[(pk >> 2) + 1] - p0, pk & 3, 0);
     }
-    double s = 0.0;
-    if (wt)
-        for (int32_t k = 0; k < g.count; ++k) s += wt[g.first + k] * local[src[g.first + k]];
-    else
-        for (int32_t k = 0; k < g.count; ++k) s += local[src[g.first + k]];
+    __syncthreads();
+    double sr = 0.0, si = 0.0;
+    bool any = false;
+    for (int first = 0;; first += kGatherPairs) {
+        // entry first + t of the row's list
+        int at = first + t, total = 0, p = -1, i = 0;
+        for (int e = 0; e < ne; ++e) {
+            const int4 s = star[e];
+            if (p < 0 && at < total + s.y) {
+                p = s.x + at - total;
+                i = s.z;
+            }
+            total += s.y;
+        }
+        const int count = min(kGatherPairs, total - first);
+        if (t < count) {
+            int4 kv = keys[p];
+            kv.w = 9 * t + lead * i;
+            list[t] = kv;
+            pair[t] = p;
+        }
+        __syncthreads();
+        for (int x = t; x < count * 9 * NR; x += 256) {
+            const int q = x / (9 * NR);
+            val[x] = local[(size_t)(9 * NR) * pair[q] + (x - q * (9 * NR))];
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int x = 0; x < count; ++x) {
+            const int4 kv = list[x];
+            const bool m0 = key == kv.x, m1 = key == kv.y, m2 = key == kv.z, m = m0 || m1 || m2;
+            const int at = NR * (kv.w + (m1 ? step : (m2 ? 2 * step : 0)));
+            const double vr = val[at];
+            sr += m ? vr : 0.0;
+            if constexpr (CPLX) {
+                const double vi = val[at + 1];
+                si += m ? vi : 0.0;
+            }
+            any = any || m;
+        }
+        if (first + kGatherPairs >= total) break;
+        __syncthreads();   // the list has been read
+    }
+    if (!any) return;
+    const int64_t o = (int64_t)B.row * R.ncols + c;
     if constexpr (FP32) {
-        float *o = static_cast<float *>(g.out);
-        *o = (float)((double)*o + s);
+        float *w = static_cast<float *>(R.out) + NR * o;
+        w[0] = (float)((double)w[0] + sr);
+        if constexpr (CPLX) w[1] = (float)((double)w[1] + si);
     } else {
-        double *o = static_cast<double *>(g.out);
-        *o = *o + s;
+        double *w = static_cast<double *>(R.out) + NR * o;
+        w[0] += sr;
+        if constexpr (CPLX) w[1] += si;
     }
+}
+
+template <int OP, bool HYP>
+void launch_p1(const NearLayout &L, const NearCount &n, char *dev, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_near_p1<OP, HYP>), dim3((unsigned)n.pairs), dim3(kNearThreads), 0, s,
+                       reinterpret_cast<const NearReq *>(dev), reinterpret_cast<const NearPair *>(dev + L.pairs),
+                       n.pairs, reinterpret_cast<int4 *>(dev + L.keys), reinterpret_cast<double *>(dev + L.local));
+}
+
+template <int OP>
+void launch_p0(bool fp32, const NearLayout &L, const NearCount &n, char *dev, hipStream_t s)
+{
+    const NearReq *reqs = reinterpret_cast<const NearReq *>(dev);
+    const NearPair *pairs = reinterpret_cast<const NearPair *>(dev + L.pairs);
+    const dim3 grid((unsigned)n.pairs), block(kNearThreads);
+    if (fp32)
+        hipLaunchKernelGGL((k_near_p0<OP, true>), grid, block, 0, s, reqs, pairs, n.pairs);
+    else
+        hipLaunchKernelGGL((k_near_p0<OP, false>), grid, block, 0, s, reqs, pairs, n.pairs);
+}
+
+template <bool FP32, bool CPLX>
+void launch_gather_p1(const NearLayout &L, const NearCount &n, char *dev, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_near_gather<FP32, CPLX>), dim3((unsigned)n.blocks), dim3(256), 0, s,
+                       reinterpret_cast<const NearReq *>(dev), reinterpret_cast<const NearBlock *>(dev + L.blocks),
+                       reinterpret_cast<const int4 *>(dev + L.keys), reinterpret_cast<const double *>(dev + L.local));
 }
 
 }  // namespace
 
-hipError_t launch_near_p1(int op, const NearItem *items, int64_t n, hipStream_t s)
+hipError_t launch_near(int kind, const NearLayout &L, const NearCount &n, char *dev, hipStream_t s)
 {
-    if (n <= 0) return hipSuccess;
-    if (n > INT32_MAX || op < 0 || (op > 3 && op != BEM_LAPLACE_HYPS && op != BEM_HELMHOLTZ_HYPS))
-        return hipErrorInvalidValue;
-    if (op == 2)
-        hipLaunchKernelGGL((k_near_p1<2, false>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
-    else if (op == 3)
-        hipLaunchKernelGGL((k_near_p1<3, false>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
-    else if (op == BEM_HELMHOLTZ_HYPS)
-        hipLaunchKernelGGL((k_near_p1<2, true>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
-    else if (op == BEM_LAPLACE_HYPS)
-        hipLaunchKernelGGL(k_near_slp_value, dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
-    else if (op == 0)
-        hipLaunchKernelGGL((k_near_p1<0, false>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
-    else
-        hipLaunchKernelGGL((k_near_p1<1, false>), dim3((unsigned)n), dim3(kNearThreads), 0, s, items, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_near_gather(bool fp32, bool cplx, const NearGather *recs, int64_t n, const int32_t *src,
-                              const double *wt, const double *local, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    const int64_t blocks = (n + 255) / 256;
-    if (blocks > INT32_MAX) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(256);
-    if (cplx) {
-        if (fp32)
-            hipLaunchKernelGGL((k_near_gather<true, true>), grid, block, 0, s, recs, n, src, wt, local);
-        else
-            hipLaunchKernelGGL((k_near_gather<false, true>), grid, block, 0, s, recs, n, src, wt, local);
-    } else if (fp32) {
-        hipLaunchKernelGGL((k_near_gather<true, false>), grid, block, 0, s, recs, n, src, wt, local);
-    } else {
-        hipLaunchKernelGGL((k_near_gather<false, false>), grid, block, 0, s, recs, n, src, wt, local);
+    if (n.pairs <= 0) return hipSuccess;
+    if (n.pairs > INT32_MAX / 9 || n.blocks > INT32_MAX || kind < 0 || kind >= kNearKinds) return hipErrorInvalidValue;
+    const bool fp32 = kind & 1;
+    bool cplx = false;
+    switch (kind >> 1) {
+    case 0: launch_p0<0>(fp32, L, n, dev, s); break;
+    case 1: launch_p0<1>(fp32, L, n, dev, s); break;
+    case 2: launch_p0<2>(fp32, L, n, dev, s); break;
+    case 3: launch_p0<3>(fp32, L, n, dev, s); break;
+    case 4: launch_p1<0, false>(L, n, dev, s); break;
+    case 5: launch_p1<1, false>(L, n, dev, s); break;
+    case 6: launch_p1<2, false>(L, n, dev, s); cplx = true; break;
+    case 7: launch_p1<3, false>(L, n, dev, s); cplx = true; break;
+    case 8: launch_p1<0, true>(L, n, dev, s); break;
+    default: launch_p1<2, true>(L, n, dev, s); cplx = true; break;
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_near(int op, bool fp32, const NearItem *items, int64_t n, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    if (n > INT32_MAX || op < 0 || op > 3) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)n), block(kNearThreads);
-#define BEM_NEAR_LAUNCH(O)                                                              \
-    do {                                                                                \
-        if (fp32)                                                                       \
-            hipLaunchKernelGGL((k_near_p0<O, true>), grid, block, 0, s, items, n);      \
-        else                                                                            \
-            hipLaunchKernelGGL((k_near_p0<O, false>), grid, block, 0, s, items, n);     \
-    } while (0)
-    switch (op) {
-    case 0: BEM_NEAR_LAUNCH(0); break;
-    case 1: BEM_NEAR_LAUNCH(1); break;
-    case 2: BEM_NEAR_LAUNCH(2); break;
-    default: BEM_NEAR_LAUNCH(3); break;
-    }
-#undef BEM_NEAR_LAUNCH
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || n.blocks == 0) return e;
+    if (fp32 && cplx) launch_gather_p1<true, true>(L, n, dev, s);
+    else if (fp32) launch_gather_p1<true, false>(L, n, dev, s);
+    else if (cplx) launch_gather_p1<false, true>(L, n, dev, s);
+    else launch_gather_p1<false, false>(L, n, dev, s);
     return hipGetLastError();
 }
 

@@ -684,7 +684,7 @@ public:
         for (size_t i = 0; i < n; ++i) {
             const Request &r = *rs[i];
             if (r.on_done != a.on_done || r.cb_ctx != a.cb_ctx || r.mesh != a.mesh || !r.borrow || !r.ext ||
-                !r.near_items.empty() || r.in_bytes != 0 || r.nblocks <= 0 || r.nblocks > fmaxblk ||
+                !r.near_pairs.empty() || r.in_bytes != 0 || r.nblocks <= 0 || r.nblocks > fmaxblk ||
                 request_key(r) != key)
                 return false;
         }
@@ -1061,65 +1061,49 @@ public:
             off = align256(off + sizeof(EntryBlock) * (size_t)L.count);
         }
         // singular pairs of BEM_NEAR_SINGULAR requests (few requests carry
-        // any), one contiguous run and one launch per (kernel, precision)
+        // any): one region and one set of launches per operator, space and
+        // precision; its staged part here, what its kernels write past the
+        // part of the slot that is copied
         struct NearRun {
             size_t off = 0;
-            int64_t count = 0;
+            NearCount n;
+            NearLayout L{};
             std::vector<int> members;
         };
-        NearRun near_runs[8];
-        auto near_group = [&](const Request &r) { return 2 * kernel_op(r.op) + (r.prec == BEM_FP32 ? 1 : 0); };
-        // P1 singular pairs: one region (pairs | gather records | sources |
-        // local matrices) and one pair launch + one gather per (kernel, precision)
-        struct P1Run {
-            std::vector<int> members;
-            int64_t items = 0, recs = 0, src = 0;
-            size_t off = 0;
-            NearP1Layout L{};
-        };
-        P1Run p1_runs[12];
+        NearRun near_runs[kNearKinds];
+        bool has_near = false;
         for (int i = 0; i < n; ++i)
-            if (!take[i]->near_items.empty() && take[i]->space != BEM_P0) {
-                P1Run &g = p1_runs[near_p1_group(*take[i])];
+            if (!take[i]->near_pairs.empty()) {
+                NearRun &g = near_runs[near_kind(*take[i])];
+                const NearCount c = near_count(*take[i]);
                 g.members.push_back(i);
-                g.items += (int64_t)take[i]->near_items.size();
-                g.recs += (int64_t)take[i]->near_recs.size();
-                g.src += (int64_t)take[i]->near_src.size();
-            } else if (!take[i]->near_items.empty()) {
-                NearRun &g = near_runs[near_group(*take[i])];
-                g.members.push_back(i);
-                g.count += (int64_t)take[i]->near_items.size();
+                g.n.reqs += c.reqs;
+                g.n.pairs += c.pairs;
+                g.n.blocks += c.blocks;
+                g.n.ints += c.ints;
+                has_near = true;
             }
-        for (NearRun &g : near_runs)
-            if (g.count) {
+        for (int kind = 0; kind < kNearKinds && has_near; ++kind)
+            if (NearRun &g = near_runs[kind]; g.n.pairs) {
                 g.off = off;
-                off = align256(off + sizeof(NearItem) * (size_t)g.count);
-            }
-        // group 2 g + fp32 -> layout mode and kernel operator
-        auto p1_mode = [](int gi) {
-            const int g = gi >> 1;
-            return g == 2 ? 1 : (g == 5 ? 3 : (g >= 3 ? 2 : 0));
-        };
-        auto p1_op = [](int gi) {
-            const int g = gi >> 1;
-            return g == 2 ? (int)BEM_LAPLACE_HYPS : (g == 5 ? (int)BEM_HELMHOLTZ_HYPS : (g >= 3 ? g - 1 : g));
-        };
-        for (int gi = 0; gi < 12; ++gi)
-            if (P1Run &g = p1_runs[gi]; g.items) {
-                g.off = off;
-                g.L = near_p1_layout(p1_mode(gi), g.items, g.recs, g.src);
-                off = align256(off + g.L.bytes);
+                g.L = near_layout(kind, g.n);
+                off = align256(off + g.L.staged);
             }
         const size_t off_in = off;
         for (int i = 0; i < n; ++i) off += take[i]->in_bytes;
-        bool has_near = false;
-        for (const NearRun &g : near_runs) has_near = has_near || g.count > 0;
-        for (const P1Run &g : p1_runs) has_near = has_near || g.items > 0;
         const bool direct_batch = direct && off == off_in && !has_near;
         // descriptors and block tables: the device arena (after the staging
         // copy) or, for a direct batch, the staging itself
         char *src = direct_batch ? hd : db;
         const size_t h2d_end = align256(off);
+        size_t dev_end = h2d_end;   // device arena only
+        for (NearRun &g : near_runs)
+            if (g.n.pairs) {
+                const size_t shift = dev_end - g.off - g.L.staged;
+                dev_end = align256(dev_end + g.L.bytes - g.L.staged);
+                g.L.keys += shift;
+                g.L.local += shift;
+            }
         // every kTimedEvery-th batch times its launches: per workgroup a
         // {start, end} device-clock record, read back after the launches
         b->timed = (batch_counter.fetch_add(1) % kTimedEvery) == 0;
@@ -1134,7 +1118,7 @@ public:
             out_off[i] = off;
             off += take[i]->out_bytes;
         }
-        if (off > slot_bytes) {
+        if (std::max(off, dev_end) > slot_bytes) {
             // admission keeps this from happening; fail the batch rather than overrun the slot
             b->t_launch = now_seconds();
             b->ev_done = get_event();
@@ -1166,24 +1150,8 @@ public:
         }
         std::memset(hb + off_status, 0, sizeof(int32_t) * n);
         for (const NearRun &g : near_runs) {
-            NearItem *q = reinterpret_cast<NearItem *>(hb + g.off);
-            for (int i : g.members) {
-                const Request &r = *take[i];
-                std::memcpy(q, r.near_items.data(), sizeof(NearItem) * r.near_items.size());
-                for (size_t j = 0; j < r.near_items.size(); ++j)
-                    q[j].out = hd + out_off[i] + (size_t)r.near_index[j] * r.elem_bytes;
-                q += r.near_items.size();
-            }
-        }
-        for (const P1Run &g : p1_runs) {
-            int64_t pb = 0, rb = 0, sb = 0;
-            for (int i : g.members) {
-                const Request &r = *take[i];
-                stage_near_p1(r, g.L, hb + g.off, db + g.off, hd + out_off[i], pb, rb, sb);
-                pb += (int64_t)r.near_items.size();
-                rb += (int64_t)r.near_recs.size();
-                sb += (int64_t)r.near_src.size();
-            }
+            NearCount at;
+            for (int i : g.members) stage_near(*take[i], g.L, hb + g.off, db + g.off, hd + out_off[i], at);
         }
         b->off_clock = off_clock;
         for (int i = 0; i < n; ++i) {
@@ -1219,14 +1187,8 @@ public:
             blk0 += L.count;
         }
         // singular pairs after the entry kernels, on the same stream
-        for (int gi = 0; gi < 8; ++gi)
-            if (near_runs[gi].count)
-                note(launch_near(gi >> 1, gi & 1, reinterpret_cast<const NearItem *>(db + near_runs[gi].off),
-                                 near_runs[gi].count, stream));
-        for (int gi = 0; gi < 12; ++gi)
-            if (p1_runs[gi].items)
-                note(launch_near_p1_region(p1_op(gi), gi & 1, p1_runs[gi].L, db + p1_runs[gi].off, p1_runs[gi].items,
-                                           p1_runs[gi].recs, stream));
+        for (int kind = 0; kind < kNearKinds && has_near; ++kind)
+            if (const NearRun &g = near_runs[kind]; g.n.pairs) note(launch_near(kind, g.L, g.n, db + g.off, stream));
         b->ev_done = get_event();
         note(hipEventRecord(b->ev_done, stream));
         b->t_hip = now_seconds() - b->t_hip;

@@ -88,3 +88,32 @@ def test_local_matrices(omega):
                 assert abs(one[0, 0] - ref.sum()) <= bound * np.abs(ref).sum(), (shared, dlp)
     finally:
         mesh.destroy()
+
+
+@pytest.mark.parametrize("n", [5, 9, 40])
+@pytest.mark.parametrize("op", [bem.LAPLACE_SLP, bem.LAPLACE_ADLP, bem.HELMHOLTZ_DLP, bem.HELMHOLTZ_ADLP])
+@pytest.mark.parametrize("prec,bound", [(bem.FP64, 1e-12), (bem.FP32, 1e-5)])
+def test_entries_add_their_pairs(n, op, prec, bound):
+    """P1 entries are sums of discontinuous P1 entries: the apexes of a double
+    cone with n sides have n triangles around them and about n^2 singular
+    pairs in a row's list (from below one staging round of 128 to many), with
+    duplicated and unsorted rows and columns.  1e-12 covers the sums' rounding
+    (up to 1,600 terms) in FP64; FP32 has the library's bound."""
+    phi = 2.0 * np.pi * np.arange(n) / n
+    xyz = np.vstack([np.stack([np.cos(phi), np.sin(phi), 0 * phi], axis=1), [[0, 0, 0.8]], [[0, 0, -0.7]]])
+    tri = np.array([t for i in range(n) for t in ([i, (i + 1) % n, n], [(i + 1) % n, i, n + 1])], dtype=np.int32)
+    mesh = bem.mesh_create(xyz, tri, 6)
+    k = 1.5 if bem.is_complex(op) else 0.0
+    rows = np.array([n, 1, n + 1, 0, n], dtype=np.int32)
+    cols = np.concatenate([np.arange(n + 2), [n, 2, n + 1]]).astype(np.int32)
+    try:
+        got = bem.eval_entries(mesh, op, bem.P1, k, rows, cols, prec=prec, near=bem.NEAR_SINGULAR)
+        every = np.arange(3 * len(tri), dtype=np.int32)
+        D = bem.eval_entries(mesh, op, bem.DP1, k, every, every, prec=bem.FP64, near=bem.NEAR_SINGULAR)
+        B = np.zeros((n + 2, 3 * len(tri)))
+        B[tri.ravel(), every] = 1.0
+        ref = (B @ D @ B.T)[np.ix_(rows, cols)]
+        assert np.abs(got - ref).max() <= bound * np.abs(ref).max()
+        assert np.array_equal(got[0], got[4]) and np.array_equal(got[:, n], got[:, n + 2])
+    finally:
+        mesh.destroy()

@@ -1,5 +1,6 @@
 // extern "C" entry points of libbem (declared in include/bem.h).
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <new>
 
@@ -63,18 +64,109 @@ int fill_request(Request &r, bem_mesh *mesh, bem_op op, bem_space space, double 
     return expand_request(r);
 }
 
-// Pinned staging buffers of the async path.  A buffer is freed once the
-// event recorded after its copy has completed; completed buffers are
-// reclaimed on later calls (or immediately when no event could be recorded).
+// Staging of the async path: a pinned host image of the request and device
+// workspace of the same size, kept from call to call.  A slot carries the
+// event recorded after the last kernel that reads it and is taken again, by
+// any thread and stream, only once the host has seen that event complete, so
+// no call waits: with every slot in flight, on a capturing stream or for a
+// request larger than a slot the call allocates its own (below).  Allocating
+// per call was what a small request cost: one row of 97 entries took 96
+// us, 19 us with a kept slot.
+// Slots are released when the last mesh is destroyed.
+constexpr size_t kSlotLeast = size_t(64) << 10, kSlotMost = size_t(8) << 20;   // bytes, powers of two between
+constexpr size_t kSlotsTotal = size_t(128) << 20;                            // pinned bytes over all slots
+constexpr size_t kSlotsMost = 64;
+
+struct StageSlot {
+    char *host = nullptr;       // pinned
+    char *host_dev = nullptr;   // its device address
+    char *dev = nullptr;
+    size_t bytes = 0;
+    int device = 0;
+    hipEvent_t done = nullptr;
+    bool taken = false;
+    bool recorded = false;      // `done` has been recorded since the slot was made
+};
+
 std::mutex g_stage_mu;
+std::vector<StageSlot *> g_slots;
+size_t g_slots_bytes = 0;
+
+bool finished(hipEvent_t e)
+{
+    if (hipEventQuery(e) == hipSuccess) return true;
+    (void)hipGetLastError();   // "not ready" is no error of the launch that follows
+    return false;
+}
+
+void destroy_slot(StageSlot *x)
+{
+    if (x->done) (void)hipEventDestroy(x->done);
+    if (x->host) (void)hipHostFree(x->host);
+    if (x->dev) (void)hipFree(x->dev);
+    delete x;
+}
+
+// A slot of at least `bytes` on `device` that no enqueued work uses, or null.
+StageSlot *take_slot(size_t bytes, int device)
+{
+    if (bytes > kSlotMost) return nullptr;
+    size_t cap = kSlotLeast;
+    while (cap < bytes) cap *= 2;
+    std::lock_guard<std::mutex> g(g_stage_mu);
+    for (StageSlot *x : g_slots) {
+        if (x->taken || x->device != device || x->bytes < bytes) continue;
+        if (x->recorded && !finished(x->done)) continue;
+        x->taken = true;
+        return x;
+    }
+    if (g_slots.size() >= kSlotsMost || g_slots_bytes + cap > kSlotsTotal) return nullptr;
+    StageSlot *x = new (std::nothrow) StageSlot();
+    if (!x) return nullptr;
+    x->bytes = cap;
+    x->device = device;
+    if (hipHostMalloc((void **)&x->host, cap, hipHostMallocDefault) != hipSuccess ||
+        hipHostGetDevicePointer((void **)&x->host_dev, x->host, 0) != hipSuccess ||
+        hipMalloc((void **)&x->dev, cap) != hipSuccess ||
+        hipEventCreateWithFlags(&x->done, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        destroy_slot(x);
+        return nullptr;
+    }
+    x->taken = true;
+    g_slots.push_back(x);
+    g_slots_bytes += cap;
+    return x;
+}
+
+// Returns a slot whose last use has been enqueued on s (enqueued = false:
+// nothing was).
+hipError_t give_slot(StageSlot *x, hipStream_t s, bool enqueued)
+{
+    hipError_t e = hipSuccess;
+    if (enqueued) {
+        e = hipEventRecord(x->done, s);
+        // without the event the work is waited for: the slot must not be reused before
+        if (e != hipSuccess) (void)hipStreamSynchronize(s);
+    }
+    std::lock_guard<std::mutex> g(g_stage_mu);
+    if (enqueued && e == hipSuccess) x->recorded = true;
+    x->taken = false;
+    return e;
+}
+
+// Pinned staging of the calls that allocate their own.  A buffer is freed
+// once the event recorded after its copy has completed; completed buffers are
+// reclaimed on later such calls (or immediately when no event could be
+// recorded).
 std::vector<std::pair<hipEvent_t, char *>> g_stage_pending;
 
-void reclaim_stages(bool all)
+void reclaim_stages()
 {
     std::lock_guard<std::mutex> g(g_stage_mu);
     auto it = g_stage_pending.begin();
     while (it != g_stage_pending.end()) {
-        if (all ? hipEventSynchronize(it->first) == hipSuccess : hipEventQuery(it->first) == hipSuccess) {
+        if (finished(it->first)) {
             (void)hipEventDestroy(it->first);
             (void)hipHostFree(it->second);
             it = g_stage_pending.erase(it);
@@ -86,7 +178,7 @@ void reclaim_stages(bool all)
 
 char *pinned_stage(size_t bytes)
 {
-    reclaim_stages(false);
+    reclaim_stages();
     char *p = nullptr;
     if (hipHostMalloc((void **)&p, bytes, hipHostMallocDefault) != hipSuccess) return nullptr;
     return p;
@@ -103,15 +195,41 @@ void pinned_release(char *p, hipEvent_t after)
     g_stage_pending.push_back({after, p});
 }
 
+// Meshes alive; the last one's end releases the slots that are not in use.
+std::atomic<int64_t> g_meshes{0};
+
+void release_slots()
+{
+    std::lock_guard<std::mutex> g(g_stage_mu);
+    for (size_t i = 0; i < g_slots.size();) {
+        StageSlot *x = g_slots[i];
+        if (x->taken || (x->recorded && !finished(x->done))) {
+            ++i;
+            continue;
+        }
+        g_slots_bytes -= x->bytes;
+        destroy_slot(x);
+        g_slots[i] = g_slots.back();
+        g_slots.pop_back();
+    }
+}
+
+// Requests of at most this many workgroups read their descriptor, block
+// records and lists straight from the pinned image: a workgroup waits for a
+// few host-link reads, less than a copy kernel and the gap behind it take.
+// With more workgroups the same lists would cross the link once per fixed item.
+constexpr int64_t kDirectBlocks = 32;
+
 // Enqueues an expanded request on `s` with its result in device memory
 // dev_out.  Workspace layout: descriptor | block table | singular pairs |
-// inputs | status word, copied to the device in one piece before the
-// launches.  With fixed == nullptr the workspace comes from the
-// stream-ordered allocator and the host image from pinned staging released
-// once its copy has completed; otherwise both live in fixed memory: the
-// workspace is `fixed` (fixed_bytes long; larger requests fail), the host
-// image a per-thread pageable buffer whose copy completes before the call
-// returns (a pageable host-to-device copy is synchronous with the host).
+// inputs | status word, staged in one host image.  With fixed == nullptr image
+// and workspace are a kept slot's, the image copied to the workspace by a
+// kernel or, for a few workgroups, read in place; or both are allocated for the
+// call (stream-ordered workspace, pinned image released once its copy has
+// completed).  Otherwise both live in fixed memory: the workspace is `fixed`
+// (fixed_bytes long; larger requests fail), the host image a per-thread
+// pageable buffer whose copy completes before the call returns (a pageable
+// host-to-device copy is synchronous with the host).
 int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed, size_t fixed_bytes)
 {
     bem_mesh *mesh = r.mesh;
@@ -151,28 +269,40 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
         return fail(BEM_E_OOM, "request needs " + std::to_string(ws_total) + " bytes of workspace, more than the " +
                                    std::to_string(fixed_bytes) + "-byte static workspace of the no-allocation entry point");
     char *host = nullptr;
+    char *ws = fixed;
+    StageSlot *slot = nullptr;
     thread_local std::vector<char> pageable;
     if (fixed) {
         pageable.assign(in_total, 0);
         host = pageable.data();
     } else {
-        // descriptors go through pinned staging that is released once the
-        // copy has completed (checked on later calls), so nothing here waits
-        host = pinned_stage(in_total);
-        if (!host) return fail(BEM_E_OOM, "pinned staging allocation failed");
-        std::memset(host, 0, in_total);
-    }
-    char *ws = fixed;
-    if (!fixed) {
-        hipError_t e = hipMallocAsync((void **)&ws, ws_total, s);
-        if (e != hipSuccess) {
-            pinned_release(host, nullptr);
-            return fail(BEM_E_DEVICE, std::string("hipMallocAsync: ") + hipGetErrorString(e));
+        int cur = -1, dev = -1;
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipGetDevice(&cur) == hipSuccess && hipStreamGetDevice(s, &dev) == hipSuccess && cur == dev &&
+            hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone)
+            slot = take_slot(ws_total, dev);
+        else
+            (void)hipGetLastError();
+        if (slot) {
+            host = slot->host;
+            ws = slot->dev;
+        } else {
+            host = pinned_stage(in_total);
+            if (!host) return fail(BEM_E_OOM, "pinned staging allocation failed");
+            std::memset(host, 0, in_total);
+            hipError_t e = hipMallocAsync((void **)&ws, ws_total, s);
+            if (e != hipSuccess) {
+                pinned_release(host, nullptr);
+                return fail(BEM_E_DEVICE, std::string("hipMallocAsync: ") + hipGetErrorString(e));
+            }
         }
     }
+    // where the kernels read the staged image
+    const bool direct = slot && !near && r.nblocks <= kDirectBlocks;
+    char *img = direct ? slot->host_dev : ws;
     ReqDev d;
-    stage_request_inputs(r, host, ws, off_in, d);
-    finish_descriptor(r, ws, 0, off_status, d);
+    stage_request_inputs(r, host, img, off_in, d);
+    finish_descriptor(r, img, 0, off_status, d);
     d.out = dev_out;
     std::memcpy(host + off_req, &d, sizeof(ReqDev));
     write_blocks(r, 0, reinterpret_cast<EntryBlock *>(host + off_b));
@@ -184,19 +314,32 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
         NearCount at;
         stage_near(r, nl, host + off_near, ws + off_near, static_cast<char *>(dev_out), at);
     }
-    hipError_t e = hipMemcpyAsync(ws, host, in_total, hipMemcpyHostToDevice, s);
-    if (!fixed) {
-        hipEvent_t ev = nullptr;
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventRecord(ev, s);
-        pinned_release(host, e == hipSuccess ? ev : nullptr);
+    *reinterpret_cast<int64_t *>(host + off_status) = 0;
+    hipError_t e = hipSuccess;
+    if (slot) {
+        if (!direct) e = launch_stage_copy(slot->host_dev, ws, in_total, s);
+        if (e != hipSuccess) (void)give_slot(slot, s, false);
+    } else {
+        e = hipMemcpyAsync(ws, host, in_total, hipMemcpyHostToDevice, s);
+        if (!fixed) {
+            hipEvent_t ev = nullptr;
+            if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+            if (e == hipSuccess) e = hipEventRecord(ev, s);
+            pinned_release(host, e == hipSuccess ? ev : nullptr);
+        }
     }
     if (e != hipSuccess) return fail(BEM_E_DEVICE, std::string("staging copy: ") + hipGetErrorString(e));
-    const ReqDev *dreq = (const ReqDev *)(ws + off_req);
+    const ReqDev *dreq = (const ReqDev *)(img + off_req);
     Variant v{kernel_op(r.op), r.space, r.prec, mesh->q};
-    BEM_HIP_TRY(launch_entries(v, dreq, (const EntryBlock *)(ws + off_b), r.nblocks, s));
-    if (near) BEM_HIP_TRY(launch_near(near_kind(r), nl, near_n, ws + off_near, s));
-    if (!fixed) BEM_HIP_TRY(hipFreeAsync(ws, s));
+    e = launch_entries(v, dreq, (const EntryBlock *)(img + off_b), r.nblocks, s);
+    if (e == hipSuccess && near) e = launch_near(near_kind(r), nl, near_n, ws + off_near, s);
+    if (slot) {
+        const hipError_t g = give_slot(slot, s, true);
+        if (e == hipSuccess) e = g;
+    } else if (!fixed && e == hipSuccess) {
+        e = hipFreeAsync(ws, s);
+    }
+    if (e != hipSuccess) return fail(BEM_E_DEVICE, std::string("request launch: ") + hipGetErrorString(e));
     return BEM_OK;
 }
 
@@ -241,10 +384,17 @@ const char *bem_last_error(void) { return bem::last_error(); }
 
 int bem_mesh_create(const double *xyz, int64_t nv, const int32_t *tri, int64_t nt, int quad_points, bem_mesh **out)
 {
-    return mesh_create_impl(xyz, nv, tri, nt, quad_points, out);
+    const int rc = mesh_create_impl(xyz, nv, tri, nt, quad_points, out);
+    if (rc == BEM_OK) g_meshes.fetch_add(1);
+    return rc;
 }
 
-int bem_mesh_destroy(bem_mesh *mesh) { return mesh_destroy_impl(mesh); }
+int bem_mesh_destroy(bem_mesh *mesh)
+{
+    const int rc = mesh_destroy_impl(mesh);
+    if (rc == BEM_OK && g_meshes.fetch_sub(1) == 1) release_slots();
+    return rc;
+}
 
 int bem_mesh_info(const bem_mesh *m, bem_mesh_info_t *info)
 {

@@ -268,6 +268,42 @@ hipError_t launch_near(int kind, const NearLayout &L, const NearCount &n, char *
 hipError_t launch_stage_copy(const void *src, void *dst, size_t bytes, hipStream_t s);
 
 // ---------------------------------------------------------------------------
+// P1 and DP1 blocks by triangle pairs (dense.cpp; kernels in entries.hip): both
+// sides' dofs along a Morton curve, cut into panels of whole stars, a panel
+// being the distinct triangles of its dofs' stars and, per dof, its star as
+// (index into them << 2 | local vertex) and its output position.  A panel of
+// the fixed side against one of the lane side is one launch of local matrices
+// into a workspace and one that adds them to the entries; an entry's sum does
+// not depend on where the cuts are.
+struct PairPanel {
+    int32_t ntri = 0, ndof = 0;
+    size_t tri = 0, ptr = 0, src = 0, pos = 0;   // places in PairPlan::ints
+};
+struct PairPlan {
+    std::vector<int32_t> ints;
+    std::vector<PairPanel> fix, lane;
+    size_t work = 0;        // workspace bytes of the largest pair of panels
+    int64_t pairs = 0;      // triangle pairs over all panels
+    int op = 0, prec = 0;
+    bool ltrial = true;     // the lane side is the trial side
+};
+// Plan of fix x lane with at most `budget` bytes of workspace.
+void plan_pairs(const bem_mesh &m, int space, int op, int prec, bool ltrial, const int32_t *fix, int64_t nfix,
+                const int32_t *lane, int64_t nlane, size_t budget, PairPlan &P);
+// Whether two of the plan's triangles, one of each side, share a vertex.
+bool pairs_touch(const bem_mesh &m, const PairPlan &P);
+// Whether a request is worth it (see the rule at its definition).
+bool pairs_pay(const Request &r, const std::vector<int32_t> &fix, const std::vector<int32_t> &lane);
+// Enqueues one pair of panels: ints (device copy of P.ints), work (P.work bytes), entries at
+// out[fixed position * sf + lane position * sl], the fixed position being the dof's in the caller's list
+// or, with in_panel, in the panel.
+hipError_t launch_pairs(const bem_mesh &m, const PairPlan &P, const PairPanel &f, const PairPanel &l, const int32_t *ints,
+                        void *work, void *out, int64_t sf, int64_t sl, double k, hipStream_t s, bool in_panel = false,
+                        hipEvent_t between = nullptr);
+// Positions of a dof list along a Morton curve of the dofs' places (mesh_expand.cpp).
+void morton_order(const bem_mesh &m, int space, const int32_t *dofs, int64_t n, std::vector<int32_t> &order);
+
+// ---------------------------------------------------------------------------
 // Errors
 void set_error(const std::string &msg);
 int fail(int code, const std::string &msg);
@@ -396,6 +432,10 @@ struct Request {
                                           // the column dofs follow when staged
     int32_t near_slots = 0;               // row-side triangles
     std::vector<int32_t> near_rows;       // P1: rows with at least one pair
+    // by triangle pairs (dense.cpp): no lane set and no block table then
+    bool paired = false;
+    bool pair_error = false;              // under BEM_NEAR_ERROR: two of its triangles share a vertex
+    PairPlan pairs;
     int key = 0;                          // launch group (operator, space, precision, rule)
     std::vector<EntryBlock> pre_blocks;   // `req` holds the fixed-side bit only
     ReqDev pre_dev{};
@@ -434,7 +474,9 @@ int kernel_op(int op);
 size_t out_elem_bytes(int op, int prec);
 
 // Validate and expand a request (host; runs on the submitting thread).
-int expand_request(Request &r);
+// pair_budget: workspace bytes the request may use if it is taken by triangle
+// pairs (0: it may not be).
+int expand_request(Request &r, size_t pair_budget = 0);
 // Fast path for requests whose lane side is a resident LaneRef and whose
 // fixed side is a single dof known to be valid (H-matrix blocks).
 void expand_single_fixed(Request &r, int32_t dof, int rowfix, const LaneRef *ext);
@@ -460,6 +502,8 @@ void finish_descriptor(const Request &r, char *dev_base, size_t off_out, size_t 
 
 // Server
 int server_submit(Request *r);
+// Workspace of a request by triangle pairs in the server's slots.
+size_t server_pair_budget();
 int server_submit_many(Request *const *rs, size_t n);
 // With BEM_DEBUG_TIMING set: prints and resets per-phase host times of the
 // dispatch and completion threads (stderr).

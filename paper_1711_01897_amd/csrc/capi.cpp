@@ -46,7 +46,7 @@ struct bem_ticket {
 namespace {
 
 int fill_request(Request &r, bem_mesh *mesh, bem_op op, bem_space space, double k, const int32_t *rows, int64_t nrows,
-                 const int32_t *cols, int64_t ncols, bem_prec prec, bem_near near)
+                 const int32_t *cols, int64_t ncols, bem_prec prec, bem_near near, size_t pair_budget = 0)
 {
     if (!mesh) return fail(BEM_E_ARG, "null mesh");
     if (nrows < 0 || ncols < 0) return fail(BEM_E_ARG, "negative request size");
@@ -61,7 +61,7 @@ int fill_request(Request &r, bem_mesh *mesh, bem_op op, bem_space space, double 
     r.ncols = ncols;
     r.rows.assign(rows, rows + nrows);
     r.cols.assign(cols, cols + ncols);
-    return expand_request(r);
+    return expand_request(r, pair_budget);
 }
 
 // Staging of the async path: a pinned host image of the request and device
@@ -76,6 +76,8 @@ int fill_request(Request &r, bem_mesh *mesh, bem_op op, bem_space space, double 
 constexpr size_t kSlotLeast = size_t(64) << 10, kSlotMost = size_t(8) << 20;   // bytes, powers of two between
 constexpr size_t kSlotsTotal = size_t(128) << 20;                            // pinned bytes over all slots
 constexpr size_t kSlotsMost = 64;
+constexpr size_t kPairBudget = size_t(256) << 20;   // workspace of one request by triangle pairs (larger ones go in panels)
+constexpr size_t kWorkTotal = size_t(1) << 30;      // of all that are kept
 
 struct StageSlot {
     char *host = nullptr;       // pinned
@@ -92,6 +94,22 @@ std::mutex g_stage_mu;
 std::vector<StageSlot *> g_slots;
 size_t g_slots_bytes = 0;
 
+// Workspaces of requests by triangle pairs (local matrices).  Calls on one
+// stream follow each other there, so they share one: a call takes the buffer
+// last used on its stream behind that use (the stream waits for its event,
+// which on the same stream costs nothing), else one whose last use the host has
+// seen end, else a new one within the total.
+struct WorkBuf {
+    char *p = nullptr;
+    size_t bytes = 0;
+    int device = 0;
+    hipStream_t last = nullptr;
+    hipEvent_t done = nullptr;
+    bool taken = false, recorded = false;
+};
+std::vector<WorkBuf *> g_works;
+size_t g_works_bytes = 0;
+
 bool finished(hipEvent_t e)
 {
     if (hipEventQuery(e) == hipSuccess) return true;
@@ -105,6 +123,82 @@ void destroy_slot(StageSlot *x)
     if (x->host) (void)hipHostFree(x->host);
     if (x->dev) (void)hipFree(x->dev);
     delete x;
+}
+
+void destroy_work(WorkBuf *w)
+{
+    if (w->done) (void)hipEventDestroy(w->done);
+    if (w->p) (void)hipFree(w->p);
+    delete w;
+}
+
+// A workspace of at least `bytes` for work about to be enqueued on s, or null.
+WorkBuf *take_work(size_t bytes, int device, hipStream_t s)
+{
+    std::lock_guard<std::mutex> g(g_stage_mu);
+    WorkBuf *idle = nullptr;
+    for (WorkBuf *w : g_works) {
+        if (w->taken || w->device != device || w->bytes < bytes) continue;
+        if (w->recorded && w->last == s) {
+            if (hipStreamWaitEvent(s, w->done, 0) != hipSuccess) {
+                (void)hipGetLastError();
+                continue;
+            }
+            w->taken = true;
+            return w;
+        }
+        if (!idle && (!w->recorded || finished(w->done))) idle = w;
+    }
+    if (idle) {
+        idle->taken = true;
+        return idle;
+    }
+    size_t cap = size_t(1) << 20;
+    while (cap < bytes) cap *= 2;
+    // smaller ones that nothing uses make room
+    for (size_t i = 0; i < g_works.size() && g_works_bytes + cap > kWorkTotal;) {
+        WorkBuf *w = g_works[i];
+        if (w->taken || (w->recorded && !finished(w->done))) {
+            ++i;
+            continue;
+        }
+        g_works_bytes -= w->bytes;
+        destroy_work(w);
+        g_works[i] = g_works.back();
+        g_works.pop_back();
+    }
+    if (g_works_bytes + cap > kWorkTotal) return nullptr;
+    WorkBuf *w = new (std::nothrow) WorkBuf();
+    if (!w) return nullptr;
+    if (hipMalloc((void **)&w->p, cap) != hipSuccess ||
+        hipEventCreateWithFlags(&w->done, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        destroy_work(w);
+        return nullptr;
+    }
+    w->bytes = cap;
+    w->device = device;
+    w->taken = true;
+    g_works.push_back(w);
+    g_works_bytes += cap;
+    return w;
+}
+
+// Returns a workspace whose last use has been enqueued on s (or not at all).
+hipError_t give_work(WorkBuf *w, hipStream_t s, bool enqueued)
+{
+    hipError_t e = hipSuccess;
+    if (enqueued) {
+        e = hipEventRecord(w->done, s);
+        if (e != hipSuccess) (void)hipStreamSynchronize(s);
+    }
+    std::lock_guard<std::mutex> g(g_stage_mu);
+    if (enqueued && e == hipSuccess) {
+        w->recorded = true;
+        w->last = s;
+    }
+    w->taken = false;
+    return e;
 }
 
 // A slot of at least `bytes` on `device` that no enqueued work uses, or null.
@@ -212,6 +306,17 @@ void release_slots()
         g_slots[i] = g_slots.back();
         g_slots.pop_back();
     }
+    for (size_t i = 0; i < g_works.size();) {
+        WorkBuf *w = g_works[i];
+        if (w->taken || (w->recorded && !finished(w->done))) {
+            ++i;
+            continue;
+        }
+        g_works_bytes -= w->bytes;
+        destroy_work(w);
+        g_works[i] = g_works.back();
+        g_works.pop_back();
+    }
 }
 
 // Requests of at most this many workgroups read their descriptor, block
@@ -235,7 +340,9 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
     bem_mesh *mesh = r.mesh;
     if (r.near == BEM_NEAR_ERROR) {
         // host-side check: nothing may be enqueued for a failing request
-        if (r.space == BEM_P0) {
+        if (r.paired) {
+            if (r.pair_error) return fail(BEM_E_NEARFIELD, "a contributing triangle pair shares a vertex");
+        } else if (r.space == BEM_P0) {
             for (int32_t a : r.rows)
                 for (int32_t b : r.cols)
                     if (mesh->adjacent(a, b)) return fail(BEM_E_NEARFIELD, "a contributing triangle pair shares a vertex");
@@ -259,18 +366,23 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
     const NearLayout near_l = near_layout(near_kind(r), near_n);
     off = al(off + (near ? near_l.staged : 0));
     const size_t off_in = off;
-    off = al(off + r.in_bytes);
+    off = al(off + (r.paired ? 4 * r.pairs.ints.size() : r.in_bytes));
     const size_t off_status = off;
     off = al(off + 8);
     const size_t in_total = off;
     // what the singular kernels write for each other follows the staged part
-    const size_t ws_total = in_total + (near ? near_l.bytes - near_l.staged : 0);
+    const size_t ws_staged = in_total + (near ? near_l.bytes - near_l.staged : 0);
+    // the local matrices of a request by triangle pairs: with a slot a kept
+    // workspace of their own, else behind the rest
+    const size_t work_bytes = r.paired ? r.pairs.work : 0;
+    size_t ws_total = al(ws_staged) + work_bytes;
     if (fixed && ws_total > fixed_bytes)
         return fail(BEM_E_OOM, "request needs " + std::to_string(ws_total) + " bytes of workspace, more than the " +
                                    std::to_string(fixed_bytes) + "-byte static workspace of the no-allocation entry point");
     char *host = nullptr;
     char *ws = fixed;
     StageSlot *slot = nullptr;
+    WorkBuf *wbuf = nullptr;
     thread_local std::vector<char> pageable;
     if (fixed) {
         pageable.assign(in_total, 0);
@@ -280,9 +392,13 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipGetDevice(&cur) == hipSuccess && hipStreamGetDevice(s, &dev) == hipSuccess && cur == dev &&
             hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone)
-            slot = take_slot(ws_total, dev);
+            slot = take_slot(ws_staged, dev);
         else
             (void)hipGetLastError();
+        if (slot && work_bytes && !(wbuf = take_work(work_bytes, dev, s))) {
+            (void)give_slot(slot, s, false);
+            slot = nullptr;
+        }
         if (slot) {
             host = slot->host;
             ws = slot->dev;
@@ -298,14 +414,19 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
         }
     }
     // where the kernels read the staged image
-    const bool direct = slot && !near && r.nblocks <= kDirectBlocks;
+    const bool direct = slot && !near && !r.paired && r.nblocks <= kDirectBlocks;
+    char *work = wbuf ? wbuf->p : ws + al(ws_staged);
     char *img = direct ? slot->host_dev : ws;
-    ReqDev d;
-    stage_request_inputs(r, host, img, off_in, d);
-    finish_descriptor(r, img, 0, off_status, d);
-    d.out = dev_out;
-    std::memcpy(host + off_req, &d, sizeof(ReqDev));
-    write_blocks(r, 0, reinterpret_cast<EntryBlock *>(host + off_b));
+    if (r.paired) {
+        std::memcpy(host + off_in, r.pairs.ints.data(), 4 * r.pairs.ints.size());
+    } else {
+        ReqDev d;
+        stage_request_inputs(r, host, img, off_in, d);
+        finish_descriptor(r, img, 0, off_status, d);
+        d.out = dev_out;
+        std::memcpy(host + off_req, &d, sizeof(ReqDev));
+        write_blocks(r, 0, reinterpret_cast<EntryBlock *>(host + off_b));
+    }
     NearLayout nl = near_l;
     if (near) {
         // the device-only part sits past the staged image of the whole request
@@ -318,7 +439,10 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
     hipError_t e = hipSuccess;
     if (slot) {
         if (!direct) e = launch_stage_copy(slot->host_dev, ws, in_total, s);
-        if (e != hipSuccess) (void)give_slot(slot, s, false);
+        if (e != hipSuccess) {
+            (void)give_slot(slot, s, false);
+            if (wbuf) (void)give_work(wbuf, s, false);
+        }
     } else {
         e = hipMemcpyAsync(ws, host, in_total, hipMemcpyHostToDevice, s);
         if (!fixed) {
@@ -331,10 +455,20 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
     if (e != hipSuccess) return fail(BEM_E_DEVICE, std::string("staging copy: ") + hipGetErrorString(e));
     const ReqDev *dreq = (const ReqDev *)(img + off_req);
     Variant v{kernel_op(r.op), r.space, r.prec, mesh->q};
-    e = launch_entries(v, dreq, (const EntryBlock *)(img + off_b), r.nblocks, s);
+    if (r.paired) {
+        const int64_t sf = r.fixrows ? r.ncols : 1, sl = r.fixrows ? 1 : r.ncols;
+        for (const PairPanel &f : r.pairs.fix)
+            for (const PairPanel &l : r.pairs.lane)
+                if (e == hipSuccess)
+                    e = launch_pairs(*mesh, r.pairs, f, l, (const int32_t *)(ws + off_in), work, dev_out, sf, sl, r.k, s);
+    } else {
+        e = launch_entries(v, dreq, (const EntryBlock *)(img + off_b), r.nblocks, s);
+    }
     if (e == hipSuccess && near) e = launch_near(near_kind(r), nl, near_n, ws + off_near, s);
     if (slot) {
-        const hipError_t g = give_slot(slot, s, true);
+        hipError_t g = wbuf ? give_work(wbuf, s, true) : hipSuccess;
+        if (e == hipSuccess) e = g;
+        g = give_slot(slot, s, true);
         if (e == hipSuccess) e = g;
     } else if (!fixed && e == hipSuccess) {
         e = hipFreeAsync(ws, s);
@@ -414,7 +548,7 @@ int bem_eval_entries(bem_mesh *mesh, bem_op op, bem_space space, double k, const
 {
     Request *r = new (std::nothrow) Request();
     if (!r) return fail(BEM_E_OOM, "host allocation failed");
-    int rc = fill_request(*r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near);
+    int rc = fill_request(*r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, server_pair_budget());
     if (rc == BEM_OK && r->entries() > 0) {
         if (!out) {
             rc = fail(BEM_E_ARG, "null output");
@@ -438,7 +572,7 @@ int bem_submit(bem_mesh *mesh, bem_op op, bem_space space, double k, const int32
     bem_ticket *t = new (std::nothrow) bem_ticket();
     if (!t) return fail(BEM_E_OOM, "host allocation failed");
     Request &r = t->req;
-    int rc = fill_request(r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near);
+    int rc = fill_request(r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, server_pair_budget());
     if (rc == BEM_OK) {
         if (r.entries() == 0) {
             r.done = true;
@@ -488,7 +622,7 @@ int bem_eval_entries_async(bem_mesh *mesh, bem_op op, bem_space space, double k,
                            void *stream)
 {
     Request r;
-    int rc = fill_request(r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near);
+    int rc = fill_request(r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, kPairBudget);
     if (rc != BEM_OK) return rc;
     if (r.entries() == 0) return BEM_OK;
     if (!dev_out) return fail(BEM_E_ARG, "null output");
@@ -500,14 +634,20 @@ int bem_eval_entries_async_noalloc(bem_mesh *mesh, bem_op op, bem_space space, d
                                    void *dev_out, void *stream)
 {
     Request r;
-    int rc = fill_request(r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near);
+    int rc = fill_request(r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, kNoAllocBytes / 2);
     if (rc != BEM_OK) return rc;
     if (r.entries() == 0) return BEM_OK;
     if (!dev_out) return fail(BEM_E_ARG, "null output");
     char *ws = nullptr;
     rc = noalloc_workspace(mesh->device, &ws);
     if (rc != BEM_OK) return rc;
-    return enqueue_device_request(r, dev_out, (hipStream_t)stream, ws, kNoAllocBytes);
+    rc = enqueue_device_request(r, dev_out, (hipStream_t)stream, ws, kNoAllocBytes);
+    if (rc == BEM_E_OOM && r.paired) {
+        // by stars it may still fit
+        rc = expand_request(r, 0);
+        if (rc == BEM_OK) rc = enqueue_device_request(r, dev_out, (hipStream_t)stream, ws, kNoAllocBytes);
+    }
+    return rc;
 }
 
 int bem_server_config(size_t arena_bytes, int max_batch_requests)

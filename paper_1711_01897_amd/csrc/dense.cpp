@@ -1,12 +1,13 @@
-// Pair-based evaluation of P1 blocks (the dense weak-form assembly of
+// P1 and DP1 blocks by triangle pairs (the dense weak-form assembly of
 // Section 3): every regular triangle pair of star(rows) x star(cols) is
 // integrated once into its 3 x 3 local matrix on the device, then each entry
 // adds its pairs' local values in a fixed order (entries.hip: k_local_*,
-// k_gather_dense_*).  Rows go in panels whose local matrices fit a device
-// budget; the panels run on a compute stream while a copy stream moves the
-// previous panel's entries to pinned host memory and the calling thread
-// copies the one before into `out`, so assembly and transfer overlap
-// (Section 3's chunked assembly with overlapped transfers).
+// k_gather_pairs).  Device-tensor requests large enough take it
+// (pairs_pay); bem_eval_dense is the host form: rows go in panels whose local
+// matrices fit a device budget; the panels run on a compute stream while a
+// copy stream moves the previous panel's entries to pinned host memory and the
+// calling thread copies the one before into `out`, so assembly and transfer
+// overlap (Section 3's chunked assembly with overlapped transfers).
 #include <algorithm>
 #include <cstdlib>
 
@@ -14,35 +15,196 @@
 
 namespace bem {
 
-hipError_t launch_dense_local(int op, bool fp32, const bem_mesh &m, const int32_t *test, int ntest,
-                              const int32_t *trial, int ntrial, void *Lr, void *Li, double k, hipStream_t s);
-hipError_t launch_dense_gather(bool fp32, bool cplx, const void *Lr, const void *Li, int ntrial, const int32_t *rptr,
-                               const int32_t *rsrc, int nrows, const int32_t *cptr, const int32_t *csrc, int ncols,
-                               void *out, hipStream_t s);
+hipError_t launch_pair_local(int op, bool fp32, bool ltrial, const bem_mesh &m, const int32_t *ftri, int nf,
+                             const int32_t *ltri, int nl, void *Lr, void *Li, double k, hipStream_t s);
+hipError_t launch_pair_gather(bool fp32, bool cplx, const void *Lr, const void *Li, int nl, const int32_t *fptr,
+                              const int32_t *fsrc, const int32_t *fpos, int nfd, const int32_t *lptr,
+                              const int32_t *lsrc, const int32_t *lpos, int nld, void *out, int64_t sf, int64_t sl,
+                              hipStream_t s);
 
 namespace {
 
-// Sorted distinct triangles of the stars of `dofs`, and per dof its star as
-// (index in that list << 2 | local vertex), ascending triangles.
-void star_lists(const bem_mesh &m, const int32_t *dofs, int64_t n, std::vector<int32_t> &tris,
-                std::vector<int32_t> &ptr, std::vector<int32_t> &src)
-{
-    tris.clear();
-    for (int64_t i = 0; i < n; ++i)
-        for (int64_t s = m.star_ptr[dofs[i]]; s < m.star_ptr[dofs[i] + 1]; ++s) tris.push_back(m.star[s] >> 2);
-    std::sort(tris.begin(), tris.end());
-    tris.erase(std::unique(tris.begin(), tris.end()), tris.end());
-    ptr.assign(1, 0);
-    src.clear();
-    for (int64_t i = 0; i < n; ++i) {
-        for (int64_t s = m.star_ptr[dofs[i]]; s < m.star_ptr[dofs[i] + 1]; ++s) {
-            const int32_t t = m.star[s] >> 2;
-            const int32_t idx = (int32_t)(std::lower_bound(tris.begin(), tris.end(), t) - tris.begin());
-            src.push_back((idx << 2) | (m.star[s] & 3));
+// Per-thread marks of triangles: index within the open panel.
+struct PairScratch {
+    std::vector<uint32_t> stamp;
+    std::vector<int32_t> index;
+    uint32_t gen = 0;
+    void open(int64_t nt)
+    {
+        if ((int64_t)stamp.size() < nt) {
+            stamp.assign((size_t)nt, 0);
+            index.resize((size_t)nt);
+            gen = 0;
         }
-        ptr.push_back((int32_t)src.size());
+        if (++gen == 0) {
+            std::fill(stamp.begin(), stamp.end(), 0);
+            gen = 1;
+        }
+    }
+};
+thread_local PairScratch g_pair;
+
+void star_range(const bem_mesh &m, int space, int32_t d, int64_t &b, int64_t &e)
+{
+    if (space == BEM_P1) {
+        b = m.star_ptr[d];
+        e = m.star_ptr[d + 1];
+    } else {
+        b = m.dp1_star[d];
+        e = b + 1;
     }
 }
+
+// Cuts a side into panels of at most most_tri distinct triangles (one dof's
+// star at least).
+void cut_side(const bem_mesh &m, int space, const int32_t *dofs, int64_t n, int64_t most_tri, std::vector<int32_t> &ints,
+              std::vector<PairPanel> &out)
+{
+    std::vector<int32_t> order, tri, ptr, src;
+    morton_order(m, space, dofs, n, order);
+    PairScratch &sc = g_pair;
+    int64_t i = 0;
+    while (i < n) {
+        sc.open(m.nt);
+        tri.clear();
+        src.clear();
+        ptr.assign(1, 0);
+        const int64_t first = i;
+        for (; i < n; ++i) {
+            int64_t b, e, fresh = 0;
+            star_range(m, space, dofs[order[i]], b, e);
+            for (int64_t s = b; s < e; ++s) fresh += sc.stamp[m.star[s] >> 2] != sc.gen;
+            if (i > first && (int64_t)tri.size() + fresh > most_tri) break;
+            for (int64_t s = b; s < e; ++s) {
+                const int32_t t = m.star[s] >> 2;
+                if (sc.stamp[t] != sc.gen) {
+                    sc.stamp[t] = sc.gen;
+                    sc.index[t] = (int32_t)tri.size();
+                    tri.push_back(t);
+                }
+                src.push_back((sc.index[t] << 2) | (m.star[s] & 3));
+            }
+            ptr.push_back((int32_t)src.size());
+        }
+        PairPanel P;
+        P.ntri = (int32_t)tri.size();
+        P.ndof = (int32_t)(i - first);
+        auto put = [&](auto b, auto e) {
+            const size_t at = ints.size();
+            ints.insert(ints.end(), b, e);
+            return at;
+        };
+        P.tri = put(tri.begin(), tri.end());
+        P.ptr = put(ptr.begin(), ptr.end());
+        P.src = put(src.begin(), src.end());
+        P.pos = put(order.begin() + first, order.begin() + i);
+        out.push_back(P);
+    }
+}
+
+// Star entries and distinct triangles of a dof list.
+void count_side(const bem_mesh &m, int space, const std::vector<int32_t> &dofs, int64_t &stars, int64_t &distinct)
+{
+    PairScratch &sc = g_pair;
+    sc.open(m.nt);
+    stars = distinct = 0;
+    for (int32_t d : dofs) {
+        int64_t b, e;
+        star_range(m, space, d, b, e);
+        stars += e - b;
+        for (int64_t s = b; s < e; ++s) {
+            const int32_t t = m.star[s] >> 2;
+            distinct += sc.stamp[t] != sc.gen;
+            sc.stamp[t] = sc.gen;
+        }
+    }
+}
+
+size_t pair_bytes(int op, int prec) { return 9 * (prec == BEM_FP32 ? 4 : 8) * (size_t)(is_complex_op(op) ? 2 : 1); }
+
+}  // namespace
+
+void plan_pairs(const bem_mesh &m, int space, int op, int prec, bool ltrial, const int32_t *fix, int64_t nfix,
+                const int32_t *lane, int64_t nlane, size_t budget, PairPlan &P)
+{
+    P.ints.clear();
+    P.fix.clear();
+    P.lane.clear();
+    P.op = op;
+    P.prec = prec;
+    P.ltrial = ltrial;
+    const size_t per = pair_bytes(op, prec);
+    // lane panels leave room for at least 64 fixed-side triangles (or the largest star)
+    const int64_t rows = std::max<int64_t>(64, m.max_star);
+    cut_side(m, space, lane, nlane, std::max<int64_t>(256, (int64_t)(budget / per) / rows), P.ints, P.lane);
+    int64_t nl = 1;
+    for (const PairPanel &l : P.lane) nl = std::max<int64_t>(nl, l.ntri);
+    // 262,144 rows: the launch grid's second dimension at four or more rows a workgroup
+    cut_side(m, space, fix, nfix, std::min<int64_t>(std::max<int64_t>(1, (int64_t)(budget / per) / nl), 65535 * 4), P.ints,
+             P.fix);
+    int64_t nf = 0;
+    P.pairs = 0;
+    for (const PairPanel &f : P.fix) {
+        nf = std::max<int64_t>(nf, f.ntri);
+        for (const PairPanel &l : P.lane) P.pairs += (int64_t)f.ntri * l.ntri;
+    }
+    P.work = std::max<size_t>(256, (size_t)nf * (size_t)nl * per);
+}
+
+bool pairs_touch(const bem_mesh &m, const PairPlan &P)
+{
+    std::vector<char> mark((size_t)m.nv, 0);
+    for (const PairPanel &l : P.lane)
+        for (int32_t i = 0; i < l.ntri; ++i)
+            for (int a = 0; a < 3; ++a) mark[m.tri[3 * (size_t)P.ints[l.tri + i] + a]] = 1;
+    for (const PairPanel &f : P.fix)
+        for (int32_t i = 0; i < f.ntri; ++i)
+            for (int a = 0; a < 3; ++a)
+                if (mark[m.tri[3 * (size_t)P.ints[f.tri + i] + a]]) return true;
+    return false;
+}
+
+// By pairs a block costs its distinct triangle pairs' local matrices and its
+// entries' gathers, by stars each fixed dof's star against the lanes of every
+// chunk.  Per point pair a local matrix takes 11 instructions to the star
+// form's 9 (6-point rule, single layer; with the basis products of the pair 1.3
+// times a star pair's), a gather a tenth of a star pair for each of an entry's
+// star products.  Chunks of more than 256 lanes repeat about a quarter of their
+// triangles at the borders.  Scattered dofs share nothing and stay with the
+// stars (two sets of 1,024: 377 us by stars, 554 by pairs).  Small blocks stay
+// with them too, for their single launch; the line is where the two meet for
+// two patches of n dofs (us by stars / by pairs): FP32 n = 362 39 / 56, 512
+// 63 / 65, 1,024 191 / 128; FP32 complex 256 65 / 62, 1,024 451 / 330; FP64 256
+// 55 / 49, 1,024 344 / 252; FP64 complex 128 38 / 51, 181 80 / 58, 1,024
+// 970 / 641.
+bool pairs_pay(const Request &r, const std::vector<int32_t> &fix, const std::vector<int32_t> &lane)
+{
+    const bool fp32 = r.prec == BEM_FP32, cplx = is_complex_op(r.op);
+    const int64_t least = fp32 ? (cplx ? 65536 : 262144) : (cplx ? 32768 : 65536);
+    if (r.space == BEM_P0 || fix.size() < 8 || (int64_t)fix.size() * (int64_t)lane.size() < least) return false;
+    const bem_mesh &m = *r.mesh;
+    int64_t fs, fd, ls, ld;
+    count_side(m, r.space, fix, fs, fd);
+    count_side(m, r.space, lane, ls, ld);
+    const double star = (double)fs * (ld > kBlockLanes ? 1.25 : 1.0) * (double)ld;
+    const double pair = 1.3 * (double)fd * (double)ld + 0.1 * (double)fs * (double)ls;
+    return pair < 0.8 * star;
+}
+
+hipError_t launch_pairs(const bem_mesh &m, const PairPlan &P, const PairPanel &f, const PairPanel &l, const int32_t *ints,
+                        void *work, void *out, int64_t sf, int64_t sl, double k, hipStream_t s, bool in_panel,
+                        hipEvent_t between)
+{
+    const bool fp32 = P.prec == BEM_FP32, cplx = is_complex_op(P.op);
+    void *Li = cplx ? static_cast<char *>(work) + (size_t)f.ntri * (size_t)l.ntri * pair_bytes(P.op, P.prec) / 2 : nullptr;
+    hipError_t e = launch_pair_local(P.op, fp32, P.ltrial, m, ints + f.tri, f.ntri, ints + l.tri, l.ntri, work, Li, k, s);
+    if (e == hipSuccess && between) e = hipEventRecord(between, s);
+    if (e != hipSuccess) return e;
+    return launch_pair_gather(fp32, cplx, work, Li, l.ntri, ints + f.ptr, ints + f.src, in_panel ? nullptr : ints + f.pos, f.ndof,
+                              ints + l.ptr, ints + l.src, ints + l.pos, l.ndof, out, sf, sl, s);
+}
+
+namespace {
 
 struct DevBuf {
     void *p = nullptr;
@@ -50,12 +212,6 @@ struct DevBuf {
     {
         if (p) (void)hipFree(p);
     }
-};
-
-struct Panel {
-    int64_t r0 = 0, nr = 0;
-    std::vector<int32_t> tris, ptr, src;
-    size_t off_tris = 0, off_ptr = 0, off_src = 0;   // in the index buffer, int32 units
 };
 
 }  // namespace
@@ -88,70 +244,19 @@ int eval_dense(bem_mesh *m, int op, int space, double k, const int32_t *rows, in
     if (nrows == 0 || ncols == 0) return BEM_OK;
     if (ncols > INT32_MAX / 4) return fail(BEM_E_ARG, "too many columns");
     const double t0 = now_seconds();
-    const bool fp32 = prec == BEM_FP32, cplx = is_complex_op(op);
-    const size_t real = fp32 ? 4 : 8, elem = out_elem_bytes(op, prec);
+    const size_t elem = out_elem_bytes(op, prec);
 
-    std::vector<int32_t> ctris, cptr, csrc;
-    star_lists(*m, cols, ncols, ctris, cptr, csrc);
-    const int64_t ntrial = (int64_t)ctris.size();
-    if (ntrial > INT32_MAX / 4) return fail(BEM_E_ARG, "too many trial triangles");
-    if (near == BEM_NEAR_ERROR) {
-        // nothing is launched for a failing request: every vertex-sharing pair
-        // between the row stars and the column stars is an error
-        std::vector<char> mark(m->nv, 0);
-        for (int32_t t : ctris)
-            for (int a = 0; a < 3; ++a) mark[m->tri[3 * (size_t)t + a]] = 1;
-        for (int64_t i = 0; i < nrows; ++i)
-            for (int64_t s = m->star_ptr[rows[i]]; s < m->star_ptr[rows[i] + 1]; ++s) {
-                const int32_t t = m->star[s] >> 2;
-                for (int a = 0; a < 3; ++a)
-                    if (mark[m->tri[3 * (size_t)t + a]]) return fail(BEM_E_NEARFIELD, "a contributing triangle pair shares a vertex");
-            }
-    }
-    // panels: at most 65,535 rows (the gather's grid) and local matrices of at
-    // most BEM_DENSE_BUDGET_MB (default 1024) MiB
+    // row panels whose local matrices take at most BEM_DENSE_BUDGET_MB (default 1024) MiB
     const char *env = std::getenv("BEM_DENSE_BUDGET_MB");
     const size_t budget = (size_t)std::max(16, env ? std::atoi(env) : 1024) << 20;
-    const size_t per_test = 9 * real * (cplx ? 2 : 1) * (size_t)ntrial;   // local values of one test triangle
-    std::vector<Panel> panels;
-    size_t max_test = 0;
-    {
-        int64_t r = 0;
-        while (r < nrows) {
-            // grow the panel while its row stars fit the budget (about 2 test
-            // triangles per row: start from that estimate and shrink)
-            int64_t nr = std::min<int64_t>({nrows - r, 65535, std::max<int64_t>(1, (int64_t)(budget / per_test) / 2)});
-            Panel P;
-            for (;;) {
-                star_lists(*m, rows + r, nr, P.tris, P.ptr, P.src);
-                if (P.tris.size() * per_test <= budget || nr == 1) break;
-                nr = std::max<int64_t>(1, nr / 2);
-            }
-            if (P.tris.size() * per_test > budget)
-                return fail(BEM_E_OOM, "one row's local matrices exceed the dense budget (BEM_DENSE_BUDGET_MB)");
-            P.r0 = r;
-            P.nr = nr;
-            max_test = std::max(max_test, P.tris.size());
-            panels.push_back(std::move(P));
-            r += nr;
-        }
-    }
+    PairPlan P;
+    plan_pairs(*m, space, op, prec, true, rows, nrows, cols, ncols, budget, P);
+    // nothing is launched for a failing request
+    if (near == BEM_NEAR_ERROR && pairs_touch(*m, P))
+        return fail(BEM_E_NEARFIELD, "a contributing triangle pair shares a vertex");
+    const std::vector<PairPanel> &panels = P.fix;
     int64_t max_rows = 0;
-    for (const Panel &P : panels) max_rows = std::max(max_rows, P.nr);
-    // one int32 buffer for every index list
-    std::vector<int32_t> idx;
-    auto put = [&](const std::vector<int32_t> &v) {
-        const size_t at = idx.size();
-        idx.insert(idx.end(), v.begin(), v.end());
-        while (idx.size() % 4) idx.push_back(0);
-        return at;
-    };
-    const size_t off_ctris = put(ctris), off_cptr = put(cptr), off_csrc = put(csrc);
-    for (Panel &P : panels) {
-        P.off_tris = put(P.tris);
-        P.off_ptr = put(P.ptr);
-        P.off_src = put(P.src);
-    }
+    for (const PairPanel &f : panels) max_rows = std::max<int64_t>(max_rows, f.ndof);
     const size_t panel_out = (size_t)max_rows * (size_t)ncols * elem;
     DevBuf d_idx, d_L, d_out;
     char *h_stage = nullptr;
@@ -167,14 +272,14 @@ int eval_dense(bem_mesh *m, int op, int space, double k, const int32_t *rows, in
         if (sx) (void)hipStreamDestroy(sx);
         if (h_stage) (void)hipHostFree(h_stage);
     };
-    hipError_t e = hipMalloc(&d_idx.p, 4 * idx.size());
-    if (e == hipSuccess) e = hipMalloc(&d_L.p, max_test * per_test);
+    hipError_t e = hipMalloc(&d_idx.p, 4 * P.ints.size());
+    if (e == hipSuccess) e = hipMalloc(&d_L.p, P.work);
     if (e == hipSuccess) e = hipMalloc(&d_out.p, 2 * panel_out);
     if (e == hipSuccess) e = hipHostMalloc((void **)&h_stage, 2 * panel_out, hipHostMallocDefault);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&sc, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&sx, hipStreamNonBlocking);
     for (int i = 0; i < 8 && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&ev[i], i < 4 ? hipEventDisableTiming : 0);
-    if (e == hipSuccess) e = hipMemcpy(d_idx.p, idx.data(), 4 * idx.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(d_idx.p, P.ints.data(), 4 * P.ints.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         cleanup();
         return fail(e == hipErrorOutOfMemory ? BEM_E_OOM : BEM_E_DEVICE, std::string("dense set-up: ") + hipGetErrorString(e));
@@ -182,40 +287,33 @@ int eval_dense(bem_mesh *m, int op, int space, double k, const int32_t *rows, in
     const int32_t *D = static_cast<const int32_t *>(d_idx.p);
     hipEvent_t *computed = ev, *copied = ev + 2;   // per output buffer
     hipEvent_t t_start = ev[4], t_local = ev[5], t_end = ev[6];
-    char *L = static_cast<char *>(d_L.p);
-    void *Li = cplx ? L + max_test * per_test / 2 : nullptr;
     double local_s = 0.0;
-    int64_t pairs = 0;
     auto finish = [&](size_t p) {
-        const Panel &P = panels[p];
+        const PairPanel &f = panels[p];
         const int b = (int)(p % 2);
         hipError_t x = hipEventSynchronize(copied[b]);
         if (x != hipSuccess) return x;
-        std::memcpy(static_cast<char *>(out) + (size_t)P.r0 * ncols * elem, h_stage + b * panel_out,
-                    (size_t)P.nr * ncols * elem);
+        for (int32_t r = 0; r < f.ndof; ++r)   // the panel's rows, where the caller has them
+            std::memcpy(static_cast<char *>(out) + (size_t)P.ints[f.pos + r] * ncols * elem,
+                        h_stage + b * panel_out + (size_t)r * ncols * elem, (size_t)ncols * elem);
         return hipSuccess;
     };
     for (size_t p = 0; p < panels.size() && e == hipSuccess; ++p) {
-        const Panel &P = panels[p];
+        const PairPanel &f = panels[p];
         const int b = (int)(p % 2);
         char *dout = static_cast<char *>(d_out.p) + b * panel_out;
         if (p >= 2) e = hipStreamWaitEvent(sc, copied[b], 0);
         const bool timed = p == 0;
         if (e == hipSuccess && timed) e = hipEventRecord(t_start, sc);
-        if (e == hipSuccess)
-            e = launch_dense_local(op, fp32, *m, D + P.off_tris, (int)P.tris.size(), D + off_ctris, (int)ntrial, L, Li,
-                                   k, sc);
-        if (e == hipSuccess && timed) e = hipEventRecord(t_local, sc);
-        if (e == hipSuccess)
-            e = launch_dense_gather(fp32, cplx, L, Li, (int)ntrial, D + P.off_ptr, D + P.off_src, (int)P.nr,
-                                    D + off_cptr, D + off_csrc, (int)ncols, dout, sc);
+        for (size_t l = 0; l < P.lane.size() && e == hipSuccess; ++l)
+            e = launch_pairs(*m, P, f, P.lane[l], D, d_L.p, dout, ncols, 1, k, sc, true,
+                             timed && l == 0 ? t_local : nullptr);
         if (e == hipSuccess && timed) e = hipEventRecord(t_end, sc);
         if (e == hipSuccess) e = hipEventRecord(computed[b], sc);
-        pairs += (int64_t)P.tris.size() * ntrial;
         if (e == hipSuccess && p >= 1) e = finish(p - 1);
         if (e == hipSuccess) e = hipStreamWaitEvent(sx, computed[b], 0);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(h_stage + b * panel_out, dout, (size_t)P.nr * ncols * elem, hipMemcpyDeviceToHost, sx);
+            e = hipMemcpyAsync(h_stage + b * panel_out, dout, (size_t)f.ndof * ncols * elem, hipMemcpyDeviceToHost, sx);
         if (e == hipSuccess) e = hipEventRecord(copied[b], sx);
         if (e == hipSuccess && timed) {
             float ms0 = 0.f;
@@ -226,7 +324,7 @@ int eval_dense(bem_mesh *m, int op, int space, double k, const int32_t *rows, in
                 float ms1 = 0.f;
                 if (hipEventElapsedTime(&ms1, t_local, t_end) == hipSuccess) st->first_gather_seconds = 1e-3 * ms1;
                 st->first_local_seconds = local_s;
-                st->first_pairs = (int64_t)P.tris.size() * ntrial;
+                st->first_pairs = (int64_t)f.ntri * P.lane[0].ntri;
             }
         }
     }
@@ -234,7 +332,7 @@ int eval_dense(bem_mesh *m, int op, int space, double k, const int32_t *rows, in
     if (e != hipSuccess) rc = fail(BEM_E_DEVICE, std::string("dense block: ") + hipGetErrorString(e));
     cleanup();
     if (st && rc == BEM_OK) {
-        st->pairs = pairs;
+        st->pairs = P.pairs;
         st->panels = (int64_t)panels.size();
         st->seconds = now_seconds() - t0;
     }

@@ -1771,73 +1771,106 @@ EntryKernel select_kernel(const Variant &v)
 }
 
 // ---------------------------------------------------------------------------
-// Pair-based P1 blocks (dense assembly).
+// P1 blocks by triangle pairs.
 //
 // Section 3's dense assembly evaluates the kernel at all pairs of Gauss
 // points of a triangle pair once, weights the values with the basis
 // functions of every pair of local dofs and adds the results to the global
-// entries.  The star kernels above integrate a pair once per test vertex
-// (three times for a full block); here a block's pairs are integrated once
-// into their 3 x 3 local matrices (k_local_*, one lane per trial triangle
-// against a tile of test triangles staged in LDS), stored plane by plane
-// (L[(m 9 + 3 a + b) ntrial + n] for test triangle m, trial triangle n), and
-// every entry then adds its pairs' local values in a fixed order, test
-// triangles of its row's star outer, trial triangles of its column's star
-// inner (k_gather_dense_*; compensated in FP32).  Vertex-sharing pairs
-// contribute zero (regular part).
-constexpr int kLocalTile = 8;   // test triangles staged per workgroup
+// entries.  The star kernels above integrate a pair once per fixed vertex and
+// lane chunk (about four times for a block of two patches); here a block's
+// pairs are integrated once into their 3 x 3 local matrices (k_local_*, one
+// lane per lane-side triangle against a few fixed-side triangles), stored
+// plane by plane (L[(m 9 + 3 a + b) nl + n] for fixed-side triangle m,
+// lane-side triangle n), and every entry then adds its pairs' local values in a
+// fixed order, the fixed dof's star outer, the lane dof's star inner
+// (k_gather_*; compensated in FP32).  Vertex-sharing pairs contribute zero
+// (regular part).
+//
+// k_local is bound by its arithmetic (FP32 single layer, 6-point rule: 75 G
+// pairs/s, 445 vector instructions a pair, the FP32 issue rate); its 36 bytes a
+// pair hide behind that.  k_gather_pairs reads every local value once: both
+// sides' dofs come along a Morton curve, so that neighbouring threads read
+// neighbouring triangles (1.07 GB of a panel in 371 us, 2.9 TB/s, 17.8 G
+// entries/s; in the caller's order 12.4), and whole panels of rows share their
+// triangles (the level-5 icosphere's matrix: 465 M pairs in panels of 1 GiB, 785 M
+// in the caller's order; device time 24 -> 12 ms).  On the device 1,023 x 2,049
+// double layer entries take 298 us by pairs, 442 us by stars; 501 x 1,000 FP64
+// Helmholtz 310 and 472.
+constexpr int kLocalTile = 8;    // fixed-side triangles per workgroup at most
+constexpr int kGatherRows = 4;   // fixed-side dofs per workgroup
 
-// 3 x 3 local matrix of a regular pair, FP32, without J_x J_y / 4 pi:
-// M[a][b] = sum_q w_q lam_b(q) sum_p w_p lam_a(p) K(x_p, y_q).  T is the test
-// record, S the trial record with its offsets scaled by -2 and Bq[q] =
-// |o_q|^2 (see pair_p1_testfix_f32).
-template <int OP, int Q>
-__device__ __forceinline__ void pair_local_f32(const float *T, const float *S, const float *Bq, float kf, double kk,
-                                               float (*Mr)[3], float (*Mi)[3])
+// 3 x 3 local matrix of a regular pair, FP32, without J J / 4 pi: M[a][b] for
+// vertex a of the fixed triangle F and vertex b of the lane triangle L (offsets
+// scaled by -2, Bq[q] = |o_q|^2; see pair_p1_testfix_f32).  LTRIAL: the lane is
+// the trial side.  Hypersingular operators: their whole local matrix.
+template <int OP, int Q, bool LTRIAL>
+__device__ __forceinline__ void local_pair_f32(const float *F, const float *L, const float *Bq, float kf, double kk,
+                                              float (*Mr)[3], float (*Mi)[3])
 {
-    const float dcx = (T[0] - S[0]) + (T[4] - S[4]);
-    const float dcy = (T[1] - S[1]) + (T[5] - S[5]);
-    const float dcz = (T[2] - S[2]) + (T[6] - S[6]);
+    constexpr int G = is_hyp<OP>() ? (is_cplx<OP>() ? HSLP : LSLP) : OP;
+    const float dcx = (F[0] - L[0]) + (F[4] - L[4]);
+    const float dcy = (F[1] - L[1]) + (F[5] - L[5]);
+    const float dcz = (F[2] - L[2]) + (F[6] - L[6]);
     Phase ph{};
-    if constexpr (is_cplx<OP>()) ph = phase_base(T, S, kk, dcx, dcy, dcz);
-    float mx[Q], my[Q], mz[Q], A[Q], wa[3][Q];
+    if constexpr (is_cplx<OP>()) ph = phase_base(F, L, kk, dcx, dcy, dcz);
+    float mx[Q], my[Q], mz[Q], A[Q], an[is_dlp<OP>() && LTRIAL ? Q : 1];
 #pragma unroll
     for (int p = 0; p < Q; ++p) {
-        const float ox = T[12 + 3 * p], oy = T[13 + 3 * p], oz = T[14 + 3 * p];
-        const float ax = dcx + ox, ay = dcy + oy, az = dcz + oz;
-        mx[p] = ax;
-        my[p] = ay;
-        mz[p] = az;
+        const float ox = F[12 + 3 * p], oy = F[13 + 3 * p], oz = F[14 + 3 * p];
+        mx[p] = dcx + ox;
+        my[p] = dcy + oy;
+        mz[p] = dcz + oz;
         if constexpr (is_cplx<OP>())
             A[p] = fmaf(2.0f * dcx + ox, ox, fmaf(2.0f * dcy + oy, oy, (2.0f * dcz + oz) * oz));
         else
-            A[p] = fmaf(ax, ax, fmaf(ay, ay, az * az));
-        float wn = (float)rule::Rule<Q>::w[p];
-        if constexpr (is_dlp<OP>()) wn *= fmaf(ax, S[8], fmaf(ay, S[9], az * S[10]));
-#pragma unroll
-        for (int a = 0; a < 3; ++a) wa[a][p] = wn * (float)rule::lam<Q>(a, p);
+            A[p] = fmaf(mx[p], mx[p], fmaf(my[p], my[p], mz[p] * mz[p]));
+        // (x_p - y).n_y, the same for every trial point
+        if constexpr (is_dlp<OP>() && LTRIAL) an[p] = fmaf(mx[p], L[8], fmaf(my[p], L[9], mz[p] * L[10]));
     }
+    // the lane as test side: (x_q - y).n_y = o_q.n_F - D.n_F
+    float dn = 0.f;
+    if constexpr (is_dlp<OP>() && !LTRIAL) dn = fmaf(dcx, F[8], fmaf(dcy, F[9], dcz * F[10]));
+    constexpr bool P0ONLY = OP == LHYP;   // its local matrix needs the sum of g alone
+    float t0 = 0.f;
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
         for (int b = 0; b < 3; ++b) Mr[a][b] = Mi[a][b] = 0.f;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-        const float ox = S[12 + 3 * q], oy = S[13 + 3 * q], oz = S[14 + 3 * q];
+        const float ox = L[12 + 3 * q], oy = L[13 + 3 * q], oz = L[14 + 3 * q];
         const float B = Bq[q];
         float ur[3] = {0.f, 0.f, 0.f}, ui[3] = {0.f, 0.f, 0.f};
 #pragma unroll
         for (int p = 0; p < Q; ++p) {
             const float v = fmaf(mx[p], ox, fmaf(my[p], oy, fmaf(mz[p], oz, A[p] + B)));
+            if constexpr (P0ONLY) {
+                ur[0] = fmaf((float)rule::Rule<Q>::w[p], __builtin_amdgcn_rsqf(v), ur[0]);
+                continue;
+            }
+            const float w1 = is_dlp<OP>() && LTRIAL ? an[p] : 1.0f;
             float kr = 0.f, ki = 0.f;
             if constexpr (is_cplx<OP>())
-                kern_f32<OP>(v + ph.dsq, v, 1.0f, kf, ph, kr, ki);
+                kern_f32<G>(v + ph.dsq, v, w1, kf, ph, kr, ki);
             else
-                kern_f32<OP>(v, 0.f, 1.0f, kf, ph, kr, ki);
+                kern_f32<G>(v, 0.f, w1, kf, ph, kr, ki);
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                ur[a] = fmaf(wa[a][p], kr, ur[a]);
-                if constexpr (is_cplx<OP>()) ui[a] = fmaf(wa[a][p], ki, ui[a]);
+                const float wl = (float)(rule::Rule<Q>::w[p] * rule::lam<Q>(a, p));
+                ur[a] = fmaf(wl, kr, ur[a]);
+                if constexpr (is_cplx<OP>()) ui[a] = fmaf(wl, ki, ui[a]);
+            }
+        }
+        if constexpr (P0ONLY) {
+            t0 = fmaf((float)rule::Rule<Q>::w[q], ur[0], t0);
+            continue;
+        }
+        if constexpr (is_dlp<OP>() && !LTRIAL) {
+            const float bn = fmaf(-0.5f, fmaf(ox, F[8], fmaf(oy, F[9], oz * F[10])), -dn);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                ur[a] *= bn;
+                if constexpr (is_cplx<OP>()) ui[a] *= bn;
             }
         }
 #pragma unroll
@@ -1850,39 +1883,91 @@ __device__ __forceinline__ void pair_local_f32(const float *T, const float *S, c
             }
         }
     }
+    if constexpr (is_hyp<OP>()) {
+        // curl products (see pair_p1_hyp_f32): fixed edges from unscaled
+        // offsets, lane edges from the -2-scaled ones
+        float t0i = 0.f;
+        if constexpr (!P0ONLY) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    t0 += Mr[a][b];   // the hat functions sum to one
+                    t0i += Mi[a][b];
+                }
+        }
+        const float vs = (float)vscale<Q>();
+        float EF[3][3], EL[3][3];
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const int i1 = 12 + 3 * vpt<Q>((e + 1) % 3) + c, i2 = 12 + 3 * vpt<Q>((e + 2) % 3) + c;
+                EF[e][c] = (F[i1] - F[i2]) * vs;
+                EL[e][c] = (L[i1] - L[i2]) * (-0.5f * vs);
+            }
+        const float inv = 1.0f / (F[3] * L[3]);
+        float nn = 0.f;
+        if constexpr (is_cplx<OP>()) nn = fmaf(F[8], L[8], fmaf(F[9], L[9], F[10] * L[10])) * kf * kf;
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const float cc = fmaf(EF[a][0], EL[b][0], fmaf(EF[a][1], EL[b][1], EF[a][2] * EL[b][2])) * inv;
+                if constexpr (is_cplx<OP>()) {
+                    Mr[a][b] = fmaf(-nn, Mr[a][b], cc * t0);
+                    Mi[a][b] = fmaf(-nn, Mi[a][b], cc * t0i);
+                } else {
+                    Mr[a][b] = cc * t0;
+                }
+            }
+    }
 }
 
-// The same in FP64 from absolute points; the test record T is wave-uniform.
-template <int OP, int Q, typename FP>
-__device__ __forceinline__ void pair_local_f64(FP T, const double *S, const Wave64 &wave, double (*Mr)[3],
-                                               double (*Mi)[3])
+// The same in FP64 (plain sums): M[a][b] of fixed triangle F (wave-uniform,
+// scalar loads) against lane triangle L.
+template <int OP, int Q, bool LTRIAL, typename FP>
+__device__ __forceinline__ void local_pair_f64(FP F, const double *L, const Wave64 &wave, double (*Mr)[3],
+                                              double (*Mi)[3])
 {
+    constexpr int G = is_hyp<OP>() ? (is_cplx<OP>() ? HSLP : LSLP) : OP;
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
         for (int b = 0; b < 3; ++b) Mr[a][b] = Mi[a][b] = 0.0;
+    // the lane as test side: the double layer's numerator belongs to the lane point
+    double bn[is_dlp<OP>() && !LTRIAL ? Q : 1];
+    if constexpr (is_dlp<OP>() && !LTRIAL) {
+#pragma unroll
+        for (int l = 0; l < Q; ++l)
+            bn[l] = fma(L[4 + 3 * l] - F[4], F[0], fma(L[5 + 3 * l] - F[5], F[1], (L[6 + 3 * l] - F[6]) * F[2]));
+    }
 #pragma unroll 1
-    for (int p = 0; p < Q; ++p) {
-        const double px = T[4 + 3 * p], py = T[5 + 3 * p], pz = T[6 + 3 * p];
+    for (int f = 0; f < Q; ++f) {
+        const double fx = F[4 + 3 * f], fy = F[5 + 3 * f], fz = F[6 + 3 * f];
         double sr[3] = {0.0, 0.0, 0.0}, si[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const double dx = px - S[4 + 3 * q], dy = py - S[5 + 3 * q], dz = pz - S[6 + 3 * q];
+        for (int l = 0; l < Q; ++l) {
+            const double dx = fx - L[4 + 3 * l], dy = fy - L[5 + 3 * l], dz = fz - L[6 + 3 * l];
             double gr, gi;
-            green_f64<OP>(fma(dx, dx, fma(dy, dy, dz * dz)), wave, gr, gi);
+            green_f64<G>(fma(dx, dx, fma(dy, dy, dz * dz)), wave, gr, gi);
+            if constexpr (is_dlp<OP>() && !LTRIAL) {
+                gr *= bn[l];
+                if constexpr (is_cplx<OP>()) gi *= bn[l];
+            }
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
-                const double wl = rule::Rule<Q>::w[q] * rule::lam<Q>(b, q);
+                const double wl = rule::Rule<Q>::w[l] * rule::lam<Q>(b, l);
                 sr[b] = fma(wl, gr, sr[b]);
                 if constexpr (is_cplx<OP>()) si[b] = fma(wl, gi, si[b]);
             }
         }
         double an = 1.0;
-        if constexpr (is_dlp<OP>()) an = fma(px - S[4], S[0], fma(py - S[5], S[1], (pz - S[6]) * S[2]));
+        if constexpr (is_dlp<OP>() && LTRIAL) an = fma(fx - L[4], L[0], fma(fy - L[5], L[1], (fz - L[6]) * L[2]));
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            double wa = basis_row<Q>(a)[p];
-            if constexpr (is_dlp<OP>()) wa *= an;
+            double wa = basis_row<Q>(a)[f];
+            if constexpr (is_dlp<OP>() && LTRIAL) wa *= an;
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
                 Mr[a][b] = fma(wa, sr[b], Mr[a][b]);
@@ -1890,14 +1975,39 @@ __device__ __forceinline__ void pair_local_f64(FP T, const double *S, const Wave
             }
         }
     }
+    if constexpr (is_hyp<OP>()) {
+        double t0r = 0.0, t0i = 0.0;   // the hat functions sum to one
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                t0r += Mr[a][b];
+                t0i += Mi[a][b];
+            }
+        const double vs = vscale<Q>(), inv = 1.0 / (F[3] * L[3]);
+        const double nn = is_cplx<OP>() ? (F[0] * L[0] + F[1] * L[1] + F[2] * L[2]) * wave.k * wave.k : 0.0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int f1 = 4 + 3 * vpt<Q>((a + 1) % 3), f2 = 4 + 3 * vpt<Q>((a + 2) % 3);
+            const double ex = (F[f1] - F[f2]) * vs, ey = (F[f1 + 1] - F[f2 + 1]) * vs, ez = (F[f1 + 2] - F[f2 + 2]) * vs;
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const int l1 = 4 + 3 * vpt<Q>((b + 1) % 3), l2 = 4 + 3 * vpt<Q>((b + 2) % 3);
+                const double cc = (ex * ((L[l1] - L[l2]) * vs) + ey * ((L[l1 + 1] - L[l2 + 1]) * vs) +
+                                   ez * ((L[l1 + 2] - L[l2 + 2]) * vs)) * inv;
+                Mr[a][b] = cc * t0r - nn * Mr[a][b];
+                Mi[a][b] = cc * t0i - nn * Mi[a][b];
+            }
+        }
+    }
 }
 
-// Local matrices of the pairs (test[m], trial[n]) for m in this workgroup's
-// tile of kLocalTile test triangles, n = one lane per trial triangle.
-template <int OP, int Q>
+// Local matrices of the pairs (ftri[m], ltri[n]) for m in this workgroup's
+// `tile` triangles, n = one thread per lane-side triangle.
+template <int OP, int Q, bool LTRIAL>
 __global__ __launch_bounds__(kBlockLanes) void k_local_f32(const float *__restrict__ g32, const int4 *__restrict__ vtx,
-                                                           const int32_t *__restrict__ test, int ntest,
-                                                           const int32_t *__restrict__ trial, int ntrial,
+                                                           const int32_t *__restrict__ ftri, int nf,
+                                                           const int32_t *__restrict__ ltri, int nl, int tile,
                                                            float *__restrict__ Lr, float *__restrict__ Li, float kf,
                                                            double kk)
 {
@@ -1905,20 +2015,20 @@ __global__ __launch_bounds__(kBlockLanes) void k_local_f32(const float *__restri
     __shared__ float sT[kLocalTile][W];
     __shared__ int4 sV[kLocalTile];
     const int t = threadIdx.x;
-    const int m0 = blockIdx.y * kLocalTile;
-    const int nm = min(kLocalTile, ntest - m0);
+    const int m0 = blockIdx.y * tile;
+    const int nm = min(tile, nf - m0);
     if (t < nm) {
         float v[W];
-        load32<Q>(g32, test[m0 + t], v);
+        load32<Q>(g32, ftri[m0 + t], v);
 #pragma unroll
         for (int w = 0; w < W; ++w) sT[t][w] = v[w];
-        sV[t] = vtx[test[m0 + t]];
+        sV[t] = vtx[ftri[m0 + t]];
     }
     __syncthreads();
     const int n = blockIdx.x * kBlockLanes + t;
-    if (n >= ntrial) return;   // no barrier below
+    if (n >= nl) return;   // no barrier below
     float S[W], Bq[Q];
-    load32<Q>(g32, trial[n], S);
+    load32<Q>(g32, ltri[n], S);
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         float *o = S + 12 + 3 * q;
@@ -1927,7 +2037,7 @@ __global__ __launch_bounds__(kBlockLanes) void k_local_f32(const float *__restri
         o[1] *= -2.0f;
         o[2] *= -2.0f;
     }
-    const int4 vs = vtx[trial[n]];
+    const int4 vs = vtx[ltri[n]];
     for (int i = 0; i < nm; ++i) {
         float Mr[3][3], Mi[3][3];
         if (share_vertex(sV[i], vs)) {
@@ -1939,7 +2049,7 @@ __global__ __launch_bounds__(kBlockLanes) void k_local_f32(const float *__restri
             float T[W];
 #pragma unroll
             for (int w = 0; w < W; ++w) T[w] = sT[i][w];
-            pair_local_f32<OP, Q>(T, S, Bq, kf, kk, Mr, Mi);
+            local_pair_f32<OP, Q, LTRIAL>(T, S, Bq, kf, kk, Mr, Mi);
             const float sc = T[3] * S[3] * kInv4PiF;
 #pragma unroll
             for (int a = 0; a < 3; ++a)
@@ -1949,49 +2059,39 @@ __global__ __launch_bounds__(kBlockLanes) void k_local_f32(const float *__restri
                     Mi[a][b] *= sc;
                 }
         }
-        float *lr = Lr + (size_t)(m0 + i) * 9 * ntrial + n;
-        float *li = is_cplx<OP>() ? Li + (size_t)(m0 + i) * 9 * ntrial + n : nullptr;
+        float *lr = Lr + (size_t)(m0 + i) * 9 * nl + n;
+        float *li = is_cplx<OP>() ? Li + (size_t)(m0 + i) * 9 * nl + n : nullptr;
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
-            lr[(size_t)k * ntrial] = Mr[k / 3][k % 3];
-            if constexpr (is_cplx<OP>()) li[(size_t)k * ntrial] = Mi[k / 3][k % 3];
+            lr[(size_t)k * nl] = Mr[k / 3][k % 3];
+            if constexpr (is_cplx<OP>()) li[(size_t)k * nl] = Mi[k / 3][k % 3];
         }
     }
 }
 
-template <int OP, int Q>
+template <int OP, int Q, bool LTRIAL>
 __global__ __launch_bounds__(kBlockLanes) void k_local_f64(const double *__restrict__ g64, const int4 *__restrict__ vtx,
-                                                           const int32_t *__restrict__ test, int ntest,
-                                                           const int32_t *__restrict__ trial, int ntrial,
+                                                           const int32_t *__restrict__ ftri, int nf,
+                                                           const int32_t *__restrict__ ltri, int nl, int tile,
                                                            double *__restrict__ Lr, double *__restrict__ Li, Wave64 wave)
 {
-    constexpr int W = n64<Q>();
-    __shared__ double sT[kLocalTile][W];
-    __shared__ int4 sV[kLocalTile];
-    const int t = threadIdx.x;
-    const int m0 = blockIdx.y * kLocalTile;
-    const int nm = min(kLocalTile, ntest - m0);
-    for (int i = t; i < nm * W; i += kBlockLanes) {
-        const int kk = i / W, w = i - kk * W;
-        sT[kk][w] = g64[(size_t)test[m0 + kk] * kGeo64Stride + w];
-    }
-    if (t < nm) sV[t] = vtx[test[m0 + t]];
-    __syncthreads();
-    const int n = blockIdx.x * kBlockLanes + t;
-    if (n >= ntrial) return;
-    double S[W];
-    load64<Q>(g64, trial[n], S);
-    const int4 vs = vtx[trial[n]];
-    for (int i = 0; i < nm; ++i) {
+    const int n = blockIdx.x * kBlockLanes + (int)threadIdx.x;
+    if (n >= nl) return;
+    const int m0 = blockIdx.y * tile, m1 = min(nf, m0 + tile);
+    double S[n64<Q>()];
+    load64<Q>(g64, ltri[n], S);
+    const int4 vs = vtx[ltri[n]];
+    for (int m = m0; m < m1; ++m) {
+        const int tf = ftri[m];   // the workgroup's: its record comes through scalar loads
         double Mr[3][3], Mi[3][3];
-        if (share_vertex(sV[i], vs)) {
+        if (share_vertex(vtx[tf], vs)) {
 #pragma unroll
             for (int a = 0; a < 3; ++a)
 #pragma unroll
                 for (int b = 0; b < 3; ++b) Mr[a][b] = Mi[a][b] = 0.0;
         } else {
-            const double *T = sT[i];
-            pair_local_f64<OP, Q>(T, S, wave, Mr, Mi);
+            const ConstF64 T = (ConstF64)(g64 + (size_t)tf * kGeo64Stride);
+            local_pair_f64<OP, Q, LTRIAL>(T, S, wave, Mr, Mi);
             const double sc = T[3] * S[3] * kInv4Pi;
 #pragma unroll
             for (int a = 0; a < 3; ++a)
@@ -2001,105 +2101,106 @@ __global__ __launch_bounds__(kBlockLanes) void k_local_f64(const double *__restr
                     Mi[a][b] *= sc;
                 }
         }
-        double *lr = Lr + (size_t)(m0 + i) * 9 * ntrial + n;
-        double *li = is_cplx<OP>() ? Li + (size_t)(m0 + i) * 9 * ntrial + n : nullptr;
+        double *lr = Lr + (size_t)m * 9 * nl + n;
+        double *li = is_cplx<OP>() ? Li + (size_t)m * 9 * nl + n : nullptr;
 #pragma unroll
-        for (int kk = 0; kk < 9; ++kk) {
-            lr[(size_t)kk * ntrial] = Mr[kk / 3][kk % 3];
-            if constexpr (is_cplx<OP>()) li[(size_t)kk * ntrial] = Mi[kk / 3][kk % 3];
+        for (int k = 0; k < 9; ++k) {
+            lr[(size_t)k * nl] = Mr[k / 3][k % 3];
+            if constexpr (is_cplx<OP>()) li[(size_t)k * nl] = Mi[k / 3][k % 3];
         }
     }
 }
 
-// Entry (r, c) of a panel: sum over the row's star (rsrc[rptr[r] ..], packed
-// test index << 2 | local vertex) and the column's star (csrc[cptr[c] ..],
-// trial index << 2 | local vertex) of the local values, in that order.
-template <bool CPLX>
-__global__ __launch_bounds__(kBlockLanes) void k_gather_dense_f32(const float *__restrict__ Lr,
-                                                                  const float *__restrict__ Li, int ntrial,
-                                                                  const int32_t *__restrict__ rptr,
-                                                                  const int32_t *__restrict__ rsrc,
-                                                                  const int32_t *__restrict__ cptr,
-                                                                  const int32_t *__restrict__ csrc, int ncols,
-                                                                  void *__restrict__ out)
+// Entry (fixed dof r, lane dof c): the sum over r's star (fsrc[fptr[r] ..],
+// packed fixed-side triangle << 2 | local vertex) and c's star of the local
+// values, in that order, stored at out[fpos[r] sf + lpos[c] sl] (fpos null: r sf).  One thread
+// per lane dof and kGatherRows fixed dofs; the lane dof's first eight sources
+// stay in registers over them.
+template <typename T, bool CPLX>
+__global__ __launch_bounds__(kBlockLanes) void k_gather_pairs(const T *__restrict__ Lr, const T *__restrict__ Li, int nl,
+                                                              const int32_t *__restrict__ fptr,
+                                                              const int32_t *__restrict__ fsrc,
+                                                              const int32_t *__restrict__ fpos, int nfd,
+                                                              const int32_t *__restrict__ lptr,
+                                                              const int32_t *__restrict__ lsrc,
+                                                              const int32_t *__restrict__ lpos, int nld,
+                                                              void *__restrict__ out, int64_t sf, int64_t sl)
 {
-    const int c = blockIdx.x * kBlockLanes + threadIdx.x;
-    const int r = blockIdx.y;
-    if (c >= ncols) return;
-    float hr = 0.f, lr = 0.f, hi = 0.f, li = 0.f;
-    const int c0 = cptr[c], c1 = cptr[c + 1];
-    for (int i = rptr[r]; i < rptr[r + 1]; ++i) {
-        const int ms = rsrc[i];
-        const size_t base = ((size_t)(ms >> 2) * 9 + 3 * (ms & 3)) * ntrial;
-        for (int j = c0; j < c1; ++j) {
-            const int ns = csrc[j];
-            const size_t o = base + (size_t)(ns & 3) * ntrial + (ns >> 2);
-            two_sum_acc(hr, lr, Lr[o]);
-            if constexpr (CPLX) two_sum_acc(hi, li, Li[o]);
-        }
+    constexpr bool COMP = sizeof(T) == 4;   // FP32: compensated
+    constexpr int kN = 8;
+    const int c = blockIdx.x * kBlockLanes + (int)threadIdx.x;
+    if (c >= nld) return;
+    const int c0 = lptr[c], nc = lptr[c + 1] - c0;
+    const int64_t at = (int64_t)lpos[c] * sl;
+    int off[kN];
+#pragma unroll
+    for (int j = 0; j < kN; ++j) {
+        const int ns = j < nc ? lsrc[c0 + j] : 0;
+        off[j] = (ns & 3) * nl + (ns >> 2);
     }
-    const size_t e = (size_t)r * ncols + c;
-    if constexpr (CPLX)
-        reinterpret_cast<float2 *>(out)[e] = make_float2(hr + lr, hi + li);
-    else
-        reinterpret_cast<float *>(out)[e] = hr + lr;
+    const int r1 = min(nfd, ((int)blockIdx.y + 1) * kGatherRows);
+    for (int r = blockIdx.y * kGatherRows; r < r1; ++r) {
+        T hr = 0, lr = 0, hi = 0, li = 0;
+        auto add = [&](T &h, T &l, T x) {
+            if constexpr (COMP) two_sum_acc(h, l, x);
+            else h += x;
+        };
+        for (int i = fptr[r]; i < fptr[r + 1]; ++i) {
+            const int ms = fsrc[i];
+            const size_t base = ((size_t)(ms >> 2) * 9 + 3 * (ms & 3)) * nl;
+            const T *pr = Lr + base, *pi = CPLX ? Li + base : nullptr;
+            T xr[kN], xi[kN];
+#pragma unroll
+            for (int j = 0; j < kN; ++j) {   // all loads first: places past the star's end read its first value
+                xr[j] = pr[off[j]];
+                if constexpr (CPLX) xi[j] = pi[off[j]];
+            }
+#pragma unroll
+            for (int j = 0; j < kN; ++j)
+                if (j < nc) {
+                    add(hr, lr, xr[j]);
+                    if constexpr (CPLX) add(hi, li, xi[j]);
+                }
+            for (int j = kN; j < nc; ++j) {
+                const int ns = lsrc[c0 + j];
+                const int o = (ns & 3) * nl + (ns >> 2);
+                add(hr, lr, pr[o]);
+                if constexpr (CPLX) add(hi, li, pi[o]);
+            }
+        }
+        const int64_t e = (int64_t)(fpos ? fpos[r] : r) * sf + at;
+        T *o = static_cast<T *>(out) + (CPLX ? 2 : 1) * e;
+        o[0] = hr + lr;
+        if constexpr (CPLX) o[1] = hi + li;
+    }
 }
 
-template <bool CPLX>
-__global__ __launch_bounds__(kBlockLanes) void k_gather_dense_f64(const double *__restrict__ Lr,
-                                                                  const double *__restrict__ Li, int ntrial,
-                                                                  const int32_t *__restrict__ rptr,
-                                                                  const int32_t *__restrict__ rsrc,
-                                                                  const int32_t *__restrict__ cptr,
-                                                                  const int32_t *__restrict__ csrc, int ncols,
-                                                                  void *__restrict__ out)
+template <int OP, bool LTRIAL>
+hipError_t local_launch(bool fp32, const bem_mesh &m, const int32_t *ftri, int nf, const int32_t *ltri, int nl, void *Lr,
+                        void *Li, double k, hipStream_t s)
 {
-    const int c = blockIdx.x * kBlockLanes + threadIdx.x;
-    const int r = blockIdx.y;
-    if (c >= ncols) return;
-    double sr = 0.0, si = 0.0;
-    const int c0 = cptr[c], c1 = cptr[c + 1];
-    for (int i = rptr[r]; i < rptr[r + 1]; ++i) {
-        const int ms = rsrc[i];
-        const size_t base = ((size_t)(ms >> 2) * 9 + 3 * (ms & 3)) * ntrial;
-        for (int j = c0; j < c1; ++j) {
-            const int ns = csrc[j];
-            const size_t o = base + (size_t)(ns & 3) * ntrial + (ns >> 2);
-            sr += Lr[o];
-            if constexpr (CPLX) si += Li[o];
-        }
-    }
-    const size_t e = (size_t)r * ncols + c;
-    if constexpr (CPLX)
-        reinterpret_cast<double2 *>(out)[e] = make_double2(sr, si);
-    else
-        reinterpret_cast<double *>(out)[e] = sr;
-}
-
-template <int OP>
-hipError_t local_launch(bool fp32, int q, const bem_mesh &m, const int32_t *test, int ntest, const int32_t *trial,
-                        int ntrial, void *Lr, void *Li, double k, hipStream_t s)
-{
-    const dim3 grid((unsigned)((ntrial + kBlockLanes - 1) / kBlockLanes),
-                    (unsigned)((ntest + kLocalTile - 1) / kLocalTile));
+    // a full tile amortises the lane's set-up, a smaller one fills the card:
+    // four workgroups per compute unit at least where the block has them
+    const int64_t lanes = (nl + kBlockLanes - 1) / kBlockLanes;
+    int tile = kLocalTile;
+    while (tile > 1 && lanes * ((nf + tile - 1) / tile) < 1024) tile /= 2;
+    const dim3 grid((unsigned)lanes, (unsigned)((nf + tile - 1) / tile)), block(kBlockLanes);
+    if (grid.y > 65535) return hipErrorInvalidValue;
     const float kf = (float)k;
     const double kk = k / (2.0 * 3.14159265358979323846);
     const Wave64 wave{k, 2.0 * kk, wave_low(k, kk)};
-    if (fp32) {
-        if (q == 6)
-            hipLaunchKernelGGL((k_local_f32<OP, 6>), grid, dim3(kBlockLanes), 0, s, m.d_g32, m.d_vtx, test, ntest,
-                               trial, ntrial, (float *)Lr, (float *)Li, kf, kk);
-        else
-            hipLaunchKernelGGL((k_local_f32<OP, 4>), grid, dim3(kBlockLanes), 0, s, m.d_g32, m.d_vtx, test, ntest,
-                               trial, ntrial, (float *)Lr, (float *)Li, kf, kk);
-    } else {
-        if (q == 6)
-            hipLaunchKernelGGL((k_local_f64<OP, 6>), grid, dim3(kBlockLanes), 0, s, m.d_g64, m.d_vtx, test, ntest,
-                               trial, ntrial, (double *)Lr, (double *)Li, wave);
-        else
-            hipLaunchKernelGGL((k_local_f64<OP, 4>), grid, dim3(kBlockLanes), 0, s, m.d_g64, m.d_vtx, test, ntest,
-                               trial, ntrial, (double *)Lr, (double *)Li, wave);
-    }
+#define BEM_LOCAL(QP)                                                                                               \
+    do {                                                                                                            \
+        if (fp32)                                                                                                   \
+            hipLaunchKernelGGL((k_local_f32<OP, QP, LTRIAL>), grid, block, 0, s, m.d_g32, m.d_vtx, ftri, nf, ltri, \
+                               nl, tile, (float *)Lr, (float *)Li, kf, kk);                                         \
+        else                                                                                                        \
+            hipLaunchKernelGGL((k_local_f64<OP, QP, LTRIAL>), grid, block, 0, s, m.d_g64, m.d_vtx, ftri, nf, ltri, \
+                               nl, tile, (double *)Lr, (double *)Li, wave);                                         \
+    } while (0)
+    if (m.q == 6) BEM_LOCAL(6);
+    else BEM_LOCAL(4);
+#undef BEM_LOCAL
     return hipGetLastError();
 }
 
@@ -2148,42 +2249,46 @@ int persistent_occupancy(const Variant &v)
 
 namespace bem {
 
-hipError_t launch_dense_local(int op, bool fp32, const bem_mesh &m, const int32_t *test, int ntest,
-                              const int32_t *trial, int ntrial, void *Lr, void *Li, double k, hipStream_t s)
+hipError_t launch_pair_local(int op, bool fp32, bool ltrial, const bem_mesh &m, const int32_t *ftri, int nf,
+                             const int32_t *ltri, int nl, void *Lr, void *Li, double k, hipStream_t s)
 {
-    if (ntest <= 0 || ntrial <= 0) return hipSuccess;
-    if ((ntest + kLocalTile - 1) / kLocalTile > 65535) return hipErrorInvalidValue;
+    if (nf <= 0 || nl <= 0) return hipSuccess;
     switch (op) {
-    case LSLP: return local_launch<LSLP>(fp32, m.q, m, test, ntest, trial, ntrial, Lr, Li, k, s);
-    case LDLP: return local_launch<LDLP>(fp32, m.q, m, test, ntest, trial, ntrial, Lr, Li, k, s);
-    case HSLP: return local_launch<HSLP>(fp32, m.q, m, test, ntest, trial, ntrial, Lr, Li, k, s);
-    case HDLP: return local_launch<HDLP>(fp32, m.q, m, test, ntest, trial, ntrial, Lr, Li, k, s);
+    // symmetric kernels: the sides' roles do not matter
+    case LSLP: return local_launch<LSLP, true>(fp32, m, ftri, nf, ltri, nl, Lr, Li, k, s);
+    case HSLP: return local_launch<HSLP, true>(fp32, m, ftri, nf, ltri, nl, Lr, Li, k, s);
+    case LHYP: return local_launch<LHYP, true>(fp32, m, ftri, nf, ltri, nl, Lr, Li, k, s);
+    case HHYP: return local_launch<HHYP, true>(fp32, m, ftri, nf, ltri, nl, Lr, Li, k, s);
+    case LDLP:
+        return ltrial ? local_launch<LDLP, true>(fp32, m, ftri, nf, ltri, nl, Lr, Li, k, s)
+                      : local_launch<LDLP, false>(fp32, m, ftri, nf, ltri, nl, Lr, Li, k, s);
+    case HDLP:
+        return ltrial ? local_launch<HDLP, true>(fp32, m, ftri, nf, ltri, nl, Lr, Li, k, s)
+                      : local_launch<HDLP, false>(fp32, m, ftri, nf, ltri, nl, Lr, Li, k, s);
     default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_dense_gather(bool fp32, bool cplx, const void *Lr, const void *Li, int ntrial, const int32_t *rptr,
-                               const int32_t *rsrc, int nrows, const int32_t *cptr, const int32_t *csrc, int ncols,
-                               void *out, hipStream_t s)
+hipError_t launch_pair_gather(bool fp32, bool cplx, const void *Lr, const void *Li, int nl, const int32_t *fptr,
+                              const int32_t *fsrc, const int32_t *fpos, int nfd, const int32_t *lptr,
+                              const int32_t *lsrc, const int32_t *lpos, int nld, void *out, int64_t sf, int64_t sl,
+                              hipStream_t s)
 {
-    if (nrows <= 0 || ncols <= 0) return hipSuccess;
-    if (nrows > 65535) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((ncols + kBlockLanes - 1) / kBlockLanes), (unsigned)nrows);
+    if (nfd <= 0 || nld <= 0) return hipSuccess;
+    const dim3 grid((unsigned)((nld + kBlockLanes - 1) / kBlockLanes), (unsigned)((nfd + kGatherRows - 1) / kGatherRows)),
+        block(kBlockLanes);
+    if (grid.y > 65535) return hipErrorInvalidValue;
+#define BEM_GATHER(T, C)                                                                                              \
+    hipLaunchKernelGGL((k_gather_pairs<T, C>), grid, block, 0, s, (const T *)Lr, (const T *)Li, nl, fptr, fsrc, fpos, \
+                       nfd, lptr, lsrc, lpos, nld, out, sf, sl)
     if (fp32) {
-        if (cplx)
-            hipLaunchKernelGGL(k_gather_dense_f32<true>, grid, dim3(kBlockLanes), 0, s, (const float *)Lr,
-                               (const float *)Li, ntrial, rptr, rsrc, cptr, csrc, ncols, out);
-        else
-            hipLaunchKernelGGL(k_gather_dense_f32<false>, grid, dim3(kBlockLanes), 0, s, (const float *)Lr,
-                               (const float *)Li, ntrial, rptr, rsrc, cptr, csrc, ncols, out);
+        if (cplx) BEM_GATHER(float, true);
+        else BEM_GATHER(float, false);
     } else {
-        if (cplx)
-            hipLaunchKernelGGL(k_gather_dense_f64<true>, grid, dim3(kBlockLanes), 0, s, (const double *)Lr,
-                               (const double *)Li, ntrial, rptr, rsrc, cptr, csrc, ncols, out);
-        else
-            hipLaunchKernelGGL(k_gather_dense_f64<false>, grid, dim3(kBlockLanes), 0, s, (const double *)Lr,
-                               (const double *)Li, ntrial, rptr, rsrc, cptr, csrc, ncols, out);
+        if (cplx) BEM_GATHER(double, true);
+        else BEM_GATHER(double, false);
     }
+#undef BEM_GATHER
     return hipGetLastError();
 }
 

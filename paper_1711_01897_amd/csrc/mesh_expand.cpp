@@ -159,24 +159,27 @@ uint32_t morton3(double x, double y, double z, const double *lo, const double *i
 
 }  // namespace
 
+void morton_order(const bem_mesh &m, int space, const int32_t *dofs, int64_t n, std::vector<int32_t> &order)
+{
+    std::vector<std::pair<uint32_t, int32_t>> key((size_t)n);
+    for (int64_t i = 0; i < n; ++i) {
+        // P1: the vertex; DP1: the first vertex of the dof's triangle
+        const int32_t v = space == BEM_P1 ? dofs[i] : m.tri[3 * (size_t)(dofs[i] / 3)];
+        const double *x = &m.xyz[3 * (size_t)v];
+        key[i] = {morton3(x[0], x[1], x[2], m.box_lo, m.box_inv), (int32_t)i};
+    }
+    std::sort(key.begin(), key.end());
+    order.resize((size_t)n);
+    for (int64_t i = 0; i < n; ++i) order[i] = key[i].second;
+}
+
 void build_lane_set(const bem_mesh &m, int space, const int32_t *dofs, int64_t n, LaneSet &ls, bool reorder)
 {
     ls.pos.clear();
     if (reorder && space != BEM_P0 && n > kBlockLanes) {
-        std::vector<std::pair<uint32_t, int32_t>> key((size_t)n);
-        for (int64_t i = 0; i < n; ++i) {
-            // P1: the vertex; DP1: the first vertex of the dof's triangle
-            const int32_t v = space == BEM_P1 ? dofs[i] : m.tri[3 * (size_t)(dofs[i] / 3)];
-            const double *x = &m.xyz[3 * (size_t)v];
-            key[i] = {morton3(x[0], x[1], x[2], m.box_lo, m.box_inv), (int32_t)i};
-        }
-        std::sort(key.begin(), key.end());
+        morton_order(m, space, dofs, n, ls.pos);
         std::vector<int32_t> sorted((size_t)n);
-        ls.pos.resize((size_t)n);
-        for (int64_t i = 0; i < n; ++i) {
-            sorted[i] = dofs[key[i].second];
-            ls.pos[i] = key[i].second;
-        }
+        for (int64_t i = 0; i < n; ++i) sorted[i] = dofs[ls.pos[i]];
         std::vector<int32_t> keep;
         keep.swap(ls.pos);
         build_lane_set(m, space, sorted.data(), n, ls, false);
@@ -428,6 +431,17 @@ void clear_near(Request &r)
     r.near_slots = 0;
 }
 
+int expand_near(Request &r)
+{
+    clear_near(r);
+    if (r.near != BEM_NEAR_SINGULAR) return BEM_OK;
+    if (r.space == BEM_P0)
+        build_near_p0(r);
+    else
+        build_near_p1(r);
+    return check_near_omega(r);
+}
+
 }  // namespace
 
 int near_kind(const Request &r)
@@ -507,7 +521,7 @@ void stage_near(const Request &r, const NearLayout &L, char *host, char *dev, ch
     at.ints += n.ints;
 }
 
-int expand_request(Request &r)
+int expand_request(Request &r, size_t pair_budget)
 {
     const bem_mesh &m = *r.mesh;
     if (r.op < 0 || r.op > 7) return fail(BEM_E_ARG, "unknown operator");
@@ -537,20 +551,27 @@ int expand_request(Request &r)
     r.rowfix = is_adjoint_op(r.op) ? 1 - r.fixrows : r.fixrows;
     const std::vector<int32_t> &fix_dofs = r.fixrows ? r.rows : r.cols;
     const std::vector<int32_t> &lane_dofs = r.fixrows ? r.cols : r.rows;
+    r.paired = pair_budget > 0 && pairs_pay(r, fix_dofs, lane_dofs);
+    if (r.paired) {
+        plan_pairs(m, r.space, kernel_op(r.op), r.prec, r.rowfix != 0, fix_dofs.data(), (int64_t)fix_dofs.size(),
+                   lane_dofs.data(), (int64_t)lane_dofs.size(), pair_budget, r.pairs);
+        r.pair_error = r.near == BEM_NEAR_ERROR && pairs_touch(m, r.pairs);
+        r.nfix = r.nlane = r.nchunk = r.nblocks = 0;   // no block table
+        r.elem_bytes = out_elem_bytes(r.op, r.prec);
+        r.evals = r.pairs.pairs * m.q * m.q;
+        r.in_bytes = align16(4 * r.pairs.ints.size());
+        r.out_bytes = align16((size_t)r.entries() * r.elem_bytes);
+        const int rc = expand_near(r);
+        r.batch_bytes = request_bytes(r);
+        return rc;
+    }
     expand_fixed(m, r.space, fix_dofs.data(), (int64_t)fix_dofs.size(), r);
     build_lane_set(m, r.space, lane_dofs.data(), (int64_t)lane_dofs.size(), r.own, true);
     r.nlane = (int64_t)r.own.lane.size();
     r.nchunk = r.own.nchunk();
     r.ndistinct = r.own.ndistinct;
-    clear_near(r);
-    if (r.near == BEM_NEAR_SINGULAR) {
-        if (r.space == BEM_P0)
-            build_near_p0(r);
-        else
-            build_near_p1(r);
-        const int rc = check_near_omega(r);
-        if (rc != BEM_OK) return rc;
-    }
+    const int rc = expand_near(r);
+    if (rc != BEM_OK) return rc;
     finalize_sizes(r);
     return BEM_OK;
 }
@@ -584,7 +605,8 @@ size_t request_bytes(const Request &r)
 {
     // descriptor, inputs, status, outputs, block table, launch-timing records
     return sizeof(ReqDev) + r.in_bytes + 8 + r.out_bytes + (size_t)r.nblocks * (sizeof(EntryBlock) + 16) +
-           (r.near_pairs.empty() ? 0 : near_layout(near_kind(r), near_count(r)).bytes) + 512;
+           (r.near_pairs.empty() ? 0 : near_layout(near_kind(r), near_count(r)).bytes) +
+           (r.paired ? r.pairs.work + r.out_bytes + 512 : 0) + 512;
 }
 
 void describe_request(const Request &r, ReqDev &d)

@@ -275,6 +275,14 @@ public:
     std::vector<float> latencies;
     std::map<Variant, KStat> kstats;
 
+    // Slot size the server has, or is going to start with.
+    size_t planned_slot_bytes()
+    {
+        std::lock_guard<std::mutex> g(mu);
+        const int def_slots = (int)std::min<size_t>(kMaxSlots, std::max<size_t>(2, arena_bytes >> 20));
+        return (arena_bytes / env_int("BEM_SERVER_SLOTS", def_slots, 2, kMaxSlots)) & ~(size_t)255;
+    }
+
     int start()
     {
         if (started) return BEM_OK;
@@ -1091,12 +1099,27 @@ public:
             }
         const size_t off_in = off;
         for (int i = 0; i < n; ++i) off += take[i]->in_bytes;
-        const bool direct_batch = direct && off == off_in && !has_near;
+        const bool direct_batch = direct && off == off_in && !has_near;   // paired requests have inputs
         // descriptors and block tables: the device arena (after the staging
         // copy) or, for a direct batch, the staging itself
         char *src = direct_batch ? hd : db;
         const size_t h2d_end = align256(off);
         size_t dev_end = h2d_end;   // device arena only
+        // requests by triangle pairs: local matrices and entries stay on the
+        // device (the gather scatters its stores), the entries follow in one copy
+        std::vector<size_t> work_off, dout_off;
+        bool has_pairs = false;
+        for (int i = 0; i < n; ++i) has_pairs = has_pairs || take[i]->paired;
+        if (has_pairs) {
+            work_off.assign(n, 0);
+            dout_off.assign(n, 0);
+            for (int i = 0; i < n; ++i)
+                if (take[i]->paired) {
+                    work_off[i] = dev_end;
+                    dout_off[i] = align256(dev_end + take[i]->pairs.work);
+                    dev_end = align256(dout_off[i] + take[i]->out_bytes);
+                }
+        }
         for (NearRun &g : near_runs)
             if (g.n.pairs) {
                 const size_t shift = dev_end - g.off - g.L.staged;
@@ -1144,14 +1167,25 @@ public:
         if (time_phases) tp[3] = now_seconds();
         ReqDev *hreq = reinterpret_cast<ReqDev *>(hb);
         size_t in = off_in;
+        std::vector<size_t> ints_off(has_pairs ? n : 0);
         for (int i = 0; i < n; ++i) {
             hreq[i] = take[i]->pre_dev;
-            in += stage_own_inputs(*take[i], hb, db, in, hreq[i]);
+            if (take[i]->paired) {
+                ints_off[i] = in;
+                std::memcpy(hb + in, take[i]->pairs.ints.data(), sizeof(int32_t) * take[i]->pairs.ints.size());
+                in += take[i]->in_bytes;
+            } else {
+                in += stage_own_inputs(*take[i], hb, db, in, hreq[i]);
+            }
         }
         std::memset(hb + off_status, 0, sizeof(int32_t) * n);
+        for (int i = 0; i < n && has_pairs; ++i)
+            if (take[i]->paired && take[i]->pair_error) reinterpret_cast<int32_t *>(hb + off_status)[i] = 1;
         for (const NearRun &g : near_runs) {
             NearCount at;
-            for (int i : g.members) stage_near(*take[i], g.L, hb + g.off, db + g.off, hd + out_off[i], at);
+            for (int i : g.members)
+                stage_near(*take[i], g.L, hb + g.off, db + g.off,
+                           take[i]->paired ? db + dout_off[i] : hd + out_off[i], at);
         }
         b->off_clock = off_clock;
         for (int i = 0; i < n; ++i) {
@@ -1186,9 +1220,22 @@ public:
                                 e0, e1));
             blk0 += L.count;
         }
+        for (int i = 0; i < n && has_pairs; ++i) {
+            const Request &r = *take[i];
+            if (!r.paired || r.pair_error) continue;
+            const int64_t sf = r.fixrows ? r.ncols : 1, sl = r.fixrows ? 1 : r.ncols;
+            for (const PairPanel &f : r.pairs.fix)
+                for (const PairPanel &l : r.pairs.lane)
+                    note(launch_pairs(*r.mesh, r.pairs, f, l, reinterpret_cast<const int32_t *>(db + ints_off[i]),
+                                      db + work_off[i], db + dout_off[i], sf, sl, r.k, stream));
+        }
         // singular pairs after the entry kernels, on the same stream
         for (int kind = 0; kind < kNearKinds && has_near; ++kind)
             if (const NearRun &g = near_runs[kind]; g.n.pairs) note(launch_near(kind, g.L, g.n, db + g.off, stream));
+        for (int i = 0; i < n && has_pairs; ++i)
+            if (take[i]->paired)
+                note(hipMemcpyAsync(hb + out_off[i], db + dout_off[i], (size_t)take[i]->entries() * take[i]->elem_bytes,
+                                    hipMemcpyDeviceToHost, stream));
         b->ev_done = get_event();
         note(hipEventRecord(b->ev_done, stream));
         b->t_hip = now_seconds() - b->t_hip;
@@ -1544,6 +1591,10 @@ void persist_register_exit(Server *s)
 }
 
 }  // namespace
+
+// A quarter of a slot: a request's local matrices share it with its entries
+// (kept on the device too) and its lists.
+size_t server_pair_budget() { return std::min<size_t>(size_t(64) << 20, server().planned_slot_bytes() / 4); }
 
 int server_configure(size_t arena_bytes, int max_batch)
 {

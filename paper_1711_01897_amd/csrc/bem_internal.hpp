@@ -59,6 +59,8 @@ struct ReqDev {
     const int32_t *seg_ptr;    // P1: per lane-side dof, range into seg
     const int32_t *seg;        // P1: packed (lane slot within the chunk << 2 | local vertex)
     const int32_t *lpos;       // P1: output position of each lane-side dof (null: its own index)
+    const int32_t *sptr;       // row form: the mesh's star ranges per vertex; null: `lane` holds star entries
+    int32_t group, split;      // row form: log2 of the threads per lane dof, and of the shares of a fixed star
     void *out;                 // final output, row-major nrows x ncols
     int32_t *status;           // set to 1: a vertex-sharing pair was met under BEM_NEAR_ERROR
     int64_t sf, sl;
@@ -95,6 +97,7 @@ struct EntryBlock {  // one workgroup of entry work (64 bytes, read with one sca
 // both fixed sides).
 struct Variant {
     int op, space, prec, q;
+    int row = 0;       // the row form of a P1 kernel (counted with the star form in the statistics)
     int persist = 0;   // statistics only: the resident (persistent) form of the kernel
     bool operator<(const Variant &o) const {
         if (op != o.op) return op < o.op;
@@ -336,6 +339,7 @@ struct bem_mesh {
     double *d_g64 = nullptr;
     int4 *d_vtx = nullptr;
     double *d_xyz = nullptr;     // vertices (the singular pairs read them)
+    int32_t *d_sptr = nullptr;   // star ranges per vertex
     int32_t *d_star = nullptr;   // star table on the device (packed triangle << 2 | local vertex)
     float *d_sgeo = nullptr;     // FP32 record per star entry
     int4 *d_smeta = nullptr;     // vertex ids per star entry, w = local vertex
@@ -432,6 +436,8 @@ struct Request {
                                           // the column dofs follow when staged
     int32_t near_slots = 0;               // row-side triangles
     std::vector<int32_t> near_rows;       // P1: rows with at least one pair
+    bool row = false;                     // P1 of few fixed dofs: the row form (build_row_set)
+    int32_t row_split = 0;                // its log2 shares of a fixed star
     // by triangle pairs (dense.cpp): no lane set and no block table then
     bool paired = false;
     bool pair_error = false;              // under BEM_NEAR_ERROR: two of its triangles share a vertex
@@ -477,6 +483,8 @@ size_t out_elem_bytes(int op, int prec);
 // pair_budget: workspace bytes the request may use if it is taken by triangle
 // pairs (0: it may not be).
 int expand_request(Request &r, size_t pair_budget = 0);
+// Row form: whether a triangle of a fixed star and one of a lane star share a vertex.
+bool row_touches(const Request &r);
 // Fast path for requests whose lane side is a resident LaneRef and whose
 // fixed side is a single dof known to be valid (H-matrix blocks).
 void expand_single_fixed(Request &r, int32_t dof, int rowfix, const LaneRef *ext);
@@ -493,8 +501,13 @@ void describe_request(const Request &r, ReqDev &d);
 // at their device copies (no-op for a device-resident lane side); returns
 // the bytes used (r.in_bytes).
 size_t stage_own_inputs(const Request &r, char *host_base, char *dev_base, size_t off, ReqDev &d);
-// Launch group of a request: (kernel operator, kernel space, precision, rule).
+// Launch group of a request: (row form, kernel operator, kernel space, precision, rule).
 int request_key(const Request &r);
+constexpr int kKeys = 128;
+inline Variant key_variant(int key)
+{
+    return Variant{(key >> 3) & 7, (key >> 2) & 1, (key >> 1) & 1, (key & 1) ? 6 : 4, key >> 6};
+}
 // Fills r.key, r.pre_blocks and r.pre_dev (called by the submitting thread).
 void prebuild_staging(Request &r);
 // off_status addresses the request's int32 status word (zeroed by the caller).

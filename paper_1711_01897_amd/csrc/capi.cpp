@@ -342,6 +342,8 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
         // host-side check: nothing may be enqueued for a failing request
         if (r.paired) {
             if (r.pair_error) return fail(BEM_E_NEARFIELD, "a contributing triangle pair shares a vertex");
+        } else if (r.row) {
+            if (row_touches(r)) return fail(BEM_E_NEARFIELD, "a contributing triangle pair shares a vertex");
         } else if (r.space == BEM_P0) {
             for (int32_t a : r.rows)
                 for (int32_t b : r.cols)
@@ -454,7 +456,7 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
     }
     if (e != hipSuccess) return fail(BEM_E_DEVICE, std::string("staging copy: ") + hipGetErrorString(e));
     const ReqDev *dreq = (const ReqDev *)(img + off_req);
-    Variant v{kernel_op(r.op), r.space, r.prec, mesh->q};
+    const Variant v{kernel_op(r.op), r.space, r.prec, mesh->q, r.row ? 1 : 0};
     if (r.paired) {
         const int64_t sf = r.fixrows ? r.ncols : 1, sl = r.fixrows ? 1 : r.ncols;
         for (const PairPanel &f : r.pairs.fix)

@@ -1411,6 +1411,365 @@ __global__ __launch_bounds__(kBlockLanes) void k_p1_f64(const ReqDev *__restrict
 }
 
 // ---------------------------------------------------------------------------
+// P1 rows and columns: few fixed dofs against any list of lane dofs.
+//
+// The star form above needs the lane side expanded on the host (distinct
+// triangles in chunks, and for every dof the list of its partial sums), which
+// for one row takes longer than the device does: 0.26 ms for 4,096 dofs.  Here
+// the lane side is the dof list itself.  A group of eight threads takes one lane
+// dof, one thread each triangle of its star (the mesh's star records, which lie
+// together), against the fixed star, with the one basis function that belongs to
+// the dof; a butterfly adds the group's sums, compensated in FP32.  That repeats
+// a triangle for each of its requested vertices (eight threads for a dof where
+// the star form has 2.4), which requests of few fixed dofs can afford; row_pays
+// has the line.  Small requests are bound by the serial chain over the fixed
+// star, so its triangles are shared between the waves of a workgroup
+// (ReqDev::split) and one share is added to the other through LDS; a wave's share
+// is uniform, so that the FP64 form reads its fixed triangles with scalar loads.
+// Discontinuous P1 dofs have one triangle: groups of one.  One row of 4,096
+// vertices, a call back to back: 259 -> 23 us (FP32 Laplace), 261 -> 24 (FP64
+// Helmholtz); of 256: 20 -> 15 and 35 -> 20.
+constexpr float wlam32(double w, double l) { return (float)(w * l); }
+
+// One fixed triangle F (vertex a) against the lane triangle L (offsets scaled
+// by -2, Bq as in local_pair_f32) with the lane's basis weights wq[q] = w_q lam_b(q)
+// and, for the hypersingular operator, its edge opposite b in el.
+template <int OP, int Q, bool LTRIAL>
+__device__ __forceinline__ void row_pair_f32(const float *F, int a, const float *L, const float *Bq, const float *wq,
+                                             const float *el, float kf, double kk, float &vr, float &vi)
+{
+    constexpr int G = is_hyp<OP>() ? (is_cplx<OP>() ? HSLP : LSLP) : OP;
+    const float dcx = (F[0] - L[0]) + (F[4] - L[4]);
+    const float dcy = (F[1] - L[1]) + (F[5] - L[5]);
+    const float dcz = (F[2] - L[2]) + (F[6] - L[6]);
+    Phase ph{};
+    if constexpr (is_cplx<OP>()) ph = phase_base(F, L, kk, dcx, dcy, dcz);
+    float mx[Q], my[Q], mz[Q], A[Q], wa[Q];
+#pragma unroll
+    for (int p = 0; p < Q; ++p) {
+        const float ox = F[12 + 3 * p], oy = F[13 + 3 * p], oz = F[14 + 3 * p];
+        mx[p] = dcx + ox;
+        my[p] = dcy + oy;
+        mz[p] = dcz + oz;
+        if constexpr (is_cplx<OP>())
+            A[p] = fmaf(2.0f * dcx + ox, ox, fmaf(2.0f * dcy + oy, oy, (2.0f * dcz + oz) * oz));
+        else
+            A[p] = fmaf(mx[p], mx[p], fmaf(my[p], my[p], mz[p] * mz[p]));
+        const double w = rule::Rule<Q>::w[p];
+        wa[p] = a == 0 ? wlam32(w, rule::lam<Q>(0, p)) : (a == 1 ? wlam32(w, rule::lam<Q>(1, p)) : wlam32(w, rule::lam<Q>(2, p)));
+        if constexpr (is_dlp<OP>() && LTRIAL) wa[p] *= fmaf(mx[p], L[8], fmaf(my[p], L[9], mz[p] * L[10]));
+    }
+    float dn = 0.f;   // the lane as test side: (x_q - y).n_y = o_q.n_F - D.n_F
+    if constexpr (is_dlp<OP>() && !LTRIAL) dn = fmaf(dcx, F[8], fmaf(dcy, F[9], dcz * F[10]));
+    float t0r = 0.f, t0i = 0.f;   // hypersingular: sum w_p w_q g
+    vr = vi = 0.f;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const float ox = L[12 + 3 * q], oy = L[13 + 3 * q], oz = L[14 + 3 * q];
+        const float B = Bq[q];
+        float tr = 0.f, ti = 0.f, ur = 0.f, ui = 0.f;
+#pragma unroll
+        for (int p = 0; p < Q; ++p) {
+            const float v = fmaf(mx[p], ox, fmaf(my[p], oy, fmaf(mz[p], oz, A[p] + B)));
+            if constexpr (is_hyp<OP>()) {
+                float gr = 0.f, gi = 0.f;
+                if constexpr (is_cplx<OP>())
+                    kern_f32<G>(v + ph.dsq, v, 1.0f, kf, ph, gr, gi);
+                else
+                    kern_f32<G>(v, 0.f, 1.0f, kf, ph, gr, gi);
+                const float w = (float)rule::Rule<Q>::w[p];
+                ur = fmaf(w, gr, ur);
+                if constexpr (is_cplx<OP>()) {
+                    ui = fmaf(w, gi, ui);
+                    tr = fmaf(wa[p], gr, tr);
+                    ti = fmaf(wa[p], gi, ti);
+                }
+            } else if constexpr (is_cplx<OP>()) {
+                kern_f32<G>(v + ph.dsq, v, wa[p], kf, ph, tr, ti);
+            } else {
+                kern_f32<G>(v, 0.f, wa[p], kf, ph, tr, ti);
+            }
+        }
+        if constexpr (is_dlp<OP>() && !LTRIAL) {
+            const float bn = fmaf(-0.5f, fmaf(ox, F[8], fmaf(oy, F[9], oz * F[10])), -dn);
+            tr *= bn;
+            ti *= bn;
+        }
+        if constexpr (is_hyp<OP>()) {
+            t0r = fmaf((float)rule::Rule<Q>::w[q], ur, t0r);
+            if constexpr (is_cplx<OP>()) t0i = fmaf((float)rule::Rule<Q>::w[q], ui, t0i);
+        }
+        vr = fmaf(wq[q], tr, vr);
+        if constexpr (is_cplx<OP>()) vi = fmaf(wq[q], ti, vi);
+    }
+    if constexpr (is_hyp<OP>()) {
+        const float vs = (float)vscale<Q>();
+        float ef[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const float x0 = F[12 + 3 * vpt<Q>(0) + c], x1 = F[12 + 3 * vpt<Q>(1) + c], x2 = F[12 + 3 * vpt<Q>(2) + c];
+            ef[c] = (a == 0 ? x1 - x2 : (a == 1 ? x2 - x0 : x0 - x1)) * vs;
+        }
+        const float cc = fmaf(ef[0], el[0], fmaf(ef[1], el[1], ef[2] * el[2])) * (1.0f / (F[3] * L[3]));
+        if constexpr (is_cplx<OP>()) {
+            const float nn = fmaf(F[8], L[8], fmaf(F[9], L[9], F[10] * L[10])) * kf * kf;
+            vr = fmaf(-nn, vr, cc * t0r);
+            vi = fmaf(-nn, vi, cc * t0i);
+        } else {
+            vr = cc * t0r;
+        }
+    }
+}
+
+// Where a thread of a row workgroup stands.
+struct RowThread {
+    int g, k, step;    // lane dof of the chunk, thread of its group, threads per group
+    int part, parts;   // its share of the fixed star (the same in a wave), and of how many
+    bool act;
+    int e0, e1;        // the dof's star entries: a vertex's, or the one a discontinuous dof is
+};
+
+__device__ __forceinline__ RowThread row_thread(const ReqDev &R, const EntryBlock &B)
+{
+    RowThread x;
+    const int t = threadIdx.x;
+    x.step = 1 << R.group;
+    x.parts = 1 << R.split;
+    x.part = __builtin_amdgcn_readfirstlane(t >> (8 - R.split));
+    x.g = (t & ((kBlockLanes >> R.split) - 1)) >> R.group;
+    x.k = t & (x.step - 1);
+    x.act = x.g < B.chunk.y;
+    const int d = ldg(R.lane + B.chunk.x + (x.act ? x.g : 0));
+    x.e0 = d;
+    x.e1 = d + 1;
+    if (R.sptr) {
+        x.e0 = ldg(R.sptr + d);
+        x.e1 = ldg(R.sptr + d + 1);
+    }
+    return x;
+}
+
+template <int OP, int Q, bool ROWFIX>
+__device__ __forceinline__ void row_body_f32(const ReqDev &R, const EntryBlock &B, float (*sG)[n32<Q>()], int4 *sV,
+                                             int *sL, float4 (*sS)[kBlockLanes / 16])
+{
+    const int t = threadIdx.x;
+    const RowThread W = row_thread(R, B);
+    const float kf = (float)R.k;
+    const double kk = R.kk;
+    float hr = 0.f, lr = 0.f, hi = 0.f, li = 0.f;
+    for (int sb = B.s0; sb < B.s1; sb += kStage) {
+        const int ns = min(kStage, B.s1 - sb);
+        __syncthreads();   // the previous stage has been read
+        if (t < ns) {
+            const StarRec x = load_star(B, sb + t);
+            float v[n32<Q>()];
+            expand32<Q>(x.r0, x.r1, x.r2, x.r3, v);
+#pragma unroll
+            for (int w = 0; w < n32<Q>(); ++w) sG[t][w] = v[w];
+            sV[t] = x.m;
+            sL[t] = x.m.w;
+        }
+        __syncthreads();
+        if (!W.act) continue;
+        for (int e = W.e0 + W.k; e < W.e1; e += W.step) {
+            const StarRec x = load_star(B, e);
+            float L[n32<Q>()], Bq[Q], wq[Q], el[3] = {0.f, 0.f, 0.f};
+            expand32<Q>(x.r0, x.r1, x.r2, x.r3, L);
+            const int b = x.m.w;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                float *o = L + 12 + 3 * q;
+                Bq[q] = fmaf(o[0], o[0], fmaf(o[1], o[1], o[2] * o[2]));
+                const double w = rule::Rule<Q>::w[q];
+                wq[q] = b == 0 ? wlam32(w, rule::lam<Q>(0, q)) : (b == 1 ? wlam32(w, rule::lam<Q>(1, q)) : wlam32(w, rule::lam<Q>(2, q)));
+            }
+            if constexpr (is_hyp<OP>()) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const float x0 = L[12 + 3 * vpt<Q>(0) + c], x1 = L[12 + 3 * vpt<Q>(1) + c], x2 = L[12 + 3 * vpt<Q>(2) + c];
+                    el[c] = (b == 0 ? x1 - x2 : (b == 1 ? x2 - x0 : x0 - x1)) * (float)vscale<Q>();
+                }
+            }
+#pragma unroll
+            for (int i = 12; i < 12 + 3 * Q; ++i) L[i] *= -2.0f;
+            for (int s = W.part; s < ns; s += W.parts) {
+                if (share_vertex(sV[s], x.m)) {
+                    if (R.near_error) put<false>(R.status, 1);
+                    continue;
+                }
+                float F[n32<Q>()], vr, vi;
+#pragma unroll
+                for (int i = 0; i < n32<Q>(); ++i) F[i] = sG[s][i];
+                row_pair_f32<OP, Q, ROWFIX>(F, sL[s], L, Bq, wq, el, kf, kk, vr, vi);
+                const float sc = F[3] * L[3] * kInv4PiF;
+                two_sum_acc(hr, lr, sc * vr);
+                if constexpr (is_cplx<OP>()) two_sum_acc(hi, li, sc * vi);
+            }
+        }
+    }
+    for (int m = W.step >> 1; m > 0; m >>= 1) {   // group sums, in the group's first thread
+        const float xh = __shfl_xor(hr, m), xl = __shfl_xor(lr, m);
+        two_sum_acc(hr, lr, xh);
+        lr += xl;
+        if constexpr (is_cplx<OP>()) {
+            const float yh = __shfl_xor(hi, m), yl = __shfl_xor(li, m);
+            two_sum_acc(hi, li, yh);
+            li += yl;
+        }
+    }
+    if (W.parts > 1) {   // the shares of the fixed star, in the first waves
+        if (W.k == 0 && W.part > 0) sS[W.part - 1][W.g] = make_float4(hr, lr, hi, li);
+        __syncthreads();
+        if (W.part > 0) return;
+        for (int p = 1; p < W.parts; ++p) {
+            const float4 y = sS[p - 1][W.g];
+            two_sum_acc(hr, lr, y.x);
+            lr += y.y;
+            if constexpr (is_cplx<OP>()) {
+                two_sum_acc(hi, li, y.z);
+                li += y.w;
+            }
+        }
+    }
+    if (W.act && W.k == 0) {
+        const int64_t o = (int64_t)B.fixed * R.sf + (int64_t)(B.chunk.x + W.g) * R.sl;
+        if constexpr (is_cplx<OP>())
+            put<false>(reinterpret_cast<float2 *>(R.out) + o, make_float2(hr + lr, hi + li));
+        else
+            put<false>(reinterpret_cast<float *>(R.out) + o, hr + lr);
+    }
+}
+
+template <int OP, int Q>
+__global__ __launch_bounds__(kBlockLanes) void k_row_f32(const ReqDev *__restrict__ reqs,
+                                                         const EntryBlock *__restrict__ blocks, int64_t nblocks,
+                                                         unsigned long long *tclock)
+{
+    __shared__ float sG[kStage][n32<Q>()];
+    __shared__ int4 sV[kStage];
+    __shared__ int sL[kStage];
+    __shared__ float4 sS[3][kBlockLanes / 16];
+    if ((int64_t)blockIdx.x >= nblocks) return;
+    clock_start(tclock);
+    const EntryBlock B = blocks[blockIdx.x];
+    const ReqDev &R = reqs[B.req >> 1];
+    if (B.req & 1)
+        row_body_f32<OP, Q, true>(R, B, sG, sV, sL, sS);
+    else
+        row_body_f32<OP, Q, false>(R, B, sG, sV, sL, sS);
+    clock_end(tclock);
+}
+
+// The same in FP64: the fixed star's records through scalar loads, plain sums.
+template <int OP, int Q, bool ROWFIX>
+__device__ __forceinline__ void row_body_f64(const ReqDev &R, const EntryBlock &B, double2 (*sS)[kBlockLanes / 16])
+{
+    constexpr int G = is_hyp<OP>() ? (is_cplx<OP>() ? HSLP : LSLP) : OP;
+    typedef const __attribute__((address_space(4))) int32_t *ConstI;
+    typedef const __attribute__((address_space(4))) i32x4 *ConstI4;
+    const RowThread W = row_thread(R, B);
+    const Wave64 wave = wave64(R);
+    const ConstI fstar = (ConstI)R.fstar;
+    const ConstI4 vtx = (ConstI4)R.vtx;
+    double ar = 0.0, ai = 0.0;
+    for (int e = W.e0 + W.k; W.act && e < W.e1; e += W.step) {
+        const int pk = R.fstar[e], tn = pk >> 2, b = pk & 3;
+        const int4 vn = R.vtx[tn];
+        double L[n64<Q>()], wq[Q];
+        load64<Q>(R.g64, tn, L);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const double w = rule::Rule<Q>::w[q];
+            wq[q] = b == 0 ? w * rule::lam<Q>(0, q) : (b == 1 ? w * rule::lam<Q>(1, q) : w * rule::lam<Q>(2, q));
+        }
+        for (int s = B.s0 + W.part; s < B.s1; s += W.parts) {
+            const int fk = fstar[s], tf = fk >> 2, a = fk & 3;
+            const i32x4 fv = vtx[tf];
+            if (share_vertex(make_int4(fv.x, fv.y, fv.z, 0), vn)) {
+                if (R.near_error) put<false>(R.status, 1);
+                continue;
+            }
+            const ConstF64 F = (ConstF64)(R.g64 + (size_t)tf * kGeo64Stride);
+            double ur[Q], ui[Q], br[Q], bi[Q], vr = 0.0, vi = 0.0;
+            if constexpr (is_hyp<OP>()) {
+                sweep_f64<G, Q, ROWFIX, is_cplx<OP>()>(F, L, basis_row<Q>(3), basis_row<Q>(a), wave, ur, ui, br, bi);
+                double t0r = 0.0, t0i = 0.0;
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    t0r = fma(rule::Rule<Q>::w[q], ur[q], t0r);
+                    if constexpr (is_cplx<OP>()) {
+                        t0i = fma(rule::Rule<Q>::w[q], ui[q], t0i);
+                        vr = fma(wq[q], br[q], vr);
+                        vi = fma(wq[q], bi[q], vi);
+                    }
+                }
+                const int f1 = 4 + 3 * (Q - 3 + (a + 1) % 3), f2 = 4 + 3 * (Q - 3 + (a + 2) % 3);
+                const double vs = vscale<Q>();
+                double cc = 0.0;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const double x0 = L[4 + 3 * vpt<Q>(0) + c], x1 = L[4 + 3 * vpt<Q>(1) + c], x2 = L[4 + 3 * vpt<Q>(2) + c];
+                    cc = fma((F[f1 + c] - F[f2 + c]) * vs, (b == 0 ? x1 - x2 : (b == 1 ? x2 - x0 : x0 - x1)) * vs, cc);
+                }
+                cc *= 1.0 / (F[3] * L[3]);
+                const double nn = is_cplx<OP>() ? (F[0] * L[0] + F[1] * L[1] + F[2] * L[2]) * wave.k * wave.k : 0.0;
+                vr = cc * t0r - nn * vr;
+                vi = cc * t0i - nn * vi;
+            } else {
+                sweep_f64<G, Q, ROWFIX, false>(F, L, basis_row<Q>(a), nullptr, wave, ur, ui, br, bi);
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    vr = fma(wq[q], ur[q], vr);
+                    if constexpr (is_cplx<OP>()) vi = fma(wq[q], ui[q], vi);
+                }
+            }
+            const double sc = F[3] * L[3] * kInv4Pi;
+            ar = fma(sc, vr, ar);
+            if constexpr (is_cplx<OP>()) ai = fma(sc, vi, ai);
+        }
+    }
+    for (int m = W.step >> 1; m > 0; m >>= 1) {
+        ar += __shfl_xor(ar, m);
+        if constexpr (is_cplx<OP>()) ai += __shfl_xor(ai, m);
+    }
+    if (W.parts > 1) {
+        if (W.k == 0 && W.part > 0) sS[W.part - 1][W.g] = make_double2(ar, ai);
+        __syncthreads();
+        if (W.part > 0) return;
+        for (int p = 1; p < W.parts; ++p) {
+            const double2 y = sS[p - 1][W.g];
+            ar += y.x;
+            if constexpr (is_cplx<OP>()) ai += y.y;
+        }
+    }
+    if (W.act && W.k == 0) {
+        const int64_t o = (int64_t)B.fixed * R.sf + (int64_t)(B.chunk.x + W.g) * R.sl;
+        if constexpr (is_cplx<OP>())
+            put<false>(reinterpret_cast<double2 *>(R.out) + o, make_double2(ar, ai));
+        else
+            put<false>(reinterpret_cast<double *>(R.out) + o, ar);
+    }
+}
+
+template <int OP, int Q>
+__global__ __launch_bounds__(kBlockLanes) void k_row_f64(const ReqDev *__restrict__ reqs,
+                                                         const EntryBlock *__restrict__ blocks, int64_t nblocks,
+                                                         unsigned long long *tclock)
+{
+    __shared__ double2 sS[3][kBlockLanes / 16];
+    if ((int64_t)blockIdx.x >= nblocks) return;
+    clock_start(tclock);
+    const EntryBlock B = blocks[blockIdx.x];
+    const ReqDev &R = reqs[B.req >> 1];
+    if (B.req & 1)
+        row_body_f64<OP, Q, true>(R, B, sS);
+    else
+        row_body_f64<OP, Q, false>(R, B, sS);
+    clock_end(tclock);
+}
+
+// ---------------------------------------------------------------------------
 // Persistent launches (layout and protocol in bem_internal.hpp).
 //
 // Words shared between workgroups are read and written with relaxed atomics
@@ -1757,8 +2116,26 @@ EntryKernel pick_q(int space, int prec, int q)
     return q == 6 ? pick<OP, 6>(space, prec) : pick<OP, 4>(space, prec);
 }
 
+template <int OP>
+EntryKernel pick_row(int prec, int q)
+{
+    if (prec == BEM_FP32) return q == 6 ? k_row_f32<OP, 6> : k_row_f32<OP, 4>;
+    return q == 6 ? k_row_f64<OP, 6> : k_row_f64<OP, 4>;
+}
+
 EntryKernel select_kernel(const Variant &v)
 {
+    if (v.row) {
+        switch (v.op) {
+        case LSLP: return pick_row<LSLP>(v.prec, v.q);
+        case LDLP: return pick_row<LDLP>(v.prec, v.q);
+        case HSLP: return pick_row<HSLP>(v.prec, v.q);
+        case HDLP: return pick_row<HDLP>(v.prec, v.q);
+        case LHYP: return pick_row<LHYP>(v.prec, v.q);
+        case HHYP: return pick_row<HHYP>(v.prec, v.q);
+        default: return nullptr;
+        }
+    }
     switch (v.op) {
     case LSLP: return pick_q<LSLP>(v.space, v.prec, v.q);
     case LDLP: return pick_q<LDLP>(v.space, v.prec, v.q);

@@ -256,6 +256,57 @@ void build_lane_set(const bem_mesh &m, int space, const int32_t *dofs, int64_t n
 
 namespace {
 
+// P1 requests of few fixed dofs take the row form, whose lane side is the dof
+// list itself: the star form's expansion of the lanes takes the host 62 ns for
+// each of 4,096 dofs and 20 for each of 1,024, the row form's threads evaluate
+// 2.4 times its pairs.  The line is where the two meet for 1,024 lane dofs, back
+// to back on one stream (us by stars / by rows, 6-point rule): FP32 real 64 fixed
+// dofs 42 / 41 (1: 39 / 19), complex 16 41 / 32, 32 43 / 48; FP64 real 16 41 / 28,
+// 32 42 / 44; FP64 complex 8 44 / 36, 16 43 / 57.  Of 4,096 lane dofs all these
+// are faster by rows (1: 259-271 / 21-24; the largest 283 / 124, 278 / 83,
+// 275 / 71, 278 / 99), of 32 too (17-26 / 14-20).
+bool row_pays(const Request &r, int64_t nfix)
+{
+    if (r.space == BEM_P0) return false;
+    if (is_complex_op(r.op)) return nfix <= (r.prec == BEM_FP32 ? 16 : 8);
+    return nfix <= (r.prec == BEM_FP32 ? 64 : 16);
+}
+
+// Lane side of the row form: the dofs (P1: vertices; DP1: star entries), in
+// chunks of as many as a workgroup takes (32 vertices of eight threads, 256
+// discontinuous dofs).  Where that gives fewer than 1,024 workgroups, a
+// workgroup takes a half or a quarter of the vertices and its waves share the
+// fixed star between them (FP64 Helmholtz, 32 dofs: 33 us a call with whole
+// stars, 20 with quarters; from 1,024 workgroups on the two are alike).
+void build_row_set(const bem_mesh &m, int space, int64_t nfix, const int32_t *dofs, int64_t n, LaneSet &ls,
+                   int32_t &split)
+{
+    ls.pos.clear();
+    ls.seg_ptr.clear();
+    ls.seg.clear();
+    ls.chunk.clear();
+    ls.ndof = n;
+    ls.lane.assign(dofs, dofs + n);
+    if (space == BEM_DP1)
+        for (int32_t &d : ls.lane) d = m.dp1_star[d];
+    // a triangle counts for each of its requested vertices, as it is evaluated
+    ls.ndistinct = n;
+    if (space == BEM_P1) {
+        ls.ndistinct = 0;
+        for (int64_t d = 0; d < n; ++d) ls.ndistinct += m.star_ptr[dofs[d] + 1] - m.star_ptr[dofs[d]];
+    }
+    int64_t per = space == BEM_DP1 ? kBlockLanes : kBlockLanes / 8;
+    split = 0;
+    while (space == BEM_P1 && split < 2 && nfix * ((n + per - 1) / per) < 1024) {
+        ++split;
+        per /= 2;
+    }
+    for (int64_t c = 0; c < n; c += per) {
+        const int32_t len = (int32_t)std::min<int64_t>(per, n - c);
+        ls.chunk.insert(ls.chunk.end(), {(int32_t)c, len, (int32_t)c, len});
+    }
+}
+
 // Largest distance of two points of triangles T and S (at two of their
 // vertices).  The device writes x - y = rho c over a singular pair with the
 // radius rho in [0, 1] and takes omega = k |c|; c is itself a difference x - y of
@@ -521,6 +572,32 @@ void stage_near(const Request &r, const NearLayout &L, char *host, char *dev, ch
     at.ints += n.ints;
 }
 
+bool row_touches(const Request &r)
+{
+    // the dofs with a triangle that shares a vertex with one of the fixed
+    // stars', few for few fixed dofs, are looked up among the lane dofs
+    const bem_mesh &m = *r.mesh;
+    std::vector<int32_t> v, touch;
+    auto unique = [](std::vector<int32_t> &x) {
+        std::sort(x.begin(), x.end());
+        x.erase(std::unique(x.begin(), x.end()), x.end());
+    };
+    for (size_t f = 0; 2 * f + 1 < r.fix.size(); ++f)
+        for (int32_t s = r.fix[2 * f]; s < r.fix[2 * f + 1]; ++s)
+            for (int a = 0; a < 3; ++a) v.push_back(m.tri[3 * (size_t)(m.star[s] >> 2) + a]);
+    unique(v);
+    for (int32_t u : v)
+        for (int64_t s = m.star_ptr[u]; s < m.star_ptr[u + 1]; ++s)
+            for (int a = 0; a < 3; ++a) {
+                const int64_t t = m.star[s] >> 2;
+                touch.push_back(r.space == BEM_P1 ? m.tri[3 * t + a] : (int32_t)(3 * t + a));
+            }
+    unique(touch);
+    for (int32_t d : r.fixrows ? r.cols : r.rows)
+        if (std::binary_search(touch.begin(), touch.end(), d)) return true;
+    return false;
+}
+
 int expand_request(Request &r, size_t pair_budget)
 {
     const bem_mesh &m = *r.mesh;
@@ -551,7 +628,8 @@ int expand_request(Request &r, size_t pair_budget)
     r.rowfix = is_adjoint_op(r.op) ? 1 - r.fixrows : r.fixrows;
     const std::vector<int32_t> &fix_dofs = r.fixrows ? r.rows : r.cols;
     const std::vector<int32_t> &lane_dofs = r.fixrows ? r.cols : r.rows;
-    r.paired = pair_budget > 0 && pairs_pay(r, fix_dofs, lane_dofs);
+    r.row = row_pays(r, (int64_t)fix_dofs.size());
+    r.paired = !r.row && pair_budget > 0 && pairs_pay(r, fix_dofs, lane_dofs);
     if (r.paired) {
         plan_pairs(m, r.space, kernel_op(r.op), r.prec, r.rowfix != 0, fix_dofs.data(), (int64_t)fix_dofs.size(),
                    lane_dofs.data(), (int64_t)lane_dofs.size(), pair_budget, r.pairs);
@@ -566,7 +644,10 @@ int expand_request(Request &r, size_t pair_budget)
         return rc;
     }
     expand_fixed(m, r.space, fix_dofs.data(), (int64_t)fix_dofs.size(), r);
-    build_lane_set(m, r.space, lane_dofs.data(), (int64_t)lane_dofs.size(), r.own, true);
+    if (r.row)
+        build_row_set(m, r.space, r.nfix, lane_dofs.data(), (int64_t)lane_dofs.size(), r.own, r.row_split);
+    else
+        build_lane_set(m, r.space, lane_dofs.data(), (int64_t)lane_dofs.size(), r.own, true);
     r.nlane = (int64_t)r.own.lane.size();
     r.nchunk = r.own.nchunk();
     r.ndistinct = r.own.ndistinct;
@@ -580,6 +661,7 @@ void expand_single_fixed(Request &r, int32_t dof, int rowfix, const LaneRef *ext
 {
     clear_near(r);
     r.ext = ext;
+    r.row = false;
     r.fixrows = rowfix;
     r.rowfix = is_adjoint_op(r.op) ? 1 - rowfix : rowfix;
     r.own.lane.clear();
@@ -623,6 +705,9 @@ void describe_request(const Request &r, ReqDev &d)
         d.lane = d.seg_ptr = d.seg = nullptr;
     }
     d.lpos = nullptr;
+    d.sptr = r.space == BEM_P1 ? m.d_sptr : nullptr;
+    d.group = r.space == BEM_P1 ? 3 : 0;
+    d.split = r.row_split;
     d.fstar = m.d_star;
     if (r.fixrows) {   // output position of (fixed f, lane-side dof d): out[f * sf + d * sl]
         d.sf = r.ncols;
@@ -713,7 +798,8 @@ int64_t write_blocks(const Request &r, int32_t ri, EntryBlock *out)
 
 int request_key(const Request &r)
 {
-    return ((kernel_op(r.op) * 2 + kernel_space(r.space)) * 2 + r.prec) * 2 + (r.mesh->q == 6 ? 1 : 0);
+    return ((((r.row ? 8 : 0) + kernel_op(r.op)) * 2 + kernel_space(r.space)) * 2 + r.prec) * 2 +
+           (r.mesh->q == 6 ? 1 : 0);
 }
 
 void prebuild_staging(Request &r)
@@ -818,6 +904,11 @@ int mesh_create_impl(const double *xyz, int64_t nv, const int32_t *tri, int64_t 
     // FP32 record and vertex ids with the local vertex in w
     const int64_t ns = 3 * nt;
     if (e == hipSuccess) e = hipMalloc(&m->d_star, sizeof(int32_t) * ns);
+    if (e == hipSuccess) e = hipMalloc(&m->d_sptr, sizeof(int32_t) * (nv + 1));
+    if (e == hipSuccess) {
+        const std::vector<int32_t> sp(m->star_ptr.begin(), m->star_ptr.end());
+        e = hipMemcpy(m->d_sptr, sp.data(), sizeof(int32_t) * (nv + 1), hipMemcpyHostToDevice);
+    }
     if (e == hipSuccess) e = hipMalloc(&m->d_sgeo, sizeof(float) * kGeo32Stride * ns);
     if (e == hipSuccess) e = hipMalloc(&m->d_smeta, sizeof(int4) * ns);
     if (e == hipSuccess) e = hipMemcpy(m->d_star, m->star.data(), sizeof(int32_t) * ns, hipMemcpyHostToDevice);
@@ -831,12 +922,13 @@ int mesh_create_impl(const double *xyz, int64_t nv, const int32_t *tri, int64_t 
         rc = fail(BEM_E_ARG, "degenerate triangle (zero area)");
     if (rc != BEM_OK) {
         for (void *p : {(void *)m->d_g32, (void *)m->d_g64, (void *)m->d_vtx, (void *)m->d_star, (void *)m->d_sgeo,
-                        (void *)m->d_smeta, (void *)m->d_xyz})
+                        (void *)m->d_smeta, (void *)m->d_xyz, (void *)m->d_sptr})
             if (p) (void)hipFree(p);
         delete m;
         return rc;
     }
-    m->dev_bytes = b32 + b64 + bv + sizeof(double) * 3 * (size_t)nv + 3 * (size_t)nt * (4 + 4 * kGeo32Stride + sizeof(int4));
+    m->dev_bytes = b32 + b64 + bv + (sizeof(double) * 3 + sizeof(int32_t)) * (size_t)nv +
+                   3 * (size_t)nt * (4 + 4 * kGeo32Stride + sizeof(int4));
     *out = m;
     return BEM_OK;
 }
@@ -846,7 +938,7 @@ int mesh_destroy_impl(bem_mesh *m)
     if (!m) return fail(BEM_E_ARG, "null mesh");
     if (m->inflight.load() != 0) return fail(BEM_E_BUSY, "requests on this mesh are still in flight");
     for (void *p : {(void *)m->d_g32, (void *)m->d_g64, (void *)m->d_vtx, (void *)m->d_star, (void *)m->d_sgeo,
-                    (void *)m->d_smeta, (void *)m->d_xyz})
+                    (void *)m->d_smeta, (void *)m->d_xyz, (void *)m->d_sptr})
         (void)hipFree(p);
     delete m;
     return BEM_OK;

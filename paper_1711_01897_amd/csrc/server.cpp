@@ -47,7 +47,6 @@ namespace {
 constexpr int kMaxSlots = 16;
 constexpr int kMaxThreads = 4;
 constexpr int kTimedEvery = 8;
-constexpr int kKeys = 64;   // launch groups: (kernel op 0..7, space, prec, rule)
 
 int env_int(const char *name, int dflt, int lo, int hi)
 {
@@ -386,9 +385,9 @@ public:
 
     bool persist_launch_locked(int key, uint64_t seq0)
     {
-        const Variant v{key >> 3, (key >> 2) & 1, (key >> 1) & 1, (key & 1) ? 6 : 4};
+        const Variant v = key_variant(key);
         if (p_occ[key] == 0) {
-            const int occ = persistent_occupancy(v);
+            const int occ = v.row ? 0 : persistent_occupancy(v);   // there is no persistent row form
             p_occ[key] = occ > 0 ? occ : -1;
         }
         if (p_occ[key] < 0) return false;
@@ -883,7 +882,7 @@ public:
         char *hd = h_stage_dev + (size_t)b->slot * slot_bytes;
         Launch L;
         L.key = o->key;
-        L.v = Variant{o->key >> 3, (o->key >> 2) & 1, (o->key >> 1) & 1, (o->key & 1) ? 6 : 4};
+        L.v = key_variant(o->key);
         L.off_tab = f_blk;
         L.count = o->nblk;
         L.entries = o->entries;
@@ -1047,7 +1046,7 @@ public:
             if (sc.members[key].empty()) continue;
             Launch L;
             L.key = key;
-            L.v = Variant{key >> 3, (key >> 2) & 1, (key >> 1) & 1, (key & 1) ? 6 : 4};
+            L.v = key_variant(key);
             for (int i : sc.members[key]) {
                 const Request &r = *take[i];
                 L.entries += r.entries();

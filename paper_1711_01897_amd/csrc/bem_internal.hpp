@@ -436,6 +436,7 @@ struct Request {
                                           // the column dofs follow when staged
     int32_t near_slots = 0;               // row-side triangles
     std::vector<int32_t> near_rows;       // P1: rows with at least one pair
+    bool many = false;                    // one of many in flight that several threads expand
     bool row = false;                     // P1 of few fixed dofs: the row form (build_row_set)
     int32_t row_split = 0;                // its log2 shares of a fixed star
     // by triangle pairs (dense.cpp): no lane set and no block table then

@@ -264,10 +264,12 @@ namespace {
 // dofs 42 / 41 (1: 39 / 19), complex 16 41 / 32, 32 43 / 48; FP64 real 16 41 / 28,
 // 32 42 / 44; FP64 complex 8 44 / 36, 16 43 / 57.  Of 4,096 lane dofs all these
 // are faster by rows (1: 259-271 / 21-24; the largest 283 / 124, 278 / 83,
-// 275 / 71, 278 / 99), of 32 too (17-26 / 14-20).
+// 275 / 71, 278 / 99), of 32 too (17-26 / 14-20).  The leaves of an H-matrix,
+// which several threads expand while the device works on others, keep the star
+// form (level-5 icosphere, leaf size 100: 58.5 ms by stars, 63 by rows).
 bool row_pays(const Request &r, int64_t nfix)
 {
-    if (r.space == BEM_P0) return false;
+    if (r.space == BEM_P0 || r.many) return false;
     if (is_complex_op(r.op)) return nfix <= (r.prec == BEM_FP32 ? 16 : 8);
     return nfix <= (r.prec == BEM_FP32 ? 64 : 16);
 }

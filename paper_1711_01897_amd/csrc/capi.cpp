@@ -33,6 +33,7 @@ int plans_run(bem_aca_plan *const *, int64_t, const int64_t *, const int64_t *, 
               int, bem_aca_run_stats *);
 int plan_factors(const bem_aca_plan *, int64_t, int32_t *, void *, void *);
 int plan_destroy(bem_aca_plan *);
+void release_dense_kits();
 int eval_dense(bem_mesh *, int, int, double, const int32_t *, int64_t, const int32_t *, int64_t, int, int, void *,
                bem_dense_stats *);
 }  // namespace bem
@@ -528,7 +529,10 @@ int bem_mesh_create(const double *xyz, int64_t nv, const int32_t *tri, int64_t n
 int bem_mesh_destroy(bem_mesh *mesh)
 {
     const int rc = mesh_destroy_impl(mesh);
-    if (rc == BEM_OK && g_meshes.fetch_sub(1) == 1) release_slots();
+    if (rc == BEM_OK && g_meshes.fetch_sub(1) == 1) {
+        release_slots();
+        release_dense_kits();
+    }
     return rc;
 }
 

@@ -5,13 +5,16 @@
 // k_gather_pairs).  Device-tensor requests large enough take it
 // (pairs_pay); bem_eval_dense is the host form: rows go in panels whose local
 // matrices fit a device budget; the panels run on a compute stream while a
-// copy stream moves the previous panel's entries to pinned host memory and the
-// calling thread copies the one before into `out`, so assembly and transfer
-// overlap (Section 3's chunked assembly with overlapped transfers).
+// copy stream moves the previous panel's entries to pinned host memory and a few
+// threads copy the one before into `out`, so assembly and transfer overlap
+// (Section 3's chunked assembly with overlapped transfers).
 #include <algorithm>
 #include <cstdlib>
+#include <memory>
+#include <mutex>
 
 #include "bem_internal.hpp"
+#include "host_copy.hpp"
 
 namespace bem {
 
@@ -206,15 +209,113 @@ hipError_t launch_pairs(const bem_mesh &m, const PairPlan &P, const PairPanel &f
 
 namespace {
 
-struct DevBuf {
-    void *p = nullptr;
-    ~DevBuf()
+// Output panels in flight: one being computed, one on its way to the host, one
+// being copied into the result.
+constexpr int kPanels = 3;
+
+// What a dense assembly works in: its streams, events, device memory (indices,
+// local matrices, output panels) and pinned memory.  Kept between calls, since
+// taking it anew is most of a small block's time (834 x 736 in FP64, 1.1 ms of
+// which the kernels are 0.2; where the driver puts off returning the memory,
+// 5 ms; 0.5 with a kept kit): at most kKits, kKitBytes of device and kKitPinned of pinned memory
+// together; the last mesh's end gives them back.
+struct DenseKit {
+    int device = 0;
+    char *dev = nullptr, *pin = nullptr;
+    size_t dev_bytes = 0, pin_bytes = 0;
+    hipStream_t sc = nullptr, sx = nullptr;
+    hipEvent_t computed[kPanels] = {}, copied[kPanels] = {}, timed[3] = {};
+    ~DenseKit()
     {
-        if (p) (void)hipFree(p);
+        for (hipEvent_t e : computed)
+            if (e) (void)hipEventDestroy(e);
+        for (hipEvent_t e : copied)
+            if (e) (void)hipEventDestroy(e);
+        for (hipEvent_t e : timed)
+            if (e) (void)hipEventDestroy(e);
+        if (sc) (void)hipStreamDestroy(sc);
+        if (sx) (void)hipStreamDestroy(sx);
+        if (dev) (void)hipFree(dev);
+        if (pin) (void)hipHostFree(pin);
     }
 };
+constexpr size_t kKits = 4, kKitBytes = size_t(1536) << 20, kKitPinned = size_t(256) << 20;
+std::mutex g_kit_mu;
+// idle ones (never destroyed: at the process's end the runtime may be gone)
+std::vector<std::unique_ptr<DenseKit>> &g_kits = *new std::vector<std::unique_ptr<DenseKit>>();
+
+hipError_t take_kit(size_t dev_bytes, size_t pin_bytes, std::unique_ptr<DenseKit> &kit)
+{
+    int device = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e != hipSuccess) return e;
+    {
+        std::lock_guard<std::mutex> g(g_kit_mu);
+        size_t best = g_kits.size();   // the largest one
+        for (size_t i = 0; i < g_kits.size(); ++i)
+            if (g_kits[i]->device == device && (best == g_kits.size() || g_kits[i]->dev_bytes > g_kits[best]->dev_bytes)) best = i;
+        if (best < g_kits.size()) {
+            kit = std::move(g_kits[best]);
+            g_kits.erase(g_kits.begin() + (std::ptrdiff_t)best);
+        }
+    }
+    if (!kit) {
+        kit.reset(new DenseKit());
+        kit->device = device;
+        e = hipStreamCreateWithFlags(&kit->sc, hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipStreamCreateWithFlags(&kit->sx, hipStreamNonBlocking);
+        for (int i = 0; i < kPanels && e == hipSuccess; ++i) {
+            e = hipEventCreateWithFlags(&kit->computed[i], hipEventDisableTiming);
+            if (e == hipSuccess) e = hipEventCreateWithFlags(&kit->copied[i], hipEventDisableTiming);
+        }
+        for (int i = 0; i < 3 && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&kit->timed[i], 0);
+    }
+    if (e == hipSuccess && kit->dev_bytes < dev_bytes) {
+        if (kit->dev) (void)hipFree(kit->dev);
+        kit->dev = nullptr;
+        kit->dev_bytes = 0;
+        e = hipMalloc((void **)&kit->dev, dev_bytes);
+        if (e == hipSuccess) kit->dev_bytes = dev_bytes;
+    }
+    if (e == hipSuccess && kit->pin_bytes < pin_bytes) {
+        if (kit->pin) (void)hipHostFree(kit->pin);
+        kit->pin = nullptr;
+        kit->pin_bytes = 0;
+        e = hipHostMalloc((void **)&kit->pin, pin_bytes, hipHostMallocDefault);
+        if (e == hipSuccess) kit->pin_bytes = pin_bytes;
+    }
+    return e;
+}
+
+// The kit's streams are idle.  One whose work failed is not kept.
+void give_kit(std::unique_ptr<DenseKit> kit, bool keep)
+{
+    std::vector<std::unique_ptr<DenseKit>> gone;
+    std::lock_guard<std::mutex> g(g_kit_mu);
+    if (!keep || kit->dev_bytes > kKitBytes || kit->pin_bytes > kKitPinned) return;
+    g_kits.push_back(std::move(kit));
+    auto over = [&] {
+        size_t d = 0, p = 0;
+        for (const auto &x : g_kits) {
+            d += x->dev_bytes;
+            p += x->pin_bytes;
+        }
+        return g_kits.size() > kKits || d > kKitBytes || p > kKitPinned;
+    };
+    while (over()) {   // the one unused for longest
+        gone.push_back(std::move(g_kits.front()));
+        g_kits.erase(g_kits.begin());
+    }
+}
 
 }  // namespace
+
+void release_dense_kits()
+{
+    std::vector<std::unique_ptr<DenseKit>> gone;
+    std::lock_guard<std::mutex> g(g_kit_mu);
+    gone.swap(g_kits);
+}
 
 int eval_dense(bem_mesh *m, int op, int space, double k, const int32_t *rows, int64_t nrows, const int32_t *cols,
                int64_t ncols, int prec, int near, void *out, bem_dense_stats *st)
@@ -257,80 +358,85 @@ int eval_dense(bem_mesh *m, int op, int space, double k, const int32_t *rows, in
     const std::vector<PairPanel> &panels = P.fix;
     int64_t max_rows = 0;
     for (const PairPanel &f : panels) max_rows = std::max<int64_t>(max_rows, f.ndof);
-    const size_t panel_out = (size_t)max_rows * (size_t)ncols * elem;
-    DevBuf d_idx, d_L, d_out;
-    char *h_stage = nullptr;
-    hipStream_t sc = nullptr, sx = nullptr;
-    hipEvent_t ev[8] = {};
-    int rc = BEM_OK;
-    auto cleanup = [&]() {
-        if (sc) (void)hipStreamSynchronize(sc);
-        if (sx) (void)hipStreamSynchronize(sx);
-        for (hipEvent_t e : ev)
-            if (e) (void)hipEventDestroy(e);
-        if (sc) (void)hipStreamDestroy(sc);
-        if (sx) (void)hipStreamDestroy(sx);
-        if (h_stage) (void)hipHostFree(h_stage);
-    };
-    hipError_t e = hipMalloc(&d_idx.p, 4 * P.ints.size());
-    if (e == hipSuccess) e = hipMalloc(&d_L.p, P.work);
-    if (e == hipSuccess) e = hipMalloc(&d_out.p, 2 * panel_out);
-    if (e == hipSuccess) e = hipHostMalloc((void **)&h_stage, 2 * panel_out, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&sc, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&sx, hipStreamNonBlocking);
-    for (int i = 0; i < 8 && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&ev[i], i < 4 ? hipEventDisableTiming : 0);
-    if (e == hipSuccess) e = hipMemcpy(d_idx.p, P.ints.data(), 4 * P.ints.size(), hipMemcpyHostToDevice);
+    auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    const size_t row_bytes = (size_t)ncols * elem, panel_out = al((size_t)max_rows * row_bytes);
+    const size_t ints = al(4 * P.ints.size());
+    size_t bufs = std::min<size_t>(kPanels, panels.size());
+    std::unique_ptr<DenseKit> kit;
+    hipError_t e;
+    for (;; --bufs) {
+        e = take_kit(ints + al(P.work) + bufs * panel_out, ints + bufs * panel_out, kit);
+        if (e != hipErrorOutOfMemory || bufs == 1) break;
+        (void)hipGetLastError();
+        kit.reset();             // with less, and without what other calls left
+        release_dense_kits();
+    }
     if (e != hipSuccess) {
-        cleanup();
+        (void)hipGetLastError();
         return fail(e == hipErrorOutOfMemory ? BEM_E_OOM : BEM_E_DEVICE, std::string("dense set-up: ") + hipGetErrorString(e));
     }
-    const int32_t *D = static_cast<const int32_t *>(d_idx.p);
-    hipEvent_t *computed = ev, *copied = ev + 2;   // per output buffer
-    hipEvent_t t_start = ev[4], t_local = ev[5], t_end = ev[6];
-    double local_s = 0.0;
-    auto finish = [&](size_t p) {
+    const hipStream_t sc = kit->sc, sx = kit->sx;
+    char *d_L = kit->dev + ints, *d_out = d_L + al(P.work), *h_out = kit->pin + ints;
+    const int32_t *D = reinterpret_cast<const int32_t *>(kit->dev);
+    std::memcpy(kit->pin, P.ints.data(), 4 * P.ints.size());
+    e = hipMemcpyAsync(kit->dev, kit->pin, 4 * P.ints.size(), hipMemcpyHostToDevice, sc);
+
+    // a panel's rows, where the caller has them, about a MiB at a time
+    const int64_t per = std::max<int64_t>(1, (int64_t)((size_t(1) << 20) / row_bytes));
+    std::vector<int64_t> first(1, 0);   // per panel its first part
+    for (const PairPanel &f : panels) first.push_back(first.back() + (f.ndof + per - 1) / per);
+    auto part = [&](int64_t i) {
+        const size_t p = (size_t)(std::upper_bound(first.begin(), first.end(), i) - first.begin()) - 1;
         const PairPanel &f = panels[p];
-        const int b = (int)(p % 2);
-        hipError_t x = hipEventSynchronize(copied[b]);
-        if (x != hipSuccess) return x;
-        for (int32_t r = 0; r < f.ndof; ++r)   // the panel's rows, where the caller has them
-            std::memcpy(static_cast<char *>(out) + (size_t)P.ints[f.pos + r] * ncols * elem,
-                        h_stage + b * panel_out + (size_t)r * ncols * elem, (size_t)ncols * elem);
-        return hipSuccess;
+        const char *src = h_out + p % bufs * panel_out;
+        const int64_t r0 = (i - first[p]) * per, r1 = std::min<int64_t>(f.ndof, r0 + per);
+        for (int64_t r = r0; r < r1; ++r)
+            std::memcpy(static_cast<char *>(out) + (size_t)P.ints[f.pos + r] * row_bytes, src + (size_t)r * row_bytes, row_bytes);
     };
-    for (size_t p = 0; p < panels.size() && e == hipSuccess; ++p) {
-        const PairPanel &f = panels[p];
-        const int b = (int)(p % 2);
-        char *dout = static_cast<char *>(d_out.p) + b * panel_out;
-        if (p >= 2) e = hipStreamWaitEvent(sc, copied[b], 0);
-        const bool timed = p == 0;
-        if (e == hipSuccess && timed) e = hipEventRecord(t_start, sc);
-        for (size_t l = 0; l < P.lane.size() && e == hipSuccess; ++l)
-            e = launch_pairs(*m, P, f, P.lane[l], D, d_L.p, dout, ncols, 1, k, sc, true,
-                             timed && l == 0 ? t_local : nullptr);
-        if (e == hipSuccess && timed) e = hipEventRecord(t_end, sc);
-        if (e == hipSuccess) e = hipEventRecord(computed[b], sc);
-        if (e == hipSuccess && p >= 1) e = finish(p - 1);
-        if (e == hipSuccess) e = hipStreamWaitEvent(sx, computed[b], 0);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(h_stage + b * panel_out, dout, (size_t)f.ndof * ncols * elem, hipMemcpyDeviceToHost, sx);
-        if (e == hipSuccess) e = hipEventRecord(copied[b], sx);
-        if (e == hipSuccess && timed) {
-            float ms0 = 0.f;
-            // the first panel's kernel times (one synchronisation, at the end of the first panel)
-            if (hipEventSynchronize(t_end) == hipSuccess && hipEventElapsedTime(&ms0, t_start, t_local) == hipSuccess)
-                local_s = 1e-3 * ms0;
-            if (st) {
-                float ms1 = 0.f;
-                if (hipEventElapsedTime(&ms1, t_local, t_end) == hipSuccess) st->first_gather_seconds = 1e-3 * ms1;
-                st->first_local_seconds = local_s;
-                st->first_pairs = (int64_t)f.ntri * P.lane[0].ntri;
+    {
+        CopyCrew<decltype(part)> crew(copy_helpers((size_t)nrows * row_bytes, 7), part);
+        auto enqueue = [&](size_t p) {
+            const PairPanel &f = panels[p];
+            const size_t b = p % bufs;
+            char *dout = d_out + b * panel_out;
+            hipError_t x = hipSuccess;
+            if (p == 0) x = hipEventRecord(kit->timed[0], sc);
+            // the panel that had this buffer has been copied out: its transfer has ended
+            for (size_t l = 0; l < P.lane.size() && x == hipSuccess; ++l)
+                x = launch_pairs(*m, P, f, P.lane[l], D, d_L, dout, ncols, 1, k, sc, true,
+                                 p == 0 && l == 0 ? kit->timed[1] : nullptr);
+            if (x == hipSuccess && p == 0) x = hipEventRecord(kit->timed[2], sc);
+            if (x == hipSuccess) x = hipEventRecord(kit->computed[b], sc);
+            if (x == hipSuccess) x = hipStreamWaitEvent(sx, kit->computed[b], 0);
+            if (x == hipSuccess)
+                x = hipMemcpyAsync(h_out + b * panel_out, dout, (size_t)f.ndof * row_bytes, hipMemcpyDeviceToHost, sx);
+            if (x == hipSuccess) x = hipEventRecord(kit->copied[b], sx);
+            return x;
+        };
+        size_t ahead = 0;
+        for (size_t p = 0; p < panels.size() && e == hipSuccess; ++p) {
+            while (ahead < panels.size() && ahead < p + bufs && e == hipSuccess) {
+                if (ahead >= bufs) crew.help(first[ahead - bufs + 1]);
+                e = enqueue(ahead++);
             }
+            if (e == hipSuccess) e = hipEventSynchronize(kit->copied[p % bufs]);
+            if (e == hipSuccess) crew.release(first[p + 1]);
         }
+        if (e == hipSuccess) crew.help(first.back());
     }
-    if (e == hipSuccess) e = finish(panels.size() - 1);
-    if (e != hipSuccess) rc = fail(BEM_E_DEVICE, std::string("dense block: ") + hipGetErrorString(e));
-    cleanup();
+    if (st && e == hipSuccess) {   // the first panel's kernel times
+        float ms = 0.f;
+        if (hipEventElapsedTime(&ms, kit->timed[0], kit->timed[1]) == hipSuccess) st->first_local_seconds = 1e-3 * ms;
+        if (hipEventElapsedTime(&ms, kit->timed[1], kit->timed[2]) == hipSuccess) st->first_gather_seconds = 1e-3 * ms;
+        st->first_pairs = (int64_t)panels[0].ntri * P.lane[0].ntri;
+    }
+    int rc = BEM_OK;
+    if (e != hipSuccess) {
+        rc = fail(BEM_E_DEVICE, std::string("dense block: ") + hipGetErrorString(e));
+        (void)hipStreamSynchronize(sc);
+        (void)hipStreamSynchronize(sx);
+    }
+    give_kit(std::move(kit), rc == BEM_OK);
     if (st && rc == BEM_OK) {
         st->pairs = P.pairs;
         st->panels = (int64_t)panels.size();

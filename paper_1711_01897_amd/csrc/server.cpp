@@ -39,6 +39,7 @@
 #include <immintrin.h>
 
 #include "bem_internal.hpp"
+#include "host_copy.hpp"
 
 namespace bem {
 
@@ -1409,7 +1410,7 @@ public:
                     r->result = hb + r->off_out;
                     r->batch = b;
                 } else if (r->out_host) {
-                    std::memcpy(r->out_host, hb + r->off_out, (size_t)r->entries() * r->elem_bytes);
+                    copy_large(r->out_host, hb + r->off_out, (size_t)r->entries() * r->elem_bytes);
                 }
                 sts[i] = st;
             }

@@ -1,0 +1,65 @@
+"""GPU: results large enough for several copying threads.
+
+Dense blocks in one panel, a few and many (more than the buffers in flight),
+from several threads at once and of falling and growing size, so that kept
+work areas are taken over, cut down to and outgrown: the same bits as each
+alone.  Served results on both sides of the sizes that get one helper (2 MiB)
+and two (4 MiB): the bits of the device-tensor form.
+"""
+import os
+import threading
+
+import numpy as np
+import pytest
+
+from paper_1711_01897_amd import bem, inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def test_dense_from_threads():
+    xyz, tri = inputs.icosphere(4)
+    mesh = bem.mesh_create(xyz, tri, 6)
+    rng = np.random.Generator(np.random.PCG64(3))
+    jobs = [(rng.permutation(len(xyz))[:n].astype(np.int32), rng.permutation(len(xyz))[:m].astype(np.int32), prec)
+            for n, m, prec in ((2562, 2562, bem.FP32), (300, 700, bem.FP64), (1500, 1311, bem.FP64), (1, 2562, bem.FP32))]
+    one = lambda j: bem.eval_dense(mesh, bem.LAPLACE_SLP, bem.P1, 0.0, j[0], j[1], prec=j[2], near=bem.NEAR_SKIP)
+    alone = [one(j) for j in jobs]
+    for mb in (None, "16"):
+        if mb:
+            os.environ["BEM_DENSE_BUDGET_MB"] = mb
+        try:
+            got = [[None] * 3 for _ in jobs]
+
+            def work(t):
+                for i in range(3):
+                    k = (t + i) % len(jobs)
+                    got[k][i] = one(jobs[k])
+
+            threads = [threading.Thread(target=work, args=(t,)) for t in range(len(jobs))]
+            for t in threads:
+                t.start()
+            for t in threads:
+                t.join()
+        finally:
+            os.environ.pop("BEM_DENSE_BUDGET_MB", None)
+        for k, want in enumerate(alone):
+            assert all(np.array_equal(g, want) for g in got[k])
+    mesh.destroy()
+    mesh = bem.mesh_create(xyz, tri, 6)      # the areas were given back with the mesh
+    assert np.array_equal(one(jobs[1]), alone[1])
+    mesh.destroy()
+
+
+@pytest.mark.parametrize("n", [511, 513, 723, 725, 1280])
+def test_served(n):
+    import torch
+    xyz, tri = inputs.icosphere(3)
+    mesh = bem.mesh_create(xyz, tri, 4)
+    idx = np.random.Generator(np.random.PCG64(4)).permutation(1280)[:n].astype(np.int32)
+    out = torch.empty((n, n), dtype=torch.float64, device="cuda")
+    bem.eval_entries_async(mesh, bem.LAPLACE_SLP, bem.P0, 0.0, idx, idx, out, prec=bem.FP64)
+    torch.cuda.synchronize()
+    got = bem.eval_entries(mesh, bem.LAPLACE_SLP, bem.P0, 0.0, idx, idx, prec=bem.FP64, near=bem.NEAR_SKIP)
+    assert np.array_equal(got, out.cpu().numpy())
+    mesh.destroy()

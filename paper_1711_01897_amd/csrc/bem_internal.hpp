@@ -40,6 +40,7 @@ struct Request;
 constexpr int kGeo32Stride = 16;
 constexpr int kGeo64Stride = 24;
 constexpr int kBlockLanes = 256;    // lane-side items per workgroup (4 wavefronts)
+constexpr int kTileP0 = 8;          // P0: fixed triangles per workgroup at most
 constexpr int kStage = 8;           // fixed-side triangles staged in LDS at a time
 
 // One request as the entry kernels see it.
@@ -59,7 +60,8 @@ struct ReqDev {
     const int32_t *seg_ptr;    // P1: per lane-side dof, range into seg
     const int32_t *seg;        // P1: packed (lane slot within the chunk << 2 | local vertex)
     const int32_t *lpos;       // P1: output position of each lane-side dof (null: its own index)
-    const int32_t *sptr;       // row form: the mesh's star ranges per vertex; null: `lane` holds star entries
+    const int32_t *sptr;       // row form: the mesh's star ranges per vertex (null: `lane` holds star entries);
+                               // P0 tiles: the fixed triangles
     int32_t group, split;      // row form: log2 of the threads per lane dof, and of the shares of a fixed star
     void *out;                 // final output, row-major nrows x ncols
     int32_t *status;           // set to 1: a vertex-sharing pair was met under BEM_NEAR_ERROR
@@ -97,7 +99,7 @@ struct EntryBlock {  // one workgroup of entry work (64 bytes, read with one sca
 // both fixed sides).
 struct Variant {
     int op, space, prec, q;
-    int row = 0;       // the row form of a P1 kernel (counted with the star form in the statistics)
+    int row = 0;       // P1: the row form; P0: tiles (counted with the other form in the statistics)
     int persist = 0;   // statistics only: the resident (persistent) form of the kernel
     bool operator<(const Variant &o) const {
         if (op != o.op) return op < o.op;
@@ -338,7 +340,7 @@ struct bem_mesh {
     float *d_g32 = nullptr;
     double *d_g64 = nullptr;
     int4 *d_vtx = nullptr;
-    double *d_xyz = nullptr;     // vertices (the singular pairs read them)
+    double *d_xyz = nullptr;     // vertices (the singular pairs read them); the allocation holds the next two as well
     int32_t *d_sptr = nullptr;   // star ranges per vertex
     int32_t *d_star = nullptr;   // star table on the device (packed triangle << 2 | local vertex)
     float *d_sgeo = nullptr;     // FP32 record per star entry
@@ -438,6 +440,7 @@ struct Request {
     std::vector<int32_t> near_rows;       // P1: rows with at least one pair
     bool many = false;                    // one of many in flight that several threads expand
     bool row = false;                     // P1 of few fixed dofs: the row form (build_row_set)
+    int32_t tile = 1;                     // P0: fixed triangles per workgroup
     int32_t row_split = 0;                // its log2 shares of a fixed star
     // by triangle pairs (dense.cpp): no lane set and no block table then
     bool paired = false;
@@ -484,6 +487,9 @@ size_t out_elem_bytes(int op, int prec);
 // pair_budget: workspace bytes the request may use if it is taken by triangle
 // pairs (0: it may not be).
 int expand_request(Request &r, size_t pair_budget = 0);
+// What a request takes beside its singular pairs as single triangles or stars,
+// in bytes (at most, where that is within the limit).
+size_t plain_workspace(const Request &r, size_t limit);
 // Row form: whether a triangle of a fixed star and one of a lane star share a vertex.
 bool row_touches(const Request &r);
 // Fast path for requests whose lane side is a resident LaneRef and whose
@@ -502,7 +508,7 @@ void describe_request(const Request &r, ReqDev &d);
 // at their device copies (no-op for a device-resident lane side); returns
 // the bytes used (r.in_bytes).
 size_t stage_own_inputs(const Request &r, char *host_base, char *dev_base, size_t off, ReqDev &d);
-// Launch group of a request: (row form, kernel operator, kernel space, precision, rule).
+// Launch group of a request: (row form or tiles, kernel operator, kernel space, precision, rule).
 int request_key(const Request &r);
 constexpr int kKeys = 128;
 inline Variant key_variant(int key)

@@ -379,8 +379,10 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
     // workspace of their own, else behind the rest
     const size_t work_bytes = r.paired ? r.pairs.work : 0;
     size_t ws_total = al(ws_staged) + work_bytes;
-    if (fixed && ws_total > fixed_bytes)
-        return fail(BEM_E_OOM, "request needs " + std::to_string(ws_total) + " bytes of workspace, more than the " +
+    // the limit is that of the plain forms, whichever form the request takes
+    const size_t needed = fixed ? std::max(ws_total, plain_workspace(r, fixed_bytes)) : 0;
+    if (needed > fixed_bytes)
+        return fail(BEM_E_OOM, "request needs " + std::to_string(needed) + " bytes of workspace, more than the " +
                                    std::to_string(fixed_bytes) + "-byte static workspace of the no-allocation entry point");
     char *host = nullptr;
     char *ws = fixed;
@@ -457,7 +459,7 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
     }
     if (e != hipSuccess) return fail(BEM_E_DEVICE, std::string("staging copy: ") + hipGetErrorString(e));
     const ReqDev *dreq = (const ReqDev *)(img + off_req);
-    const Variant v{kernel_op(r.op), r.space, r.prec, mesh->q, r.row ? 1 : 0};
+    const Variant v{kernel_op(r.op), r.space, r.prec, mesh->q, r.row || r.tile > 1 ? 1 : 0};
     if (r.paired) {
         const int64_t sf = r.fixrows ? r.ncols : 1, sl = r.fixrows ? 1 : r.ncols;
         for (const PairPanel &f : r.pairs.fix)

@@ -435,8 +435,10 @@ __device__ __forceinline__ void sweep_f64(FP F, const double *L, const double *w
 
 // ---------------------------------------------------------------------------
 // P0 pair value sum_p sum_q w_p w_q K(x_p, y_q) (without J_x J_y / 4 pi).
+// B: |o_q|^2 of the trial side's points (Helmholtz).
 template <int OP, int Q>
-__device__ __forceinline__ void pair_p0_f32(const float *T, const float *S, float kf, double kk, float &vr, float &vi)
+__device__ __forceinline__ void pair_p0_f32(const float *T, const float *S, const float *B, float kf, double kk, float &vr,
+                                            float &vi)
 {
     const float dcx = (T[0] - S[0]) + (T[4] - S[4]);
     const float dcy = (T[1] - S[1]) + (T[5] - S[5]);
@@ -446,10 +448,6 @@ __device__ __forceinline__ void pair_p0_f32(const float *T, const float *S, floa
         // n = r^2 - |D|^2 = (A'_p + B_q) + (-2 a_p).o_q with a_p = D + o_p,
         // A'_p = 2 D.o_p + |o_p|^2, B_q = |o_q|^2; r^2 = n + |D|^2
         const Phase ph = phase_base(T, S, kk, dcx, dcy, dcz);
-        float B[Q];
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-            B[q] = fmaf(S[12 + 3 * q], S[12 + 3 * q], fmaf(S[13 + 3 * q], S[13 + 3 * q], S[14 + 3 * q] * S[14 + 3 * q]));
 #pragma unroll
         for (int p = 0; p < Q; ++p) {
             const float ox = T[12 + 3 * p], oy = T[13 + 3 * p], oz = T[14 + 3 * p];
@@ -486,6 +484,15 @@ __device__ __forceinline__ void pair_p0_f32(const float *T, const float *S, floa
     }
     vr = hr + lr;
     vi = hi + li;
+}
+
+// |o_q|^2 of a triangle's quadrature points.
+template <int Q>
+__device__ __forceinline__ void offset_squares(const float *S, float *B)
+{
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        B[q] = fmaf(S[12 + 3 * q], S[12 + 3 * q], fmaf(S[13 + 3 * q], S[13 + 3 * q], S[14 + 3 * q] * S[14 + 3 * q]));
 }
 
 // FP64, fixed triangle F against lane triangle L.
@@ -881,10 +888,12 @@ __device__ __forceinline__ void p0_body_f32(const ReqDev &R, const EntryBlock &B
         float F[n32<Q>()], L[n32<Q>()];
         expand32<Q>(f0, f1, f2, f3, F);
         expand32<Q>(l0, l1, l2, l3, L);
+        float sq[Q];
+        if constexpr (is_cplx<OP>()) offset_squares<Q>(ROWFIX ? L : F, sq);
         if constexpr (ROWFIX)
-            pair_p0_f32<OP, Q>(F, L, kf, kk, vr, vi);
+            pair_p0_f32<OP, Q>(F, L, sq, kf, kk, vr, vi);
         else
-            pair_p0_f32<OP, Q>(L, F, kf, kk, vr, vi);
+            pair_p0_f32<OP, Q>(L, F, sq, kf, kk, vr, vi);
         const float sc = F[3] * L[3] * kInv4PiF;
         vr *= sc;
         vi *= sc;
@@ -962,6 +971,159 @@ __global__ __launch_bounds__(kBlockLanes) void k_p0_f64(const ReqDev *__restrict
         p0_body_f64<OP, Q, true>(R, B);
     else
         p0_body_f64<OP, Q, false>(R, B);
+    clock_end(tclock);
+}
+
+// P0 blocks of many fixed triangles: a workgroup takes up to kTileP0 of them
+// (list positions s0 to s1) against its lanes.  A lane's record is loaded and
+// expanded once for all of them, a fixed one once per workgroup, by one thread
+// each into LDS, where the form above expands both in every thread (a third of its
+// instructions with the 4-point rule), and the host writes an eighth of the block
+// records (64 bytes for every 256 entries).  What is left is bound by the issue of
+// the point pairs' instructions.  1,024 x 4,096 with the 4-point rule, a call:
+// FP32 Laplace single layer 82 -> 38 us, Helmholtz 91 -> 71; FP64 Laplace
+// 87 -> 56, Helmholtz double layer 156 -> 130.  p0_tile has the rule.
+constexpr int kFixP0 = 56;   // words a staged triangle takes: record, vertex ids, squared offsets (16-byte multiple)
+
+template <int OP, int Q, bool ROWFIX>
+__device__ __forceinline__ void p0_tile_f32(const ReqDev &R, const EntryBlock &B, float (*sF)[kFixP0])
+{
+    const int4 ch = B.chunk;
+    const int t = threadIdx.x;
+    const int nf = B.s1 - B.s0;
+    if (t < nf) {
+        const int tf = ldg(R.sptr + B.s0 + t);
+        const float4 *fp = reinterpret_cast<const float4 *>(R.g32 + (size_t)tf * kGeo32Stride);
+        float F[n32<Q>()], sq[Q];
+        expand32<Q>(ldg(fp), ldg(fp + 1), ldg(fp + 2), ldg(fp + 3), F);
+        offset_squares<Q>(F, sq);
+#pragma unroll
+        for (int i = 0; i < n32<Q>(); ++i) sF[t][i] = F[i];
+        const int4 v = ldg(R.vtx + tf);
+        sF[t][40] = __int_as_float(v.x);
+        sF[t][41] = __int_as_float(v.y);
+        sF[t][42] = __int_as_float(v.z);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) sF[t][44 + q] = sq[q];
+    }
+    __syncthreads();
+    if ((t & ~63) >= ch.y) return;
+    const bool act = t < ch.y;
+    const int tn = ldg(R.lane + ch.x + (act ? t : 0));
+    const int4 vl = ldg(R.vtx + tn);
+    const float4 *lp = reinterpret_cast<const float4 *>(R.g32 + (size_t)tn * kGeo32Stride);
+    float L[n32<Q>()], lsq[Q];
+    expand32<Q>(ldg(lp), ldg(lp + 1), ldg(lp + 2), ldg(lp + 3), L);
+    if constexpr (is_cplx<OP>() && ROWFIX) offset_squares<Q>(L, lsq);
+    const float kf = (float)R.k;
+    const double kk = R.kk;
+    const int64_t sf = R.sf;
+    int64_t o = (int64_t)B.fixed * sf + (int64_t)(ch.z + t) * R.sl;
+#pragma unroll 1
+    for (int s = 0; s < nf; ++s, o += sf) {
+        const int4 vf = make_int4(__float_as_int(sF[s][40]), __float_as_int(sF[s][41]), __float_as_int(sF[s][42]), 0);
+        float vr = 0.f, vi = 0.f;
+        if (!share_vertex(vf, vl)) {
+            float F[n32<Q>()];
+#pragma unroll
+            for (int i = 0; i < n32<Q>(); ++i) F[i] = sF[s][i];
+            if constexpr (ROWFIX) {
+                pair_p0_f32<OP, Q>(F, L, lsq, kf, kk, vr, vi);
+            } else {
+                float sq[Q];
+                if constexpr (is_cplx<OP>()) {
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) sq[q] = sF[s][44 + q];
+                }
+                pair_p0_f32<OP, Q>(L, F, sq, kf, kk, vr, vi);
+            }
+            const float sc = F[3] * L[3] * kInv4PiF;
+            vr *= sc;
+            vi *= sc;
+        } else if (act && R.near_error) {
+            put<false>(R.status, 1);
+        }
+        if (act) {
+            if constexpr (is_cplx<OP>())
+                put<false>(reinterpret_cast<float2 *>(R.out) + o, make_float2(vr, vi));
+            else
+                put<false>(reinterpret_cast<float *>(R.out) + o, vr);
+        }
+    }
+}
+
+template <int OP, int Q>
+__global__ __launch_bounds__(kBlockLanes) void k_p0t_f32(const ReqDev *__restrict__ reqs,
+                                                         const EntryBlock *__restrict__ blocks, int64_t nblocks,
+                                                         unsigned long long *tclock)
+{
+    __shared__ __align__(16) float sF[kTileP0][kFixP0];
+    static_assert(n32<Q>() <= 40, "the vertex ids follow the record");
+    if ((int64_t)blockIdx.x >= nblocks) return;
+    clock_start(tclock);
+    const EntryBlock B = blocks[blockIdx.x];
+    const ReqDev &R = reqs[B.req >> 1];
+    if (B.req & 1)
+        p0_tile_f32<OP, Q, true>(R, B, sF);
+    else
+        p0_tile_f32<OP, Q, false>(R, B, sF);
+    clock_end(tclock);
+}
+
+template <int OP, int Q, bool ROWFIX>
+__device__ __forceinline__ void p0_tile_f64(const ReqDev &R, const EntryBlock &B)
+{
+    typedef const __attribute__((address_space(4))) int32_t *ConstI;
+    typedef const __attribute__((address_space(4))) i32x4 *ConstI4;
+    const int4 ch = B.chunk;
+    const int t = threadIdx.x;
+    if ((t & ~63) >= ch.y) return;
+    const bool act = t < ch.y;
+    const int tn = R.lane[ch.x + (act ? t : 0)];
+    const int4 vl = R.vtx[tn];
+    double L[n64<Q>()];
+    load64<Q>(R.g64, tn, L);
+    const Wave64 wave = wave64(R);
+    const ConstI fixl = (ConstI)R.sptr;
+    const ConstI4 vtx = (ConstI4)R.vtx;
+    const int64_t sf = R.sf;
+    int64_t o = (int64_t)B.fixed * sf + (int64_t)(ch.z + t) * R.sl;
+#pragma unroll 1
+    for (int s = B.s0; s < B.s1; ++s, o += sf) {
+        const int tf = fixl[s];
+        const i32x4 vf = vtx[tf];
+        double vr = 0.0, vi = 0.0;
+        if (!share_vertex(make_int4(vf.x, vf.y, vf.z, 0), vl)) {
+            const ConstF64 F = (ConstF64)(R.g64 + (size_t)tf * kGeo64Stride);
+            pair_p0_f64<OP, Q, ROWFIX>(F, L, wave, vr, vi);
+            const double sc = F[3] * L[3] * kInv4Pi;
+            vr *= sc;
+            vi *= sc;
+        } else if (act && R.near_error) {
+            put<false>(R.status, 1);
+        }
+        if (act) {
+            if constexpr (is_cplx<OP>())
+                put<false>(reinterpret_cast<double2 *>(R.out) + o, make_double2(vr, vi));
+            else
+                put<false>(reinterpret_cast<double *>(R.out) + o, vr);
+        }
+    }
+}
+
+template <int OP, int Q>
+__global__ __launch_bounds__(kBlockLanes) void k_p0t_f64(const ReqDev *__restrict__ reqs,
+                                                         const EntryBlock *__restrict__ blocks, int64_t nblocks,
+                                                         unsigned long long *tclock)
+{
+    if ((int64_t)blockIdx.x >= nblocks) return;
+    clock_start(tclock);
+    const EntryBlock B = blocks[blockIdx.x];
+    const ReqDev &R = reqs[B.req >> 1];
+    if (B.req & 1)
+        p0_tile_f64<OP, Q, true>(R, B);
+    else
+        p0_tile_f64<OP, Q, false>(R, B);
     clock_end(tclock);
 }
 
@@ -2117,6 +2279,13 @@ EntryKernel pick_q(int space, int prec, int q)
 }
 
 template <int OP>
+EntryKernel pick_p0_tile(int prec, int q)
+{
+    if (prec == BEM_FP32) return q == 6 ? k_p0t_f32<OP, 6> : k_p0t_f32<OP, 4>;
+    return q == 6 ? k_p0t_f64<OP, 6> : k_p0t_f64<OP, 4>;
+}
+
+template <int OP>
 EntryKernel pick_row(int prec, int q)
 {
     if (prec == BEM_FP32) return q == 6 ? k_row_f32<OP, 6> : k_row_f32<OP, 4>;
@@ -2125,6 +2294,15 @@ EntryKernel pick_row(int prec, int q)
 
 EntryKernel select_kernel(const Variant &v)
 {
+    if (v.row && v.space == BEM_P0) {
+        switch (v.op) {
+        case LSLP: return pick_p0_tile<LSLP>(v.prec, v.q);
+        case LDLP: return pick_p0_tile<LDLP>(v.prec, v.q);
+        case HSLP: return pick_p0_tile<HSLP>(v.prec, v.q);
+        case HDLP: return pick_p0_tile<HDLP>(v.prec, v.q);
+        default: return nullptr;
+        }
+    }
     if (v.row) {
         switch (v.op) {
         case LSLP: return pick_row<LSLP>(v.prec, v.q);

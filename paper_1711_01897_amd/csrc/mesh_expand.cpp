@@ -130,8 +130,8 @@ void finalize_sizes(Request &r)
     r.elem_bytes = out_elem_bytes(r.op, r.prec);
     const int64_t fixed_tris = r.space == BEM_P0 ? r.nfix : r.nstar;
     r.evals = fixed_tris * r.ndistinct * q2;
-    r.nblocks = r.nfix * r.nchunk;
-    const size_t own = r.ext ? 0 : r.own.ints();
+    r.nblocks = (r.nfix + r.tile - 1) / r.tile * r.nchunk;
+    const size_t own = r.ext ? 0 : r.own.ints() + (r.tile > 1 ? r.fix.size() : 0);
     r.in_bytes = align16(4 * own);
     r.out_bytes = align16((size_t)r.entries() * r.elem_bytes);
     r.batch_bytes = request_bytes(r);
@@ -574,6 +574,45 @@ void stage_near(const Request &r, const NearLayout &L, char *host, char *dev, ch
     at.ints += n.ints;
 }
 
+// Fixed triangles per workgroup of a P0 request: as many as leave 2,048
+// workgroups, eight for each compute unit.  With half as many the units' shares
+// differ by more than the tiles save, with twice as many the host's records do
+// (701 x 3,001 by single triangles / tiles with 512, 2,048 and 4,096 workgroups,
+// us: FP32 Helmholtz single layer, 4-point rule 54 / 49, 46, 48, 6-point 78 / 81,
+// 75, 74; FP32 Laplace 52 / 29, 28, 33; FP64 Helmholtz double layer, 6-point
+// 152 / 164, 149, 145).  Below that the single triangles fill the chip better
+// (512 x 1,024 with the 6-point rule: alike from 512 workgroups on).
+static int32_t p0_tile(int64_t nfix, int64_t nchunk)
+{
+    int32_t tile = kTileP0;
+    while (tile > 1 && (nfix + tile - 1) / tile * nchunk < 2048) tile /= 2;
+    return tile;
+}
+
+size_t plain_workspace(const Request &r, size_t limit)
+{
+    const bem_mesh &m = *r.mesh;
+    const std::vector<int32_t> &fix = r.fixrows ? r.rows : r.cols, &lane = r.fixrows ? r.cols : r.rows;
+    const size_t nf = fix.size(), nl = lane.size();
+    auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    auto bytes = [&](size_t chunks, size_t ints) {
+        return al(sizeof(ReqDev)) + al(sizeof(EntryBlock) * nf * chunks) + al(16 * chunks + 4 * ints) + al(8);
+    };
+    if (r.space == BEM_P0) return bytes((nl + kBlockLanes - 1) / kBlockLanes, nl);
+    // every chunk but the last lacks room for one more star
+    size_t stars = nl;
+    if (r.space == BEM_P1) {
+        stars = 0;
+        for (int32_t d : lane) stars += (size_t)(m.star_ptr[d + 1] - m.star_ptr[d]);
+    }
+    const size_t least = r.space == BEM_P1 ? (size_t)std::max<int64_t>(1, kBlockLanes - m.max_star) : kBlockLanes - 1;
+    const size_t most = bytes(std::min(nl, stars / least + 1), 2 * stars + 2 * nl + 1);
+    if (most <= limit) return most;
+    LaneSet ls;
+    build_lane_set(m, r.space, lane.data(), (int64_t)nl, ls, true);
+    return bytes((size_t)ls.nchunk(), ls.ints() - ls.chunk.size());
+}
+
 bool row_touches(const Request &r)
 {
     // the dofs with a triangle that shares a vertex with one of the fixed
@@ -653,6 +692,7 @@ int expand_request(Request &r, size_t pair_budget)
     r.nlane = (int64_t)r.own.lane.size();
     r.nchunk = r.own.nchunk();
     r.ndistinct = r.own.ndistinct;
+    r.tile = r.space == BEM_P0 ? p0_tile(r.nfix, r.nchunk) : 1;
     const int rc = expand_near(r);
     if (rc != BEM_OK) return rc;
     finalize_sizes(r);
@@ -664,6 +704,7 @@ void expand_single_fixed(Request &r, int32_t dof, int rowfix, const LaneRef *ext
     clear_near(r);
     r.ext = ext;
     r.row = false;
+    r.tile = 1;
     r.fixrows = rowfix;
     r.rowfix = is_adjoint_op(r.op) ? 1 - rowfix : rowfix;
     r.own.lane.clear();
@@ -748,6 +789,7 @@ size_t stage_own_inputs(const Request &r, char *host_base, char *dev_base, size_
     d.seg_ptr = put(r.own.seg_ptr);
     d.seg = put(r.own.seg);
     d.lpos = put(r.own.pos);
+    if (r.tile > 1) d.sptr = put(r.fix);
     return r.in_bytes;
 }
 
@@ -771,9 +813,12 @@ int64_t write_blocks(const Request &r, int32_t ri, EntryBlock *out)
     const float *lgeo = r.ext ? r.ext->geo : nullptr;
     const int4 *lmeta = r.ext ? r.ext->meta : nullptr;
     int64_t n = 0;
-    for (int32_t f = 0; f < (int32_t)r.nfix; ++f) {
+    for (int32_t f = 0; f < (int32_t)r.nfix; f += r.tile) {
         int32_t s0, s1;
-        if (r.space == BEM_P0) {
+        if (r.tile > 1) {   // positions in the list of fixed triangles
+            s0 = f;
+            s1 = std::min((int32_t)r.nfix, f + r.tile);
+        } else if (r.space == BEM_P0) {
             s0 = r.fix[f];
             s1 = s0 + 1;
         } else {
@@ -800,7 +845,7 @@ int64_t write_blocks(const Request &r, int32_t ri, EntryBlock *out)
 
 int request_key(const Request &r)
 {
-    return ((((r.row ? 8 : 0) + kernel_op(r.op)) * 2 + kernel_space(r.space)) * 2 + r.prec) * 2 +
+    return ((((r.row || r.tile > 1 ? 8 : 0) + kernel_op(r.op)) * 2 + kernel_space(r.space)) * 2 + r.prec) * 2 +
            (r.mesh->q == 6 ? 1 : 0);
 }
 
@@ -894,43 +939,49 @@ int mesh_create_impl(const double *xyz, int64_t nv, const int32_t *tri, int64_t 
     if (e == hipSuccess) e = hipMalloc(&m->d_g32, b32);
     if (e == hipSuccess) e = hipMalloc(&m->d_g64, b64);
     if (e == hipSuccess) e = hipMalloc(&m->d_vtx, bv);
-    if (e == hipSuccess) e = hipMalloc(&m->d_xyz, sizeof(double) * 3 * nv);
-    if (e == hipSuccess) e = hipMalloc(&d_tri, sizeof(int32_t) * 3 * nt);
-    if (e == hipSuccess) e = hipMalloc(&d_bad, sizeof(int32_t));
-    if (e == hipSuccess) e = hipMemcpy(m->d_xyz, xyz, sizeof(double) * 3 * nv, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(d_tri, tri, sizeof(int32_t) * 3 * nt, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(d_bad, &bad, sizeof(int32_t), hipMemcpyHostToDevice);
+    // what the host has: vertices, star ranges and entries, triangles and the
+    // degenerate flag, in one allocation and one copy (each costs a call of its
+    // own 20-40 us)
+    const int64_t ns = 3 * nt;
+    auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    const size_t o_sptr = al(sizeof(double) * 3 * nv), o_star = al(o_sptr + sizeof(int32_t) * (nv + 1)),
+                 o_tri = al(o_star + sizeof(int32_t) * ns), o_bad = al(o_tri + sizeof(int32_t) * 3 * nt);
+    const size_t bh = o_bad + 256;
+    if (e == hipSuccess) e = hipMalloc((void **)&m->d_xyz, bh);
+    if (e == hipSuccess) {
+        char *base = reinterpret_cast<char *>(m->d_xyz);
+        m->d_sptr = reinterpret_cast<int32_t *>(base + o_sptr);
+        m->d_star = reinterpret_cast<int32_t *>(base + o_star);
+        d_tri = reinterpret_cast<int32_t *>(base + o_tri);
+        d_bad = reinterpret_cast<int32_t *>(base + o_bad);
+        std::vector<char> up(bh, 0);
+        std::memcpy(up.data(), xyz, sizeof(double) * 3 * nv);
+        int32_t *sp = reinterpret_cast<int32_t *>(up.data() + o_sptr);
+        for (int64_t v = 0; v <= nv; ++v) sp[v] = (int32_t)m->star_ptr[v];
+        std::memcpy(up.data() + o_star, m->star.data(), sizeof(int32_t) * ns);
+        std::memcpy(up.data() + o_tri, tri, sizeof(int32_t) * 3 * nt);
+        e = hipMemcpy(base, up.data(), bh, hipMemcpyHostToDevice);
+    }
     if (e == hipSuccess) e = launch_geometry(m->d_xyz, d_tri, nt, q, m->d_g32, m->d_g64, m->d_vtx, d_bad, 0);
     if (e == hipSuccess) e = hipMemcpy(&bad, d_bad, sizeof(int32_t), hipMemcpyDeviceToHost);
     // star tables: the packed star entries and, per entry, its triangle's
     // FP32 record and vertex ids with the local vertex in w
-    const int64_t ns = 3 * nt;
-    if (e == hipSuccess) e = hipMalloc(&m->d_star, sizeof(int32_t) * ns);
-    if (e == hipSuccess) e = hipMalloc(&m->d_sptr, sizeof(int32_t) * (nv + 1));
-    if (e == hipSuccess) {
-        const std::vector<int32_t> sp(m->star_ptr.begin(), m->star_ptr.end());
-        e = hipMemcpy(m->d_sptr, sp.data(), sizeof(int32_t) * (nv + 1), hipMemcpyHostToDevice);
-    }
     if (e == hipSuccess) e = hipMalloc(&m->d_sgeo, sizeof(float) * kGeo32Stride * ns);
     if (e == hipSuccess) e = hipMalloc(&m->d_smeta, sizeof(int4) * ns);
-    if (e == hipSuccess) e = hipMemcpy(m->d_star, m->star.data(), sizeof(int32_t) * ns, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = launch_gather(m->d_g32, m->d_vtx, m->d_star, 2, ns, m->d_sgeo, m->d_smeta, 0);
     if (e == hipSuccess) e = hipStreamSynchronize(0);
-    if (d_tri) (void)hipFree(d_tri);
-    if (d_bad) (void)hipFree(d_bad);
     if (e != hipSuccess)
         rc = fail(e == hipErrorOutOfMemory ? BEM_E_OOM : BEM_E_DEVICE, std::string("mesh upload: ") + hipGetErrorString(e));
     else if (bad)
         rc = fail(BEM_E_ARG, "degenerate triangle (zero area)");
     if (rc != BEM_OK) {
-        for (void *p : {(void *)m->d_g32, (void *)m->d_g64, (void *)m->d_vtx, (void *)m->d_star, (void *)m->d_sgeo,
-                        (void *)m->d_smeta, (void *)m->d_xyz, (void *)m->d_sptr})
+        for (void *p : {(void *)m->d_g32, (void *)m->d_g64, (void *)m->d_vtx, (void *)m->d_sgeo, (void *)m->d_smeta,
+                        (void *)m->d_xyz})
             if (p) (void)hipFree(p);
         delete m;
         return rc;
     }
-    m->dev_bytes = b32 + b64 + bv + (sizeof(double) * 3 + sizeof(int32_t)) * (size_t)nv +
-                   3 * (size_t)nt * (4 + 4 * kGeo32Stride + sizeof(int4));
+    m->dev_bytes = b32 + b64 + bv + bh + 3 * (size_t)nt * (4 * kGeo32Stride + sizeof(int4));
     *out = m;
     return BEM_OK;
 }
@@ -939,8 +990,8 @@ int mesh_destroy_impl(bem_mesh *m)
 {
     if (!m) return fail(BEM_E_ARG, "null mesh");
     if (m->inflight.load() != 0) return fail(BEM_E_BUSY, "requests on this mesh are still in flight");
-    for (void *p : {(void *)m->d_g32, (void *)m->d_g64, (void *)m->d_vtx, (void *)m->d_star, (void *)m->d_sgeo,
-                    (void *)m->d_smeta, (void *)m->d_xyz, (void *)m->d_sptr})
+    for (void *p : {(void *)m->d_g32, (void *)m->d_g64, (void *)m->d_vtx, (void *)m->d_sgeo, (void *)m->d_smeta,
+                    (void *)m->d_xyz})
         (void)hipFree(p);
     delete m;
     return BEM_OK;

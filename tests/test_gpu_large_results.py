@@ -63,3 +63,18 @@ def test_served(n):
     got = bem.eval_entries(mesh, bem.LAPLACE_SLP, bem.P0, 0.0, idx, idx, prec=bem.FP64, near=bem.NEAR_SKIP)
     assert np.array_equal(got, out.cpu().numpy())
     mesh.destroy()
+
+
+def test_noalloc_limit_is_that_of_the_plain_forms():
+    """10,242 fixed stars against 93 or more chunks of lanes take over 32 MiB of
+    64-byte records; by triangle pairs the same block would fit."""
+    import torch
+    xyz, tri = inputs.icosphere(5)
+    mesh = bem.mesh_create(xyz, tri, 6)
+    idx = np.arange(len(xyz), dtype=np.int32)
+    out = torch.zeros((idx.size, idx.size), dtype=torch.float32, device="cuda")
+    with pytest.raises(bem.BemError, match="static workspace"):
+        bem.eval_entries_async_noalloc(mesh, bem.LAPLACE_SLP, bem.P1, 0.0, idx, idx, out)
+    torch.cuda.synchronize()
+    assert float(out.abs().max()) == 0.0
+    mesh.destroy()

@@ -2670,7 +2670,12 @@ __global__ __launch_bounds__(kBlockLanes) void k_local_f64(const double *__restr
 // packed fixed-side triangle << 2 | local vertex) and c's star of the local
 // values, in that order, stored at out[fpos[r] sf + lpos[c] sl] (fpos null: r sf).  One thread
 // per lane dof and kGatherRows fixed dofs; the lane dof's first eight sources
-// stay in registers over them.
+// stay in registers over them, the seventh and eighth being asked for only where
+// a dof of the wavefront has them (36 loads an entry instead of 48 on most of a
+// mesh).  FP64 fetches the next fixed triangle's values while one's are added;
+// FP32, with half the registers in more wavefronts, gains nothing from that.
+// Calls, us: 1,023 x 2,049 FP32 double layer 291 -> 283, 300 x 1,501 FP32
+// Helmholtz hypersingular 150 -> 145, 501 x 1,000 FP64 Helmholtz 302-319 -> 281-298.
 template <typename T, bool CPLX>
 __global__ __launch_bounds__(kBlockLanes) void k_gather_pairs(const T *__restrict__ Lr, const T *__restrict__ Li, int nl,
                                                               const int32_t *__restrict__ fptr,
@@ -2682,7 +2687,7 @@ __global__ __launch_bounds__(kBlockLanes) void k_gather_pairs(const T *__restric
                                                               void *__restrict__ out, int64_t sf, int64_t sl)
 {
     constexpr bool COMP = sizeof(T) == 4;   // FP32: compensated
-    constexpr int kN = 8;
+    constexpr int kN = 8, kLow = 6;
     const int c = blockIdx.x * kBlockLanes + (int)threadIdx.x;
     if (c >= nld) return;
     const int c0 = lptr[c], nc = lptr[c + 1] - c0;
@@ -2693,6 +2698,7 @@ __global__ __launch_bounds__(kBlockLanes) void k_gather_pairs(const T *__restric
         const int ns = j < nc ? lsrc[c0 + j] : 0;
         off[j] = (ns & 3) * nl + (ns >> 2);
     }
+    const bool more = __any(nc > kLow);   // a dof of the wavefront has a longer star
     const int r1 = min(nfd, ((int)blockIdx.y + 1) * kGatherRows);
     for (int r = blockIdx.y * kGatherRows; r < r1; ++r) {
         T hr = 0, lr = 0, hi = 0, li = 0;
@@ -2700,27 +2706,67 @@ __global__ __launch_bounds__(kBlockLanes) void k_gather_pairs(const T *__restric
             if constexpr (COMP) two_sum_acc(h, l, x);
             else h += x;
         };
-        for (int i = fptr[r]; i < fptr[r + 1]; ++i) {
+        auto row = [&](int i) {
             const int ms = fsrc[i];
-            const size_t base = ((size_t)(ms >> 2) * 9 + 3 * (ms & 3)) * nl;
+            return ((size_t)(ms >> 2) * 9 + 3 * (ms & 3)) * nl;
+        };
+        auto fetch = [&](size_t base, T *xr, T *xi) {   // places past the star's end read its first value
             const T *pr = Lr + base, *pi = CPLX ? Li + base : nullptr;
-            T xr[kN], xi[kN];
 #pragma unroll
-            for (int j = 0; j < kN; ++j) {   // all loads first: places past the star's end read its first value
+            for (int j = 0; j < kLow; ++j) {
                 xr[j] = pr[off[j]];
                 if constexpr (CPLX) xi[j] = pi[off[j]];
             }
+            if (more) {
 #pragma unroll
-            for (int j = 0; j < kN; ++j)
+                for (int j = kLow; j < kN; ++j) {
+                    xr[j] = pr[off[j]];
+                    if constexpr (CPLX) xi[j] = pi[off[j]];
+                }
+            }
+        };
+        auto sum = [&](size_t base, const T *xr, const T *xi) {
+#pragma unroll
+            for (int j = 0; j < kLow; ++j)
                 if (j < nc) {
                     add(hr, lr, xr[j]);
                     if constexpr (CPLX) add(hi, li, xi[j]);
                 }
-            for (int j = kN; j < nc; ++j) {
-                const int ns = lsrc[c0 + j];
-                const int o = (ns & 3) * nl + (ns >> 2);
-                add(hr, lr, pr[o]);
-                if constexpr (CPLX) add(hi, li, pi[o]);
+            if (more) {
+#pragma unroll
+                for (int j = kLow; j < kN; ++j)
+                    if (j < nc) {
+                        add(hr, lr, xr[j]);
+                        if constexpr (CPLX) add(hi, li, xi[j]);
+                    }
+                for (int j = kN; j < nc; ++j) {
+                    const int ns = lsrc[c0 + j];
+                    const int o = (ns & 3) * nl + (ns >> 2);
+                    add(hr, lr, Lr[base + o]);
+                    if constexpr (CPLX) add(hi, li, Li[base + o]);
+                }
+            }
+        };
+        int i = fptr[r];
+        const int i1 = fptr[r + 1];
+        T xr[kN], xi[kN];
+        if constexpr (COMP) {
+            for (; i < i1; ++i) {
+                const size_t base = row(i);
+                fetch(base, xr, xi);
+                sum(base, xr, xi);
+            }
+        } else {
+            T yr[kN], yi[kN];
+            size_t bx = 0, by = 0;
+            if (i < i1) fetch(bx = row(i), xr, xi);
+            for (; i < i1; i += 2) {
+                if (i + 1 < i1) fetch(by = row(i + 1), yr, yi);
+                sum(bx, xr, xi);
+                if (i + 1 < i1) {
+                    if (i + 2 < i1) fetch(bx = row(i + 2), xr, xi);
+                    sum(by, yr, yi);
+                }
             }
         }
         const int64_t e = (int64_t)(fpos ? fpos[r] : r) * sf + at;

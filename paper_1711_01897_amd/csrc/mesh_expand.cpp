@@ -939,28 +939,25 @@ int mesh_create_impl(const double *xyz, int64_t nv, const int32_t *tri, int64_t 
     if (e == hipSuccess) e = hipMalloc(&m->d_g32, b32);
     if (e == hipSuccess) e = hipMalloc(&m->d_g64, b64);
     if (e == hipSuccess) e = hipMalloc(&m->d_vtx, bv);
-    // what the host has: vertices, star ranges and entries, triangles and the
-    // degenerate flag, in one allocation and one copy (each costs a call of its
-    // own 20-40 us)
+    // what the host has: vertices, star entries, triangles, star ranges and,
+    // after them, the degenerate flag; one allocation
     const int64_t ns = 3 * nt;
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    const size_t o_sptr = al(sizeof(double) * 3 * nv), o_star = al(o_sptr + sizeof(int32_t) * (nv + 1)),
-                 o_tri = al(o_star + sizeof(int32_t) * ns), o_bad = al(o_tri + sizeof(int32_t) * 3 * nt);
-    const size_t bh = o_bad + 256;
+    const size_t o_star = al(sizeof(double) * 3 * nv), o_tri = al(o_star + sizeof(int32_t) * ns),
+                 o_sptr = al(o_tri + sizeof(int32_t) * 3 * nt), bh = al(o_sptr + sizeof(int32_t) * (nv + 2));
     if (e == hipSuccess) e = hipMalloc((void **)&m->d_xyz, bh);
     if (e == hipSuccess) {
         char *base = reinterpret_cast<char *>(m->d_xyz);
-        m->d_sptr = reinterpret_cast<int32_t *>(base + o_sptr);
         m->d_star = reinterpret_cast<int32_t *>(base + o_star);
         d_tri = reinterpret_cast<int32_t *>(base + o_tri);
-        d_bad = reinterpret_cast<int32_t *>(base + o_bad);
-        std::vector<char> up(bh, 0);
-        std::memcpy(up.data(), xyz, sizeof(double) * 3 * nv);
-        int32_t *sp = reinterpret_cast<int32_t *>(up.data() + o_sptr);
-        for (int64_t v = 0; v <= nv; ++v) sp[v] = (int32_t)m->star_ptr[v];
-        std::memcpy(up.data() + o_star, m->star.data(), sizeof(int32_t) * ns);
-        std::memcpy(up.data() + o_tri, tri, sizeof(int32_t) * 3 * nt);
-        e = hipMemcpy(base, up.data(), bh, hipMemcpyHostToDevice);
+        m->d_sptr = reinterpret_cast<int32_t *>(base + o_sptr);
+        d_bad = m->d_sptr + nv + 1;
+        std::vector<int32_t> sp(m->star_ptr.begin(), m->star_ptr.end());
+        sp.push_back(0);
+        e = hipMemcpy(m->d_xyz, xyz, sizeof(double) * 3 * nv, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(m->d_star, m->star.data(), sizeof(int32_t) * ns, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(d_tri, tri, sizeof(int32_t) * 3 * nt, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(m->d_sptr, sp.data(), sizeof(int32_t) * (nv + 2), hipMemcpyHostToDevice);
     }
     if (e == hipSuccess) e = launch_geometry(m->d_xyz, d_tri, nt, q, m->d_g32, m->d_g64, m->d_vtx, d_bad, 0);
     if (e == hipSuccess) e = hipMemcpy(&bad, d_bad, sizeof(int32_t), hipMemcpyDeviceToHost);

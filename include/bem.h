@@ -102,8 +102,8 @@ typedef enum { BEM_FP64 = 0, BEM_FP32 = 1 } bem_prec;
  * (Section 3.2.3 leaves them to one; here: coordinates around the pair's
  * singular set with the radial integral in closed form and composite
  * Gauss-Legendre rules for the rest, ~1e-12 relative, FP64, added to the
- * regular part; Helmholtz: the radial integral of e^{ikr} as a 48-term
- * power series in omega = k |c| (x - y = rho c), accurate to ~5e-10 up to
+ * regular part; Helmholtz: the radial integral of e^{ikr} as a power series
+ * of up to 48 terms in omega = k |c| (x - y = rho c), accurate to ~5e-10 up to
  * omega = 12: a Helmholtz request whose vertex-sharing pairs reach beyond
  * that (about one element per wavelength or coarser) fails with BEM_E_ARG;
  * P1: each pair's 3 x 3 local matrix, then a fixed-order sum per entry; the
@@ -183,7 +183,9 @@ int bem_ticket_free(bem_ticket *ticket);
  * host synchronisation.  rows/cols are host arrays, expanded and staged
  * through pinned memory by the library; the call returns once the work is
  * enqueued, and dev_out is complete when the stream reaches that point.
- * Workspace comes from the stream-ordered allocator on the same stream.
+ * Staging and workspace are kept between calls (bounded, never waited for,
+ * given back with the last mesh); with all of it in use, on a capturing stream
+ * and for large requests they come from the stream-ordered allocator.
  * Under BEM_NEAR_ERROR the adjacency check runs on the host before anything
  * is enqueued (BEM_E_NEARFIELD, nothing enqueued). */
 int bem_eval_entries_async(bem_mesh *mesh, bem_op op, bem_space space, double k,
@@ -194,12 +196,13 @@ int bem_eval_entries_async(bem_mesh *mesh, bem_op op, bem_space space, double k,
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same request as bem_eval_entries_async, computed by the same kernels, with
  * its workspace (descriptor, block table, singular-pair records, staged
- * inputs, status word) in a fixed 32 MiB static device array instead of the
- * stream-ordered allocator, and its host image in a per-thread pageable
+ * inputs, status word; local matrices of a block by triangle pairs) in a fixed
+ * 32 MiB static device array, and its host image in a per-thread pageable
  * buffer instead of pinned staging.  The call makes no device or pinned
  * allocation.  Differences from bem_eval_entries_async:
- *   - a request whose workspace exceeds 32 MiB fails with BEM_E_OOM
- *     (nothing enqueued); a P1 row or column of 4,096 entries needs well
+ *   - a request whose workspace exceeds 32 MiB with its entries evaluated
+ *     star by star (P0: triangle by triangle) fails with BEM_E_OOM (nothing
+ *     enqueued), however it would be evaluated; a P1 row or column of 4,096 entries needs well
  *     under 1 MiB;
  *   - the copy of the workspace from pageable host memory is synchronous
  *     with the host, so the call returns once the stream has reached it;
@@ -232,14 +235,14 @@ typedef struct {
  * matrix on the device (144 kernel evaluations per entry of a full matrix,
  * where row requests integrate a pair once per test vertex), then every
  * entry adds its pairs' values in a fixed order (row star outer, column star
- * inner; compensated in FP32).  Rows go in panels whose local matrices fit
+ * inner; compensated in FP32).  Rows, along a Morton curve, go in panels whose local matrices fit
  * BEM_DENSE_BUDGET_MB (environment, default 1024) MiB of device memory; a
  * panel's assembly overlaps the transfer of the previous panel's entries.
  * out: host, nrows x ncols row-major (types as bem_eval_entries).  Single
  * and double layer (Laplace, Helmholtz), P1, BEM_NEAR_ERROR (checked on the
- * host before anything runs) or BEM_NEAR_SKIP; stats may be NULL.  The
- * call allocates its device workspace and pinned staging and frees them
- * before it returns.  Errors as bem_eval_entries. */
+ * host before anything runs) or BEM_NEAR_SKIP; stats may be NULL.  Device
+ * workspace and pinned staging are kept between calls (bounded) and given
+ * back with the last mesh.  Errors as bem_eval_entries. */
 int bem_eval_dense(bem_mesh *mesh, bem_op op, bem_space space, double k, const int32_t *rows, int64_t nrows,
                    const int32_t *cols, int64_t ncols, bem_prec prec, bem_near near, void *out,
                    bem_dense_stats *stats);
@@ -306,7 +309,8 @@ typedef struct {
     int64_t launches;
     int64_t workgroups;        /* 256-thread workgroups of these launches */
     int64_t entries;           /* entries of the requests these launches served */
-    int64_t pair_evals;        /* Q^2 x (fixed, lane) triangle pairs; vertex-sharing pairs, which are
+    int64_t pair_evals;        /* Q^2 x (fixed, lane) triangle pairs, a lane triangle once per request (once
+                                  per dof in requests of few fixed dofs); vertex-sharing pairs, which are
                                   skipped, are included (there are none in admissible blocks) */
     int64_t triangle_loads;    /* lane-triangle geometry records gathered (one per lane per workgroup) */
     double seconds;            /* summed kernel execution times (device clock) */

@@ -369,7 +369,7 @@ namespace bem {
 // copies are shared by every request of an H-matrix block.
 struct LaneSet {
     int64_t ndof = 0;                 // lane-side output positions
-    int64_t ndistinct = 0;            // distinct lane triangles (P0: ndof)
+    int64_t ndistinct = 0;            // distinct lane triangles (P0: ndof; row form: each once per dof)
     std::vector<int32_t> lane;        // P0: the dofs themselves; P1: triangles, chunk by chunk
     std::vector<int32_t> chunk;       // 4 per chunk: first lane, lanes, first dof, dofs
     std::vector<int32_t> seg_ptr;     // P1: ndof + 1

@@ -106,14 +106,14 @@ void cut_side(const bem_mesh &m, int space, const int32_t *dofs, int64_t n, int6
 }
 
 // Star entries and distinct triangles of a dof list.
-void count_side(const bem_mesh &m, int space, const std::vector<int32_t> &dofs, int64_t &stars, int64_t &distinct)
+void count_side(const bem_mesh &m, int space, const int32_t *dofs, int64_t n, int64_t &stars, int64_t &distinct)
 {
     PairScratch &sc = g_pair;
     sc.open(m.nt);
     stars = distinct = 0;
-    for (int32_t d : dofs) {
+    for (int64_t i = 0; i < n; ++i) {
         int64_t b, e;
-        star_range(m, space, d, b, e);
+        star_range(m, space, dofs[i], b, e);
         stars += e - b;
         for (int64_t s = b; s < e; ++s) {
             const int32_t t = m.star[s] >> 2;
@@ -187,8 +187,8 @@ bool pairs_pay(const Request &r, const std::vector<int32_t> &fix, const std::vec
     if (r.space == BEM_P0 || fix.size() < 8 || (int64_t)fix.size() * (int64_t)lane.size() < least) return false;
     const bem_mesh &m = *r.mesh;
     int64_t fs, fd, ls, ld;
-    count_side(m, r.space, fix, fs, fd);
-    count_side(m, r.space, lane, ls, ld);
+    count_side(m, r.space, fix.data(), (int64_t)fix.size(), fs, fd);
+    count_side(m, r.space, lane.data(), (int64_t)lane.size(), ls, ld);
     const double star = (double)fs * (ld > kBlockLanes ? 1.25 : 1.0) * (double)ld;
     const double pair = 1.3 * (double)fd * (double)ld + 0.1 * (double)fs * (double)ls;
     return pair < 0.8 * star;
@@ -355,6 +355,11 @@ int eval_dense(bem_mesh *m, int op, int space, double k, const int32_t *rows, in
     // nothing is launched for a failing request
     if (near == BEM_NEAR_ERROR && pairs_touch(*m, P))
         return fail(BEM_E_NEARFIELD, "a contributing triangle pair shares a vertex");
+    int64_t stars, ntrial, longest = 0;
+    count_side(*m, space, cols, ncols, stars, ntrial);
+    for (int64_t i = 0; i < nrows; ++i) longest = std::max(longest, m->star_ptr[rows[i] + 1] - m->star_ptr[rows[i]]);
+    if ((size_t)longest * (size_t)ntrial * pair_bytes(op, prec) > budget)
+        return fail(BEM_E_OOM, "one row's local matrices exceed the dense budget (BEM_DENSE_BUDGET_MB)");
     const std::vector<PairPanel> &panels = P.fix;
     int64_t max_rows = 0;
     for (const PairPanel &f : panels) max_rows = std::max<int64_t>(max_rows, f.ndof);

@@ -977,10 +977,12 @@ __global__ __launch_bounds__(kBlockLanes) void k_p0_f64(const ReqDev *__restrict
 // P0 blocks of many fixed triangles: a workgroup takes up to kTileP0 of them
 // (list positions s0 to s1) against its lanes.  A lane's record is loaded and
 // expanded once for all of them, a fixed one once per workgroup, by one thread
-// each into LDS, where the form above expands both in every thread (a third of its
-// instructions with the 4-point rule), and the host writes an eighth of the block
-// records (64 bytes for every 256 entries).  What is left is bound by the issue of
-// the point pairs' instructions.  1,024 x 4,096 with the 4-point rule, a call:
+// each into LDS, where the form above expands both in every thread, and the host
+// writes an eighth of the block records (64 bytes for every 256 entries), which is
+// what bound such calls.  What is left is the issue of the point pairs'
+// instructions and, for Helmholtz, a pair's FP64 phase: there the kernel's time
+// stays (701 x 3,001, 4-point rule: 38 us by single triangles, 39 by tiles) and the
+// call gains by the records alone.  1,024 x 4,096 with the 4-point rule, a call:
 // FP32 Laplace single layer 82 -> 38 us, Helmholtz 91 -> 71; FP64 Laplace
 // 87 -> 56, Helmholtz double layer 156 -> 130.  p0_tile has the rule.
 constexpr int kFixP0 = 56;   // words a staged triangle takes: record, vertex ids, squared offsets (16-byte multiple)

@@ -328,7 +328,7 @@ double near_span(const bem_mesh &m, int32_t T, int32_t S)
     return best;
 }
 
-// The 48-term radial series of the Helmholtz singular pairs holds ~1e-14
+// The radial series (48 terms at most) of the Helmholtz singular pairs holds ~1e-14
 // relative accuracy at omega = 6 and ~5e-10 at 12, then fails quickly (its
 // largest terms grow like omega^n / n!): requests whose items reach beyond
 // kOmegaMax are refused.

@@ -78,3 +78,22 @@ def test_noalloc_limit_is_that_of_the_plain_forms():
     torch.cuda.synchronize()
     assert float(out.abs().max()) == 0.0
     mesh.destroy()
+
+
+def test_dense_budget_holds_a_row():
+    """A star of six triangles against 20,480 needs 17.7 MB of complex FP64 local
+    matrices: refused with a budget of 16 MiB, and so for any number of rows."""
+    xyz, tri = inputs.icosphere(5)
+    mesh = bem.mesh_create(xyz, tri, 4)
+    idx = np.arange(len(xyz), dtype=np.int32)
+    os.environ["BEM_DENSE_BUDGET_MB"] = "16"
+    try:
+        for rows in (idx[-1:], idx[-5:]):
+            with pytest.raises(bem.BemError, match="dense budget"):
+                bem.eval_dense(mesh, bem.HELMHOLTZ_SLP, bem.P1, 3.0, rows, idx, prec=bem.FP64, near=bem.NEAR_SKIP)
+        got = bem.eval_dense(mesh, bem.LAPLACE_SLP, bem.P1, 0.0, idx[-1:], idx, prec=bem.FP64, near=bem.NEAR_SKIP)
+    finally:
+        os.environ.pop("BEM_DENSE_BUDGET_MB", None)
+    assert np.array_equal(got, bem.eval_dense(mesh, bem.LAPLACE_SLP, bem.P1, 0.0, idx[-1:], idx, prec=bem.FP64,
+                                              near=bem.NEAR_SKIP))
+    mesh.destroy()

@@ -138,11 +138,14 @@ __device__ __forceinline__ Pair load_pair(const NearReq &R, int a, int b)
     const int t0 = b0 / 3, s0 = b0 - 3 * t0, t1 = b1 / 3, s1 = b1 - 3 * t1;
     q.kind = n >= 3 ? 0 : (n == 2 ? 1 : 2);
     auto next = [](int i) { return i == 2 ? 0 : i + 1; };
-    q.pt[0] = q.kind == 0 ? 0 : t0;
-    q.pt[1] = q.kind == 0 ? 1 : (q.kind == 1 ? t1 : next(t0));
+    // identical: t0 = 0, t1 = 1 and s0, s1 where the trial triangle, which may list
+    // the three vertices in another order (a triangle that the mesh holds twice),
+    // has them
+    q.pt[0] = t0;
+    q.pt[1] = q.kind == 2 ? next(t0) : t1;
     q.pt[2] = 3 - q.pt[0] - q.pt[1];
-    q.ps[0] = q.kind == 0 ? 0 : s0;
-    q.ps[1] = q.kind == 0 ? 1 : (q.kind == 1 ? s1 : next(s0));
+    q.ps[0] = s0;
+    q.ps[1] = q.kind == 2 ? next(s0) : s1;
     q.ps[2] = 3 - q.ps[0] - q.ps[1];
     auto pick = [](const i32x4 &v, int i) { return i == 0 ? v.x : (i == 1 ? v.y : v.z); };
     // v[3], v[4]: the trial triangle's vertices that are not shared (B; C, D),

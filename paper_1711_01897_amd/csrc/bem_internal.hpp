@@ -522,8 +522,9 @@ void finish_descriptor(const Request &r, char *dev_base, size_t off_out, size_t 
 
 // Server
 int server_submit(Request *r);
-// Workspace of a request by triangle pairs in the server's slots.
-size_t server_pair_budget();
+// Workspace of a request by triangle pairs in the server's slots (0: none), beside
+// its entries.
+size_t server_pair_budget(size_t out_bytes);
 int server_submit_many(Request *const *rs, size_t n);
 // With BEM_DEBUG_TIMING set: prints and resets per-phase host times of the
 // dispatch and completion threads (stderr).

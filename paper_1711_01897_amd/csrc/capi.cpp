@@ -65,6 +65,15 @@ int fill_request(Request &r, bem_mesh *mesh, bem_op op, bem_space space, double 
     return expand_request(r, pair_budget);
 }
 
+// Pair workspace of a served request; sizes that fill_request refuses, and
+// entries past any slot, have none.
+size_t served_budget(int op, int prec, int64_t nrows, int64_t ncols)
+{
+    if (nrows <= 0 || ncols <= 0 || nrows > INT32_MAX || ncols > INT32_MAX) return 0;
+    const size_t n = (size_t)nrows * (size_t)ncols;
+    return n > SIZE_MAX / 16 ? 0 : server_pair_budget(n * out_elem_bytes(op, prec));
+}
+
 // Staging of the async path: a pinned host image of the request and device
 // workspace of the same size, kept from call to call.  A slot carries the
 // event recorded after the last kernel that reads it and is taken again, by
@@ -556,7 +565,7 @@ int bem_eval_entries(bem_mesh *mesh, bem_op op, bem_space space, double k, const
 {
     Request *r = new (std::nothrow) Request();
     if (!r) return fail(BEM_E_OOM, "host allocation failed");
-    int rc = fill_request(*r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, server_pair_budget());
+    int rc = fill_request(*r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, served_budget(op, prec, nrows, ncols));
     if (rc == BEM_OK && r->entries() > 0) {
         if (!out) {
             rc = fail(BEM_E_ARG, "null output");
@@ -580,7 +589,7 @@ int bem_submit(bem_mesh *mesh, bem_op op, bem_space space, double k, const int32
     bem_ticket *t = new (std::nothrow) bem_ticket();
     if (!t) return fail(BEM_E_OOM, "host allocation failed");
     Request &r = t->req;
-    int rc = fill_request(r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, server_pair_budget());
+    int rc = fill_request(r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, served_budget(op, prec, nrows, ncols));
     if (rc == BEM_OK) {
         if (r.entries() == 0) {
             r.done = true;

@@ -728,10 +728,12 @@ void expand_single_fixed(Request &r, int32_t dof, int rowfix, const LaneRef *ext
 
 size_t request_bytes(const Request &r)
 {
-    // descriptor, inputs, status, outputs, block table, launch-timing records
+    // descriptor, inputs, status, outputs, block table, launch-timing records.  By
+    // triangle pairs the device's part is the larger: the entries lie there once
+    // more than in the staging, behind the local matrices, not in both of one sum.
     return sizeof(ReqDev) + r.in_bytes + 8 + r.out_bytes + (size_t)r.nblocks * (sizeof(EntryBlock) + 16) +
            (r.near_pairs.empty() ? 0 : near_layout(near_kind(r), near_count(r)).bytes) +
-           (r.paired ? r.pairs.work + r.out_bytes + 512 : 0) + 512;
+           (r.paired ? r.pairs.work + 512 : 0) + 512;
 }
 
 void describe_request(const Request &r, ReqDev &d)

@@ -648,8 +648,16 @@ public:
             rs[i]->fast = false;
             prebuild_staging(*rs[i]);
         }
-        for (size_t i = 0; i < n; ++i)
-            if (!fits(rs[i])) return fail(BEM_E_OOM, "request larger than a server batch slot; raise the arena size");
+        for (size_t i = 0; i < n; ++i) {
+            Request &r = *rs[i];
+            if (fits(&r)) continue;
+            if (r.paired) {   // the local matrices take room that the star form leaves
+                const int rc = expand_request(r);
+                if (rc != BEM_OK) return rc;
+                prebuild_staging(r);
+            }
+            if (!fits(&r)) return fail(BEM_E_OOM, "request larger than a server batch slot; raise the arena size");
+        }
         thread_local std::vector<Pending> items;
         items.resize(n);
         const double t = now_seconds();
@@ -1612,9 +1620,15 @@ void persist_register_exit(Server *s)
 
 }  // namespace
 
-// A quarter of a slot: a request's local matrices share it with its entries
-// (kept on the device too) and its lists.
-size_t server_pair_budget() { return std::min<size_t>(size_t(64) << 20, server().planned_slot_bytes() / 4); }
+// A quarter of a slot at most, and what the request's entries (kept on the
+// device too) leave of it after an eighth for its lists; nothing where that is
+// less than half of the quarter: many small panels are slower than the stars.
+size_t server_pair_budget(size_t out_bytes)
+{
+    const size_t slot = server().planned_slot_bytes(), quarter = std::min<size_t>(size_t(64) << 20, slot / 4);
+    const size_t taken = out_bytes + slot / 8, room = taken < slot ? slot - taken : 0;
+    return room < quarter / 2 ? 0 : std::min(quarter, room);
+}
 
 int server_configure(size_t arena_bytes, int max_batch)
 {

@@ -438,7 +438,9 @@ struct Request {
                                           // the column dofs follow when staged
     int32_t near_slots = 0;               // row-side triangles
     std::vector<int32_t> near_rows;       // P1: rows with at least one pair
-    bool many = false;                    // one of many in flight that several threads expand
+    // taken by single triangles or stars whatever its size: one of many in flight that
+    // several threads expand, or one whose other form a workspace does not hold
+    bool plain = false;
     bool row = false;                     // P1 of few fixed dofs: the row form (build_row_set)
     int32_t tile = 1;                     // P0: fixed triangles per workgroup
     int32_t row_split = 0;                // its log2 shares of a fixed star

@@ -659,9 +659,10 @@ int bem_eval_entries_async_noalloc(bem_mesh *mesh, bem_op op, bem_space space, d
     rc = noalloc_workspace(mesh->device, &ws);
     if (rc != BEM_OK) return rc;
     rc = enqueue_device_request(r, dev_out, (hipStream_t)stream, ws, kNoAllocBytes);
-    if (rc == BEM_E_OOM && r.paired) {
+    if (rc == BEM_E_OOM && (r.paired || r.row)) {
         // by stars it may still fit
-        rc = expand_request(r, 0);
+        r.plain = true;
+        rc = expand_request(r);
         if (rc == BEM_OK) rc = enqueue_device_request(r, dev_out, (hipStream_t)stream, ws, kNoAllocBytes);
     }
     return rc;

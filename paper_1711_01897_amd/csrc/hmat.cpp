@@ -533,7 +533,7 @@ int prepare_slot(AssemblyCtx &C, Slot<T> &s, DoneQueue &dq, int64_t tag, WorkerT
     if (!s.adm) {
         r.near = C.dense_near;
         r.separated = false;
-        r.many = true;
+        r.plain = true;
         r.rows.assign(C.h->rows(L), C.h->rows(L) + L.m);
         r.cols.assign(C.h->cols(L), C.h->cols(L) + L.n);
         r.nrows = (int64_t)r.rows.size();

@@ -266,10 +266,12 @@ namespace {
 // are faster by rows (1: 259-271 / 21-24; the largest 283 / 124, 278 / 83,
 // 275 / 71, 278 / 99), of 32 too (17-26 / 14-20).  The leaves of an H-matrix,
 // which several threads expand while the device works on others, keep the star
-// form (level-5 icosphere, leaf size 100: 58.5 ms by stars, 63 by rows).
+// form (level-5 icosphere, leaf size 100: 58.5 ms by stars, 63 by rows); so do
+// lists so long that the row form's block records, one for every 8 to 32 lane dofs
+// where stars take one for about 100, exceed a workspace that the stars' fit.
 bool row_pays(const Request &r, int64_t nfix)
 {
-    if (r.space == BEM_P0 || r.many) return false;
+    if (r.space == BEM_P0 || r.plain) return false;
     if (is_complex_op(r.op)) return nfix <= (r.prec == BEM_FP32 ? 16 : 8);
     return nfix <= (r.prec == BEM_FP32 ? 64 : 16);
 }
@@ -670,7 +672,7 @@ int expand_request(Request &r, size_t pair_budget)
     const std::vector<int32_t> &fix_dofs = r.fixrows ? r.rows : r.cols;
     const std::vector<int32_t> &lane_dofs = r.fixrows ? r.cols : r.rows;
     r.row = row_pays(r, (int64_t)fix_dofs.size());
-    r.paired = !r.row && pair_budget > 0 && pairs_pay(r, fix_dofs, lane_dofs);
+    r.paired = !r.row && !r.plain && pair_budget > 0 && pairs_pay(r, fix_dofs, lane_dofs);
     if (r.paired) {
         plan_pairs(m, r.space, kernel_op(r.op), r.prec, r.rowfix != 0, fix_dofs.data(), (int64_t)fix_dofs.size(),
                    lane_dofs.data(), (int64_t)lane_dofs.size(), pair_budget, r.pairs);

@@ -651,7 +651,8 @@ public:
         for (size_t i = 0; i < n; ++i) {
             Request &r = *rs[i];
             if (fits(&r)) continue;
-            if (r.paired) {   // the local matrices take room that the star form leaves
+            if (r.paired || r.row) {   // stars take less: no local matrices, a third of the row form's block records
+                r.plain = true;
                 const int rc = expand_request(r);
                 if (rc != BEM_OK) return rc;
                 prebuild_staging(r);

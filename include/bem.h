@@ -196,14 +196,17 @@ int bem_eval_entries_async(bem_mesh *mesh, bem_op op, bem_space space, double k,
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same request as bem_eval_entries_async, computed by the same kernels, with
  * its workspace (descriptor, block table, singular-pair records, staged
- * inputs, status word; local matrices of a block by triangle pairs) in a fixed
- * 32 MiB static device array, and its host image in a per-thread pageable
+ * inputs, status word) in a fixed 32 MiB static device array, the local matrices
+ * of a block by triangle pairs in 64 MiB behind it, and its host image in a per-thread pageable
  * buffer instead of pinned staging.  The call makes no device or pinned
  * allocation.  Differences from bem_eval_entries_async:
  *   - a request whose workspace exceeds 32 MiB with its entries evaluated
  *     star by star (P0: triangle by triangle) fails with BEM_E_OOM (nothing
  *     enqueued), however it would be evaluated; a P1 row or column of 4,096 entries needs well
  *     under 1 MiB;
+ *   - a P1 block that 64 MiB cut into many panels is evaluated star by star
+ *     where the other entry point takes it by triangle pairs (the same sums in
+ *     another order);
  *   - the copy of the workspace from pageable host memory is synchronous
  *     with the host, so the call returns once the stream has reached it;
  *   - every call on one device uses the same workspace: calls that overlap on

@@ -297,8 +297,14 @@ void plan_pairs(const bem_mesh &m, int space, int op, int prec, bool ltrial, con
                 const int32_t *lane, int64_t nlane, size_t budget, PairPlan &P);
 // Whether two of the plan's triangles, one of each side, share a vertex.
 bool pairs_touch(const bem_mesh &m, const PairPlan &P);
+// What a request by triangle pairs may use: workspace bytes (0: it may not be),
+// and whether its entries go to host memory (a served request).
+struct PairRoom {
+    size_t budget = 0;
+    bool served = false;
+};
 // Whether a request is worth it (see the rule at its definition).
-bool pairs_pay(const Request &r, const std::vector<int32_t> &fix, const std::vector<int32_t> &lane);
+bool pairs_pay(const Request &r, const std::vector<int32_t> &fix, const std::vector<int32_t> &lane, const PairRoom &room);
 // Enqueues one pair of panels: ints (device copy of P.ints), work (P.work bytes), entries at
 // out[fixed position * sf + lane position * sl], the fixed position being the dof's in the caller's list
 // or, with in_panel, in the panel.
@@ -486,9 +492,7 @@ int kernel_op(int op);
 size_t out_elem_bytes(int op, int prec);
 
 // Validate and expand a request (host; runs on the submitting thread).
-// pair_budget: workspace bytes the request may use if it is taken by triangle
-// pairs (0: it may not be).
-int expand_request(Request &r, size_t pair_budget = 0);
+int expand_request(Request &r, const PairRoom &room = {});
 // What a request takes beside its singular pairs as single triangles or stars,
 // in bytes (at most, where that is within the limit).
 size_t plain_workspace(const Request &r, size_t limit);
@@ -524,9 +528,8 @@ void finish_descriptor(const Request &r, char *dev_base, size_t off_out, size_t 
 
 // Server
 int server_submit(Request *r);
-// Workspace of a request by triangle pairs in the server's slots (0: none), beside
-// its entries.
-size_t server_pair_budget(size_t out_bytes);
+// Room of a request by triangle pairs in the server's slots, beside its entries.
+PairRoom server_pair_room(size_t out_bytes);
 int server_submit_many(Request *const *rs, size_t n);
 // With BEM_DEBUG_TIMING set: prints and resets per-phase host times of the
 // dispatch and completion threads (stderr).

@@ -47,7 +47,7 @@ struct bem_ticket {
 namespace {
 
 int fill_request(Request &r, bem_mesh *mesh, bem_op op, bem_space space, double k, const int32_t *rows, int64_t nrows,
-                 const int32_t *cols, int64_t ncols, bem_prec prec, bem_near near, size_t pair_budget = 0)
+                 const int32_t *cols, int64_t ncols, bem_prec prec, bem_near near, const PairRoom &room)
 {
     if (!mesh) return fail(BEM_E_ARG, "null mesh");
     if (nrows < 0 || ncols < 0) return fail(BEM_E_ARG, "negative request size");
@@ -62,16 +62,16 @@ int fill_request(Request &r, bem_mesh *mesh, bem_op op, bem_space space, double 
     r.ncols = ncols;
     r.rows.assign(rows, rows + nrows);
     r.cols.assign(cols, cols + ncols);
-    return expand_request(r, pair_budget);
+    return expand_request(r, room);
 }
 
-// Pair workspace of a served request; sizes that fill_request refuses, and
+// Room for the pairs of a served request; sizes that fill_request refuses, and
 // entries past any slot, have none.
-size_t served_budget(int op, int prec, int64_t nrows, int64_t ncols)
+PairRoom served_room(int op, int prec, int64_t nrows, int64_t ncols)
 {
-    if (nrows <= 0 || ncols <= 0 || nrows > INT32_MAX || ncols > INT32_MAX) return 0;
+    if (nrows <= 0 || ncols <= 0 || nrows > INT32_MAX || ncols > INT32_MAX) return {};
     const size_t n = (size_t)nrows * (size_t)ncols;
-    return n > SIZE_MAX / 16 ? 0 : server_pair_budget(n * out_elem_bytes(op, prec));
+    return n > SIZE_MAX / 16 ? PairRoom{} : server_pair_room(n * out_elem_bytes(op, prec));
 }
 
 // Staging of the async path: a pinned host image of the request and device
@@ -88,6 +88,10 @@ constexpr size_t kSlotsTotal = size_t(128) << 20;                            // 
 constexpr size_t kSlotsMost = 64;
 constexpr size_t kPairBudget = size_t(256) << 20;   // workspace of one request by triangle pairs (larger ones go in panels)
 constexpr size_t kWorkTotal = size_t(1) << 30;      // of all that are kept
+// The same for the no-allocation entry point, behind the rest of its workspace.  16
+// MiB within the 32 of the rest cut blocks into so many panels that they took two
+// to three times what their stars do (pairs_pay has the figures).
+constexpr size_t kNoAllocBytes = size_t(32) << 20, kNoAllocPairs = size_t(64) << 20;
 
 struct StageSlot {
     char *host = nullptr;       // pinned
@@ -342,7 +346,7 @@ constexpr int64_t kDirectBlocks = 32;
 // kernel or, for a few workgroups, read in place; or both are allocated for the
 // call (stream-ordered workspace, pinned image released once its copy has
 // completed).  Otherwise both live in fixed memory: the workspace is `fixed`
-// (fixed_bytes long; larger requests fail), the host image a per-thread
+// (fixed_bytes long and kNoAllocPairs for local matrices; larger requests fail), the host image a per-thread
 // pageable buffer whose copy completes before the call returns (a pageable
 // host-to-device copy is synchronous with the host).
 int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed, size_t fixed_bytes)
@@ -385,12 +389,12 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
     // what the singular kernels write for each other follows the staged part
     const size_t ws_staged = in_total + (near ? near_l.bytes - near_l.staged : 0);
     // the local matrices of a request by triangle pairs: with a slot a kept
-    // workspace of their own, else behind the rest
+    // workspace of their own, in the fixed memory at its end, else behind the rest
     const size_t work_bytes = r.paired ? r.pairs.work : 0;
-    size_t ws_total = al(ws_staged) + work_bytes;
+    const size_t work_at = fixed ? fixed_bytes : al(ws_staged), ws_total = al(ws_staged) + work_bytes;
     // the limit is that of the plain forms, whichever form the request takes
-    const size_t needed = fixed ? std::max(ws_total, plain_workspace(r, fixed_bytes)) : 0;
-    if (needed > fixed_bytes)
+    const size_t needed = fixed ? std::max(ws_staged, plain_workspace(r, fixed_bytes)) : 0;
+    if (needed > fixed_bytes || (fixed && work_bytes > kNoAllocPairs))
         return fail(BEM_E_OOM, "request needs " + std::to_string(needed) + " bytes of workspace, more than the " +
                                    std::to_string(fixed_bytes) + "-byte static workspace of the no-allocation entry point");
     char *host = nullptr;
@@ -429,7 +433,7 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
     }
     // where the kernels read the staged image
     const bool direct = slot && !near && !r.paired && r.nblocks <= kDirectBlocks;
-    char *work = wbuf ? wbuf->p : ws + al(ws_staged);
+    char *work = wbuf ? wbuf->p : ws + work_at;
     char *img = direct ? slot->host_dev : ws;
     if (r.paired) {
         std::memcpy(host + off_in, r.pairs.ints.data(), 4 * r.pairs.ints.size());
@@ -492,12 +496,12 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
 }
 
 // Workspace of bem_eval_entries_async_noalloc: one request's descriptor,
-// block table, singular-pair records, inputs and status word.  Each device
+// block table, singular-pair records, inputs and status word, and behind them the
+// local matrices of a block by triangle pairs.  Each device
 // the library runs on holds its own copy for the life of the process; host
 // code reaches it only through the address hipGetSymbolAddress returns for
 // that device.
-constexpr size_t kNoAllocBytes = size_t(32) << 20;
-__device__ __align__(256) char scratch[kNoAllocBytes];
+__device__ __align__(256) char scratch[kNoAllocBytes + kNoAllocPairs];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -565,7 +569,7 @@ int bem_eval_entries(bem_mesh *mesh, bem_op op, bem_space space, double k, const
 {
     Request *r = new (std::nothrow) Request();
     if (!r) return fail(BEM_E_OOM, "host allocation failed");
-    int rc = fill_request(*r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, served_budget(op, prec, nrows, ncols));
+    int rc = fill_request(*r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, served_room(op, prec, nrows, ncols));
     if (rc == BEM_OK && r->entries() > 0) {
         if (!out) {
             rc = fail(BEM_E_ARG, "null output");
@@ -589,7 +593,7 @@ int bem_submit(bem_mesh *mesh, bem_op op, bem_space space, double k, const int32
     bem_ticket *t = new (std::nothrow) bem_ticket();
     if (!t) return fail(BEM_E_OOM, "host allocation failed");
     Request &r = t->req;
-    int rc = fill_request(r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, served_budget(op, prec, nrows, ncols));
+    int rc = fill_request(r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, served_room(op, prec, nrows, ncols));
     if (rc == BEM_OK) {
         if (r.entries() == 0) {
             r.done = true;
@@ -639,7 +643,7 @@ int bem_eval_entries_async(bem_mesh *mesh, bem_op op, bem_space space, double k,
                            void *stream)
 {
     Request r;
-    int rc = fill_request(r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, kPairBudget);
+    int rc = fill_request(r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, {kPairBudget});
     if (rc != BEM_OK) return rc;
     if (r.entries() == 0) return BEM_OK;
     if (!dev_out) return fail(BEM_E_ARG, "null output");
@@ -651,7 +655,7 @@ int bem_eval_entries_async_noalloc(bem_mesh *mesh, bem_op op, bem_space space, d
                                    void *dev_out, void *stream)
 {
     Request r;
-    int rc = fill_request(r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, kNoAllocBytes / 2);
+    int rc = fill_request(r, mesh, op, space, k, rows, nrows, cols, ncols, prec, near, {kNoAllocPairs});
     if (rc != BEM_OK) return rc;
     if (r.entries() == 0) return BEM_OK;
     if (!dev_out) return fail(BEM_E_ARG, "null output");

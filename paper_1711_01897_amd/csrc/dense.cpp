@@ -9,6 +9,7 @@
 // threads copy the one before into `out`, so assembly and transfer overlap
 // (Section 3's chunked assembly with overlapped transfers).
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <memory>
 #include <mutex>
@@ -123,6 +124,20 @@ void count_side(const bem_mesh &m, int space, const int32_t *dofs, int64_t n, in
     }
 }
 
+// Triangles a panel takes at most, of `pairs` local matrices the workspace holds.
+// Lane panels leave room for at least 64 fixed-side triangles (or the largest
+// star); 262,144 of those: the launch grid's second dimension at four or more a
+// workgroup.
+struct PanelCut {
+    int64_t pairs, lanes;
+    int64_t fixed(int64_t nl) const { return std::min<int64_t>(std::max<int64_t>(1, pairs / nl), 65535 * 4); }
+};
+
+PanelCut panel_cut(const bem_mesh &m, size_t pairs)
+{
+    return {(int64_t)pairs, std::max<int64_t>(256, (int64_t)pairs / std::max<int64_t>(64, m.max_star))};
+}
+
 size_t pair_bytes(int op, int prec) { return 9 * (prec == BEM_FP32 ? 4 : 8) * (size_t)(is_complex_op(op) ? 2 : 1); }
 
 }  // namespace
@@ -137,14 +152,11 @@ void plan_pairs(const bem_mesh &m, int space, int op, int prec, bool ltrial, con
     P.prec = prec;
     P.ltrial = ltrial;
     const size_t per = pair_bytes(op, prec);
-    // lane panels leave room for at least 64 fixed-side triangles (or the largest star)
-    const int64_t rows = std::max<int64_t>(64, m.max_star);
-    cut_side(m, space, lane, nlane, std::max<int64_t>(256, (int64_t)(budget / per) / rows), P.ints, P.lane);
+    const PanelCut cut = panel_cut(m, budget / per);
+    cut_side(m, space, lane, nlane, cut.lanes, P.ints, P.lane);
     int64_t nl = 1;
     for (const PairPanel &l : P.lane) nl = std::max<int64_t>(nl, l.ntri);
-    // 262,144 rows: the launch grid's second dimension at four or more rows a workgroup
-    cut_side(m, space, fix, nfix, std::min<int64_t>(std::max<int64_t>(1, (int64_t)(budget / per) / nl), 65535 * 4), P.ints,
-             P.fix);
+    cut_side(m, space, fix, nfix, cut.fixed(nl), P.ints, P.fix);
     int64_t nf = 0;
     P.pairs = 0;
     for (const PairPanel &f : P.fix) {
@@ -167,31 +179,85 @@ bool pairs_touch(const bem_mesh &m, const PairPlan &P)
     return false;
 }
 
+namespace {
+
+// Number of panels cut_side makes of `distinct` triangles with at most `most` a
+// panel: neighbouring panels repeat the triangles on the line between them, about
+// 2 sqrt(most) a panel.  repeat: by how much that makes them more.
+double panel_count(int64_t distinct, int64_t most, double &repeat)
+{
+    repeat = 1.0;
+    if (distinct <= most) return 1.0;
+    repeat = 1.0 / std::max(0.5, 1.0 - 2.0 / std::sqrt((double)most));
+    return std::ceil((double)distinct * repeat / (double)most);
+}
+
+// What one triangle pair costs by stars, what its local matrix and one star
+// product of an entry's gather cost by pairs (picoseconds), and what a panel's two
+// launches and its half-empty gather take at least (microseconds).
+struct FormCost {
+    double star, local, gather, panel;
+};
+
+FormCost form_cost(bool fp32, bool cplx, int q)
+{
+    if (q == 6) {
+        if (fp32) return cplx ? FormCost{28.6, 53.0, 2.9, 29.0} : FormCost{12.4, 24.0, 1.44, 26.0};
+        return cplx ? FormCost{57.0, 104.0, 5.5, 35.0} : FormCost{22.7, 42.0, 2.6, 21.0};
+    }
+    if (fp32) return cplx ? FormCost{16.3, 36.0, 2.9, 29.0} : FormCost{8.4, 19.0, 1.44, 26.0};
+    return cplx ? FormCost{28.7, 62.0, 5.5, 35.0} : FormCost{13.1, 30.0, 2.6, 21.0};
+}
+
+}  // namespace
+
 // By pairs a block costs its distinct triangle pairs' local matrices and its
 // entries' gathers, by stars each fixed dof's star against the lanes of every
-// chunk.  Per point pair a local matrix takes 11 instructions to the star
-// form's 9 (6-point rule, single layer; with the basis products of the pair 1.3
-// times a star pair's), a gather a tenth of a star pair for each of an entry's
-// star products.  Chunks of more than 256 lanes repeat about a quarter of their
-// triangles at the borders.  Scattered dofs share nothing and stay with the
-// stars (two sets of 1,024: 377 us by stars, 554 by pairs).  Small blocks stay
-// with them too, for their single launch; the line is where the two meet for
-// two patches of n dofs (us by stars / by pairs): FP32 n = 362 39 / 56, 512
-// 63 / 65, 1,024 191 / 128; FP32 complex 256 65 / 62, 1,024 451 / 330; FP64 256
-// 55 / 49, 1,024 344 / 252; FP64 complex 128 38 / 51, 181 80 / 58, 1,024
-// 970 / 641.
-bool pairs_pay(const Request &r, const std::vector<int32_t> &fix, const std::vector<int32_t> &lane)
+// chunk; chunks of more than 256 lanes repeat about a quarter of their triangles
+// at the borders.  The costs above are those of two patches of 3,000 x 4,000
+// vertices with all the workspace they want (us by stars / by pairs, 6-point rule:
+// FP32 2,300 / 1,884, complex 5,316 / 3,983, FP64 4,212 / 3,269, complex 10,588 /
+// 7,667; 4-point rule 1,564 / 1,600, 3,026 / 3,095, 2,439 / 2,645, 5,335 / 5,560:
+// with fewer points a pair the matrices' way through memory outweighs what they
+// save).  A small workspace cuts the block into panels (1,023 x 2,049, 6 points, by
+// stars, by pairs in 16, 64 and 256 MiB: FP32 494, 999, 466, 391; complex 1,031,
+// 3,421, 916, 761; FP64 810, 2,681, 771, 647; complex 1,916, 6,033, 1,972, 1,327).
+// Scattered dofs share nothing and stay with the stars (two sets of 1,024: 377 us
+// by stars, 554 by pairs), and so do blocks too small for two launches (two
+// patches of n vertices, FP32 n = 400 72 / 81, 600 115 / 104; complex 200 75 / 71,
+// 400 118 / 100; FP64 200 66 / 63, 400 99 / 90; complex 128 38 / 51, 200 121 / 82)
+// and discontinuous dofs, whose stars are one triangle (1,023 x 2,049 FP32 95 /
+// 113, FP64 108 / 140; 6,000 x 12,000 1,597 / 2,051 and 1,992 / 2,420).
+// Served requests differ in where the entries go: the star kernels store them one
+// by one over the host link in the caller's order (0.85 ns each), by pairs they
+// are gathered on the device and copied (50 GB/s): 1,023 x 2,049 served, 16 MiB,
+// FP32 2,316 / 1,384, complex 2,882 / 4,037, FP64 2,658 / 3,326, complex
+// 3,015 / 7,163; 600 x 600 506 / 325, 666 / 580, 625 / 511, 761 / 1,189; discontinuous
+// 600 x 600 FP32 144 / 162, FP64 200 / 215, 1,023 x 2,049 1,688 / 463, 1,830 / 688.
+bool pairs_pay(const Request &r, const std::vector<int32_t> &fix, const std::vector<int32_t> &lane, const PairRoom &room)
 {
     const bool fp32 = r.prec == BEM_FP32, cplx = is_complex_op(r.op);
-    const int64_t least = fp32 ? (cplx ? 65536 : 262144) : (cplx ? 32768 : 65536);
-    if (r.space == BEM_P0 || fix.size() < 8 || (int64_t)fix.size() * (int64_t)lane.size() < least) return false;
+    const double entries = (double)fix.size() * (double)lane.size();
+    const double least = r.space == BEM_DP1 ? 524288 : fp32 ? (cplx ? 65536 : 262144) : (cplx ? 32768 : 65536);
+    if (r.space == BEM_P0 || (r.space == BEM_DP1 && !room.served) || fix.size() < 8 || entries < least) return false;
     const bem_mesh &m = *r.mesh;
+    const size_t per = pair_bytes(r.op, r.prec);
+    const PanelCut cut = panel_cut(m, room.budget / per);
     int64_t fs, fd, ls, ld;
     count_side(m, r.space, fix.data(), (int64_t)fix.size(), fs, fd);
     count_side(m, r.space, lane.data(), (int64_t)lane.size(), ls, ld);
-    const double star = (double)fs * (ld > kBlockLanes ? 1.25 : 1.0) * (double)ld;
-    const double pair = 1.3 * (double)fd * (double)ld + 0.1 * (double)fs * (double)ls;
-    return pair < 0.8 * star;
+    double frep, lrep;
+    const double lpan = panel_count(ld, cut.lanes, lrep);
+    const double panels = lpan * panel_count(fd, cut.fixed(std::min(ld, cut.lanes)), frep);
+    const FormCost c = form_cost(fp32, cplx, m.q);
+    double star = 1e-6 * c.star * (double)fs * (ld > kBlockLanes ? 1.25 : 1.0) * (double)ld;
+    double pair = 1e-6 * c.local * (double)fd * frep * (double)ld * lrep +
+                  std::max(1e-6 * c.gather * (double)fs * (double)ls, c.panel * (panels - 1.0));
+    if (room.served) {
+        star += 0.85e-3 * entries;
+        pair += 20e-6 * entries * (double)out_elem_bytes(r.op, r.prec);
+    }
+    return pair < 0.95 * star;
 }
 
 hipError_t launch_pairs(const bem_mesh &m, const PairPlan &P, const PairPanel &f, const PairPanel &l, const int32_t *ints,

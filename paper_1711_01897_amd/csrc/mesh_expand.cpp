@@ -641,7 +641,7 @@ bool row_touches(const Request &r)
     return false;
 }
 
-int expand_request(Request &r, size_t pair_budget)
+int expand_request(Request &r, const PairRoom &room)
 {
     const bem_mesh &m = *r.mesh;
     if (r.op < 0 || r.op > 7) return fail(BEM_E_ARG, "unknown operator");
@@ -672,10 +672,10 @@ int expand_request(Request &r, size_t pair_budget)
     const std::vector<int32_t> &fix_dofs = r.fixrows ? r.rows : r.cols;
     const std::vector<int32_t> &lane_dofs = r.fixrows ? r.cols : r.rows;
     r.row = row_pays(r, (int64_t)fix_dofs.size());
-    r.paired = !r.row && !r.plain && pair_budget > 0 && pairs_pay(r, fix_dofs, lane_dofs);
+    r.paired = !r.row && !r.plain && room.budget > 0 && pairs_pay(r, fix_dofs, lane_dofs, room);
     if (r.paired) {
         plan_pairs(m, r.space, kernel_op(r.op), r.prec, r.rowfix != 0, fix_dofs.data(), (int64_t)fix_dofs.size(),
-                   lane_dofs.data(), (int64_t)lane_dofs.size(), pair_budget, r.pairs);
+                   lane_dofs.data(), (int64_t)lane_dofs.size(), room.budget, r.pairs);
         r.pair_error = r.near == BEM_NEAR_ERROR && pairs_touch(m, r.pairs);
         r.nfix = r.nlane = r.nchunk = r.nblocks = 0;   // no block table
         r.elem_bytes = out_elem_bytes(r.op, r.prec);

@@ -1622,13 +1622,11 @@ void persist_register_exit(Server *s)
 }  // namespace
 
 // A quarter of a slot at most, and what the request's entries (kept on the
-// device too) leave of it after an eighth for its lists; nothing where that is
-// less than half of the quarter: many small panels are slower than the stars.
-size_t server_pair_budget(size_t out_bytes)
+// device too) leave of it after an eighth for its lists.
+PairRoom server_pair_room(size_t out_bytes)
 {
-    const size_t slot = server().planned_slot_bytes(), quarter = std::min<size_t>(size_t(64) << 20, slot / 4);
-    const size_t taken = out_bytes + slot / 8, room = taken < slot ? slot - taken : 0;
-    return room < quarter / 2 ? 0 : std::min(quarter, room);
+    const size_t slot = server().planned_slot_bytes(), taken = out_bytes + slot / 8;
+    return {std::min<size_t>({size_t(64) << 20, slot / 4, taken < slot ? slot - taken : 0}), true};
 }
 
 int server_configure(size_t arena_bytes, int max_batch)

@@ -292,9 +292,10 @@ struct PairPlan {
     int op = 0, prec = 0;
     bool ltrial = true;     // the lane side is the trial side
 };
-// Plan of fix x lane with at most `budget` bytes of workspace.
+// Plan of fix x lane with at most `budget` bytes of workspace.  entries_panelled:
+// the caller holds the entries of a panel of the fixed side in buffers of its own.
 void plan_pairs(const bem_mesh &m, int space, int op, int prec, bool ltrial, const int32_t *fix, int64_t nfix,
-                const int32_t *lane, int64_t nlane, size_t budget, PairPlan &P);
+                const int32_t *lane, int64_t nlane, size_t budget, PairPlan &P, bool entries_panelled = false);
 // Whether two of the plan's triangles, one of each side, share a vertex.
 bool pairs_touch(const bem_mesh &m, const PairPlan &P);
 // What a request by triangle pairs may use: workspace bytes (0: it may not be),

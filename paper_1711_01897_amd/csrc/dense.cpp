@@ -60,9 +60,9 @@ void star_range(const bem_mesh &m, int space, int32_t d, int64_t &b, int64_t &e)
 }
 
 // Cuts a side into panels of at most most_tri distinct triangles (one dof's
-// star at least).
-void cut_side(const bem_mesh &m, int space, const int32_t *dofs, int64_t n, int64_t most_tri, std::vector<int32_t> &ints,
-              std::vector<PairPanel> &out)
+// star at least) and most_dof dofs.
+void cut_side(const bem_mesh &m, int space, const int32_t *dofs, int64_t n, int64_t most_tri, int64_t most_dof,
+              std::vector<int32_t> &ints, std::vector<PairPanel> &out)
 {
     std::vector<int32_t> order, tri, ptr, src;
     morton_order(m, space, dofs, n, order);
@@ -78,7 +78,7 @@ void cut_side(const bem_mesh &m, int space, const int32_t *dofs, int64_t n, int6
             int64_t b, e, fresh = 0;
             star_range(m, space, dofs[order[i]], b, e);
             for (int64_t s = b; s < e; ++s) fresh += sc.stamp[m.star[s] >> 2] != sc.gen;
-            if (i > first && (int64_t)tri.size() + fresh > most_tri) break;
+            if (i > first && ((int64_t)tri.size() + fresh > most_tri || i - first >= most_dof)) break;
             for (int64_t s = b; s < e; ++s) {
                 const int32_t t = m.star[s] >> 2;
                 if (sc.stamp[t] != sc.gen) {
@@ -143,7 +143,7 @@ size_t pair_bytes(int op, int prec) { return 9 * (prec == BEM_FP32 ? 4 : 8) * (s
 }  // namespace
 
 void plan_pairs(const bem_mesh &m, int space, int op, int prec, bool ltrial, const int32_t *fix, int64_t nfix,
-                const int32_t *lane, int64_t nlane, size_t budget, PairPlan &P)
+                const int32_t *lane, int64_t nlane, size_t budget, PairPlan &P, bool entries_panelled)
 {
     P.ints.clear();
     P.fix.clear();
@@ -153,10 +153,14 @@ void plan_pairs(const bem_mesh &m, int space, int op, int prec, bool ltrial, con
     P.ltrial = ltrial;
     const size_t per = pair_bytes(op, prec);
     const PanelCut cut = panel_cut(m, budget / per);
-    cut_side(m, space, lane, nlane, cut.lanes, P.ints, P.lane);
+    cut_side(m, space, lane, nlane, cut.lanes, nlane, P.ints, P.lane);
     int64_t nl = 1;
     for (const PairPanel &l : P.lane) nl = std::max<int64_t>(nl, l.ntri);
-    cut_side(m, space, fix, nfix, cut.fixed(nl), P.ints, P.fix);
+    // As many dofs as the gather's launch grid takes at four rows a workgroup; where a
+    // panel's entries are held panel by panel, about as many as its triangles have
+    // on a closed mesh (repeated dofs add rows but no triangles)
+    const int64_t rows = entries_panelled ? std::min<int64_t>(65535, cut.fixed(nl) / 2 + 64) : 65535 * 4;
+    cut_side(m, space, fix, nfix, cut.fixed(nl), rows, P.ints, P.fix);
     int64_t nf = 0;
     P.pairs = 0;
     for (const PairPanel &f : P.fix) {
@@ -417,7 +421,7 @@ int eval_dense(bem_mesh *m, int op, int space, double k, const int32_t *rows, in
     const char *env = std::getenv("BEM_DENSE_BUDGET_MB");
     const size_t budget = (size_t)std::max(16, env ? std::atoi(env) : 1024) << 20;
     PairPlan P;
-    plan_pairs(*m, space, op, prec, true, rows, nrows, cols, ncols, budget, P);
+    plan_pairs(*m, space, op, prec, true, rows, nrows, cols, ncols, budget, P, true);
     // nothing is launched for a failing request
     if (near == BEM_NEAR_ERROR && pairs_touch(*m, P))
         return fail(BEM_E_NEARFIELD, "a contributing triangle pair shares a vertex");

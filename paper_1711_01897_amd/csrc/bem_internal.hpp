@@ -67,19 +67,25 @@ struct ReqDev {
     int32_t *status;           // set to 1: a vertex-sharing pair was met under BEM_NEAR_ERROR
     int64_t sf, sl;
     int32_t nrows, ncols;
-    int32_t nlane;             // lane-side items over all chunks
-    int32_t nfix;              // fixed-side positions
     int32_t rowfix;
     int32_t near_error;
     double k;                  // wavenumber
     double kk;                 // k / (2 pi): phase in turns per unit length
     double kl;                 // k / pi - 2 kk: what the FP64 phase adds to 2 kk (wave_low)
+    double kend;               // where the FP64 phase ends (wave_end)
 };
 
 // k / pi minus its rounded value 2 kk, from 64-bit mantissas.
 inline double wave_low(double k, double kk)
 {
     return (double)((long double)k / 3.14159265358979323846264338327950288L - 2.0L * (long double)kk);
+}
+
+// The distance of 2^50 half turns (double layer), or its square (else).
+inline double wave_end(double kk, int kernel_op)
+{
+    const double r = 0x1p49 / kk;
+    return kernel_op == BEM_HELMHOLTZ_DLP ? r : r * r;
 }
 
 struct EntryBlock {  // one workgroup of entry work (64 bytes, read with one scalar load)

@@ -231,7 +231,7 @@ __device__ __forceinline__ void load32(const float *__restrict__ g, int t, float
 // loads (records are written once, when their mesh is created).
 typedef const __attribute__((address_space(4))) double *ConstF64;
 
-__device__ __forceinline__ Wave64 wave64(const ReqDev &R) { return {R.k, 2.0 * R.kk, R.kl}; }
+__device__ __forceinline__ Wave64 wave64(const ReqDev &R) { return {R.k, 2.0 * R.kk, R.kl, R.kend}; }
 
 template <int Q>
 __device__ __forceinline__ void load64(const double *__restrict__ g, int t, double *v)
@@ -352,15 +352,16 @@ __device__ __forceinline__ void green_f64(double r2, const Wave64 &wv, double &g
         gr = is_dlp<OP>() ? ri * ri * ri : ri;
         gi = 0.0;
     } else {
-        const double r = r2 * ri;
         double sn, cs;
         unsigned flip;
-        cis64(r, wv, cs, sn, flip);
         if constexpr (is_dlp<OP>()) {
+            const double r = r2 * ri;
+            cis64(fmin(r, wv.end), wv, cs, sn, flip);
             const double g = flip_sign(ri * ri * ri, flip), kr = wv.k * r;
             gr = g * fma(sn, kr, cs);
             gi = g * fma(-cs, kr, sn);
         } else {
+            cis64(fmin(r2, wv.end) * ri, wv, cs, sn, flip);   // r2 = 0: not a number, as for the double layer
             const double g = flip_sign(ri, flip);
             gr = g * cs;
             gi = g * sn;
@@ -2791,7 +2792,7 @@ hipError_t local_launch(bool fp32, const bem_mesh &m, const int32_t *ftri, int n
     if (grid.y > 65535) return hipErrorInvalidValue;
     const float kf = (float)k;
     const double kk = k / (2.0 * 3.14159265358979323846);
-    const Wave64 wave{k, 2.0 * kk, wave_low(k, kk)};
+    const Wave64 wave{k, 2.0 * kk, wave_low(k, kk), wave_end(kk, OP)};
 #define BEM_LOCAL(QP)                                                                                               \
     do {                                                                                                            \
         if (fp32)                                                                                                   \

@@ -27,9 +27,12 @@ __device__ __forceinline__ double rsqrt64(double x)
 }
 
 // The wavenumber as the phase needs it: k / pi (half turns per unit length) as
-// a sum of two doubles.
+// a sum of two doubles, and the distance (double layer) or its square (else) that
+// ends the phase: 2^50 half turns, past which a rounding of r turns the phase by as
+// much as it likes.  Beyond it the phase must only stay what cis64 can reduce (the
+// amplitude is still the true r's).  One minimum in 55 instructions.
 struct Wave64 {
-    double k, h, l;
+    double k, h, l, end;
 };
 
 // e^{ikr} up to a sign: returns cos and sin of pi f, f in [-1/2, 1/2] the
@@ -37,7 +40,7 @@ struct Wave64 {
 // parity in bit 31 of `flip` (set: both change sign).  r h is split exactly
 // into n + f by the fused product, so the phase carries no rounding of k r.
 // n comes from adding 1.5 x 2^52, which leaves its parity in the last bit of
-// the sum (phases up to 2^51 half turns, where a double resolves none).
+// the sum (phases up to 2^51 half turns; Wave64::end keeps them there).
 // Polynomials in f^2: minimax fits (Remez exchange in 60 digits) of
 // sin(pi f) / f and (cos(pi f) - 1) / f^2 on f^2 in [0, 1/4], errors 6.5e-19
 // relative and 1.6e-17 absolute.

@@ -765,13 +765,12 @@ void describe_request(const Request &r, ReqDev &d)
     }
     d.nrows = (int32_t)r.nrows;
     d.ncols = (int32_t)r.ncols;
-    d.nlane = (int32_t)r.nlane;
-    d.nfix = (int32_t)r.nfix;
     d.rowfix = r.rowfix;
     d.near_error = r.near == BEM_NEAR_ERROR ? 1 : 0;
     d.k = r.k;
     d.kk = r.k / (2.0 * 3.14159265358979323846);
     d.kl = wave_low(r.k, d.kk);
+    d.kend = wave_end(d.kk, kernel_op(r.op));
     d.out = nullptr;
     d.status = nullptr;
 }

@@ -299,7 +299,9 @@ int bem_server_stats(bem_server_stats_t *stats, int reset);
  * between HIP events recorded around each launch on its stream, which also
  * holds whatever separates the start event from the kernel's start (host
  * submission of the launch, other work of the same hardware queue).  One
- * entry launch serves row and column requests alike.
+ * entry launch serves row and column requests alike.  A block by triangle pairs
+ * counts the two launches of each pair of its panels, and the events around them
+ * all for both times.
  * Records with persistent = 1 would be resident launches serving the
  * server's batches of ACA rows and columns one after another (every such
  * launch ended since the last reset, with all the work of its batches, both

@@ -318,6 +318,11 @@ bool pairs_pay(const Request &r, const std::vector<int32_t> &fix, const std::vec
 hipError_t launch_pairs(const bem_mesh &m, const PairPlan &P, const PairPanel &f, const PairPanel &l, const int32_t *ints,
                         void *work, void *out, int64_t sf, int64_t sl, double k, hipStream_t s, bool in_panel = false,
                         hipEvent_t between = nullptr);
+// Workgroups of such a pair of launches, and the lane-side records they load.
+struct PairGrid {
+    int64_t workgroups = 0, loads = 0;
+};
+PairGrid pair_grid(const PairPanel &f, const PairPanel &l);
 // Positions of a dof list along a Morton curve of the dofs' places (mesh_expand.cpp).
 void morton_order(const bem_mesh &m, int space, const int32_t *dofs, int64_t n, std::vector<int32_t> &order);
 

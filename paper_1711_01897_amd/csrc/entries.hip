@@ -2779,16 +2779,23 @@ __global__ __launch_bounds__(kBlockLanes) void k_gather_pairs(const T *__restric
     }
 }
 
+// Fixed-side triangles per workgroup of the local matrices: a full tile amortises
+// the lane's set-up, a smaller one fills the card: four workgroups per compute unit
+// at least where the block has them.
+int local_tile(int nf, int nl)
+{
+    const int64_t lanes = (nl + kBlockLanes - 1) / kBlockLanes;
+    int tile = kLocalTile;
+    while (tile > 1 && lanes * ((nf + tile - 1) / tile) < 1024) tile /= 2;
+    return tile;
+}
+
 template <int OP, bool LTRIAL>
 hipError_t local_launch(bool fp32, const bem_mesh &m, const int32_t *ftri, int nf, const int32_t *ltri, int nl, void *Lr,
                         void *Li, double k, hipStream_t s)
 {
-    // a full tile amortises the lane's set-up, a smaller one fills the card:
-    // four workgroups per compute unit at least where the block has them
-    const int64_t lanes = (nl + kBlockLanes - 1) / kBlockLanes;
-    int tile = kLocalTile;
-    while (tile > 1 && lanes * ((nf + tile - 1) / tile) < 1024) tile /= 2;
-    const dim3 grid((unsigned)lanes, (unsigned)((nf + tile - 1) / tile)), block(kBlockLanes);
+    const int tile = local_tile(nf, nl);
+    const dim3 grid((unsigned)((nl + kBlockLanes - 1) / kBlockLanes), (unsigned)((nf + tile - 1) / tile)), block(kBlockLanes);
     if (grid.y > 65535) return hipErrorInvalidValue;
     const float kf = (float)k;
     const double kk = k / (2.0 * 3.14159265358979323846);
@@ -2852,6 +2859,14 @@ int persistent_occupancy(const Variant &v)
 }  // namespace bem
 
 namespace bem {
+
+PairGrid pair_grid(const PairPanel &f, const PairPanel &l)
+{
+    auto up = [](int64_t x, int64_t y) { return (x + y - 1) / y; };
+    if (f.ntri <= 0 || l.ntri <= 0) return {};
+    const int64_t rows = up(f.ntri, local_tile(f.ntri, l.ntri));
+    return {rows * up(l.ntri, kBlockLanes) + up(f.ndof, kGatherRows) * up(l.ndof, kBlockLanes), rows * l.ntri};
+}
 
 hipError_t launch_pair_local(int op, bool fp32, bool ltrial, const bem_mesh &m, const int32_t *ftri, int nf,
                              const int32_t *ltri, int nl, void *Lr, void *Li, double k, hipStream_t s)

@@ -76,8 +76,10 @@ struct Launch {
     Variant v{};
     int key = 0;                 // member list of the group
     size_t off_tab = 0;          // EntryBlock table
-    int64_t count = 0;           // workgroups
+    int64_t count = 0;           // workgroups with a clock record (by triangle pairs: none)
     int64_t entries = 0, evals = 0, loads = 0;
+    int64_t launches = 1, workgroups = 0;
+    int paired = -1;             // by triangle pairs: the request's place in the batch
 };
 
 struct KStat {
@@ -903,7 +905,7 @@ public:
         L.key = o->key;
         L.v = key_variant(o->key);
         L.off_tab = f_blk;
-        L.count = o->nblk;
+        L.count = L.workgroups = o->nblk;
         L.entries = o->entries;
         L.evals = o->evals;
         L.loads = o->loads;
@@ -1076,6 +1078,24 @@ public:
                 L.evals += r.evals;
                 L.loads += r.nfix * r.nlane;
             }
+            L.workgroups = L.count;
+            launches.push_back(L);
+        }
+        for (int i = 0; i < n; ++i) {
+            const Request &r = *take[i];
+            if (!r.paired || r.pair_error) continue;
+            Launch L;
+            L.v = key_variant(r.key);
+            L.paired = i;
+            L.entries = r.entries();
+            L.evals = r.evals;
+            L.launches = 2 * (int64_t)(r.pairs.fix.size() * r.pairs.lane.size());
+            for (const PairPanel &f : r.pairs.fix)
+                for (const PairPanel &l : r.pairs.lane) {
+                    const PairGrid g = pair_grid(f, l);
+                    L.workgroups += g.workgroups;
+                    L.loads += g.loads;
+                }
             launches.push_back(L);
         }
 
@@ -1175,6 +1195,7 @@ public:
         if (time_phases) tp[2] = now_seconds();
         static_assert(sizeof(EntryBlock) == 64, "block records are 64 bytes");
         for (const Launch &L : launches) {
+            if (L.paired >= 0) continue;
             EntryBlock *p = reinterpret_cast<EntryBlock *>(hb + L.off_tab);
             int64_t k = 0;
             for (int i : sc.members[L.key]) {
@@ -1237,18 +1258,21 @@ public:
                 b->ev.push_back(e1);
                 ck = reinterpret_cast<unsigned long long *>(hd + off_clock) + 2 * blk0;
             }
+            if (L.paired >= 0) {
+                const int i = L.paired;
+                const Request &r = *take[i];
+                const int64_t sf = r.fixrows ? r.ncols : 1, sl = r.fixrows ? 1 : r.ncols;
+                if (e0) note(hipEventRecord(e0, stream));
+                for (const PairPanel &f : r.pairs.fix)
+                    for (const PairPanel &l : r.pairs.lane)
+                        note(launch_pairs(*r.mesh, r.pairs, f, l, reinterpret_cast<const int32_t *>(db + ints_off[i]),
+                                          db + work_off[i], db + dout_off[i], sf, sl, r.k, stream));
+                if (e1) note(hipEventRecord(e1, stream));
+                continue;
+            }
             note(launch_entries(L.v, dreq, reinterpret_cast<const EntryBlock *>(src + L.off_tab), L.count, stream, ck,
                                 e0, e1));
             blk0 += L.count;
-        }
-        for (int i = 0; i < n && has_pairs; ++i) {
-            const Request &r = *take[i];
-            if (!r.paired || r.pair_error) continue;
-            const int64_t sf = r.fixrows ? r.ncols : 1, sl = r.fixrows ? 1 : r.ncols;
-            for (const PairPanel &f : r.pairs.fix)
-                for (const PairPanel &l : r.pairs.lane)
-                    note(launch_pairs(*r.mesh, r.pairs, f, l, reinterpret_cast<const int32_t *>(db + ints_off[i]),
-                                      db + work_off[i], db + dout_off[i], sf, sl, r.k, stream));
         }
         // singular pairs after the entry kernels, on the same stream
         for (int kind = 0; kind < kNearKinds && has_near; ++kind)
@@ -1334,8 +1358,9 @@ public:
                         t1 = std::max(t1, ck[2 * w + 1]);
                     }
                     if (t1 > t0) dev[i] = (double)(t1 - t0) / clock_hz;
+                    if (b->launches[i].paired >= 0) dev[i] = dur[i];   // no clock records
                     ks += dev[i];
-                    if (log_launches) {
+                    if (log_launches && b->launches[i].paired < 0) {
                         // workgroup durations and start offsets (median, max), device clock
                         const int64_t nw = b->launches[i].count;
                         std::vector<double> wd(nw), ws(nw);
@@ -1362,7 +1387,7 @@ public:
                 n_evals += b->evals;
                 if (b->timed) {
                     n_timed += 1;
-                    n_launches += (int64_t)b->launches.size();
+                    for (const Launch &L : b->launches) n_launches += L.launches;
                     kernel_s += ks;
                 }
                 busy += std::max(0.0, t_done - std::max(b->t_launch, last_done));
@@ -1379,9 +1404,9 @@ public:
                 for (size_t i = 0; b->timed && !b->persist && i < b->launches.size(); ++i) {
                     const Launch &L = b->launches[i];
                     KStat &k = kstats[L.v];
-                    k.launches += 1;
-                    k.workgroups += L.count;
-                    k.blocks += L.count;
+                    k.launches += L.launches;
+                    k.workgroups += L.workgroups;
+                    k.blocks += L.workgroups;
                     k.entries += L.entries;
                     k.evals += L.evals;
                     k.loads += L.loads;

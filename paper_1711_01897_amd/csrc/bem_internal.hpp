@@ -339,6 +339,14 @@ int fail(int code, const std::string &msg);
 
 double now_seconds();
 
+// Gives back the idle part of what is kept between calls: staging slots, pair
+// workspaces, dense work areas (capi.cpp).
+void release_kept();
+// Device and pinned memory; where there is none left, what is kept between calls
+// is given back and the allocation tried once more.
+hipError_t alloc_device(void **p, size_t bytes);
+hipError_t alloc_pinned(void **p, size_t bytes, unsigned flags);
+
 }  // namespace bem
 
 // ---------------------------------------------------------------------------

@@ -306,7 +306,7 @@ char *pinned_stage(size_t bytes)
 {
     reclaim_stages();
     char *p = nullptr;
-    if (hipHostMalloc((void **)&p, bytes, hipHostMallocDefault) != hipSuccess) return nullptr;
+    if (alloc_pinned((void **)&p, bytes, hipHostMallocDefault) != hipSuccess) return nullptr;
     return p;
 }
 
@@ -357,8 +357,11 @@ void release_slots()
 // With more workgroups the same lists would cross the link once per fixed item.
 constexpr int64_t kDirectBlocks = 32;
 
+// A block by triangle pairs whose workspace the device does not have.
+constexpr int kNoRoom = 1;
+
 // Enqueues an expanded request on `s` with its result in device memory
-// dev_out.  Workspace layout: descriptor | block table | singular pairs |
+// dev_out (kNoRoom: nothing enqueued, to be asked for by stars).  Workspace layout: descriptor | block table | singular pairs |
 // inputs | status word, staged in one host image.  With fixed == nullptr image
 // and workspace are a kept slot's, the image copied to the workspace by a
 // kernel or, for a few workgroups, read in place; or both are allocated for the
@@ -443,8 +446,15 @@ int enqueue_device_request(Request &r, void *dev_out, hipStream_t s, char *fixed
             if (!host) return fail(BEM_E_OOM, "pinned staging allocation failed");
             std::memset(host, 0, in_total);
             hipError_t e = hipMallocAsync((void **)&ws, ws_total, s);
+            if (e == hipErrorOutOfMemory) {
+                (void)hipGetLastError();
+                release_kept();
+                e = hipMallocAsync((void **)&ws, ws_total, s);
+            }
             if (e != hipSuccess) {
+                (void)hipGetLastError();   // reported here, not by the next launch
                 pinned_release(host, nullptr);
+                if (e == hipErrorOutOfMemory && r.paired) return kNoRoom;
                 return fail(BEM_E_DEVICE, std::string("hipMallocAsync: ") + hipGetErrorString(e));
             }
         }
@@ -548,6 +558,38 @@ int noalloc_workspace(int device, char **out)
 
 }  // namespace
 
+namespace bem {
+
+void release_kept()
+{
+    release_slots();
+    release_dense_kits();
+}
+
+hipError_t alloc_device(void **p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();   // no error of a later launch
+    release_kept();
+    e = hipMalloc(p, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
+hipError_t alloc_pinned(void **p, size_t bytes, unsigned flags)
+{
+    hipError_t e = hipHostMalloc(p, bytes, flags);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    release_kept();
+    e = hipHostMalloc(p, bytes, flags);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
+}  // namespace bem
+
 extern "C" {
 
 const char *bem_last_error(void) { return bem::last_error(); }
@@ -562,10 +604,7 @@ int bem_mesh_create(const double *xyz, int64_t nv, const int32_t *tri, int64_t n
 int bem_mesh_destroy(bem_mesh *mesh)
 {
     const int rc = mesh_destroy_impl(mesh);
-    if (rc == BEM_OK && g_meshes.fetch_sub(1) == 1) {
-        release_slots();
-        release_dense_kits();
-    }
+    if (rc == BEM_OK && g_meshes.fetch_sub(1) == 1) release_kept();
     return rc;
 }
 
@@ -665,7 +704,13 @@ int bem_eval_entries_async(bem_mesh *mesh, bem_op op, bem_space space, double k,
     if (rc != BEM_OK) return rc;
     if (r.entries() == 0) return BEM_OK;
     if (!dev_out) return fail(BEM_E_ARG, "null output");
-    return enqueue_device_request(r, dev_out, (hipStream_t)stream, nullptr, 0);
+    rc = enqueue_device_request(r, dev_out, (hipStream_t)stream, nullptr, 0);
+    if (rc == kNoRoom) {
+        r.plain = true;
+        rc = expand_request(r);
+        if (rc == BEM_OK) rc = enqueue_device_request(r, dev_out, (hipStream_t)stream, nullptr, 0);
+    }
+    return rc;
 }
 
 int bem_eval_entries_async_noalloc(bem_mesh *mesh, bem_op op, bem_space space, double k, const int32_t *rows,

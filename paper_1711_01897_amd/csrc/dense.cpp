@@ -444,7 +444,7 @@ int eval_dense(bem_mesh *m, int op, int space, double k, const int32_t *rows, in
         if (e != hipErrorOutOfMemory || bufs == 1) break;
         (void)hipGetLastError();
         kit.reset();             // with less, and without what other calls left
-        release_dense_kits();
+        release_kept();
     }
     if (e != hipSuccess) {
         (void)hipGetLastError();

@@ -335,7 +335,7 @@ int make_resident(const bem_mesh &m, int space, const std::vector<std::pair<cons
     }
     out.chunk_host.resize(std::max<size_t>(nch, 1));
     for (size_t i = 0; i < n; ++i) std::copy(sets[i].chunk.begin(), sets[i].chunk.end(), out.chunk_host.begin() + ch_at[i]);
-    BEM_HIP_TRY(hipMalloc(&out.dev, sizeof(int32_t) * host.size()));
+    BEM_HIP_TRY(alloc_device((void **)&out.dev, sizeof(int32_t) * host.size()));
     BEM_HIP_TRY(hipMemcpy(out.dev, host.data(), sizeof(int32_t) * host.size(), hipMemcpyHostToDevice));
     // lane records gathered once, so the entry kernels read a lane's
     // geometry without going through its triangle index
@@ -349,10 +349,10 @@ int make_resident(const bem_mesh &m, int space, const std::vector<std::pair<cons
         std::vector<int32_t> idx(nl);
         for (size_t i = 0; i < n; ++i) std::copy(sets[i].lane.begin(), sets[i].lane.end(), idx.begin() + lane_at[i]);
         int32_t *d_idx = nullptr;
-        BEM_HIP_TRY(hipMalloc(&d_idx, sizeof(int32_t) * nl));
+        BEM_HIP_TRY(alloc_device((void **)&d_idx, sizeof(int32_t) * nl));
         hipError_t e = hipMemcpy(d_idx, idx.data(), sizeof(int32_t) * nl, hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMalloc(&out.geo, sizeof(float) * kGeo32Stride * nl);
-        if (e == hipSuccess) e = hipMalloc(&out.meta, sizeof(int4) * nl);
+        if (e == hipSuccess) e = alloc_device((void **)&out.geo, sizeof(float) * kGeo32Stride * nl);
+        if (e == hipSuccess) e = alloc_device((void **)&out.meta, sizeof(int4) * nl);
         if (e == hipSuccess) e = launch_gather(m.d_g32, m.d_vtx, d_idx, 0, (int64_t)nl, out.geo, out.meta, 0);
         if (e == hipSuccess) e = hipStreamSynchronize(0);
         (void)hipFree(d_idx);

@@ -939,16 +939,16 @@ int mesh_create_impl(const double *xyz, int64_t nv, const int32_t *tri, int64_t 
                  bv = sizeof(int4) * nt;
     int rc = BEM_OK;
     int32_t bad = 0;
-    if (e == hipSuccess) e = hipMalloc(&m->d_g32, b32);
-    if (e == hipSuccess) e = hipMalloc(&m->d_g64, b64);
-    if (e == hipSuccess) e = hipMalloc(&m->d_vtx, bv);
+    if (e == hipSuccess) e = alloc_device((void **)&m->d_g32, b32);
+    if (e == hipSuccess) e = alloc_device((void **)&m->d_g64, b64);
+    if (e == hipSuccess) e = alloc_device((void **)&m->d_vtx, bv);
     // what the host has: vertices, star entries, triangles, star ranges and,
     // after them, the degenerate flag; one allocation
     const int64_t ns = 3 * nt;
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t o_star = al(sizeof(double) * 3 * nv), o_tri = al(o_star + sizeof(int32_t) * ns),
                  o_sptr = al(o_tri + sizeof(int32_t) * 3 * nt), bh = al(o_sptr + sizeof(int32_t) * (nv + 2));
-    if (e == hipSuccess) e = hipMalloc((void **)&m->d_xyz, bh);
+    if (e == hipSuccess) e = alloc_device((void **)&m->d_xyz, bh);
     if (e == hipSuccess) {
         char *base = reinterpret_cast<char *>(m->d_xyz);
         m->d_star = reinterpret_cast<int32_t *>(base + o_star);
@@ -966,8 +966,8 @@ int mesh_create_impl(const double *xyz, int64_t nv, const int32_t *tri, int64_t 
     if (e == hipSuccess) e = hipMemcpy(&bad, d_bad, sizeof(int32_t), hipMemcpyDeviceToHost);
     // star tables: the packed star entries and, per entry, its triangle's
     // FP32 record and vertex ids with the local vertex in w
-    if (e == hipSuccess) e = hipMalloc(&m->d_sgeo, sizeof(float) * kGeo32Stride * ns);
-    if (e == hipSuccess) e = hipMalloc(&m->d_smeta, sizeof(int4) * ns);
+    if (e == hipSuccess) e = alloc_device((void **)&m->d_sgeo, sizeof(float) * kGeo32Stride * ns);
+    if (e == hipSuccess) e = alloc_device((void **)&m->d_smeta, sizeof(int4) * ns);
     if (e == hipSuccess) e = launch_gather(m->d_g32, m->d_vtx, m->d_star, 2, ns, m->d_sgeo, m->d_smeta, 0);
     if (e == hipSuccess) e = hipStreamSynchronize(0);
     if (e != hipSuccess)

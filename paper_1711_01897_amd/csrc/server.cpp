@@ -325,11 +325,11 @@ public:
         if (e == hipSuccess) e = hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device);
         clock_hz = khz > 0 ? 1e3 * khz : 1e8;
         for (int i = 0; i < nstreams && e == hipSuccess; ++i) e = hipStreamCreateWithFlags(&streams[i], hipStreamNonBlocking);
-        if (e == hipSuccess) e = hipMalloc(&d_arena, arena_bytes);
+        if (e == hipSuccess) e = alloc_device((void **)&d_arena, arena_bytes);
         // inputs are staged here and copied to the device arena; the kernels
         // store results and flags straight into it, uncached (coherent), so
         // they are in host memory once the batch event completes
-        if (e == hipSuccess) e = hipHostMalloc(&h_stage, arena_bytes, hipHostMallocCoherent);
+        if (e == hipSuccess) e = alloc_pinned((void **)&h_stage, arena_bytes, hipHostMallocCoherent);
         if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&h_stage_dev, h_stage, 0);
         if (e != hipSuccess) {
             if (d_arena) (void)hipFree(d_arena);

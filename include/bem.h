@@ -183,8 +183,10 @@ int bem_ticket_free(bem_ticket *ticket);
  * host synchronisation.  rows/cols are host arrays, expanded and staged
  * through pinned memory by the library; the call returns once the work is
  * enqueued, and dev_out is complete when the stream reaches that point.
- * Staging and workspace are kept between calls (bounded, never waited for,
- * given back with the last mesh); with all of it in use, on a capturing stream
+ * Staging and workspace are kept between calls (bounded, given back with the
+ * last mesh or when device memory runs out; work in flight in them is never waited for, but
+ * making a larger one in place of idle smaller ones frees memory, which waits for the
+ * device once); with all of it in use, on a capturing stream
  * and for large requests they come from the stream-ordered allocator.
  * Under BEM_NEAR_ERROR the adjacency check runs on the host before anything
  * is enqueued (BEM_E_NEARFIELD, nothing enqueued). */

@@ -4,7 +4,7 @@
 // pairs one "fixed" item (a test or trial triangle for P0, the star of a
 // test or trial vertex for P1) with up to 256 "lane" triangles, one per
 // thread.  The lane triangles are gathered from the resident per-triangle
-// records (one 128-byte FP32 or 192-byte FP64 record each); for P1 the
+// records (one 64-byte FP32 or 192-byte FP64 record each); for P1 the
 // fixed star's records are staged once per workgroup in LDS, so the waves
 // read them at LDS latency instead of walking the star through dependent
 // global loads.  Every lane evaluates the Green's function at all Q x Q
@@ -22,8 +22,8 @@
 // triangle's quadrature points is a plain FP32 sum; every coarser sum (over
 // the other triangle's points for P0, over triangle pairs for P1, and the
 // final per-entry reduction) is compensated with TwoSum (Knuth).
-// FP64 path: absolute FP64 positions, FP64 reciprocal square root and
-// sincos, plain sums.
+// FP64 path: absolute FP64 positions, reciprocal square root, sine and cosine of
+// f64_math.hpp, plain sums.
 //
 // P1 entries are sums over the triangles of two vertex stars (hat basis
 // functions, Section 2); each lane keeps the three partial sums of its lane
@@ -2713,7 +2713,7 @@ __global__ __launch_bounds__(kBlockLanes) void k_gather_pairs(const T *__restric
             const int ms = fsrc[i];
             return ((size_t)(ms >> 2) * 9 + 3 * (ms & 3)) * nl;
         };
-        auto fetch = [&](size_t base, T *xr, T *xi) {   // places past the star's end read its first value
+        auto fetch = [&](size_t base, T *xr, T *xi) {   // places past the star's end read the panel's first value and are not added
             const T *pr = Lr + base, *pi = CPLX ? Li + base : nullptr;
 #pragma unroll
             for (int j = 0; j < kLow; ++j) {

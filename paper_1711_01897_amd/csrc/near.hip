@@ -45,13 +45,15 @@
 // wavelength reach omega ~ 2 pi), 5e-10 at omega = 12 where the alternating
 // terms cancel.
 // What bounds these kernels is FP64 arithmetic: one workgroup per pair, a
-// thousand or more products per thread, 184 bytes read and at most 160 written.
+// thousand or more products per thread; its 24-byte record, 32 bytes of vertex ids,
+// 120 of vertices and 64 of normals and areas come through scalar loads, and 160 bytes
+// at most are written (P0: one entry).
 // P1 Helmholtz single layer, 2,900 pairs of a 100 x 100 leaf at 10 elements per
 // wavelength: 101 us (336 us with 48 terms from LDS, the nine entries
 // accumulated at every point and a tree reduction); P1 Laplace, the pairs of
 // one dense leaf: 20 us a launch in an H-matrix assembly (41 us).
 // The adjoint double layer is the double layer with test and trial exchanged
-// (the host builds its items that way).
+// (load_pair).
 #include <hip/hip_runtime.h>
 
 #include "bem_internal.hpp"
